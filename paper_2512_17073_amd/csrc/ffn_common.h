@@ -97,6 +97,18 @@ template <int N> __device__ inline void lds_wait(half8_t& a, half8_t& b) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
 
+// Waits until every vector memory load of the wavefront has landed (the direct global -> LDS copies
+// among them), then passes the block's barrier.  The wait is a builtin and not inline asm because the
+// compiler counts with it: a direct global -> LDS copy that it believes in flight makes it treat
+// vmcnt as out of order, and from then on every use of a loaded register waits for vmcnt(0), i.e.
+// for the refills just issued as well (the ring of loads is then one deep instead of two; a Mixtral-shaped forward at T = 64 and 2 bits
+// took 160.5 us with inline asm waits and takes 156.0 with these).
+__device__ inline void wait_loads_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), the other counters as they are
+  __syncthreads();
+}
+
 // A pointer read from memory, moved into scalar registers (a buffer resource must be wave-uniform).
 template <class T> __device__ inline const T* uniform_ptr(const T* p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);

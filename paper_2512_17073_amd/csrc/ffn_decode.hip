@@ -187,7 +187,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     Slot<BITS, NS> ring[RING];
 #pragma unroll
     for (int i = 0; i < RING; ++i) fetch(ring[i]);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    wait_loads_barrier();
 
     float4_t acc[TS][MT][NS];
 #pragma unroll
@@ -283,8 +283,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       if (ph > 0) {
         __syncthreads();                      // everyone is done with the previous phase
         stage_issue(ph, nk);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
+        wait_loads_barrier();
       }
 #pragma unroll
       for (int ts = 0; ts < TS; ++ts) {
@@ -301,8 +300,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     if (p_late && LS > 0) {                   // many rank steps: their (in A) fragments replace the activations
       __syncthreads();
       p_issue();
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
+      wait_loads_barrier();
     }
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts) {         // the rank steps (none unless this block adds the term)
