@@ -5,25 +5,29 @@
 //
 // With hundreds of rows per expert the work is a grouped GEMM and the matrix cores are the bound.
 // Kernel design (gfx950):
-//   - a block of 8 wavefronts owns 128 rows of one expert x 256 output columns (of both W1 and W3
-//     in the fused kernel); a wavefront owns two n-tiles (16 columns each) for all 128 rows, so a
-//     tile of weights unpacked once in registers (unpack.h) feeds all the rows;
+//   - a block of 4 wavefronts owns 128 rows of one expert x 128 output columns (of both W1 and W3 in
+//     the fused kernel; 128 or 256 columns of W2); a wavefront owns two n-tiles (16 columns each; four
+//     of W2) for all 128 rows, so a tile of weights unpacked once in registers (unpack.h) feeds all
+//     the rows.  Two blocks share a CU (80 KB of LDS and one wavefront per SIMD each): what a block
+//     waits for on its own (its first loads, the barriers, its epilogue) is time the other one
+//     multiplies in.  With one block of 8 wavefronts per CU that time was lost: the fused launch took
+//     272 us and W2 194 on the Qwen3 shape at T = 4096 (8 and 3 k-steps per block), 248 and 150 so;
+//     a long K (Mixtral, 16 and 56 k-steps) gains 2 %: there the chip's power sets the clock (1.6 GHz
+//     instead of 2.3 with nothing but the products left in the loop);
 //   - the products run on v_mfma_f32_32x32x16_f16 (the same peak rate as the 16x16x32 shape, half
-//     as many MFMA and LDS-read instructions per flop, and on this chip the matrix pipe and the
-//     vector ALU share the wavefront's issue slots, so instructions saved are time saved): two
-//     streams of 16 output columns that meet the same activations (W1 and W3 of one n-tile, or two
-//     n-tiles of W2) become the 32 rows of one A operand by a swap of 16-lane rows between their
-//     registers, which puts the same inputs of both streams side by side; the activations are
-//     staged as fragments of 32 rows;
-//   - the packed weights never touch LDS: each wavefront streams its tiles HBM -> registers through
-//     a two-slot ring of buffer loads (a load past the end of the resource returns zeros, so the
-//     refills are unconditional and the waits static);
-//   - the activations of one k-step (128 rows x 256 columns, 64 KB, MFMA operand order) are
-//     double-buffered in LDS: the copy of the next k-step goes from global memory straight to LDS
-//     (no registers) while the current one is multiplied; one barrier per k-step;
-//   - the rank-r term rides the same stream as extra steps: the B factor's 32-wide units take the
-//     place of the codes in a ring slot and meet (in A), which a small kernel of the same shape
-//     (xa_tile_kernel: fp16 factor tiles instead of packed codes) has left in global memory.
+//     as many MFMA and LDS-read instructions per flop): two streams of 16 output columns that meet
+//     the same activations (W1 and W3 of one n-tile, or two n-tiles of W2) become the 32 rows of one
+//     A operand by a swap of 16-lane rows between their registers, which puts the same inputs of both
+//     streams side by side; the activations are staged as fragments of 32 rows;
+//   - the packed weights never touch LDS: each wavefront loads its tiles HBM -> registers, the next
+//     k-step's into the registers of the current one as soon as its last code is unpacked (a second
+//     set of registers does not fit beside 128 accumulators at 3 and 4 bits);
+//   - the activations of half a k-step (128 rows x 128 columns, 32 KB, MFMA operand order) are
+//     double-buffered in LDS: the copy of the next half goes from memory straight to LDS (no
+//     registers) while the current one is multiplied; one barrier per half;
+//   - the rank-r term is extra steps: the B factor's 32-wide units take the place of the codes and
+//     meet (in A), which a small kernel of the same shape (xa_tile_kernel: fp16 factor tiles instead
+//     of packed codes) has left in global memory; its first fragments are copied into LDS at the start.
 // Experts with few rows (decode) take the other flavour, ffn_decode.hip.
 #include <algorithm>
 #include <type_traits>
@@ -40,10 +44,13 @@ namespace {
 
 using namespace ffn;
 
-constexpr int kTileWaves = 8;             // wavefronts per block
+constexpr int kTileWaves = 8;             // wavefronts per block of the (in A) kernel
+constexpr int kGemmWaves = 4;             // wavefronts per block of the grouped GEMM (two blocks per CU)
 constexpr int kBM = 128;                  // rows of an expert per block
 constexpr int kTMT = kBM / 16;            // row tiles
 constexpr int kStepUnits = kTMT * 8 * 64; // 16-byte units of one k-step of activations (64 KB)
+constexpr int kHalfUnits = kStepUnits / 2;
+constexpr int kGemmLdsUnits = 5120;       // LDS of a grouped-GEMM block: 80 KB, half of a CU's
 // Work item `item` of a launch -> (expert, first row of its 128-row chunk).  Routed experts: the
 // items enumerate the chunks of the experts in order (an expert with cnt rows has ceil(cnt / 128));
 // shared experts: every expert has the same T rows.
@@ -101,7 +108,6 @@ __device__ inline void stage_step_rows(const KArgs& a, uint4* buf, int ks, const
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
 constexpr int kRP = kBM / 32;             // 32-row fragments ("row pairs") of a chunk
-constexpr int kTileLdsAhead = 2;          // LDS fragment reads in flight ahead of the MFMAs (1 to 4 measured alike)
 
 // fn(std::integral_constant<int, 0>{}) ... fn(std::integral_constant<int, N - 1>{})
 template <int... I, class Fn> __device__ inline void static_for_impl(std::integer_sequence<int, I...>, Fn&& fn) {
@@ -109,34 +115,44 @@ template <int... I, class Fn> __device__ inline void static_for_impl(std::intege
 }
 template <int N, class Fn> __device__ inline void static_for(Fn&& fn) { static_for_impl(std::make_integer_sequence<int, N>{}, fn); }
 
-// The same k-step as fragments for the 32x32x16 products: fragment (row pair rp, sub-step s, operand p)
-// at unit ((rp * 8 + s) * 2 + p) * 64; lane l holds, of row 32 rp + l % 32, the 8 inputs of lane
-// group q = p + 2 (l / 32) of sub-step s.  (After the row swap, operand p of a sub-step holds in
-// lanes 0..31 the weights of lane group q = p and in lanes 32..63 those of q = p + 2.)  Wavefront w
-// of the block's WAVES copies the fragments of sub-steps s = w, w + WAVES, ...
-// Only the first rp_n row pairs are copied (the others hold no rows of the expert and are not read);
-// `rows` of the chunk's rows are the expert's.
-template <int WAVES>
-__device__ inline void stage_step32(const KArgs& a, uint4* buf, int ks, int rin, int rows, int rp_n, int wave, int lane) {
-  const uint4* in_units = reinterpret_cast<const uint4*>(a.in);
-  const int n = lane & 31, h = lane >> 5;
-#pragma unroll
-  for (int s0 = 0; s0 < 8; s0 += WAVES) {
-    const int s = s0 + wave;
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const int k8 = min(ks * 32 + (p + 2 * h) * 8 + s, a.K / 8 - 1);
-#pragma unroll
-      for (int rp = 0; rp < kRP; ++rp) {
-        if (rp >= rp_n) continue;
-        // (a row past the chunk's last one: one of the zero rows at the end of the buffer, see staged_row)
-        const int R = 32 * rp + n < rows ? rin + 32 * rp + n : a.in_rt - dec::kZeroRows + (n & 15);
-        __builtin_amdgcn_global_load_lds(
-            reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(in_units + act_unit(k8, R, a.in_rt))),
-            reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(buf + ((rp * 8 + s) * 2 + p) * 64)), 16, 0, 0);
-      }
-    }
-  }
+// Half a k-step (sub-steps 4 half .. 4 half + 3) as fragments for the 32x32x16 products: fragment (row
+// pair rp, sub-step s, operand p) at unit ((rp * 4 + s % 4) * 2 + p) * 64; lane l holds, of row
+// 32 rp + l % 32, the 8 inputs of lane group q = p + 2 (l / 32) of sub-step s.  (After the row swap,
+// operand p of a sub-step holds in lanes 0..31 the weights of lane group q = p and in lanes 32..63
+// those of q = p + 2.)  Wavefront w of the block's four copies the fragments of sub-step 4 half + w.
+// Only the first rp_n row pairs are copied (the others hold no rows of the expert and are not read).
+// A lane's address is a wave-uniform base (k-step, sub-step, operand, first row of the chunk) plus a
+// 32-bit offset that is the same for every k-step: `full` for the row pairs before the last one
+// (512 bytes apart), `last` for the last one, whose rows past the chunk's last one read the zero rows
+// at the end of the buffer (see staged_row).
+struct StageOffsets { uint32_t full, last; };
+__device__ inline StageOffsets stage_offsets(const KArgs& a, int rin, int rows, int rp_n, int lane) {
+  const int n = lane & 31, R = 32 * (rp_n - 1) + n;
+  const uint32_t q2 = (lane >> 5) ? 2u * uint32_t(a.in_rt) : 0u;      // lane group q = p + 2 (l / 32)
+  return {(q2 + uint32_t(n)) * 16u, (q2 + uint32_t(R < rows ? R : a.in_rt - dec::kZeroRows + (n & 15) - rin)) * 16u};
+}
+template <int RPN>
+__device__ inline void stage_half(const KArgs& a, uint4* buf, int ks, int half, int rin, const StageOffsets& so, int wave, int lane) {
+  const int s = 4 * half + wave;
+  const uint32_t group = uint32_t(a.in_rt) * 16u;       // bytes of one lane group's units
+  const uint8_t* base = reinterpret_cast<const uint8_t*>(a.in) + (size_t(ks) * 8 + s) * 4 * group + size_t(rin) * 16;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, 0xffffffffu, 0x00020000);
+  const int qv = a.K / kLaneK - 4 * ks;                 // lane groups of this k-step that lie below K
+  static_for<2>([&](auto P) {
+    constexpr int p = decltype(P)::value;
+    // K is a multiple of 64: past it the padded weights are exact zeros and any finite activation will
+    // do; lanes that would read there take a lane group below K instead
+    uint32_t back = (p + 2 < qv || lane < 32) ? 0u : 2u * group;
+    asm volatile("" : "+v"(back));                      // (made here, not kept in registers for every case)
+    const int soff = p < qv ? int(p * group) : 0;
+    const int full = int(so.full - back), last = int(so.last - back);
+    static_for<RPN>([&](auto Rp) {
+      constexpr int rp = decltype(Rp)::value;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(buf + ((rp * 4 + wave) * 2 + p) * 64)), 16,
+          rp == RPN - 1 ? last : full, rp == RPN - 1 ? soff : soff + rp * 512, 0, 0);   // (an immediate offset would move the LDS address too)
+    });
+  });
 }
 
 // (in A) fragments of a rank step for the 32x32x16 products: V variants per rank step (4 fused, 2
@@ -153,25 +169,23 @@ __device__ inline void rank_frag_source(int v, int lane, bool dual, int& m, int&
 // Codes and metadata of one k-step of a wavefront's two n-tiles.
 template <int BITS, int NM, int NTW> struct Slot2 { Slot<BITS, NM> t[NTW]; };
 
-// WAVES wavefronts per block.  8 (two per SIMD, 256 registers each) is what the launches use: with 4
-// (one per SIMD with 512 registers and twice the n-tiles, so that a fragment read from LDS feeds
-// twice the MFMAs) the fused kernel measured 19 % slower: nothing fills a wavefront's waits.
 // Q3: some factor pair of the layer is held at 3 bits (layout.h): the rank steps of such a pair fetch
 // the unit's code dword and the lane's half of the unit's metadata with loads of their own, one rank
-// step ahead (the ring and the k-loop are those of the plain kernel), and dequantize them into the
+// step ahead (the k-loop is that of the plain kernel), and dequantize them into the
 // fp16 unit before it is used.
-template <int BITS, bool DUAL, int NTW, int WAVES = kTileWaves, bool Q3 = false>
-__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_kernel(KArgs a) {
-  extern __shared__ uint4 xs[];           // two k-steps of activations; afterwards the (in A) fragments
+template <int BITS, bool DUAL, int NTW, bool Q3 = false>
+__global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a) {
+  extern __shared__ uint4 xs[];           // two halves of a k-step of activations, then (in A) fragments
+  constexpr int WAVES = kGemmWaves;
   constexpr int NM = DUAL ? 2 : 1;
   constexpr int kNTW = NTW;                              // n-tiles per wavefront
   constexpr int DW = 2 * BITS;
   constexpr int NC = Extract<BITS>::kClasses;
-  constexpr int LPS = BITS == 2 ? 2 : 3;                 // loads per tile and projection
-  constexpr int kSlotOps = kNTW * NM * LPS;              // loads of one ring slot
   Chunk ch;
   if (!find_chunk(a, blockIdx.y, ch)) return;
-  const int e = ch.e, r0 = ch.r0, cnt = ch.cnt, r = ch.r;
+  // (found by shuffles, the same in every lane: moved into scalar registers, and with them every base address)
+  const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
+  const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
   const ExpertDesc& d = a.desc[e];
   const int th = threadIdx.x, lane = th & 63;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
@@ -185,7 +199,6 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
   // every projection has the rank of its own factor pair (Section 3.1): the expert runs the rank
   // steps of the larger one, a resource of the size its rank fills makes the other read zeros
   int LSm[NM];
-  const int bf_bytes = a.NT * a.ls * 1024;
   __amdgpu_buffer_rsrc_t code_rs[NM], meta_rs[NM], bf_rs[NM];
   bool q3m[NM];
   float lam[NM];
@@ -196,7 +209,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
     q3m[m] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
     code_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(uniform_ptr(d.codes[mat])), 0, code_bytes, 0x00020000);
     meta_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(uniform_ptr(d.meta[mat])), 0, meta_bytes, 0x00020000);
-    // (a 3-bit pair does not ride the ring: its rank steps read zeros here and fetch their units themselves)
+    // (a 3-bit pair's rank steps read zeros here and fetch their units themselves)
     bf_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(uniform_ptr(d.bf[mat])), 0,
                                                  q3m[m] ? 0 : a.NT * LSm[m] * 1024, 0x00020000);
     lam[m] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(d.inv_lambda[mat])));
@@ -205,30 +218,42 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
   const int gps = kTileK >> a.group_shift;               // groups per k-step
   const int meta_lane = ((q * kLaneK) >> a.group_shift) * (a.NT * kTileN * 4) + c * 4;
 
-  // step < KS: the packed tiles of k-step `step`; KS <= step < KS + LS: the B-factor units of rank
-  // step (step - KS); anything else (and an n-tile past the last) reads zeros past the resources
+  // The packed tiles of a k-step: one 32-bit lane offset per kind of load, everything else scalar.
+  // (An n-tile past the last one is clamped: its columns are never stored.)
+  const int lane16 = lane * 16, lane1 = 1024 + lane * (BITS == 3 ? 8 : 16);
   auto fetch = [&](int step, Slot2<BITS, NM, kNTW>& sl) {
 #pragma unroll
     for (int t = 0; t < kNTW; ++t) {
-      const int tile = tile0 + t;
-      const bool ok = step < a.KS && tile < a.NT;
-      const bool lr = step >= a.KS && step < a.KS + LS && tile < a.NT;
-      const int tile_off = (ok ? (step * a.NT + tile) * (tdw * 4) : lr ? ((step - a.KS) * a.NT + tile) * 1024 : max(code_bytes, bf_bytes)) + lane * 16;
-      const int tile_off2 = (ok ? (step * a.NT + tile) * (tdw * 4) : code_bytes) + 1024 + lane * (BITS == 3 ? 8 : 16);
-      const int meta_off = (ok ? (step * gps * a.NT + tile) * (kTileN * 4) : meta_bytes) + meta_lane;
+      const int tile = min(tile0 + t, a.NT - 1);
+      const int tile_off = (step * a.NT + tile) * (tdw * 4), meta_off = (step * gps * a.NT + tile) * (kTileN * 4);
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         Slot<BITS, NM>& s1 = sl.t[t];
-        const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(lr ? bf_rs[m] : code_rs[m], tile_off, 0, 0);
+        const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], lane16, tile_off, 0);
         s1.cw[m][0] = v0[0]; s1.cw[m][1] = v0[1]; s1.cw[m][2] = v0[2]; s1.cw[m][3] = v0[3];
         if constexpr (BITS == 3) {
-          const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(code_rs[m], tile_off2, 0, 0);
+          const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(code_rs[m], lane1, tile_off, 0);
           s1.cw[m][4] = v1[0]; s1.cw[m][5] = v1[1];
         } else if constexpr (BITS == 4) {
-          const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], tile_off2, 0, 0);
+          const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], lane1, tile_off, 0);
           s1.cw[m][4] = v1[0]; s1.cw[m][5] = v1[1]; s1.cw[m][6] = v1[2]; s1.cw[m][7] = v1[3];
         }
-        s1.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(meta_rs[m], meta_off, 0, 0);
+        s1.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(meta_rs[m], meta_lane, meta_off, 0);
+      }
+    }
+  };
+  // The B-factor units of a rank step: range-checked lane offsets, so that a stream past its own rank
+  // (and one whose pair is held at 3 bits) reads zeros.
+  auto fetch_rank = [&](int st, Slot2<BITS, NM, kNTW>& sl) {
+#pragma unroll
+    for (int t = 0; t < kNTW; ++t) {
+      int unit = st * a.NT + min(tile0 + t, a.NT - 1);
+      asm volatile("" : "+s"(unit));       // (the offsets are made here, not kept in registers through the k-steps)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(bf_rs[m], unit * 1024 + lane16, 0, 0);
+        Slot<BITS, NM>& s1 = sl.t[t];
+        s1.cw[m][0] = v0[0]; s1.cw[m][1] = v0[1]; s1.cw[m][2] = v0[2]; s1.cw[m][3] = v0[3];
       }
     }
   };
@@ -256,47 +281,45 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
     else { t = 2 * j + side; m = 0; }
   };
 
-  // One k-step for a chunk with RPN row pairs that hold rows.  A sub-step (32 inputs per lane
-  // group) has F = 2 RPN fragments of activations, operand p major; fragment g of the k-step's
-  // 8 F is read from LDS kPF fragments ahead of its two MFMAs (one per pair), and the weights of
-  // the next sub-step are unpacked, a piece per fragment, behind the MFMAs of the current one, so
+  // Half a k-step (four sub-steps) for a chunk with RPN row pairs that hold rows.  A sub-step (32
+  // inputs per lane group) has F = 2 RPN fragments of activations, operand p major; fragment g of the
+  // half's 4 F is read from LDS kPF fragments ahead of its two MFMAs (one per pair), and the weights
+  // of the next sub-step are unpacked, a piece per fragment, behind the MFMAs of the current one, so
   // that the matrix pipe, the LDS reads and the unpacking run side by side within a wavefront.
-  constexpr int kPF = kTileLdsAhead;
-  auto compute = [&](auto RPN_, const Slot2<BITS, NM, kNTW>& cur, const uint4* buf) {
-    constexpr int RPN = decltype(RPN_)::value;
-    constexpr int F = 2 * RPN, G = 8 * F;
-    uint32_t s2[kNTW][NM][NC], c2[kNTW][NM];
+  constexpr int kPF = BITS == 2 ? 2 : 1;   // (1 to 4 measure alike; 3 and 4 bits need the registers)
+  uint32_t sc[kNTW][NM][NC];               // the slot's metadata, one dword per field class
+  uint32_t v[NPAIR][2][4];                 // operand registers of the next sub-step, before the swap
+  constexpr int PIECES = NPAIR * 4;
+  auto unpack_piece = [&](const Slot2<BITS, NM, kNTW>& sl, int s, int piece) {
+    const int j = piece / 4, i = piece % 4;
 #pragma unroll
-    for (int t = 0; t < kNTW; ++t)
-#pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        const uint32_t mw = cur.t[t].mw[m];
-        s2[t][m][0] = (mw & 0xffffu) | (mw << 16);
-        c2[t][m] = (mw >> 16) | (mw & 0xffff0000u);
-        constexpr uint32_t step = Extract<BITS>::kStepBits == 2 ? 0x44004400u : 0x48004800u;   // 4.0 or 8.0
-#pragma unroll
-        for (int p = 1; p < NC; ++p) s2[t][m][p] = pk_mul(s2[t][m][p - 1], step);
-      }
-    const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>(buf + lane));
-    // LDS byte offset of fragment g: sub-step g / F, operand (g % F) / RPN, row pair (g % F) % RPN
-    auto frag_off = [](int g) constexpr { return (g / F) * 2048 + ((g % F) % RPN) * 16384 + ((g % F) / RPN) * 1024; };
+    for (int side = 0; side < 2; ++side) {
+      int t, m;
+      pair_stream(j, side, t, m);
+      v[j][side][i] = dequant(Extract<BITS>::field(sl.t[t].cw[m], 4 * s + i), sc[t][m][Extract<BITS>::cls(4 * s + i)]);
+    }
+  };
+  auto compute = [&](auto RPN_, auto HALF_, Slot2<BITS, NM, kNTW>& sl, auto&& request) {
+    constexpr int RPN = decltype(RPN_)::value, HALF = decltype(HALF_)::value;
+    constexpr int F = 2 * RPN, G = 4 * F;
+    const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>(xs + lane));
+    // LDS byte offset of fragment g of the half: sub-step g / F, operand (g % F) / RPN, row pair (g % F) % RPN
+    auto frag_off = [](int g) constexpr { return HALF * kHalfUnits * 16 + (g / F) * 2048 + ((g % F) % RPN) * 8192 + ((g % F) / RPN) * 1024; };
     half8_t xf[kPF + 1];
     static_for<(kPF < G ? kPF : G)>([&](auto g) { xf[g] = lds_read16<frag_off(g)>(base); });
-    // piece (j, i) of a sub-step: operand register i of the two streams of pair j, before the swap
-    uint32_t v[NPAIR][2][4];
-    auto unpack_piece = [&](int s, int piece) {
-      const int j = piece / 4, i = piece % 4;
+    if constexpr (HALF == 0) {             // the slot's metadata and its first sub-step
 #pragma unroll
-      for (int side = 0; side < 2; ++side) {
-        int t, m;
-        pair_stream(j, side, t, m);
-        v[j][side][i] = pk_fma(Extract<BITS>::field(cur.t[t].cw[m], 4 * s + i), s2[t][m][Extract<BITS>::cls(4 * s + i)], c2[t][m]);
-      }
-    };
-    constexpr int PIECES = NPAIR * 4;
-    static_for<PIECES>([&](auto pc) { unpack_piece(0, pc); });
-    static_for<8>([&](auto S) {
-      constexpr int s = decltype(S)::value;
+      for (int t = 0; t < kNTW; ++t)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          sc[t][m][0] = sl.t[t].mw[m];
+#pragma unroll
+          for (int p = 1; p < NC; ++p) sc[t][m][p] = meta_class<BITS>(sc[t][m][p - 1]);
+        }
+      static_for<PIECES>([&](auto pc) { unpack_piece(sl, 0, pc); });
+    }
+    static_for<4>([&](auto S) {
+      constexpr int sl4 = decltype(S)::value, s = 4 * HALF + sl4;
       // rows of 16 lanes swapped between the two streams of a pair: operand 0 = lane groups q = 0, 2
       // of both streams side by side, operand 1 = q = 1, 3
       uint32_t A[2][NPAIR][4];
@@ -307,9 +330,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
           const auto sw = __builtin_amdgcn_permlane16_swap(v[j][0][i], v[j][1][i], false, false);
           A[0][j][i] = sw[0]; A[1][j][i] = sw[1];
         }
+      if constexpr (s == 7) request();     // (every code of the slot has been unpacked: the next k-step's take its registers)
       __builtin_amdgcn_sched_barrier(0);
       static_for<F>([&](auto Fi) {
-        constexpr int f = decltype(Fi)::value, g = s * F + f, p = f / RPN, rp = f % RPN;
+        constexpr int f = decltype(Fi)::value, g = sl4 * F + f, p = f / RPN, rp = f % RPN;
         if constexpr (g + kPF < G) xf[(g + kPF) % (kPF + 1)] = lds_read16<frag_off(g + kPF)>(base);
         lds_wait<(G - 1 - g < kPF ? G - 1 - g : kPF)>(xf[g % (kPF + 1)]);
 #pragma unroll
@@ -319,42 +343,63 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
         }
         if constexpr (s < 7) {
 #pragma unroll
-          for (int pc = PIECES * f / F; pc < PIECES * (f + 1) / F; ++pc) unpack_piece(s + 1, pc);
+          for (int pc = PIECES * f / F; pc < PIECES * (f + 1) / F; ++pc) unpack_piece(sl, s + 1, pc);
         }
         __builtin_amdgcn_sched_barrier(0);
       });
     });
   };
 
-  // ---- prologue: the first k-step of activations and the first two ring slots
-  Slot2<BITS, NM, kNTW> ring[2];
-  stage_step32<WAVES>(a, xs, 0, rin, cnt - r, rp_n, wave, lane);
-  __builtin_amdgcn_sched_barrier(0);
-  fetch(0, ring[0]);
-  fetch(1, ring[1]);
-  // only the packed tiles are still in flight when the barrier is passed (written out: a
-  // __syncthreads() would first wait for every load in flight)
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * kSlotOps) : "memory");
+  // ---- prologue: the first half k-step of activations, the first tiles, and the (in A) fragments of
+  //      the first rank steps.  (in A) of the chunk's rows is fp16 row-major in global memory
+  //      (xa_tile_kernel has scaled it and zeroed the rows without the term); fragment (rank step st,
+  //      variant v, row pair rp) sits at unit ((st * V + v) * 4 + rp) * 64 of its region
+  //      (rank_frag_source).  The 16 KB behind the activations hold kRankFirst rank steps: ranks up
+  //      to 32 (fused) or 64; later ones take the place of the activations, kRankChunk at a time.
+  constexpr int V = DUAL ? 4 : 2;
+  constexpr int kRankFirst = (kGemmLdsUnits - 2 * kHalfUnits) / (V * kRP * 64), kRankChunk = 2 * kHalfUnits / (V * kRP * 64);
+  auto stage_rank = [&](uint4* region, int c0, int c1) {
+    const _Float16* P = reinterpret_cast<const _Float16*>(a.p);
+    const int pitch = NM * a.ls * 32;                                // halves per row
+    for (int f = wave; f < (c1 - c0) * V * kRP; f += WAVES) {
+      const int rp = f % kRP, g = f / kRP, vi = g % V, sl = g / V;
+      int m, grp;
+      rank_frag_source(vi, lane, DUAL, m, grp);
+      const int row = min(r0 + r + 32 * rp + (lane & 31), a.total_rows - 1);
+      const _Float16* src = P + size_t(row) * pitch + m * a.ls * 32 + 32 * (c0 + sl) + 8 * grp;
+      __builtin_amdgcn_global_load_lds(
+          reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(src)),
+          reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(region + ((size_t(sl) * V + vi) * kRP + rp) * 64)), 16, 0, 0);
+    }
+  };
+  const StageOffsets so = stage_offsets(a, rin, cnt - r, rp_n, lane);
+  Slot2<BITS, NM, kNTW> cur;
+  fetch(0, cur);
+  if (rp_n == 4) stage_half<4>(a, xs, 0, 0, rin, so, wave, lane);
+  else if (rp_n == 3) stage_half<3>(a, xs, 0, 0, rin, so, wave, lane);
+  else if (rp_n == 2) stage_half<2>(a, xs, 0, 0, rin, so, wave, lane);
+  else stage_half<1>(a, xs, 0, 0, rin, so, wave, lane);
+  if (LS > 0) stage_rank(xs + 2 * kHalfUnits, 0, min(LS, kRankFirst));
+  wait_loads_barrier();
 
-  // ---- the k-steps, two per trip so that the ring slots are indexed statically.  In a step: the
-  //      copy of the next step's activations is issued into the other half of LDS (free since the
-  //      barrier that ended the previous step), the current step is multiplied, its slot refilled;
-  //      then only that refill may still be in flight (the copy has landed) and the barrier ends
-  //      the step.  One copy of the loop per number of row pairs, so that every count is static.
+  // ---- the k-steps, in halves: while one half of the activations is multiplied, the next half is
+  //      copied into the other half of the buffer (free since the last barrier); the next k-step's
+  //      tiles are requested at the start of a k-step.  One copy of the loop per number of row pairs,
+  //      so that every count is static.
   const int steps = a.KS;
   auto k_loop = [&](auto RPN_) {
-    for (int s0 = 0; s0 < steps; s0 += 2) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int step = s0 + i;
-        if (step < steps) {
-          stage_step32<WAVES>(a, xs + ((step + 1) & 1) * kStepUnits, step + 1, rin, cnt - r, decltype(RPN_)::value, wave, lane);
-          __builtin_amdgcn_sched_barrier(0);     // (the wait below counts the refill as the only later loads)
-          compute(RPN_, ring[i], xs + (step & 1) * kStepUnits);
-          fetch(step + 2, ring[i]);
-          asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kSlotOps) : "memory");
-        }
-      }
+    constexpr int RPN = decltype(RPN_)::value;
+    for (int step = 0; step < steps; ++step) {
+      stage_half<RPN>(a, xs + kHalfUnits, step, 1, rin, so, wave, lane);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(RPN_, std::integral_constant<int, 0>{}, cur, [] {});
+      wait_loads_barrier();
+      if (step + 1 < steps) stage_half<RPN>(a, xs, step + 1, 0, rin, so, wave, lane);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(RPN_, std::integral_constant<int, 1>{}, cur, [&] {
+        if (step + 1 < steps) fetch(step + 1, cur);
+      });
+      wait_loads_barrier();
     }
   };
   if (rp_n == 4) k_loop(std::integral_constant<int, 4>{});
@@ -362,12 +407,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
   else if (rp_n == 2) k_loop(std::integral_constant<int, 2>{});
   else k_loop(std::integral_constant<int, 1>{});
 
-  // ---- rank steps.  (in A) of the chunk's rows, fp16 row-major in global memory (xa_tile_kernel
-  //      has scaled it and zeroed the rows without the term), is copied into LDS as fragments of 32
-  //      rows, kRankChunk rank steps at a time (all of them for ranks up to 256): fragment (rank step
-  //      st, variant v, row pair rp) at unit (((st - c0) * V + v) * 4 + rp) * 64 (rank_frag_source).
-  constexpr int V = DUAL ? 4 : 2;
-  constexpr int kRankChunk = 2 * kStepUnits / (V * kRP * 64);       // 8 (fused) or 16 rank steps fill the 128 KB
+  // ---- rank steps ----
   // 3-bit pairs: the code dword and the lane's half of the metadata (layout.h) of every stream's unit
   // of one rank step; zeros for fp16 pairs, past the stream's own rank and past the last n-tile
   struct QUnits { uint32_t codes[kNTW][NM]; uint32_t meta[kNTW][NM][4]; };
@@ -392,25 +432,16 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
       }
   };
   QUnits qnext;
-  for (int c0 = 0; c0 < LS; c0 += kRankChunk) {
-    const int c1 = min(LS, c0 + kRankChunk);
-    q_load(c0, qnext);                       // (arrives with the copies below)
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // (everyone is done with what LDS held)
-    const _Float16* P = reinterpret_cast<const _Float16*>(a.p);
-    const int pitch = NM * a.ls * 32;                                // halves per row
-    for (int f = wave; f < (c1 - c0) * V * kRP; f += WAVES) {
-      const int rp = f % kRP, g = f / kRP, v = g % V, sl = g / V;
-      int m, grp;
-      rank_frag_source(v, lane, DUAL, m, grp);
-      const int row = min(r0 + r + 32 * rp + (lane & 31), a.total_rows - 1);
-      const _Float16* src = P + size_t(row) * pitch + m * a.ls * 32 + 32 * (c0 + sl) + 8 * grp;
-      __builtin_amdgcn_global_load_lds(
-          reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(src)),
-          reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(xs + ((size_t(sl) * V + v) * kRP + rp) * 64)), 16, 0, 0);
+  if (LS > 0) fetch_rank(0, cur);
+  for (int c0 = 0, c1; c0 < LS; c0 = c1) {
+    c1 = min(LS, c0 == 0 ? kRankFirst : c0 + kRankChunk);
+    const uint4* region = c0 == 0 ? xs + 2 * kHalfUnits : xs;
+    q_load(c0, qnext);
+    if (c0 > 0) {
+      __syncthreads();                       // (everyone is done with what the buffer held)
+      stage_rank(xs, c0, c1);
+      wait_loads_barrier();
     }
-    // (the ring slots are refilled below, after this wait: only the copies just issued and the two
-    // slots requested before them are outstanding)
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     // the fp16 B-factor unit of stream (t, m) of a rank step: from the slot, or rebuilt from a 3-bit unit
     auto b_unit = [&](const Slot2<BITS, NM, kNTW>& cur, const QUnits& qu, int t, int m, uint32_t (&u)[4]) {
 #pragma unroll
@@ -457,44 +488,36 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
 #pragma unroll
           for (int rp = 0; rp < kRP; ++rp)
             if (rp < rp_n) {
-              const half8_t pf = __builtin_bit_cast(half8_t, xs[((size_t(st - c0) * V + v) * kRP + rp) * 64 + lane]);
+              const half8_t pf = __builtin_bit_cast(half8_t, region[((size_t(st - c0) * V + v) * kRP + rp) * 64 + lane]);
               acc[j][rp] = __builtin_amdgcn_mfma_f32_32x32x16_f16(avh, pf, acc[j][rp], 0, 0, 0);
             }
         }
       }
     };
-    // the slot of step KS + st is ring[(KS + st) % 2]: walk the chunk's steps in aligned pairs
-    for (int s0 = (steps + c0) & ~1; s0 < steps + c1; s0 += 2) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int step = s0 + i;
-        if (step >= steps + c0 && step < steps + c1) {
-          const QUnits qcur = qnext;
-          q_load(step - steps + 1 < c1 ? step - steps + 1 : LS, qnext);   // (LS: nothing to fetch)
-          rank_step(ring[i], qcur, step - steps);
-          fetch(step + 2, ring[i]);
-        }
-      }
+    for (int st = c0; st < c1; ++st) {
+      const QUnits qcur = qnext;
+      q_load(st + 1 < c1 ? st + 1 : LS, qnext);   // (LS: nothing to fetch)
+      Slot2<BITS, NM, kNTW> nxt;
+      fetch_rank(st + 1, nxt);
+      rank_step(cur, qcur, st);
+      cur = nxt;
     }
   }
 
   // ---- epilogue: lane l holds, of row 32 rp + l % 32, columns 8 g + 4 (l / 32) .. + 3 (g = 0, 1) of
   //      both streams of every pair ----
   const int hh = lane >> 5;
+  if constexpr (DUAL) {
 #pragma unroll
-  for (int j = 0; j < NPAIR; ++j)
+    for (int j = 0; j < NPAIR; ++j)
 #pragma unroll
-    for (int rp = 0; rp < kRP; ++rp) {
-      const int row = r + 32 * rp + (lane & 31);
-      if (rp >= rp_n || row >= cnt) continue;
-      const int se = a.row_exp[(a.offsets ? r0 : 0) + row];        // the row's inputs were scaled by 2^se
-      const float dn = pow2i(DUAL ? -se : -2 * se), up = pow2i(2 * se);
+      for (int rp = 0; rp < kRP; ++rp) {
+        const int row = r + 32 * rp + (lane & 31), tile = tile0 + j;
+        if (rp >= rp_n || row >= cnt || tile >= a.NT) continue;
+        const int se = a.row_exp[(a.offsets ? r0 : 0) + row];        // the row's inputs were scaled by 2^se
+        const float dn = pow2i(-se), up = pow2i(2 * se);
 #pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const int col4 = 8 * g + 4 * hh;
-        if constexpr (DUAL) {
-          const int tile = tile0 + j;
-          if (tile >= a.NT) continue;
+        for (int g = 0; g < 2; ++g) {
           half4_t hv;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -502,23 +525,43 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 1 : 2) void qgemm_tile_ker
             hv[i] = to_f16_sat(gg * __builtin_amdgcn_rcpf(1.0f + __expf(-gg)) * uu * up);
           }
           // h in operand order for the W2 kernel: columns f .. f+3 are half of one 16-byte unit
-          const int f = tile * kTileN + col4;
+          const int f = tile * kTileN + 8 * g + 4 * hh;
           *reinterpret_cast<half4_t*>(reinterpret_cast<_Float16*>(a.out) + act_unit(f >> 3, r0 + row, a.out_rt) * 8 + (f & 7)) = hv;
-        } else {
-#pragma unroll
-          for (int side = 0; side < 2; ++side) {
-            const int tile = tile0 + 2 * j + side;
-            if (tile >= a.NT) continue;
-            const size_t o = size_t(r0 + row) * a.N + tile * kTileN + col4;
-            uint2 yv;
-            const float l2 = lam[0] * dn;
-            yv.x = f32x2_to_bf16x2(acc[j][rp][8 * side + 4 * g] * l2, acc[j][rp][8 * side + 4 * g + 1] * l2);
-            yv.y = f32x2_to_bf16x2(acc[j][rp][8 * side + 4 * g + 2] * l2, acc[j][rp][8 * side + 4 * g + 3] * l2);
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + o) = yv;
-          }
         }
       }
+  } else {
+    // y_rows is row-major: a lane's four columns would be an 8-byte store per row (32 rows per
+    // instruction).  The wavefront turns its 128 x (16 kNTW) results round in its own part of the
+    // activation buffer and stores whole 16-byte pieces of 32 kNTW contiguous bytes per row.
+    constexpr int kPitch = 16 * kNTW * 2 + 16;                       // bytes per row in LDS
+    static_assert(kGemmWaves * kBM * kPitch <= kGemmLdsUnits * 16, "the results of a block must fit its LDS");
+    __syncthreads();                                                 // (everyone is done with the buffer and the (in A) fragments)
+    uint8_t* mine = reinterpret_cast<uint8_t*>(xs) + wave * (kBM * kPitch);
+#pragma unroll
+    for (int rp = 0; rp < kRP; ++rp) {
+      const int row = r + 32 * rp + (lane & 31);
+      if (rp >= rp_n) continue;
+      const int se = a.row_exp[(a.offsets ? r0 : 0) + min(row, cnt - 1)];
+      const float l2 = lam[0] * pow2i(-2 * se);
+#pragma unroll
+      for (int j = 0; j < NPAIR; ++j)
+#pragma unroll
+        for (int side = 0; side < 2; ++side)
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            uint2 yv;
+            yv.x = f32x2_to_bf16x2(acc[j][rp][8 * side + 4 * g] * l2, acc[j][rp][8 * side + 4 * g + 1] * l2);
+            yv.y = f32x2_to_bf16x2(acc[j][rp][8 * side + 4 * g + 2] * l2, acc[j][rp][8 * side + 4 * g + 3] * l2);
+            *reinterpret_cast<uint2*>(mine + (32 * rp + (lane & 31)) * kPitch + ((2 * j + side) * 16 + 8 * g + 4 * hh) * 2) = yv;
+          }
     }
+    constexpr int kPieces = 2 * kNTW;                                // 16-byte pieces per row
+    const int piece = lane % kPieces;
+    if (tile0 + piece / 2 < a.NT)
+      for (int i = lane / kPieces; i < min(kBM, cnt - r); i += 64 / kPieces)
+        *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.out) + size_t(r0 + r + i) * a.N + tile0 * kTileN + 8 * piece) =
+            *reinterpret_cast<const uint4*>(mine + i * kPitch + 16 * piece);
+  }
 }
 
 // (in A)[row][rho] for the 128-row chunks of every expert, in two launches.
@@ -721,7 +764,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   const bool comp = f.rank > 0 && f.top_n > 0 && f.row_pair != nullptr;
   // 128-row chunks: at most one partly filled chunk per expert
   const int items = f.offsets ? f.total_rows / kBM + f.n_exp : f.n_exp * ((f.T + kBM - 1) / kBM);
-  const size_t lds = size_t(2) * kStepUnits * 16;
+  const size_t lds = size_t(2) * kStepUnits * 16, glds = size_t(kGemmLdsUnits) * 16;
 
   // (in A): fp16 result at the start of the buffer, the K-block partial sums behind it
   auto xa = [&](auto k2, auto k4, float* buf, int nm, int ksplit) {
@@ -751,8 +794,8 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   if (comp && f.q3) xa(xa_tile_kernel<true, 2, true>, xa_tile_kernel<true, 4, true>, f.p13, 2, f.ksplit13);
   else if (comp) xa(xa_tile_kernel<true, 2, false>, xa_tile_kernel<true, 4, false>, f.p13, 2, f.ksplit13);
   if (f.marks) (void)hipEventRecord(f.marks[0], s);
-  if (comp && f.q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2, kTileWaves, true>), dim3((a.NT + 15) / 16, items), dim3(64 * kTileWaves), lds, s, a);
-  else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2>), dim3((a.NT + 15) / 16, items), dim3(64 * kTileWaves), lds, s, a);
+  if (comp && f.q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
+  else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
   if (f.marks) (void)hipEventRecord(f.marks[1], s);
   }
   if (which & 2) {
@@ -767,14 +810,14 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   // blocks twice as large: take the one with fewer (weighted) rounds of blocks over the 256 CUs
   // (expected number of chunks: about half of the experts end with a partly filled one)
   const int chunks = std::max(1, f.offsets ? f.total_rows / kBM + (f.n_exp + 1) / 2 : f.n_exp * ((f.T + kBM - 1) / kBM));
-  auto rounds = [&](int ntw) { return (chunks * ((a.NT + 8 * ntw - 1) / (8 * ntw)) + f.n_cu - 1) / f.n_cu * ntw; };
+  auto rounds = [&](int ntw) { return (chunks * ((a.NT + kGemmWaves * ntw - 1) / (kGemmWaves * ntw)) + 2 * f.n_cu - 1) / (2 * f.n_cu) * ntw; };
   const bool q3 = comp && f.q3;
   if (rounds(4) * 100 <= rounds(2) * 108) {
-    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4, kTileWaves, true>), dim3((a.NT + 31) / 32, items), dim3(64 * kTileWaves), lds, s, a);
-    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4>), dim3((a.NT + 31) / 32, items), dim3(64 * kTileWaves), lds, s, a);
+    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4, true>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
+    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
   } else {
-    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2, kTileWaves, true>), dim3((a.NT + 15) / 16, items), dim3(64 * kTileWaves), lds, s, a);
-    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2>), dim3((a.NT + 15) / 16, items), dim3(64 * kTileWaves), lds, s, a);
+    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
+    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
   }
   if (f.marks) (void)hipEventRecord(f.marks[3], s);
   }
@@ -805,11 +848,11 @@ template <int BITS> static hipError_t tile_init_bits() {
   const void* fns[6] = {reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, true, 2>),
                         reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, false, 4>),
                         reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, false, 2>),
-                        reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, true, 2, kTileWaves, true>),
-                        reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, false, 4, kTileWaves, true>),
-                        reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, false, 2, kTileWaves, true>)};
+                        reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, true, 2, true>),
+                        reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, false, 4, true>),
+                        reinterpret_cast<const void*>(&qgemm_tile_kernel<BITS, false, 2, true>)};
   for (const void* fn : fns) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kStepUnits * 16);
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLdsUnits * 16);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

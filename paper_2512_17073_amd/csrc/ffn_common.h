@@ -25,6 +25,20 @@ __device__ inline uint32_t pk_mul(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, r);
 }
 
+// A field (unpack.h) and its metadata dword (scale in the low half, offset in the high half, layout.h)
+// -> two dequantized weights, one packed FMA: both halves take the one scale and the one offset by
+// operand selection, so the dword is used as it was loaded.
+__device__ inline uint32_t dequant(uint32_t field, uint32_t mw) {
+  const half2_t m = __builtin_bit_cast(half2_t, mw);
+  const half2_t r = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, field), __builtin_shufflevector(m, m, 0, 0),
+                                              __builtin_shufflevector(m, m, 1, 1));
+  return __builtin_bit_cast(uint32_t, r);
+}
+// the metadata for fields one class lower in the mantissa (the scale times 4 or 8)
+template <int BITS> __device__ inline uint32_t meta_class(uint32_t mw) {
+  return pk_mul(mw, Extract<BITS>::kStepBits == 2 ? 0x3c004400u : 0x3c004800u);
+}
+
 struct KArgs {
   const ExpertDesc* desc;
   const int32_t* offsets;    // null: shared experts, expert e owns rows e*T .. e*T+T-1
@@ -103,11 +117,11 @@ template <int N> __device__ inline void lds_wait(half8_t& a, half8_t& b) {
 // vmcnt as out of order, and from then on every use of a loaded register waits for vmcnt(0), i.e.
 // for the refills just issued as well (the ring of loads is then one deep instead of two; a Mixtral-shaped forward at T = 64 and 2 bits
 // took 160.5 us with inline asm waits and takes 156.0 with these).
-__device__ inline void wait_loads_barrier() {
+__device__ inline void wait_loads() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), the other counters as they are
-  __syncthreads();
 }
+__device__ inline void wait_loads_barrier() { wait_loads(); __syncthreads(); }
 
 // A pointer read from memory, moved into scalar registers (a buffer resource must be wave-uniform).
 template <class T> __device__ inline const T* uniform_ptr(const T* p) {
