@@ -9,13 +9,21 @@
 //   Y = E Omega;  repeat `power_iters` times:  Y <- E (E^T orth(Y));  Q = orth(Y);  Bm = Q^T E  (l x N)
 //   SVD of the small matrix Bm by one-sided Jacobi rotations of its rows (Hestenes), which leaves
 //   rows sigma_i w_i^T and accumulates the rotations G: Bm = G diag(sigma) W^T, so U = Q G.
-// orth() is a Cholesky QR applied twice (Gram matrix, Cholesky factor, triangular solve): the
-// residual of a quantizer is close to white noise, its leading singular values are nearly flat, and
-// the Gram matrix of l such directions is well conditioned.
+// orth() is a Cholesky QR (Gram matrix, Cholesky factor, triangular solve), applied twice where
+// the result is used as an orthonormal basis and once between the passes of the iteration, where only
+// its span counts: the residual of a quantizer is close to white noise, its leading singular values
+// are nearly flat, and the Gram matrix of l such directions is well conditioned.
+// What the call cannot do without is six products with E (K x N times N x l, or transposed); they run
+// on the fp64 matrix cores (dgemm_kernel).  Everything else is small: for l <= kSmallL it stays on the
+// device without a host round trip, and the Jacobi rotations run on the l x l Cholesky factor of
+// Bm Bm^T in the LDS of one block (Bm = L Q_b^T: rotating rows of Bm and of L is the same thing)
+// instead of l - 1 launches per sweep over the l x N matrix (9.4 -> 0.26 ms at l = 40, N = 14336).  The
+// whole call at 4096 x 14336, rank 32, l = 40, two passes: 24.2 -> 1.72 ms.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -151,68 +159,467 @@ __global__ __launch_bounds__(256) void moment_kernel(const double* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------------- dense fp64 products
-// C[M][Nc] = op(A) B with op(A)[i][k] = TRANS ? A[k * lda + i] : A[i * lda + k] and B[k * ldb + j]:
-// 64 x 64 tiles of C per block of 256 threads (a 4 x 4 block of C each), k in steps of 16 through LDS,
-// sums in increasing k.  Plain vector fp64 FMAs: the products here are tall and skinny and run once.
-template <bool TRANS>
-__global__ __launch_bounds__(256) void dgemm_kernel(int M, int Nc, int Kd, const double* __restrict__ A, int lda,
-                                                    const double* __restrict__ B, int ldb, double* __restrict__ C, int ldc) {
-  __shared__ double As[16][65], Bs[16][65];
-  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  double acc[4][4] = {};
-  for (int k0 = 0; k0 < Kd; k0 += 16) {
-    if (TRANS) {
-      const int kk = t >> 4, r4 = (t & 15) * 4;
+// C[M][Nc] = op(A) B with op(A)[i][k] = TRANS ? A[k * lda + i] : A[i * lda + k] and B[k * ldb + j], on
+// v_mfma_f64_16x16x4.  The products here are tall and skinny: A is the K x N matrix, read once, and B
+// is a few megabytes, so a block of four wavefronts takes 128 rows of C and all its columns up to
+// 16 CT, a wavefront 32 rows (two tiles that share every B operand read from LDS); the reduction
+// dimension is split over grid.z so that there are about two blocks per CU, each writing its own
+// partial C (dsum_kernel adds them in order).  k advances in chunks of 32: the next chunk of A (registers) and of B
+// (registers, then the other half of LDS) is requested before the current one is multiplied.  Inside
+// a chunk, MFMA step (h, s) covers k = 16 h + 4 kq + s for lane group kq, so that a lane reads 32
+// contiguous bytes of a row of A.  TRANS: a lane reads two adjacent entries of a row of A, which are
+// rows 2 i and 2 i + 1 of the wavefront's 32: tile rt holds the rows of parity rt.
+// Bound: HBM (470 MB per product at 4096 x 14336: 80 us at the streaming rate) and the fp64 matrix rate
+// (5.6 GFLOP with 40 columns padded to 48: 80 us) about equally; measured 130-135 us per product, plain
+// or transposed, against 2520 and 730 us with 4 x 4 vector products per thread on a 64 x 64 tile and
+// no split (64 or 224 blocks); more wavefronts per SIMD change nothing.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+typedef double double2_t __attribute__((ext_vector_type(2), aligned(8)));
+constexpr int kGemmRows = 128, kGemmK = 32, kGemmBlocks = 768;
+
+// The loop over whole chunks has no branch in it (a guarded load is a branch, and the compiler then
+// waits for every load in flight before the next): the last chunk's prefetch repeats that chunk, rows
+// of a wavefront that would end past M start earlier (PAIR; for M < 32 the entries are read one by one,
+// clamped), what lies past the edges of B becomes zero on its way into LDS, and a last partial chunk is
+// read with clamped indices after the loop.
+template <bool TRANS, int CT, bool PAIR = true>
+__global__ __launch_bounds__(256, CT <= 3 ? 3 : 2) void dgemm_kernel(int M, int Nc, int Kd, int k_per, const double* __restrict__ A, int lda,
+                                                    const double* __restrict__ B, int ldb, double* __restrict__ C, int ldc,
+                                                    size_t c_stride) {
+  constexpr int kPitch = 16 * CT + 4;                  // (lane groups 4 rows apart then sit in different halves of the banks)
+  constexpr int kLoadsB = kGemmK * 16 * CT / 256;
+  __shared__ double Bs[2][kGemmK * kPitch];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), i = lane & 15, kq = lane >> 4;
+  const int m_first = blockIdx.y * kGemmRows + wave * 32, j0 = blockIdx.x * (16 * CT);
+  const int m0 = TRANS && PAIR ? max(0, min(m_first, M - 32)) : m_first;
+  const int k_lo = blockIdx.z * k_per, k_hi = min(Kd, k_lo + k_per);
+  double4_t acc[2][CT];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + r4 + u, k = k0 + kk;
-        As[kk][r4 + u] = (i < M && k < Kd) ? A[size_t(k) * lda + i] : 0.0;
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = double4_t{0.0, 0.0, 0.0, 0.0};
+  // a[rt][4 h + s]: this lane's A operand of step (h, s)
+  const double* a_row[2] = {A + size_t(min(m0 + i, M - 1)) * lda + 4 * kq, A + size_t(min(m0 + 16 + i, M - 1)) * lda + 4 * kq};   // !TRANS
+  const double* a_col = A + size_t(4 * kq) * lda + (PAIR ? m0 + 2 * i : 0);                                                  // TRANS
+  const int c0 = min(m0 + 2 * i, M - 1), c1 = min(m0 + 2 * i + 1, M - 1);
+  auto load_a = [&](int k0, double (&a)[2][8]) {           // a whole chunk
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if constexpr (TRANS) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double* row = a_col + size_t(k0 + 16 * h + u) * lda;
+          if constexpr (PAIR) {
+            const double2_t v = *reinterpret_cast<const double2_t*>(row);
+            a[0][4 * h + u] = v[0]; a[1][4 * h + u] = v[1];
+          } else {
+            a[0][4 * h + u] = row[c0]; a[1][4 * h + u] = row[c1];
+          }
+        }
+      } else {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+          const double* p = a_row[rt] + k0 + 16 * h;
+          const double2_t v = *reinterpret_cast<const double2_t*>(p), w = *reinterpret_cast<const double2_t*>(p + 2);
+          a[rt][4 * h] = v[0]; a[rt][4 * h + 1] = v[1]; a[rt][4 * h + 2] = w[0]; a[rt][4 * h + 3] = w[1];
+        }
       }
-    } else {
-      const int r = t >> 2, k4 = (t & 3) * 4;
+  };
+  auto load_a_edge = [&](int k0, double (&a)[2][8]) {      // past k_hi: any finite value, B is zero there
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + r, k = k0 + k4 + u;
-        As[k4 + u][r] = (i < M && k < Kd) ? A[size_t(i) * lda + k] : 0.0;
+    for (int u = 0; u < 8; ++u) {
+      const int k = min(k0 + 16 * (u >> 2) + 4 * kq + (u & 3), k_hi - 1);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+        a[rt][u] = TRANS ? A[size_t(k) * lda + (rt ? c1 : c0)] : A[size_t(min(m0 + 16 * rt + i, M - 1)) * lda + k];
+    }
+  };
+  auto load_b = [&](int k0, double (&b)[kLoadsB]) {
+#pragma unroll
+    for (int u = 0; u < kLoadsB; ++u) {
+      const int x = t + 256 * u, kk = x / (16 * CT), j = j0 + x % (16 * CT);
+      b[u] = B[size_t(min(k0 + kk, k_hi - 1)) * ldb + min(j, Nc - 1)];
+    }
+  };
+  auto store_b = [&](double* bs, int k0, const double (&b)[kLoadsB]) {
+#pragma unroll
+    for (int u = 0; u < kLoadsB; ++u) {
+      const int x = t + 256 * u, kk = x / (16 * CT), j = j0 + x % (16 * CT);
+      bs[kk * kPitch + x % (16 * CT)] = (k0 + kk < k_hi && j < Nc) ? b[u] : 0.0;
+    }
+  };
+  auto multiply = [&](const double (&a)[2][8], const double* buf) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double* bs = buf + (16 * (u >> 2) + 4 * kq + (u & 3)) * kPitch + i;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const double b = bs[16 * ct];
+        acc[0][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][u], b, acc[0][ct], 0, 0, 0);
+        acc[1][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][u], b, acc[1][ct], 0, 0, 0);
       }
     }
-    {
-      const int kk = t >> 4, c4 = (t & 15) * 4;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = j0 + c4 + u, k = k0 + kk;
-        Bs[kk][c4 + u] = (j < Nc && k < Kd) ? B[size_t(k) * ldb + j] : 0.0;
-      }
-    }
+  };
+  const int whole = (k_hi - k_lo) / kGemmK;
+  double a[2][8], b[kLoadsB];
+  if (whole > 0) {
+    load_a(k_lo, a);
+    load_b(k_lo, b);
+    store_b(Bs[0], k_lo, b);
     __syncthreads();
+    for (int ch = 0; ch < whole; ++ch) {
+      const int k_next = k_lo + min(ch + 1, whole - 1) * kGemmK;
+      double a_next[2][8];
+      load_a(k_next, a_next);
+      load_b(k_next, b);
+      __builtin_amdgcn_sched_barrier(0);                 // (the requests stay in front of the products)
+      multiply(a, Bs[ch & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      store_b(Bs[(ch + 1) & 1], k_next, b);
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      double a[4], b[4];
+      for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { a[u] = As[kk][ty * 4 + u]; b[u] = Bs[kk][tx * 4 + u]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
+        for (int u = 0; u < 8; ++u) a[rt][u] = a_next[rt][u];
+      __syncthreads();
     }
+  }
+  const int k_tail = k_lo + whole * kGemmK;
+  if (k_tail < k_hi) {
+    load_a_edge(k_tail, a);
+    load_b(k_tail, b);
+    store_b(Bs[whole & 1], k_tail, b);
+    __syncthreads();
+    multiply(a, Bs[whole & 1]);
+  }
+  // register r of lane (i, kq): row kq + 4 r, column i of the tile
+  double* Cz = C + blockIdx.z * c_stride;
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int rho = kq + 4 * r, m = TRANS ? m0 + 2 * rho + rt : m0 + 16 * rt + rho;
+      if (m >= m_first && m < M)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          const int j = j0 + 16 * ct + i;
+          if (j < Nc) Cz[size_t(m) * ldc + j] = acc[rt][ct][r];
+        }
+    }
+}
+
+// C[x] = sum over z (in order) of part[z][x]
+__global__ __launch_bounds__(256) void dsum_kernel(const double* __restrict__ part, int parts, size_t n, double* __restrict__ C) {
+  const size_t x = size_t(blockIdx.x) * 256 + threadIdx.x;
+  if (x >= n) return;
+  double v = part[x];
+  for (int z = 1; z < parts; ++z) v += part[size_t(z) * n + x];
+  C[x] = v;
+}
+
+// How a product is cut: column tiles per block, and parts of the reduction (at least 64 long each) so
+// that the blocks number about 512.  (A Gram matrix whose parts the factorisation adds up itself: at
+// most kGramParts of them, all in flight at once there.)
+constexpr int kGramParts = 32;
+struct GemmCut { int ct, gx, gy, parts, k_per; };
+GemmCut gemm_cut(int M, int Nc, int Kd, int max_parts = 512) {
+  GemmCut c;
+  c.ct = std::min(4, (Nc + 15) / 16);
+  c.gx = (Nc + 16 * c.ct - 1) / (16 * c.ct);
+  c.gy = (M + kGemmRows - 1) / kGemmRows;
+  const long long blocks = (long long)c.gx * c.gy;
+  const int parts = int(std::max(1LL, std::min<long long>(std::min<long long>(kGemmBlocks / std::max(1LL, blocks), max_parts), Kd / 64)));
+  c.k_per = ((Kd + parts - 1) / parts + kGemmK - 1) / kGemmK * kGemmK;
+  c.parts = (Kd + c.k_per - 1) / c.k_per;
+  return c;
+}
+size_t gemm_part_doubles(int M, int Nc, int Kd) { return size_t(gemm_cut(M, Nc, Kd).parts) * M * Nc; }
+
+// part: room for gemm_part_doubles doubles.  keep_parts: leaves the partial sums there (returns their
+// number); else C (ldc == Nc when the reduction is split) holds the product.
+template <bool TRANS>
+int dgemm(int M, int Nc, int Kd, const double* A, int lda, const double* B, int ldb, double* C, double* part, bool keep_parts = false) {
+  const GemmCut g = gemm_cut(M, Nc, Kd, keep_parts ? kGramParts : 512);
+  const bool direct = g.parts == 1 && !keep_parts;
+  double* out = direct ? C : part;
+  const dim3 grid(g.gx, g.gy, g.parts);
+  const size_t cs = size_t(M) * Nc;
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, nullptr, M, Nc, Kd, g.k_per, A, lda, B, ldb, out, Nc, cs); };
+  auto pick = [&](auto CT_) {
+    constexpr int CT = decltype(CT_)::value;
+    if constexpr (TRANS) {
+      if (M < 32) return go(dgemm_kernel<true, CT, false>);
+    }
+    go(dgemm_kernel<TRANS, CT, true>);
+  };
+  switch (g.ct) {
+    case 1: pick(std::integral_constant<int, 1>{}); break;
+    case 2: pick(std::integral_constant<int, 2>{}); break;
+    case 3: pick(std::integral_constant<int, 3>{}); break;
+    default: pick(std::integral_constant<int, 4>{}); break;
+  }
+  if (!direct && !keep_parts)
+    hipLaunchKernelGGL(dsum_kernel, dim3((unsigned)((cs + 255) / 256)), dim3(256), 0, nullptr, part, g.parts, cs, C);
+  return g.parts;
+}
+
+// ---------------------------------------------------------------------------------- small l: everything in one block's LDS
+constexpr int kSmallL = 96;              // two l x (l + 1) fp64 matrices fit the LDS of a CU
+
+// 1 / sqrt(v) for a positive normal v, from the hardware's estimate and two Newton steps
+__device__ inline double rsqrt_newton(double v) {
+  double y = __builtin_amdgcn_rsq(v);
+  y = fma(y * 0.5, fma(-v * y, y, 1.0), y);
+  return fma(y * 0.5, fma(-v * y, y, 1.0), y);
+}
+
+// Lower Cholesky factor L of the l x l matrix G = sum of `parts` partial matrices, and L^-1 (the same
+// elimination applied to the identity); *bad is set if a pivot is not positive.  One block, one barrier
+// per column: column j and row j of the inverse are read by everyone and written by nobody in step j.
+constexpr int kCholThreads = 1024;
+__global__ __launch_bounds__(kCholThreads) void cholesky_small_kernel(const double* __restrict__ part, int parts, int l,
+                                                             double* __restrict__ L, double* __restrict__ Linv, int* __restrict__ bad) {
+  extern __shared__ double sm[];
+  const int pitch = l + 1, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  double* G = sm;
+  double* X = sm + l * pitch;
+  for (int e = threadIdx.x; e < l * l; e += kCholThreads) {
+    double pv[kGramParts];
+#pragma unroll
+    for (int z = 0; z < kGramParts; ++z) pv[z] = part[size_t(min(z, parts - 1)) * l * l + e];
+    double v = pv[0];
+#pragma unroll
+    for (int z = 1; z < kGramParts; ++z) v += z < parts ? pv[z] : 0.0;
+    const int r = e / l, c = e - r * l;
+    G[r * pitch + c] = v;
+    X[r * pitch + c] = r == c ? 1.0 : 0.0;
+    L[e] = 0.0; Linv[e] = 0.0;
+  }
+  for (int j = 0; j < l; ++j) {
+    __syncthreads();
+    const double p = G[j * pitch + j];
+    if (!(p > 0.0) && threadIdx.x == 0) *bad = 1;
+    const double inv = rsqrt_newton(p > 0.0 ? p : 1.0);
+    for (int x = threadIdx.x; x < l; x += kCholThreads) {
+      if (x >= j) L[size_t(x) * l + j] = G[x * pitch + j] * inv;
+      if (x <= j) Linv[size_t(j) * l + x] = X[j * pitch + x] * inv;
+    }
+    for (int r = j + 1 + ty; r < l; r += kCholThreads / 32) {
+      const double f = G[r * pitch + j] * inv;
+#pragma unroll
+      for (int u = 0; u < kSmallL / 32; ++u) {
+        const int c = tx + 32 * u;
+        if (c > r) break;
+        double* at = c <= j ? X + r * pitch + c : G + r * pitch + c;
+        const double v = c <= j ? X[j * pitch + c] : G[c * pitch + j];
+        *at = fma(-f, v * inv, *at);
+      }
+    }
+  }
+}
+
+// out = in S for in [rows][l], S [l][cols] (ST: S is given transposed, [cols][l]); cols, l <= kSmallL.
+// A wavefront holds its 16 rows in registers before it writes: out may be in.
+template <bool ST>
+__global__ __launch_bounds__(256) void rmul_kernel(const double* in, int rows, int l, const double* __restrict__ S, int cols, double* out,
+                                                   const int* __restrict__ status) {
+  extern __shared__ double sm[];
+  if (status != nullptr && (status[0] | status[1] | status[2])) return;
+  const int ct_n = (cols + 15) / 16, ks_n = (l + 3) / 4, pitch = 16 * ct_n + 4;
+  for (int e = threadIdx.x; e < 4 * ks_n * 16 * ct_n; e += 256) {
+    const int k = e / (16 * ct_n), c = e - k * (16 * ct_n);
+    sm[k * pitch + c] = (k < l && c < cols) ? (ST ? S[size_t(c) * l + k] : S[size_t(k) * cols + c]) : 0.0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int r0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 16;
+  if (r0 >= rows) return;
+  double a[kSmallL / 4];
+  const double* row = in + size_t(min(r0 + i, rows - 1)) * l;
+#pragma unroll
+  for (int s = 0; s < kSmallL / 4; ++s) a[s] = s < ks_n ? row[min(4 * s + kq, l - 1)] : 0.0;   // (past l: times a zero row of S)
+  for (int ct = 0; ct < ct_n; ++ct) {
+    double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < kSmallL / 4; ++s)
+      if (s < ks_n) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], sm[(4 * s + kq) * pitch + 16 * ct + i], acc, 0, 0, 0);
+    const int c = 16 * ct + i;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int rr = r0 + kq + 4 * r;
+      if (rr < rows && c < cols) out[size_t(rr) * cols + c] = acc[r];
+    }
+  }
+}
+
+// B[r][n] = sum_j S[r][j] Z[n][j] for S [rank][l], Z [N][l]: the transposed product, stored in rows of n.
+__global__ __launch_bounds__(256) void bt_kernel(const double* __restrict__ Z, int N, int l, const double* __restrict__ S, int rank,
+                                                 double* __restrict__ B, const int* __restrict__ status) {
+  extern __shared__ double sm[];
+  if (status[0] | status[1] | status[2]) return;
+  const int rt_n = (rank + 15) / 16, ks_n = (l + 3) / 4, pitch = 4 * ks_n + 1;
+  for (int e = threadIdx.x; e < 16 * rt_n * 4 * ks_n; e += 256) {
+    const int r = e / (4 * ks_n), k = e - r * (4 * ks_n);
+    sm[r * pitch + k] = (r < rank && k < l) ? S[size_t(r) * l + k] : 0.0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 16;
+  if (n0 >= N) return;
+  double z[kSmallL / 4];
+  const double* row = Z + size_t(min(n0 + i, N - 1)) * l;
+#pragma unroll
+  for (int s = 0; s < kSmallL / 4; ++s) z[s] = s < ks_n ? row[min(4 * s + kq, l - 1)] : 0.0;
+  for (int rt = 0; rt < rt_n; ++rt) {
+    double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < kSmallL / 4; ++s)
+      if (s < ks_n) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sm[(16 * rt + i) * pitch + 4 * s + kq], z[s], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int rr = 16 * rt + kq + 4 * r, n = n0 + i;
+      if (rr < rank && n < N) B[size_t(rr) * N + n] = acc[r];
+    }
+  }
+}
+
+// Sum over the 16 lanes of a DPP row, in every lane (four exchanges inside the vector registers).
+template <int CTRL> __device__ inline double dpp_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(u)), CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, int(uint32_t(u >> 32)), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
+}
+__device__ inline double row16_sum(double v) {
+  v = dpp_add<0xb1>(v);       // quad_perm 1, 0, 3, 2
+  v = dpp_add<0x4e>(v);       // quad_perm 2, 3, 0, 1
+  v = dpp_add<0x141>(v);      // row_half_mirror
+  return dpp_add<0x140>(v);   // row_mirror
+}
+// One-sided Jacobi on the rows of W = L1 L2 (l x l, LDS), rotations accumulated in Gt: a round-robin
+// tournament, 16 lanes per pair (all pairs of a step at once), one barrier per step, sweeps until the
+// largest |<p, q>| / (|p| |q|) of a sweep is below 1e-14.  Then the rows in descending order of their
+// norms sigma_i: sigma [rank], M [l][rank] = G sqrt(sigma) and Mi [rank][l] = G^T / sqrt(sigma).
+// *unconverged is set after 30 sweeps.
+// Bound: the serial chain of a step (LDS reads, sums over 16 lanes, the rotation's angle, LDS writes,
+// barrier), l - 1 steps a sweep.  The tangent of the angle needs no more than the convergence does and
+// is taken from reciprocal estimates with a Newton step; cosine and sine keep c^2 + s^2 = 1 to rounding.
+// kU: ceil(l / 16), so that a pair's entries are read from LDS together.
+template <int kU>
+__global__ __launch_bounds__(1024) void jacobi_small_kernel(const double* __restrict__ L1, const double* __restrict__ L2, int l, int rank,
+                                                            double* __restrict__ sigma, double* __restrict__ M, double* __restrict__ Mi,
+                                                            const int* __restrict__ bad, int* __restrict__ unconverged) {
+  extern __shared__ double sm[];
+  __shared__ double norm2[kSmallL];
+  __shared__ unsigned off[2];
+  if (bad[0] | bad[1]) return;
+  const int pitch = l + 1, lp = l + (l & 1), threads = blockDim.x;
+  double* W = sm;
+  double* Gt = sm + l * pitch;
+  for (int e = threadIdx.x; e < l * l; e += threads) {
+    const int r = e / l, c = e - r * l;
+    double v = 0.0;
+    for (int k = c; k <= r; ++k) v = fma(L1[size_t(r) * l + k], L2[size_t(k) * l + c], v);
+    W[r * pitch + c] = v;
+    Gt[r * pitch + c] = r == c ? 1.0 : 0.0;
+  }
+  if (threadIdx.x < 2) off[threadIdx.x] = 0;
+  __syncthreads();
+  const int k = threadIdx.x >> 4, e0 = threadIdx.x & 15;     // pair k of every step
+  bool done = false;
+  for (int sweep = 0; sweep < 30 && !done; ++sweep) {
+    float worst = 0.f;
+    // pair k of step st: rows (st + k) and (st - k) mod (lp - 1); pair 0: the last row and row st
+    int p = k == 0 ? lp - 1 : k, q = k == 0 ? 0 : lp - 1 - k;
+    for (int st = 0; st < lp - 1; ++st) {
+      if (k < lp / 2 && p < l && q < l) {                    // (an odd l gets a bye)
+        double* wp = W + p * pitch;
+        double* wq = W + q * pitch;
+        double x[kU], y[kU], gx[kU], gy[kU], al = 0.0, be = 0.0, ga = 0.0;
+        double* gp = Gt + p * pitch;
+        double* gq = Gt + q * pitch;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int e = e0 + 16 * u;
+          const int ec = u < kU - 1 ? e : min(e, l - 1);
+          x[u] = wp[ec]; y[u] = wq[ec]; gx[u] = gp[ec]; gy[u] = gq[ec];
+        }
+        x[kU - 1] = e0 + 16 * (kU - 1) < l ? x[kU - 1] : 0.0;
+        y[kU - 1] = e0 + 16 * (kU - 1) < l ? y[kU - 1] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          al = fma(x[u], x[u], al); be = fma(y[u], y[u], be); ga = fma(x[u], y[u], ga);
+        }
+        al = row16_sum(al); be = row16_sum(be); ga = row16_sum(ga);
+        if (al > 0.0 && be > 0.0) {
+          const double rel = fabs(ga) * __builtin_amdgcn_rsq(al) * __builtin_amdgcn_rsq(be);   // (an estimate will do)
+          worst = fmaxf(worst, float(rel));
+          if (rel > 1e-16) {
+            // t = 2 ga sign(be - al) / (|be - al| + sqrt((be - al)^2 + 4 ga^2)), scaled by the larger norm
+            const double sc = __builtin_amdgcn_rcp(fmax(al, be)), d = (be - al) * sc, g2 = 2.0 * ga * sc;
+            const double h2 = fma(d, d, g2 * g2), den = fabs(d) + h2 * __builtin_amdgcn_rsq(h2);
+            double rc = __builtin_amdgcn_rcp(den);
+            rc = fma(rc, fma(-den, rc, 1.0), rc);
+            const double tt = (d >= 0.0 ? g2 : -g2) * rc;
+            const double c = rsqrt_newton(fma(tt, tt, 1.0)), s = c * tt;
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+              const int e = e0 + 16 * u;
+              if (u < kU - 1 || e < l) {
+                wp[e] = c * x[u] - s * y[u];
+                wq[e] = s * x[u] + c * y[u];
+                gp[e] = c * gx[u] - s * gy[u];
+                gq[e] = s * gx[u] + c * gy[u];
+              }
+            }
+          }
+        }
+      }
+      if (k != 0) p = p + 1 == lp - 1 ? 0 : p + 1;
+      q = q + 1 == lp - 1 ? 0 : q + 1;
+      __syncthreads();
+    }
+    // (two cells in turn: one is read while the other is cleared)
+    atomicMax(&off[sweep & 1], __float_as_uint(worst));
+    __syncthreads();
+    done = __uint_as_float(off[sweep & 1]) < 1e-14f;
+    if (threadIdx.x == 0) off[(sweep + 1) & 1] = 0;
     __syncthreads();
   }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = i0 + ty * 4 + u, j = j0 + tx * 4 + v;
-      if (i < M && j < Nc) C[size_t(i) * ldc + j] = acc[u][v];
+  if (!done) {
+    if (threadIdx.x == 0) *unconverged = 1;
+    return;
+  }
+  for (int r = threadIdx.x; r < l; r += threads) {
+    double v = 0.0;
+    for (int c = 0; c < l; ++c) v = fma(W[r * pitch + c], W[r * pitch + c], v);
+    norm2[r] = v;
+  }
+  __syncthreads();
+  for (int r = threadIdx.x >> 4; r < l; r += threads / 16) {   // 16 lanes per row
+    int at = 0;
+    for (int c = 0; c < l; ++c) at += (norm2[c] > norm2[r] || (norm2[c] == norm2[r] && c < r)) ? 1 : 0;
+    if (at >= rank) continue;
+    const double sg = sqrt(norm2[r]), root = sqrt(sg), inv = sg > 0.0 ? 1.0 / root : 0.0;
+    if (e0 == 0) sigma[at] = sg;
+    for (int c = e0; c < l; c += 16) {                       // G[c][r] = Gt[r][c]
+      M[size_t(c) * rank + at] = Gt[r * pitch + c] * root;
+      Mi[size_t(at) * l + c] = Gt[r * pitch + c] * inv;
     }
+  }
 }
 
-template <bool TRANS>
-void dgemm(int M, int Nc, int Kd, const double* A, int lda, const double* B, int ldb, double* C, int ldc) {
-  hipLaunchKernelGGL(dgemm_kernel<TRANS>, dim3((Nc + 63) / 64, (M + 63) / 64), dim3(256), 0, nullptr, M, Nc, Kd, A, lda, B, ldb, C, ldc);
+// [N][l] -> [l][N]
+__global__ __launch_bounds__(256) void transpose_kernel(const double* __restrict__ Z, int N, int l, double* __restrict__ Bm) {
+  __shared__ double tile[32][33];
+  const int n0 = blockIdx.x * 32, c0 = blockIdx.y * 32, x = threadIdx.x & 31;
+  for (int y = threadIdx.x >> 5; y < 32; y += 8)
+    if (n0 + y < N && c0 + x < l) tile[y][x] = Z[size_t(n0 + y) * l + c0 + x];
+  __syncthreads();
+  for (int y = threadIdx.x >> 5; y < 32; y += 8)
+    if (c0 + y < l && n0 + x < N) Bm[size_t(c0 + y) * N + n0 + x] = tile[x][y];
 }
 
-// ---------------------------------------------------------------------------------- Cholesky QR
+// ---------------------------------------------------------------------------------- Cholesky QR, larger l
 // In-place lower Cholesky factor of the l x l matrix G (one block; right-looking): *bad is set if a
 // pivot is not positive.
 __global__ __launch_bounds__(1024) void cholesky_kernel(double* __restrict__ G, int l, int* __restrict__ bad) {
@@ -409,100 +816,147 @@ int moe_lrc_offline_factors(const double* E_dev, int K, int N, int rank, const d
     return set_error(MOE_LRC_ESHAPE, "offline_factors: need 0 < rank <= l <= min(K, N, 1088)");
   if (power_iters < 0 || power_iters > 8) return set_error(MOE_LRC_EINVAL, "offline_factors: power_iters outside 0..8");
   int rc = MOE_LRC_OK;
-  double *Y = nullptr, *Z = nullptr, *G = nullptr, *Bm = nullptr, *Gt = nullptr, *norm2 = nullptr, *M = nullptr, *mul = nullptr;
-  int *bad = nullptr, *pairs = nullptr, *sel = nullptr;
-  unsigned* off = nullptr;
+  const bool small = l <= kSmallL;
   const int lp = l + (l & 1);                       // rows of the tournament (an odd l gets a bye)
-  std::vector<int> h_pairs(size_t(lp - 1) * lp, -1), order(l);
-  std::vector<double> h_norm2(l), h_Gt, h_M, h_mul(rank);
-  std::vector<int> h_sel(rank);
-  int h_bad = 0;
-  // orth(Y): Cholesky QR, twice
-  auto orth = [&]() -> int {
-    for (int rep = 0; rep < 2; ++rep) {
-      dgemm<true>(l, l, K, Y, l, Y, l, G, l);
-      hipLaunchKernelGGL(cholesky_kernel, dim3(1), dim3(1024), 0, nullptr, G, l, bad);
-      hipLaunchKernelGGL(trsm_kernel, dim3((K + 255) / 256), dim3(256), 0, nullptr, Y, K, l, G);
-    }
-    if (hipMemcpy(&h_bad, bad, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return -1;
-    return h_bad;
+  // one allocation for everything (a dozen of them, and their release, cost as much as a product)
+  size_t bytes = 0;
+  auto take = [&](size_t n) { const size_t at = bytes; bytes += (n + 255) & ~size_t(255); return at; };
+  const size_t oY = take(size_t(K) * l * 8), oZ = take(size_t(N) * l * 8);
+  const size_t oZ2 = take(size_t(N) * l * 8);       // small l: the orthonormalised copy of Z; else (and as the fallback) Bm
+  const size_t part_n = std::max({gemm_part_doubles(K, l, N), gemm_part_doubles(N, l, K), gemm_part_doubles(l, l, K), gemm_part_doubles(l, l, N),
+                                  gemm_part_doubles(K, rank, l)});
+  const size_t oPart = take(part_n * 8);
+  const size_t oL1 = take(size_t(l) * l * 8), oL2 = take(size_t(l) * l * 8), oLi = take(size_t(l) * l * 8);
+  const size_t oM = take(size_t(l) * rank * 8), oMi = take(size_t(l) * rank * 8);
+  const size_t oGt = take(size_t(l) * l * 8), oNorm = take(size_t(l) * 8), oMul = take(size_t(rank) * 8), oSig = take(size_t(rank) * 8);
+  const size_t oPairs = take(size_t(lp - 1) * lp * sizeof(int)), oSel = take(size_t(rank) * sizeof(int)), oStatus = take(4 * sizeof(int));
+  uint8_t* base = nullptr;
+  std::vector<int> h_pairs, order(l), h_sel(rank);
+  std::vector<double> h_norm2(l), h_Gt, h_M, h_mul(rank), h_sig(rank);
+  int h_status[4] = {0, 0, 0, 0};                   // sketch lost rank; Gram matrix of Bm not positive; rotations unconverged; scratch
+  double *Y, *Z, *Z2, *part, *L1, *L2, *Li, *M, *Mi, *Gt, *norm2, *mul, *sig;
+  int *pairs, *sel, *status;
+  unsigned* off;
+  size_t small_lds = 0, rmul_lds = 0;
+  void (*jacobi)(const double*, const double*, int, int, double*, double*, double*, const int*, int*) = nullptr;
+  // one Cholesky QR of X [rows][l] (in place, or into `to`); factor and its inverse in L, Li
+  auto qr_once = [&](double* X, int rows, double* to, double* L, int* bad) {
+    const int parts = dgemm<true>(l, l, rows, X, l, X, l, nullptr, part, true);
+    hipLaunchKernelGGL(cholesky_small_kernel, dim3(1), dim3(kCholThreads), small_lds, nullptr, part, parts, l, L, Li, bad);
+    if (to) hipLaunchKernelGGL(rmul_kernel<true>, dim3((rows + 63) / 64), dim3(256), rmul_lds, nullptr, X, rows, l, Li, l, to, (const int*)nullptr);
   };
-  OFF_HIP(hipMalloc((void**)&Y, size_t(K) * l * 8));
-  OFF_HIP(hipMalloc((void**)&Z, size_t(N) * l * 8));
-  OFF_HIP(hipMalloc((void**)&G, size_t(l) * l * 8));
-  OFF_HIP(hipMalloc((void**)&Bm, size_t(l) * N * 8));
-  OFF_HIP(hipMalloc((void**)&Gt, size_t(l) * l * 8));
-  OFF_HIP(hipMalloc((void**)&norm2, size_t(l) * 8));
-  OFF_HIP(hipMalloc((void**)&M, size_t(l) * rank * 8));
-  OFF_HIP(hipMalloc((void**)&mul, size_t(rank) * 8));
-  OFF_HIP(hipMalloc((void**)&bad, sizeof(int)));
-  OFF_HIP(hipMalloc((void**)&off, sizeof(unsigned)));
-  OFF_HIP(hipMalloc((void**)&pairs, h_pairs.size() * sizeof(int)));
-  OFF_HIP(hipMalloc((void**)&sel, size_t(rank) * sizeof(int)));
-  OFF_HIP(hipMemset(bad, 0, sizeof(int)));
+  auto orth = [&](int reps) {
+    for (int rep = 0; rep < reps; ++rep) {
+      if (small) {
+        qr_once(Y, K, Y, L1, status);
+      } else {
+        dgemm<true>(l, l, K, Y, l, Y, l, L1, part);
+        hipLaunchKernelGGL(cholesky_kernel, dim3(1), dim3(1024), 0, nullptr, L1, l, status);
+        hipLaunchKernelGGL(trsm_kernel, dim3((K + 255) / 256), dim3(256), 0, nullptr, Y, K, l, L1);
+      }
+    }
+  };
+  OFF_HIP(hipMalloc((void**)&base, bytes));
+  Y = (double*)(base + oY); Z = (double*)(base + oZ); Z2 = (double*)(base + oZ2); part = (double*)(base + oPart);
+  L1 = (double*)(base + oL1); L2 = (double*)(base + oL2); Li = (double*)(base + oLi); M = (double*)(base + oM); Mi = (double*)(base + oMi);
+  Gt = (double*)(base + oGt); norm2 = (double*)(base + oNorm); mul = (double*)(base + oMul); sig = (double*)(base + oSig);
+  pairs = (int*)(base + oPairs); sel = (int*)(base + oSel); status = (int*)(base + oStatus);
+  off = (unsigned*)(status + 3);
+  OFF_HIP(hipMemset(status, 0, 4 * sizeof(int)));
+  if (small) {
+    small_lds = size_t(2) * l * (l + 1) * 8;
+    rmul_lds = size_t((l + 3) / 4 * 4) * ((l + 15) / 16 * 16 + 4) * 8;
+    // (above 64 KB a kernel has to be allowed its LDS)
+    OFF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&cholesky_small_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kSmallL * (kSmallL + 1) * 8));
+    jacobi = l <= 16 ? jacobi_small_kernel<1> : l <= 32 ? jacobi_small_kernel<2> : l <= 48 ? jacobi_small_kernel<3>
+             : l <= 64 ? jacobi_small_kernel<4> : l <= 80 ? jacobi_small_kernel<5> : jacobi_small_kernel<6>;
+    OFF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(jacobi), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kSmallL * (kSmallL + 1) * 8));
+    for (const void* f : {reinterpret_cast<const void*>(&rmul_kernel<true>), reinterpret_cast<const void*>(&rmul_kernel<false>), reinterpret_cast<const void*>(&bt_kernel)})
+      OFF_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallL * (kSmallL + 4) * 8));
+  }
 
   // ---- range finder
-  dgemm<false>(K, l, N, E_dev, N, omega_dev, l, Y, l);                  // Y = E Omega
+  dgemm<false>(K, l, N, E_dev, N, omega_dev, l, Y, part);               // Y = E Omega
   for (int it = 0; it < power_iters; ++it) {
-    if (orth() != 0) { rc = set_error(MOE_LRC_ESHAPE, "offline_factors: the sketch lost rank (Gram matrix not positive definite)"); goto done; }
-    dgemm<true>(N, l, K, E_dev, N, Y, l, Z, l);                         // Z = E^T Q
-    dgemm<false>(K, l, N, E_dev, N, Z, l, Y, l);                        // Y = E Z
+    orth(1);
+    dgemm<true>(N, l, K, E_dev, N, Y, l, Z, part);                      // Z = E^T Q
+    dgemm<false>(K, l, N, E_dev, N, Z, l, Y, part);                     // Y = E Z
   }
-  if (orth() != 0) { rc = set_error(MOE_LRC_ESHAPE, "offline_factors: the sketch lost rank (Gram matrix not positive definite)"); goto done; }
-  dgemm<true>(l, N, K, Y, l, E_dev, N, Bm, N);                          // Bm = Q^T E
+  orth(2);
+  dgemm<true>(N, l, K, E_dev, N, Y, l, Z, part);                        // Z = E^T Q = Bm^T
 
-  // ---- SVD of Bm: sweeps of a round-robin tournament over the row pairs
-  for (int s = 0; s < lp - 1; ++s) {
-    int* row = h_pairs.data() + size_t(s) * lp;
-    for (int k = 0; k < lp / 2; ++k) {
-      int a = k == 0 ? lp - 1 : (s + k) % (lp - 1), b = (s - k + (lp - 1)) % (lp - 1);
-      if (a >= l || b >= l) { a = -1; b = -1; }
-      row[2 * k] = a; row[2 * k + 1] = b;
+  if (small) {
+    // ---- SVD of Bm = L1 L2 Q_b^T (Cholesky QR of Z, twice) by rotations of the rows of L1 L2
+    qr_once(Z, N, Z2, L1, status + 1);
+    qr_once(Z2, N, nullptr, L2, status + 1);
+    hipLaunchKernelGGL(jacobi, dim3(1), dim3((lp / 2 * 16 + 63) / 64 * 64), small_lds, nullptr, L1, L2, l, rank, sig, M, Mi, status, status + 2);
+    // A = Q G sqrt(sigma), B = rows of G^T Bm / sqrt(sigma) (neither is written if a step failed)
+    hipLaunchKernelGGL(rmul_kernel<false>, dim3((K + 63) / 64), dim3(256), rmul_lds, nullptr, Y, K, l, M, rank, A_dev, status);
+    hipLaunchKernelGGL(bt_kernel, dim3((N + 63) / 64), dim3(256), rmul_lds, nullptr, Z, N, l, Mi, rank, B_dev, status);
+    OFF_HIP(hipGetLastError());
+  }
+  OFF_HIP(hipMemcpy(h_status, status, 3 * sizeof(int), hipMemcpyDeviceToHost));
+  if (h_status[0]) { rc = set_error(MOE_LRC_ESHAPE, "offline_factors: the sketch lost rank (Gram matrix not positive definite)"); goto done; }
+  if (h_status[2]) { rc = set_error(MOE_LRC_ESHAPE, "offline_factors: Jacobi sweeps did not converge"); goto done; }
+  if (small && !h_status[1]) {
+    OFF_HIP(hipMemcpy(h_sig.data(), sig, size_t(rank) * 8, hipMemcpyDeviceToHost));
+    if (sigma_host) std::copy(h_sig.begin(), h_sig.end(), sigma_host);
+  } else {
+    // ---- larger l (or a Bm whose Gram matrix is not positive in fp64): SVD of Bm itself, sweeps of a
+    //      round-robin tournament over its row pairs
+    double* Bm = Z2;
+    hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (l + 31) / 32), dim3(256), 0, nullptr, Z, N, l, Bm);
+    h_pairs.assign(size_t(lp - 1) * lp, -1);
+    for (int s = 0; s < lp - 1; ++s) {
+      int* row = h_pairs.data() + size_t(s) * lp;
+      for (int k = 0; k < lp / 2; ++k) {
+        int a = k == 0 ? lp - 1 : (s + k) % (lp - 1), b = (s - k + (lp - 1)) % (lp - 1);
+        if (a >= l || b >= l) { a = -1; b = -1; }
+        row[2 * k] = a; row[2 * k + 1] = b;
+      }
     }
+    OFF_HIP(hipMemcpy(pairs, h_pairs.data(), h_pairs.size() * sizeof(int), hipMemcpyHostToDevice));
+    h_Gt.assign(size_t(l) * l, 0.0);
+    for (int i = 0; i < l; ++i) h_Gt[size_t(i) * l + i] = 1.0;
+    OFF_HIP(hipMemcpy(Gt, h_Gt.data(), h_Gt.size() * 8, hipMemcpyHostToDevice));
+    for (int sweep = 0; sweep < 30; ++sweep) {
+      unsigned h_off = 0;
+      OFF_HIP(hipMemset(off, 0, sizeof(unsigned)));
+      for (int s = 0; s < lp - 1; ++s)
+        hipLaunchKernelGGL(jacobi_kernel, dim3(lp / 2), dim3(256), 0, nullptr, Bm, N, Gt, l, pairs + size_t(s) * lp, off);
+      OFF_HIP(hipMemcpy(&h_off, off, sizeof(unsigned), hipMemcpyDeviceToHost));
+      float rel;
+      std::memcpy(&rel, &h_off, 4);
+      if (rel < 1e-14f) break;
+      if (sweep == 29) { rc = set_error(MOE_LRC_ESHAPE, "offline_factors: Jacobi sweeps did not converge"); goto done; }
+    }
+    hipLaunchKernelGGL(row_norm2_kernel, dim3(l), dim3(256), 0, nullptr, Bm, N, norm2);
+    OFF_HIP(hipMemcpy(h_norm2.data(), norm2, size_t(l) * 8, hipMemcpyDeviceToHost));
+    OFF_HIP(hipMemcpy(h_Gt.data(), Gt, h_Gt.size() * 8, hipMemcpyDeviceToHost));
+    // the `rank` largest singular values, in descending order; A = Q G_sel sqrt(sigma), B = rows / sqrt(sigma)
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return h_norm2[a] > h_norm2[b]; });
+    h_M.assign(size_t(l) * rank, 0.0);
+    for (int i = 0; i < rank; ++i) {
+      const int src = order[i];
+      const double sigma = std::sqrt(h_norm2[src]), root = std::sqrt(sigma);
+      if (sigma_host) sigma_host[i] = sigma;
+      h_sel[i] = src;
+      h_mul[i] = sigma > 0.0 ? 1.0 / root : 0.0;
+      for (int j = 0; j < l; ++j) h_M[size_t(j) * rank + i] = h_Gt[size_t(src) * l + j] * root;   // G[j][src] = Gt[src][j]
+    }
+    OFF_HIP(hipMemcpy(M, h_M.data(), h_M.size() * 8, hipMemcpyHostToDevice));
+    OFF_HIP(hipMemcpy(mul, h_mul.data(), size_t(rank) * 8, hipMemcpyHostToDevice));
+    OFF_HIP(hipMemcpy(sel, h_sel.data(), size_t(rank) * sizeof(int), hipMemcpyHostToDevice));
+    dgemm<false>(K, rank, l, Y, l, M, rank, A_dev, part);
+    hipLaunchKernelGGL(pick_rows_kernel, dim3((N + 255) / 256, rank), dim3(256), 0, nullptr, Bm, N, sel, mul, B_dev);
   }
-  OFF_HIP(hipMemcpy(pairs, h_pairs.data(), h_pairs.size() * sizeof(int), hipMemcpyHostToDevice));
-  h_Gt.assign(size_t(l) * l, 0.0);
-  for (int i = 0; i < l; ++i) h_Gt[size_t(i) * l + i] = 1.0;
-  OFF_HIP(hipMemcpy(Gt, h_Gt.data(), h_Gt.size() * 8, hipMemcpyHostToDevice));
-  for (int sweep = 0; sweep < 30; ++sweep) {
-    unsigned h_off = 0;
-    OFF_HIP(hipMemset(off, 0, sizeof(unsigned)));
-    for (int s = 0; s < lp - 1; ++s)
-      hipLaunchKernelGGL(jacobi_kernel, dim3(lp / 2), dim3(256), 0, nullptr, Bm, N, Gt, l, pairs + size_t(s) * lp, off);
-    OFF_HIP(hipMemcpy(&h_off, off, sizeof(unsigned), hipMemcpyDeviceToHost));
-    float rel;
-    std::memcpy(&rel, &h_off, 4);
-    if (rel < 1e-14f) break;
-    if (sweep == 29) { rc = set_error(MOE_LRC_ESHAPE, "offline_factors: Jacobi sweeps did not converge"); goto done; }
-  }
-  hipLaunchKernelGGL(row_norm2_kernel, dim3(l), dim3(256), 0, nullptr, Bm, N, norm2);
-  OFF_HIP(hipMemcpy(h_norm2.data(), norm2, size_t(l) * 8, hipMemcpyDeviceToHost));
-  OFF_HIP(hipMemcpy(h_Gt.data(), Gt, h_Gt.size() * 8, hipMemcpyDeviceToHost));
-
-  // ---- the `rank` largest singular values, in descending order; A = Q G_sel sqrt(sigma), B = rows / sqrt(sigma)
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return h_norm2[a] > h_norm2[b]; });
-  h_M.assign(size_t(l) * rank, 0.0);
-  for (int i = 0; i < rank; ++i) {
-    const int src = order[i];
-    const double sigma = std::sqrt(h_norm2[src]), root = std::sqrt(sigma);
-    if (sigma_host) sigma_host[i] = sigma;
-    h_sel[i] = src;
-    h_mul[i] = sigma > 0.0 ? 1.0 / root : 0.0;
-    for (int j = 0; j < l; ++j) h_M[size_t(j) * rank + i] = h_Gt[size_t(src) * l + j] * root;   // G[j][src] = Gt[src][j]
-  }
-  OFF_HIP(hipMemcpy(M, h_M.data(), h_M.size() * 8, hipMemcpyHostToDevice));
-  OFF_HIP(hipMemcpy(mul, h_mul.data(), size_t(rank) * 8, hipMemcpyHostToDevice));
-  OFF_HIP(hipMemcpy(sel, h_sel.data(), size_t(rank) * sizeof(int), hipMemcpyHostToDevice));
-  dgemm<false>(K, rank, l, Y, l, M, rank, A_dev, rank);
-  hipLaunchKernelGGL(pick_rows_kernel, dim3((N + 255) / 256, rank), dim3(256), 0, nullptr, Bm, N, sel, mul, B_dev);
   if (A_bf16_dev) hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((size_t(K) * rank + 255) / 256)), dim3(256), 0, nullptr, A_dev, size_t(K) * rank, A_bf16_dev);
   if (B_bf16_dev) hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((size_t(rank) * N + 255) / 256)), dim3(256), 0, nullptr, B_dev, size_t(rank) * N, B_bf16_dev);
   OFF_HIP(hipGetLastError());
   OFF_HIP(hipDeviceSynchronize());
 done:
-  for (void* p : {(void*)Y, (void*)Z, (void*)G, (void*)Bm, (void*)Gt, (void*)norm2, (void*)M, (void*)mul, (void*)bad, (void*)off, (void*)pairs, (void*)sel})
-    if (p) (void)hipFree(p);
+  if (base) (void)hipFree(base);
   return rc;
 }
 

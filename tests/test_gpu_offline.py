@@ -133,6 +133,36 @@ def test_residual_factors(amd, K, N, r, bits):
     np.testing.assert_array_equal(_bits(Bb), compress.round_to_bf16_bits(B))
 
 
+# edges of the tiles and of the choice between the one-block and the many-launch SVD: l odd, l = 96 (the
+# largest that fits one block's LDS) and 97, fewer than 32 rows in a transposed product, K and N that
+# are no multiple of a chunk, a single pair
+@pytest.mark.parametrize("K,N,r,over,iters", [(70, 97, 24, 9, 2), (131, 161, 88, 8, 1), (131, 161, 89, 8, 1), (33, 45, 3, 2, 2),
+                                              (1000, 131, 8, 0, 0), (64, 64, 1, 0, 1), (129, 777, 40, 9, 2)])
+def test_residual_factors_at_the_edges(amd, K, N, r, over, iters):
+    rng = np.random.default_rng(K * N + r)
+    E, omega = rng.standard_normal((K, N)), rng.standard_normal((N, r + over))
+    Y = E @ omega
+    for _ in range(iters):
+        Y = E @ (E.T @ np.linalg.qr(Y)[0])
+    Q = np.linalg.qr(Y)[0]
+    U, S, Vt = np.linalg.svd(Q.T @ E, full_matrices=False)
+    A, B, sigma, _, _ = amd.offline_factors(_dev(E), r, _dev(omega), power_iters=iters)
+    np.testing.assert_allclose(sigma, S[:r], rtol=1e-9)
+    assert orc.rel_frobenius(A.cpu().numpy() @ B.cpu().numpy(), (Q @ U[:, :r] * S[:r]) @ Vt[:r]) <= 1e-8
+
+
+def test_residual_factors_of_a_matrix_whose_gram_matrix_is_singular(amd):
+    # ten singular values near 1, ten near 1e-12, and a test matrix that weighs them alike: Y is well
+    # conditioned, Bm Bm^T is not positive definite in fp64
+    rng = np.random.default_rng(9)
+    U, V = np.linalg.qr(rng.standard_normal((64, 20)))[0], np.linalg.qr(rng.standard_normal((96, 20)))[0]
+    S = np.concatenate([np.linspace(1.0, 0.5, 10), np.linspace(2e-12, 1e-12, 10)])
+    E, omega = (U * S) @ V.T, V / S
+    A, B, sigma, _, _ = amd.offline_factors(_dev(E), 20, _dev(omega), power_iters=0)
+    np.testing.assert_allclose(sigma[:10], S[:10], rtol=1e-9)
+    assert orc.rel_frobenius(A.cpu().numpy() @ B.cpu().numpy(), E) <= 1e-10
+
+
 def test_low_rank_matrix_is_recovered(amd):
     # E of exact rank 6 plus nothing: the factors of rank 6 reproduce it (l = rank: no room to spare)
     rng = np.random.default_rng(8)
