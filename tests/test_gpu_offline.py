@@ -88,6 +88,36 @@ def test_refined_quantizer_against_the_oracle(amd, bits, group):
     np.testing.assert_array_equal(_bits(z0), base["zero"])
 
 
+# odd widths (one column per lane), a single column, every register form and a group that has none
+@pytest.mark.parametrize("bits,group,K,N", [(2, 32, 96, 63), (3, 64, 128, 129), (4, 128, 256, 1), (2, 256, 256, 65), (3, 48, 96, 70), (2, 32, 32, 2)])
+def test_quantizer_at_the_edges(amd, bits, group, K, N):
+    rng = np.random.default_rng(K * N + group)
+    W = rng.standard_normal((K, N)) * 0.02
+    W[:group, 0] = 0.0
+    want = compress.quantize_groupwise(W, bits, group)
+    codes, scale, zero, resid = amd.offline_quantize(_dev(W), bits, group)
+    np.testing.assert_array_equal(codes.cpu().numpy(), want["codes"])
+    np.testing.assert_array_equal(_bits(scale), want["scale"])
+    np.testing.assert_array_equal(_bits(zero), want["zero"])
+    np.testing.assert_array_equal(resid.cpu().numpy(), W - compress.dequantize(want, group))
+
+
+# entries on both sides of the threshold below which shrink() is zero (beta = 10 puts it at 0.17: far
+# above every error; 3e3 and 3e4 put it inside their range), with and without the register form
+@pytest.mark.parametrize("group,beta", [(32, 10.0), (64, 3e3), (64, 3e4), (96, 3e3)])
+def test_refined_quantizer_around_its_threshold(amd, group, beta):
+    rng = np.random.default_rng(int(beta) + group)
+    W = rng.standard_normal((192, 75)) * 0.02
+    want = compress.quantize_refined(W, 3, group, beta=beta)
+    codes, scale, zero, _ = amd.offline_quantize(_dev(W), 3, group, refine={"beta": beta})
+    np.testing.assert_array_equal(_bits(scale), want["scale"])
+    # as above: the last bit of pow() may move a value over a rounding boundary
+    dz = _bits(zero).astype(np.int64) - want["zero"].astype(np.int64)
+    assert (np.abs(dz) <= 1).all() and (dz != 0).sum() <= 1
+    dc = codes.cpu().numpy().astype(np.int64) - want["codes"].astype(np.int64)
+    assert (np.abs(dc) <= 1).all() and (dc != 0).sum() <= 2
+
+
 def test_kurtosis(amd):
     rng = np.random.default_rng(3)
     for W in (rng.standard_normal((700, 513)), rng.laplace(size=(300, 1001)) * 0.05 + 0.01, rng.random((257, 129))):
