@@ -26,8 +26,8 @@
 //     double-buffered in LDS: the copy of the next half goes from memory straight to LDS (no
 //     registers) while the current one is multiplied; one barrier per half;
 //   - the rank-r term is extra steps: the B factor's 32-wide units take the place of the codes and
-//     meet (in A), which a small kernel of the same shape (xa_tile_kernel: fp16 factor tiles instead
-//     of packed codes) has left in global memory; its first fragments are copied into LDS at the start.
+//     meet (in A), which a small kernel (xa_kernel) has left in global memory; its first fragments are
+//     copied into LDS at the start.
 // Experts with few rows (decode) take the other flavour, ffn_decode.hip.
 #include <algorithm>
 #include <type_traits>
@@ -44,21 +44,19 @@ namespace {
 
 using namespace ffn;
 
-constexpr int kTileWaves = 8;             // wavefronts per block of the (in A) kernel
 constexpr int kGemmWaves = 4;             // wavefronts per block of the grouped GEMM (two blocks per CU)
 constexpr int kBM = 128;                  // rows of an expert per block
-constexpr int kTMT = kBM / 16;            // row tiles
-constexpr int kStepUnits = kTMT * 8 * 64; // 16-byte units of one k-step of activations (64 KB)
-constexpr int kHalfUnits = kStepUnits / 2;
+constexpr int kHalfUnits = kBM / 16 * 4 * 64;   // 16-byte units of half a k-step of activations (32 KB)
 constexpr int kGemmLdsUnits = 5120;       // LDS of a grouped-GEMM block: 80 KB, half of a CU's
-// Work item `item` of a launch -> (expert, first row of its 128-row chunk).  Routed experts: the
-// items enumerate the chunks of the experts in order (an expert with cnt rows has ceil(cnt / 128));
+// Work item `item` of a launch -> (expert, first row of its chunk of ROWS rows).  Routed experts: the
+// items enumerate the chunks of the experts in order (an expert with cnt rows has ceil(cnt / ROWS));
 // shared experts: every expert has the same T rows.
 struct Chunk { int e, r0, cnt, r; };
+template <int ROWS>
 __device__ inline bool find_chunk(const KArgs& a, int item, Chunk& c) {
   if (!a.offsets) {
-    const int per = (a.T + kBM - 1) / kBM;
-    c.e = item / per; c.r = (item - c.e * per) * kBM; c.r0 = c.e * a.T; c.cnt = a.T;
+    const int per = (a.T + ROWS - 1) / ROWS;
+    c.e = item / per; c.r = (item - c.e * per) * ROWS; c.r0 = c.e * a.T; c.cnt = a.T;
     return c.e < a.n_exp;
   }
   // 64 experts at a time: every lane counts the chunks of one expert, a prefix sum over the
@@ -69,7 +67,7 @@ __device__ inline bool find_chunk(const KArgs& a, int item, Chunk& c) {
     const int e = e0 + lane;
     int r0 = 0, cnt = 0;
     if (e < a.n_exp) { r0 = a.offsets[e]; cnt = a.row_list ? a.comp_rows[e] : a.offsets[e + 1] - r0; }
-    const int n = (cnt + kBM - 1) / kBM;
+    const int n = (cnt + ROWS - 1) / ROWS;
     int incl = n;
 #pragma unroll
     for (int dlt = 1; dlt < 64; dlt *= 2) {
@@ -82,28 +80,12 @@ __device__ inline bool find_chunk(const KArgs& a, int item, Chunk& c) {
       const int first = __ffsll(hit) - 1;
       c.e = e0 + first;
       c.r0 = __shfl(r0, first); c.cnt = __shfl(cnt, first);
-      c.r = (item - base - __shfl(incl - n, first)) * kBM;
+      c.r = (item - base - __shfl(incl - n, first)) * ROWS;
       return true;
     }
     base += total;
   }
   return false;
-}
-
-// Copy of the activations of k-step ks for the 128 rows of a chunk into `buf`, as 64 fragments (row
-// tile mt, sub-step s) of 64 units: wavefront w copies the fragments with s = w, each lane its own 16
-// bytes from global memory straight to LDS; R[mt] is this lane's input row of row tile mt.  A column
-// past the end is clamped to a valid unit (the padded weights of such columns are exact zeros).
-__device__ inline void stage_step_rows(const KArgs& a, uint4* buf, int ks, const int (&R)[kTMT], int mt_n, int wave, int lane) {
-  const uint4* in_units = reinterpret_cast<const uint4*>(a.in);
-  const int q = lane >> 4, s = wave;
-  const int k8 = min(ks * 32 + q * 8 + s, a.K / 8 - 1);
-#pragma unroll
-  for (int mt = 0; mt < kTMT; ++mt)
-    if (mt < mt_n)        // (row tiles past the chunk's last row are not read)
-    __builtin_amdgcn_global_load_lds(
-        reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(in_units + act_unit(k8, R[mt], a.in_rt))),
-        reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(buf + (mt * 8 + s) * 64)), 16, 0, 0);
 }
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
@@ -182,7 +164,7 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   constexpr int DW = 2 * BITS;
   constexpr int NC = Extract<BITS>::kClasses;
   Chunk ch;
-  if (!find_chunk(a, blockIdx.y, ch)) return;
+  if (!find_chunk<kBM>(a, blockIdx.y, ch)) return;
   // (found by shuffles, the same in every lane: moved into scalar registers, and with them every base address)
   const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
   const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
@@ -352,7 +334,7 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
 
   // ---- prologue: the first half k-step of activations, the first tiles, and the (in A) fragments of
   //      the first rank steps.  (in A) of the chunk's rows is fp16 row-major in global memory
-  //      (xa_tile_kernel has scaled it and zeroed the rows without the term); fragment (rank step st,
+  //      (xa_kernel has scaled it and zeroed the rows without the term); fragment (rank step st,
   //      variant v, row pair rp) sits at unit ((st * V + v) * 4 + rp) * 64 of its region
   //      (rank_frag_source).  The 16 KB behind the activations hold kRankFirst rank steps: ranks up
   //      to 32 (fused) or 64; later ones take the place of the activations, kRankChunk at a time.
@@ -564,192 +546,159 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   }
 }
 
-// (in A)[row][rho] for the 128-row chunks of every expert, in two launches.
-// xa_tile_kernel: K-block partial sums in fp32, [K-block][row][NM * ls * 32 columns] ([A1 | A3] in
-// the fused case, each padded to a multiple of 32), already multiplied by the projection's
-// power-of-two pre-scale.  Same shape as the kernel above (activations through double-buffered LDS,
-// eight row tiles per fragment of weights), with the fp16 factor tiles [rpad/16][K/32][lane][8] as
-// the weight operand: wavefront w owns the 16-column factor tiles w, w + 8, ... (at most four);
-// grid.x splits K so that the launch fills the chip.
-// xa_finish_kernel: adds the K-blocks in order, zeroes the rows without the rank-r term and the
-// padding columns, writes fp16 row-major.
-// Only the rows that take the term are computed: the chunks run over the compact rows the preparing
-// launch has made of them (CompactArgs: the front of every expert's row range), the partial sums
-// are indexed by compact row, and the finish kernel puts every routed row's sum (or zeros) in its
-// place.
+// (in A)[row][rho], fp16 row-major [routed row][NM * ls * 32 columns] ([A1 | A3] in the fused case, each
+// padded to a multiple of 32), multiplied by the projection's power-of-two pre-scale, zero for rows
+// without the rank-r term and in the padding columns.
+// Only the rows that take the term are computed: the items run over 16 MT of the compact rows that the
+// preparing launch has made of them (CompactArgs: the front of every expert's row range), and every
+// sum goes to its routed row.  Blocks past the items write the zero rows.
+// The product is skinny (16 to 128 columns) and its operands are in cache, so it is bound by latency:
+// a block of 16 wavefronts takes 16 MT rows x at most T 16-column factor tiles (grid.y: groups of T
+// tiles), the wavefronts share K and read both operands straight into registers, three or four units of 32
+// inputs ahead; their sums meet in LDS, in wavefront
+// order.  Qwen3 T = 4096: 30 + 19 us for the two products, DeepSeek T = 512: 14 + 9, Mixtral T = 2048:
+// 28 + 67.  Staging 128 rows at a time through LDS, K split over blocks, and a second launch that added
+// the K-blocks took 46 + 37, 20 + 18 and 30 + 54 us.
 // Q3: some factor pair of the layer is held at 3 bits (layout.h); such a pair's units are fetched as
-// (codes, metadata) dwords and dequantized when their k-step comes up.
-template <bool DUAL, int NT, bool Q3>
-__global__ __launch_bounds__(64 * kTileWaves, 2) void xa_tile_kernel(KArgs a) {
-  extern __shared__ uint4 xs[];
+// (codes, metadata) dwords and dequantized.
+constexpr int kXaWaves = 16, kXaTiles = 4;
+constexpr int kXaZeroUnits = 8192;         // 16-byte units a zeroing block looks after
+template <bool DUAL, int T, int MT, bool Q3>
+__global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, const int32_t* __restrict__ comp_index,
+                                                           const uint16_t* __restrict__ x_bf16, _Float16* __restrict__ P) {
   constexpr int NM = DUAL ? 2 : 1;
-  constexpr int kMaxT = NT;                              // factor tiles per wavefront (2 or 4); grid.z: groups of 8 * NT tiles
-  constexpr bool kAhead = NT <= 2;                       // registers for the factor units of a whole k-step ahead
-  Chunk ch;
-  if (!find_chunk(a, blockIdx.y, ch)) return;
-  const int e = ch.e, r0 = ch.r0, cnt = ch.cnt, r = ch.r;
-  const ExpertDesc& d = a.desc[e];
-  if (!d.has_factors || a.comp_rows[e] == 0) return;
+  constexpr int kAhead = T * MT == 8 ? 3 : 4;     // units in flight (registers)
+  __shared__ float4_t red[kXaWaves][MT][64];
   const int th = threadIdx.x, lane = th & 63;
+  const int pitch = NM * a.ls * 32;
+  if ((int)blockIdx.x >= items) {                        // rows without the term
+    if (blockIdx.y != 0) return;
+    const int per_row = pitch / 8;
+    const size_t u0 = size_t((int)blockIdx.x - items) * kXaZeroUnits, end = size_t(a.total_rows) * per_row;
+    for (size_t u = u0 + th; u < u0 + kXaZeroUnits && u < end; u += 64 * kXaWaves)
+      if (comp_index[u / per_row] < 0) reinterpret_cast<uint4*>(P)[u] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  Chunk ch;
+  if (!find_chunk<16 * MT>(a, blockIdx.x, ch)) return;
+  const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
+  const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
+  const ExpertDesc& d = a.desc[e];
+  if (!d.has_factors) return;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
   const int q = lane >> 4, c = lane & 15;
-  const int mt_n = min(kTMT, (cnt - r + 15) >> 4);
-  const int rt = a.rpad / 16, tiles = NM * rt;           // 16-column factor tiles in all
-  const int pitch = NM * a.ls * 32;
-  // The chunk's rows are compact rows (the rows of the expert that take the rank-r term, in row
-  // order): row_list names the routed row whose activations each one reads.  A row past the
-  // expert's last compact row reads one of the zero rows at the end of the buffer (its results are
-  // never stored).
-  int Rm[kTMT];
+  // The chunk's rows are compact rows: row_list names the routed row of each (past the last one: the
+  // last one again, its sums are not stored).  The fused projections read the rows' bf16 tokens (whole
+  // lines; the compact rows of the operand-order buffer are 16-byte pieces of lines shared with rows
+  // that do not take the term) and scale them as the preparing launch does, W2 reads h.
+  int R[MT];
+  const u32x4* xrow[MT];
+  float xs2[MT];
 #pragma unroll
-  for (int mt = 0; mt < kTMT; ++mt) {
-    const int i = r0 + min(r + 16 * mt + c, cnt - 1);
-    Rm[mt] = r + 16 * mt + c < cnt ? (a.row_list ? a.row_list[i] : i) : a.in_rt - dec::kZeroRows + c;
+  for (int mt = 0; mt < MT; ++mt) {
+    R[mt] = a.row_list[r0 + min(r + 16 * mt + c, cnt - 1)];
+    xrow[mt] = DUAL ? reinterpret_cast<const u32x4*>(x_bf16 + size_t(a.row_pair[R[mt]] / a.top_k) * a.K) : nullptr;
+    xs2[mt] = DUAL ? pow2i(a.row_exp[R[mt]]) : 1.f;
   }
-
-  float4_t acc[kMaxT][kTMT];
+  // factor tile t of this block: 16 columns of projection m.  (The loads are unconditional: what a tile past
+  // the projection's own rank or past the last one reads lies inside the factor sections, and its
+  // products are dropped.)
+  const uint32_t* af[T];
+  const uint32_t* am[T];                     // 3-bit pairs: the tile's metadata, [group of 64 inputs][16 columns]
+  bool q3t[T], valid[T];
+  float scale[T];
+  const int rt = a.rpad / 16, tiles = NM * rt;
 #pragma unroll
-  for (int t = 0; t < kMaxT; ++t)
-#pragma unroll
-    for (int mt = 0; mt < kTMT; ++mt) acc[t][mt] = float4_t{0.f, 0.f, 0.f, 0.f};
-  // A fragment of activations (k-step ks, sub-step s) holds, in lane (q, row), the columns
-  // 256 ks + 64 q + 8 s + j: the factor unit that meets it is the one with those K rows, unit
-  // (8 ks + 2 q + s / 4, tile) of the packed factor, lane (s % 4, c) of it.
-  const half8_t* af[kMaxT];
-  const uint32_t* am[kMaxT];                 // 3-bit pairs: the tile's metadata, [group of 64 inputs][16 columns]
-  bool q3t[kMaxT], valid[kMaxT];             // (a tile past the projection's own rank holds nothing: its columns stay zero)
-  int nmine = 0;
-#pragma unroll
-  for (int t = 0; t < kMaxT; ++t) {
-    const int tile = blockIdx.z * (kTileWaves * kMaxT) + wave + t * kTileWaves;
-    af[t] = nullptr; am[t] = nullptr; q3t[t] = false; valid[t] = false;
-    if (tile < tiles) {
-      const int m = tile / rt, tl = tile - m * rt, mat = DUAL ? m : 2;
-      valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d.rank[mat]);
-      q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
-      if (q3t[t]) {
-        af[t] = reinterpret_cast<const half8_t*>(reinterpret_cast<const uint32_t*>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave + c);
-        am[t] = uniform_ptr(d.afm[mat]) + size_t(tl) * (a.K / 64) * 16 + c;
-      } else {
-        af[t] = reinterpret_cast<const half8_t*>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave + c;
-      }
-      nmine = t + 1;
-    }
+  for (int t = 0; t < T; ++t) {
+    const int tile = min(blockIdx.y * T + t, tiles - 1), m = tile / rt, tl = tile - m * rt, mat = DUAL ? m : 2;
+    valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d.rank[mat]);
+    q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
+    scale[t] = d.xa_scale[mat];
+    af[t] = reinterpret_cast<const uint32_t*>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave * (q3t[t] ? 1 : 4);
+    am[t] = q3t[t] ? uniform_ptr(d.afm[mat]) + size_t(valid[t] ? tl : 0) * (a.K / 64) * 16 + c : nullptr;
   }
+  float4_t acc[T][MT];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int all_steps = (a.K + kTileK - 1) / kTileK, per_kb = (all_steps + gridDim.x - 1) / gridDim.x;
-  const int step_lo = blockIdx.x * per_kb, steps = min(all_steps, step_lo + per_kb);
-  if (step_lo >= steps) return;              // (the finish kernel reads only K-blocks that exist)
-  // the factor units of sub-step s of k-step `step` for this lane (zero past K)
-  auto load_unit = [&](int step, int s, int t) {
-    const int kk = step * 8 + 2 * q + (s >> 2);          // this lane's 32-row unit of the factor
-    u32x4 v = u32x4{0, 0, 0, 0};
-    if (valid[t] && kk * 32 < a.K) {
+  // Unit kk: inputs 32 kk + 8 q + j of lane group q.  Wavefront w takes a contiguous run of units.
+  struct Ops { u32x4 x[MT], w[T]; uint32_t mw[T]; };
+  const u32x4* in_units = reinterpret_cast<const u32x4*>(a.in);
+  const int units = a.K / 32, per = (units + kXaWaves - 1) / kXaWaves, k_lo = wave * per, k_hi = min(units, k_lo + per);
+  auto load = [&](int kk_, Ops& o) {
+    const int kk = max(0, min(kk_, k_hi - 1));
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) o.x[mt] = DUAL ? xrow[mt][4 * kk + q] : in_units[act_unit(4 * kk + q, R[mt], a.in_rt)];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      o.mw[t] = 0;
       if (Q3 && q3t[t]) {
-        v[0] = reinterpret_cast<const uint32_t*>(af[t])[size_t(kk) * kWave + (s & 3) * 16];
+        o.w[t] = u32x4{af[t][kk * kWave + lane], 0, 0, 0};
+        o.mw[t] = am[t][(kk >> 1) * 16];
       } else {
-        v = __builtin_bit_cast(u32x4, af[t][size_t(kk) * kWave + (s & 3) * 16]);
+        o.w[t] = reinterpret_cast<const u32x4*>(af[t])[kk * kWave + lane];
       }
     }
-    return v;
   };
-  // 3-bit pairs: a lane's eight units of a k-step lie in one group of 64 inputs (rows 256 step + 64 q ..):
-  // one dword of metadata per k-step and tile
-  auto load_meta = [&](int step, int t) {
-    uint32_t mv = 0;
-    if (Q3 && q3t[t] && valid[t] && (step * 4 + q) * 64 < a.K) mv = am[t][(step * 4 + q) * 16];
-    return mv;
-  };
-  // the operand of a fetched unit (a unit that was not fetched is all zeros in either format)
-  auto operand = [&](const u32x4& v, uint32_t mv, int t) {
-    if (Q3 && q3t[t]) return q3_unit_a(v[0], mv);
-    return __builtin_bit_cast(half8_t, v);
-  };
-  u32x4 wnext[kAhead ? 8 : 1][kMaxT];
-  uint32_t mnext[kMaxT];
+  auto multiply = [&](const Ops& o) {
+    half8_t x[MT];
 #pragma unroll
-  for (int t = 0; t < kMaxT; ++t) mnext[t] = load_meta(step_lo, t);
-  if constexpr (kAhead) {
+    for (int mt = 0; mt < MT; ++mt) {
+      if constexpr (DUAL) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int t = 0; t < kMaxT; ++t) wnext[s][t] = load_unit(step_lo, s, t);
-  }
-  stage_step_rows(a, xs + (step_lo & 1) * kStepUnits, step_lo, Rm, mt_n, wave, lane);
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-  for (int step = step_lo; step < steps; ++step) {
-    stage_step_rows(a, xs + ((step + 1) & 1) * kStepUnits, step + 1, Rm, mt_n, wave, lane);
-    const uint4* buf = xs + (step & 1) * kStepUnits;
-    half8_t wcur[kAhead ? 8 : 1][kMaxT];
-    uint32_t mcur[kMaxT];
-#pragma unroll
-    for (int t = 0; t < kMaxT; ++t) { mcur[t] = mnext[t]; mnext[t] = load_meta(step + 1, t); }
-    if constexpr (kAhead) {                  // this step's units have arrived; ask for the next step's
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int t = 0; t < kMaxT; ++t) wcur[s][t] = operand(wnext[s][t], mcur[t], t);
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int t = 0; t < kMaxT; ++t) wnext[s][t] = load_unit(step + 1, s, t);
-    }
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      half8_t wf[kMaxT];
-#pragma unroll
-      for (int t = 0; t < kMaxT; ++t) {
-        if constexpr (kAhead) wf[t] = wcur[s][t];
-        else wf[t] = operand(load_unit(step, s, t), mcur[t], t);
-      }
-#pragma unroll
-      for (int mt = 0; mt < kTMT; ++mt)
-        if (mt < mt_n) {
-          const half8_t xf = __builtin_bit_cast(half8_t, buf[(mt * 8 + s) * 64 + lane]);
-#pragma unroll
-          for (int t = 0; t < kMaxT; ++t)
-            if (t < nmine) acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[t], xf, acc[t][mt], 0, 0, 0);
+        for (int i = 0; i < 4; ++i) {
+          x[mt][2 * i] = (_Float16)(__uint_as_float(o.x[mt][i] << 16) * xs2[mt]);
+          x[mt][2 * i + 1] = (_Float16)(__uint_as_float(o.x[mt][i] & 0xffff0000u) * xs2[mt]);
         }
+      } else {
+        x[mt] = __builtin_bit_cast(half8_t, o.x[mt]);
+      }
     }
-    // the copy of the next step has landed; everyone is done with this step's half of LDS
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  }
-
-  // lane holds columns 16*tile + 4*q .. +3 of row 16 mt + c
-  float* part = a.partial + size_t(blockIdx.x) * a.total_rows * pitch;
 #pragma unroll
-  for (int t = 0; t < kMaxT; ++t) {
-    const int tile = blockIdx.z * (kTileWaves * kMaxT) + wave + t * kTileWaves;
+    for (int t = 0; t < T; ++t) {
+      half8_t w = Q3 && q3t[t] ? q3_unit_a(o.w[t][0], o.mw[t]) : __builtin_bit_cast(half8_t, o.w[t]);
+      if (!valid[t]) w = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w, x[mt], acc[t][mt], 0, 0, 0);
+    }
+  };
+  Ops ring[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) load(k_lo + i, ring[i]);
+  for (int k0 = k_lo; k0 < k_hi; k0 += kAhead)
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      if (k0 + i < k_hi) multiply(ring[i]);
+      load(k0 + i + kAhead, ring[i]);
+    }
+
+  // the wavefronts' sums, one factor tile at a time: lane (q, c) holds columns 4 q .. + 3 of row 16 mt + c
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int tile = blockIdx.y * T + t, m = tile / rt;
     if (tile >= tiles) continue;
-    const int m = tile / rt, tl = tile - m * rt;
-    const float lam = d.xa_scale[DUAL ? m : 2];
+    if (t > 0) __syncthreads();
 #pragma unroll
-    for (int mt = 0; mt < kTMT; ++mt) {
-      const int row = r + 16 * mt + c;
-      if (mt >= mt_n || row >= cnt) continue;
-      *reinterpret_cast<float4_t*>(part + size_t(r0 + row) * pitch + m * a.ls * 32 + 16 * tl + 4 * q) = acc[t][mt] * lam;
+    for (int mt = 0; mt < MT; ++mt) red[wave][mt][lane] = acc[t][mt];
+    __syncthreads();
+    if (wave < MT) {
+      float4_t sum = red[0][wave][lane];
+#pragma unroll
+      for (int w = 1; w < kXaWaves; ++w) sum += red[w][wave][lane];
+      sum *= scale[t];
+      if (r + 16 * wave + c < cnt)
+        *reinterpret_cast<half4_t*>(P + size_t(wave ? R[MT - 1] : R[0]) * pitch + m * a.ls * 32 + 16 * (tile - m * rt) + 4 * q) =
+            half4_t{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
     }
   }
-}
-
-// P[row][col] = fp16(sum over K-blocks of part[kb][row][col]) for rows that take the rank-r term and
-// columns below the rank rounded up to 16; zero elsewhere.  One thread per four columns.
-__global__ __launch_bounds__(256) void xa_finish_kernel(const float* __restrict__ part, int kblocks, int rows, int pitch,
-                                                        int ls32, int rpad, const int32_t* __restrict__ comp_index,
-                                                        int comp_rows, _Float16* __restrict__ P) {
-  const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;       // index of a group of four columns
-  const int per_row = pitch / 4;
-  if (i >= size_t(rows) * per_row) return;
-  const int row = int(i / per_row), col = int(i - size_t(row) * per_row) * 4;
-  half4_t v = half4_t{0, 0, 0, 0};
-  const int ci = comp_index[row];                                // the row's place among the rows with the term (-1: none)
-  if (ci >= 0 && (col % ls32) < rpad) {
-    float4_t sum = *reinterpret_cast<const float4_t*>(part + size_t(ci) * pitch + col);
-    for (int kb = 1; kb < kblocks; ++kb)
-      sum += *reinterpret_cast<const float4_t*>(part + (size_t(kb) * comp_rows + ci) * pitch + col);
-    v = half4_t{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
+  // the padding columns of a rank that is an odd number of tiles
+  if ((rt & 1) && blockIdx.y == 0 && wave >= 2 && wave < 2 + MT * NM) {
+    const int mt = (wave - 2) % MT, m = (wave - 2) / MT;
+    if (r + 16 * mt + c < cnt)
+      *reinterpret_cast<half4_t*>(P + size_t(mt ? R[MT - 1] : R[0]) * pitch + m * a.ls * 32 + 16 * rt + 4 * q) = half4_t{0, 0, 0, 0};
   }
-  *reinterpret_cast<half4_t*>(P + size_t(row) * pitch + col) = v;
 }
 
 template <int BITS>
@@ -764,35 +713,42 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   const bool comp = f.rank > 0 && f.top_n > 0 && f.row_pair != nullptr;
   // 128-row chunks: at most one partly filled chunk per expert
   const int items = f.offsets ? f.total_rows / kBM + f.n_exp : f.n_exp * ((f.T + kBM - 1) / kBM);
-  const size_t lds = size_t(2) * kStepUnits * 16, glds = size_t(kGemmLdsUnits) * 16;
+  const size_t glds = size_t(kGemmLdsUnits) * 16;
 
-  // (in A): fp16 result at the start of the buffer, the K-block partial sums behind it
-  auto xa = [&](auto k2, auto k4, float* buf, int nm, int ksplit) {
-    const int per_wave = (nm * f.rpad / 16 + kTileWaves - 1) / kTileWaves;   // factor tiles per wavefront
-    const int pitch = nm * a.ls * 32, steps = (a.K + kTileK - 1) / kTileK;
-    const int per_kb = (steps + std::max(1, ksplit) - 1) / std::max(1, ksplit);
-    const int kblocks = (steps + per_kb - 1) / per_kb;      // no K-block without a k-step
+  // (in A) of the rows that take the term (T * top_n in all), zeros for the others
+  auto xa = [&](auto DUAL_, float* buf) {
+    constexpr bool DUAL = decltype(DUAL_)::value;
+    constexpr int nm = DUAL ? 2 : 1;
+    const int tiles = nm * f.rpad / 16;
     a.p = buf;
-    // the kernel's rows are the compact rows of the pairs that take the term (T * top_n in all), at
-    // the front of every expert's row range
     KArgs ax = a;
     ax.row_list = f.cmp_list;
-    ax.partial = buf + (size_t(f.total_rows) * pitch / 2 + 63) / 64 * 64;
-    const int xitems = f.T * f.top_n / kBM + f.n_exp;
-    // (more than 32 factor tiles, i.e. ranks above 256: further groups of 32 tiles in grid.z)
-    if (per_wave <= 2) hipLaunchKernelGGL(k2, dim3(kblocks, xitems), dim3(64 * kTileWaves), lds, s, ax);
-    else hipLaunchKernelGGL(k4, dim3(kblocks, xitems, (per_wave + 3) / 4), dim3(64 * kTileWaves), lds, s, ax);
-    const size_t groups = size_t(f.total_rows) * pitch / 4;
-    hipLaunchKernelGGL(xa_finish_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, ax.partial, kblocks,
-                       f.total_rows, pitch, a.ls * 32, a.rpad, f.cmp_index, f.total_rows, reinterpret_cast<_Float16*>(buf));
+    // 32 rows per block share the factor units it reads; 16 when that makes too few blocks: W2's longer
+    // K wants more of them (Mixtral T = 2048, 2048 rows with the term: fused 28 us with 32 rows, 36 with
+    // 16; W2 88 and 67, and 79 with 16 rows and two factor tiles per block, which reads h twice)
+    const int per = tiles <= 2 ? tiles : kXaTiles, gy = (tiles + per - 1) / per;
+    const bool wide = f.T * f.top_n / 32 * gy >= (DUAL ? f.n_cu / 4 : f.n_cu);
+    const int xitems = f.T * f.top_n / (wide ? 32 : 16) + f.n_exp;
+    const size_t units = size_t(f.total_rows) * nm * a.ls * 4;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(xitems + unsigned((units + kXaZeroUnits - 1) / kXaZeroUnits), gy), dim3(64 * kXaWaves), 0, s, ax,
+                         xitems, f.cmp_index, (const uint16_t*)f.x_tokens, reinterpret_cast<_Float16*>(buf));
+    };
+    auto pick = [&](auto T_) {
+      constexpr int T = decltype(T_)::value;
+      if (f.q3) wide ? go(xa_kernel<DUAL, T, 2, true>) : go(xa_kernel<DUAL, T, 1, true>);
+      else wide ? go(xa_kernel<DUAL, T, 2, false>) : go(xa_kernel<DUAL, T, 1, false>);
+    };
+    if (per == kXaTiles) pick(std::integral_constant<int, kXaTiles>{});
+    else if (per == 2) pick(std::integral_constant<int, 2>{});
+    else if constexpr (!DUAL) pick(std::integral_constant<int, 1>{});
   };
   if (which & 1) {
   // W1 | W3 with the SwiGLU epilogue
   a.in = f.xh; a.out = f.h; a.K = f.H; a.N = f.F; a.NT = f.F / kTileN;
   a.in_rt = f.x_rt; a.out_rt = f.h_rt;
   a.KS = padded_k(f.H) / kTileK; a.G = padded_k(f.H) / f.group;
-  if (comp && f.q3) xa(xa_tile_kernel<true, 2, true>, xa_tile_kernel<true, 4, true>, f.p13, 2, f.ksplit13);
-  else if (comp) xa(xa_tile_kernel<true, 2, false>, xa_tile_kernel<true, 4, false>, f.p13, 2, f.ksplit13);
+  if (comp) xa(std::true_type{}, f.p13);
   if (f.marks) (void)hipEventRecord(f.marks[0], s);
   if (comp && f.q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
   else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
@@ -803,8 +759,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.in = f.h; a.out = f.y_rows; a.K = f.F; a.N = f.H; a.NT = f.H / kTileN;
   a.in_rt = f.h_rt; a.out_rt = 0;
   a.KS = padded_k(f.F) / kTileK; a.G = padded_k(f.F) / f.group;
-  if (comp && f.q3) xa(xa_tile_kernel<false, 2, true>, xa_tile_kernel<false, 4, true>, f.p2, 1, f.ksplit2);
-  else if (comp) xa(xa_tile_kernel<false, 2, false>, xa_tile_kernel<false, 4, false>, f.p2, 1, f.ksplit2);
+  if (comp) xa(std::false_type{}, f.p2);
   if (f.marks) (void)hipEventRecord(f.marks[2], s);
   // four n-tiles per wavefront use a fragment of activations twice as often as two, but make
   // blocks twice as large: take the one with fewer (weighted) rounds of blocks over the 256 CUs
@@ -859,14 +814,6 @@ template <int BITS> static hipError_t tile_init_bits() {
 }
 
 hipError_t ffn_init_device() {
-  const void* fns[8] = {reinterpret_cast<const void*>(&xa_tile_kernel<true, 2, false>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 2, false>),
-                        reinterpret_cast<const void*>(&xa_tile_kernel<true, 4, false>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 4, false>),
-                        reinterpret_cast<const void*>(&xa_tile_kernel<true, 2, true>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 2, true>),
-                        reinterpret_cast<const void*>(&xa_tile_kernel<true, 4, true>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 4, true>)};
-  for (const void* fn : fns) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kStepUnits * 16);
-    if (e != hipSuccess) return e;
-  }
   hipError_t e = tile_init_bits<2>();
   if (e == hipSuccess) e = tile_init_bits<3>();
   if (e == hipSuccess) e = tile_init_bits<4>();

@@ -166,8 +166,8 @@ struct FfnArgs {
   const _Float16* xh;         // gathered activations in operand order, x_rt rows (routed: one per pair)
   _Float16* h;                // SwiGLU output in operand order, h_rt rows
   int x_rt, h_rt;
-  float* p13;                 // [ksplit13][rows][2*rpad]
-  float* p2;                  // [ksplit2][rows][rpad]
+  float* p13;                 // (x A1 | x A3), fp16 [rows][2 * ls * 32] (ffn_common.h, KArgs::p)
+  float* p2;                  // (h A2), fp16 [rows][ls * 32]; decode flavour: one per W2 K-block
   void* y_rows;               // [rows][H] bf16
   float* y_part;              // fp32 partial outputs of the W2 K-blocks (decode flavour), or null
   int32_t* plan;              // decode flavour, routed experts: the block tables (plan.h) of the two projections
@@ -177,7 +177,7 @@ struct FfnArgs {
                               // of by further blocks of the preparing launch
   int keep_partials;          // decode flavour, W2 split into K-blocks: leave the fp32 partial sums in y_part for
                               // the combine instead of adding them into y_rows
-  int ksplit13, ksplit2, total_rows;
+  int total_rows;
   int n_cu;                   // compute units of the device (the launches size their grids to fill them)
   int q3;                     // some factor pair of the layer is held at 3 bits: the launches take the kernels that
                               // can dequantize such pairs
