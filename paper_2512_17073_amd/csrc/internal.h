@@ -104,6 +104,14 @@ Workspace plan_workspace(const moe_lrc_layer* L, int T);
 hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* idx, float* w,
                         _Float16* xh /*may be null*/, int32_t* tok_exp, hipStream_t s);
 bool route_writes_exponents(const moe_lrc_layer* L, int T);
+// Batches whose routing is tiled on the fp64 matrix cores instead of one block per token: at least 128
+// tiles of 16 tokens x 16 experts and 2^26 products.  Both launches, one block per token -> tiled, us:
+// H = 2048, E = 128: T = 256 27 -> 20, 512 34 -> 26; E = 64: 256 16.2 -> 15.8, 512 20 -> 18, 2048 47 -> 39;
+// H = 4096, E = 8: 2048 24 -> 21, 4096 45 -> 24; just below the line H = 4096, E = 32: 512 17 -> 21;
+// H = 1024, E = 16: 2048 11.5 -> 12.3.
+inline bool tiled_gate(int T, int E, int H) {
+  return ((T + 15) / 16) * ((E + 15) / 16) >= 128 && (long long)T * E * H >= (1 << 26);
+}
 hipError_t launch_permute(const moe_lrc_layer* L, const int32_t* idx, int T, int32_t* counts,
                           int32_t* offsets, int32_t* row_pair, int32_t* pair_row,
                           int32_t* comp_counts, hipStream_t s);

@@ -1,5 +1,7 @@
 // Routing (Section 2.1: w = softmax(G(x)), Top-k; Section 3.2: Top-n = first n of the sorted list)
 // and the grouping of (token, slot) pairs by expert.
+#include <type_traits>
+
 #include "internal.h"
 #include "permute_body.h"
 #include "route_body.h"
@@ -119,12 +121,93 @@ __global__ __launch_bounds__(64 * NW) void route_kernel(const uint16_t* __restri
 // Many tokens: the logits of a 16-token x 16-expert tile on the fp64 matrix cores (every wavefront
 // of the other kernel re-reads the whole gate for one token; here a gate row serves 16 tokens).
 // v_mfma_f64_16x16x4: experts are the rows, tokens the columns; lane (i = lane % 16, kq = lane / 16)
-// supplies gate row i and token i at the k index of the step; it walks quarter kq of the hidden
-// dimension in order, eight elements per 16-byte load.  Products of bf16 values are exact in fp64
-// and every (expert, token) pair sees the same sequence of operations, so duplicated gate rows
-// give bit-identical logits.  Grid: (token tiles, groups of four expert tiles); logits [T][E].
+// supplies gate row i and token i at the k index of the step.  The chain of dependent 64-cycle MFMAs is
+// what a tile takes, so the NW wavefronts of a block share the hidden dimension (each lane group kq of
+// each wavefront walks its own contiguous run of 16-byte chunks in order, the next batch of four in
+// flight while one is multiplied) and add their parts through LDS in wavefront order.  Products of bf16 values are
+// exact in fp64 and every (expert, token) pair sees the same sequence of operations, so duplicated gate
+// rows give bit-identical logits.  The blocks of the first expert tile also write the tokens' pre-scale
+// exponents.  Grid: (token tiles, expert tiles); logits [T][E].
 typedef double double4_t __attribute__((ext_vector_type(4)));
-__global__ __launch_bounds__(256) void gate_logits_kernel(const uint16_t* __restrict__ x,
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void gate_logits_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T,
+                                                              int H, int E, double* __restrict__ logits, int32_t* __restrict__ tok_exp) {
+  __shared__ double4_t red[NW][64];
+  __shared__ uint32_t peak[NW][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int et = blockIdx.y, i = lane & 15, kq = lane >> 4;
+  const int token = min((int)blockIdx.x * 16 + i, T - 1), expert = min(et * 16 + i, E - 1);
+  const int chunks = H / 8, per = (chunks + 4 * NW - 1) / (4 * NW), lo = (wave * 4 + kq) * per;
+  const uint4* xp = reinterpret_cast<const uint4*>(x + size_t(token) * H);
+  const uint4* wp = reinterpret_cast<const uint4*>(wg + size_t(expert) * H);
+  double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
+  uint32_t top = 0;
+  auto load = [&](int c0, uint4 (&xv)[4], uint4 (&wv)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = min(lo + c0 + u, chunks - 1);
+      xv[u] = xp[c]; wv[u] = wp[c];
+    }
+  };
+  const bool whole = chunks == 4 * NW * per && per % 4 == 0, peaks = tok_exp != nullptr && et == 0;
+  auto multiply = [&](auto WHOLE_, int c0, const uint4 (&xv)[4], const uint4 (&wv)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool in = decltype(WHOLE_)::value || (c0 + u < per && lo + c0 + u < chunks);          // (else zeros)
+      const uint32_t xa[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+      const uint32_t wa[4] = {in ? wv[u].x : 0u, in ? wv[u].y : 0u, in ? wv[u].z : 0u, in ? wv[u].w : 0u};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (peaks) top = max(top, in ? max(xa[j] & 0x7fffu, (xa[j] >> 16) & 0x7fffu) : 0u);
+        const uint32_t xj = in ? xa[j] : 0u;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf16_to_double(wa[j] & 0xffffu), bf16_to_double(xj & 0xffffu), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf16_to_double(wa[j] >> 16), bf16_to_double(xj >> 16), acc, 0, 0, 0);
+      }
+    }
+  };
+  uint4 xv[2][4], wv[2][4];
+  load(0, xv[0], wv[0]);
+  auto walk = [&](auto WHOLE_) {
+    for (int c0 = 0; c0 < per; c0 += 8) {
+      load(c0 + 4, xv[1], wv[1]);
+      multiply(WHOLE_, c0, xv[0], wv[0]);
+      load(c0 + 8, xv[0], wv[0]);
+      if (c0 + 4 < per) multiply(WHOLE_, c0 + 4, xv[1], wv[1]);
+    }
+  };
+  if (whole) walk(std::true_type{});
+  else walk(std::false_type{});
+  red[wave][lane] = acc;
+  if (peaks) {
+    top = max(top, (uint32_t)__shfl_xor((int)top, 16));
+    top = max(top, (uint32_t)__shfl_xor((int)top, 32));
+    if (kq == 0) peak[wave][i] = top;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  acc = red[0][lane];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) acc += red[w][lane];
+  // register r of lane (i, kq) holds row kq + 4 r of the tile (the fp64 variant interleaves the
+  // rows by four), i.e. expert 16 et + kq + 4 r, of token 16 tile + i
+  const int t = blockIdx.x * 16 + i;
+  if (t >= T) return;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int e = et * 16 + kq + 4 * r;
+    if (e < E) logits[size_t(t) * E + e] = acc[r];
+  }
+  if (peaks && kq == 0) {
+#pragma unroll
+    for (int w = 1; w < NW; ++w) peak[0][i] = max(peak[0][i], peak[w][i]);
+    const int eb = int(peak[0][i] >> 7);
+    tok_exp[t] = eb == 0 ? 0 : min(60, max(-60, 127 - eb));
+  }
+}
+
+// The same with one wavefront per tile, four expert tiles per block (which share the tokens through the
+// L1), for so many tiles that they fill the chip by themselves: E = 128, T = 4096: 63 us with the Top-k, 91 split.
+__global__ __launch_bounds__(256) void gate_logits_many_kernel(const uint16_t* __restrict__ x,
                                                           const uint16_t* __restrict__ wg, int T, int H, int E,
                                                           double* __restrict__ logits) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -291,19 +374,26 @@ __global__ __launch_bounds__(1024) void permute_scatter_kernel(const int32_t* __
 
 }  // namespace
 
-bool route_writes_exponents(const moe_lrc_layer* L, int T) {
-  return !(T >= 1024 && L->cfg.n_experts >= 128 && L->d_logits != nullptr);
+// which of the two tiled forms (or neither) a batch takes
+static bool gate_many(const moe_lrc_layer* L, int T) { return T >= 1024 && L->cfg.n_experts >= 128 && L->d_logits != nullptr; }
+static bool gate_split(const moe_lrc_layer* L, int T) {
+  return !gate_many(L, T) && tiled_gate(T, L->cfg.n_experts, L->cfg.hidden) && L->d_logits != nullptr;
 }
+
+bool route_writes_exponents(const moe_lrc_layer* L, int T) { return !gate_many(L, T); }
 
 hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* idx, float* w,
                         _Float16* xh, int32_t* tok_exp, hipStream_t s) {
   const moe_lrc_config& c = L->cfg;
-  // Many tokens and many experts: tiled on the fp64 matrix cores.  (With few expert tiles a tile's
-  // chain of H / 4 dependent 64-cycle MFMAs is longer than the per-token kernel takes: measured
-  // slower for 8 and 64 experts up to T = 2048.)
-  if (T >= 1024 && c.n_experts >= 128 && xh == nullptr && L->d_logits != nullptr) {
-    hipLaunchKernelGGL(gate_logits_kernel, dim3((T + 15) / 16, (c.n_experts + 63) / 64), dim3(256), 0, s,
-                       (const uint16_t*)x, L->d_wg, T, c.hidden, c.n_experts, L->d_logits);
+  // Many (token, expert) products: tiled on the fp64 matrix cores.
+  if (xh == nullptr && (gate_many(L, T) || gate_split(L, T))) {
+    const int tt = (T + 15) / 16, et = (c.n_experts + 15) / 16;
+    if (gate_many(L, T))
+      hipLaunchKernelGGL(gate_logits_many_kernel, dim3(tt, (et + 3) / 4), dim3(256), 0, s, (const uint16_t*)x, L->d_wg, T, c.hidden,
+                         c.n_experts, L->d_logits);
+    else
+      hipLaunchKernelGGL(gate_logits_kernel<8>, dim3(tt, et), dim3(512), 0, s, (const uint16_t*)x, L->d_wg, T, c.hidden, c.n_experts,
+                         L->d_logits, tok_exp);
     hipLaunchKernelGGL(topk_kernel, dim3((T + 3) / 4), dim3(256), 0, s, L->d_logits,
                        L->has_bias ? L->d_bias : nullptr, T, c.n_experts, c.top_k, c.renormalize, idx, w);
     return hipGetLastError();
@@ -316,7 +406,7 @@ hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* i
   // ... and, while the tokens alone leave CUs idle, several blocks per token, each with at least
   // one gate row per wavefront (the fp64 dot products of a token's rows are what the launch takes)
   int G = 1;
-  if (wide && L->d_logits != nullptr && T <= c.max_tokens)
+  if (wide && c.n_experts >= 128 && L->d_logits != nullptr && T <= c.max_tokens)
     while (G < kRouteGroups && T * G * 2 <= L->n_cu && c.n_experts / (G * 2) >= 16) G *= 2;
   auto go = [&](auto kernel, int nw) {
     hipLaunchKernelGGL(kernel, dim3(T, G), dim3(64 * nw), 0, s, (const uint16_t*)x, L->d_wg,

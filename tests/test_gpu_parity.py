@@ -47,6 +47,9 @@ SMALL = {
     # several 128-row chunks per expert with a ragged last one; a rank that is no multiple of 16 or 32
     # (padding columns of the factors) at 4 bit
     "tiny_T700_r40": configs.TINY.with_(tokens=700, rank=40, bits=4, name="tiny_T700_r40"),
+    # thousands of rows with the rank-r term: 32 rows per block in both (in A) launches; routing of many
+    # tokens by few experts on the fp64 matrix cores
+    "tiny_T8300_r64": configs.TINY.with_(tokens=8300, rank=64, name="tiny_T8300_r64"),
     # heavily skewed routing at decode size: some experts get more than 32 rows (several passes of
     # the decode kernel), others none
     "tiny_skew": configs.TINY.with_(tokens=44, gate_kind="unit", gate_std=1.0, zipf_s=3.0, name="tiny_skew"),
