@@ -165,6 +165,12 @@ void factor_section_bytes(const moe_lrc_layer* L, int e, int mat, size_t& a_byte
   }
 }
 
+static void set_mat_rank(moe_lrc_layer* L, int e, int mat, int rank) {
+  int& r = L->mat_rank[e * 3 + mat];
+  (mat == 2 ? L->live2 : L->live13) += (rank + 15) / 16 - (r + 15) / 16;
+  r = rank;
+}
+
 // Points projection `mat` of an expert table entry at its factor sections (a_base, b_base: the
 // starts of the projection's A and B sections on the device).
 void set_factor_ptrs(const moe_lrc_layer* L, int e, int mat, ExpertDesc& d, const uint8_t* a_base, const uint8_t* b_base) {
@@ -236,6 +242,7 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   a.p13 = reinterpret_cast<float*>(ws + w.p13); a.p2 = reinterpret_cast<float*>(ws + w.p2);
   a.y_part = reinterpret_cast<float*>(ws + w.y_part);
   a.plan = reinterpret_cast<int32_t*>(ws + w.plan);
+  a.live13 = L->live13; a.live2 = L->live2;
   a.y_rows = y_rows; a.total_rows = T * c.top_k;
   a.n_cu = L->n_cu;
   a.q3 = L->n_q3 > 0;
@@ -479,8 +486,8 @@ int moe_lrc_set_expert_ranked(moe_lrc_layer* L, int expert, int mat, const uint8
 
   // Factors: the layouts are rank-major, so the pair of rank `rank` is a prefix of the projection's A
   // section and a prefix of its B section; only the prefixes are staged.  (The kernels take each
-  // projection's own rank from the expert table and read nothing past it; the rest of both sections
-  // is kept zero in the device slot all the same.)
+  // projection's own rank from the expert table; a block of factor tiles that begins below it may read on past
+  // it, inside the section, and drops the products; the rest of both sections is kept zero in the device slot.)
   if (b.f_bytes > 0) {
     const MatLayout fm = make_layout(m.K, m.N, m.bits, m.group, rank);     // sizes of the prefixes
     const size_t aoff = L->f_off[expert] + b.off_af[mat], boff = L->f_off[expert] + b.off_bf[mat];
@@ -503,7 +510,7 @@ int moe_lrc_set_expert_ranked(moe_lrc_layer* L, int expert, int mat, const uint8
     if (!pooled && m.af_bytes > fm.af_bytes) LRC_HIP(hipMemset(L->d_f + aoff + fm.af_bytes, 0, m.af_bytes - fm.af_bytes));
     if (!pooled && m.bf_bytes > fm.bf_bytes) LRC_HIP(hipMemset(L->d_f + boff + fm.bf_bytes, 0, m.bf_bytes - fm.bf_bytes));
   }
-  L->mat_rank[expert * 3 + mat] = rank;
+  set_mat_rank(L, expert, mat, rank);
   L->n_q3 -= L->mat_q3[expert * 3 + mat];
   L->mat_q3[expert * 3 + mat] = 0;
   L->mat_inv_mu[expert * 3 + mat] = 1.f;
@@ -561,7 +568,7 @@ int moe_lrc_set_expert_factors_quantized(moe_lrc_layer* L, int expert, int mat, 
   // what an earlier upload may have left behind the pair
   if (pooled) std::memset(L->h_f + aoff + piece.size(), 0, span - piece.size());
   else LRC_HIP(hipMemset(L->d_f + aoff + piece.size(), 0, span - piece.size()));
-  L->mat_rank[expert * 3 + mat] = rank;
+  set_mat_rank(L, expert, mat, rank);
   L->n_q3 += 1 - L->mat_q3[expert * 3 + mat];
   L->mat_q3[expert * 3 + mat] = 1;
   L->mat_inv_mu[expert * 3 + mat] = 1.0f / (mu_a * mu_b);

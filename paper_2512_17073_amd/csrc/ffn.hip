@@ -564,7 +564,7 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
 constexpr int kXaWaves = 16, kXaTiles = 4;
 constexpr int kXaZeroUnits = 8192;         // 16-byte units a zeroing block looks after
 template <bool DUAL, int T, int MT, bool Q3>
-__global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, const int32_t* __restrict__ comp_index,
+__global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, bool uneven, const int32_t* __restrict__ comp_index,
                                                            const uint16_t* __restrict__ x_bf16, _Float16* __restrict__ P) {
   constexpr int NM = DUAL ? 2 : 1;
   constexpr int kAhead = T * MT == 8 ? 3 : 4;     // units in flight (registers)
@@ -600,6 +600,35 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, c
     xrow[mt] = DUAL ? reinterpret_cast<const u32x4*>(x_bf16 + size_t(a.row_pair[R[mt]] / a.top_k) * a.K) : nullptr;
     xs2[mt] = DUAL ? pow2i(a.row_exp[R[mt]]) : 1.f;
   }
+  const int rt = a.rpad / 16, tiles = NM * rt;
+  // zeros in 16 columns of the chunk's rows
+  const int R_first = R[0], R_last = R[MT - 1];
+  auto zero_tile = [=](int m, int tl, int mt) {
+    if (r + 16 * mt + c < cnt)
+      *reinterpret_cast<half4_t*>(P + size_t(mt ? R_last : R_first) * pitch + m * a.ls * 32 + 16 * tl + 4 * q) = half4_t{0, 0, 0, 0};
+  };
+  // the padding columns of a rank that is an odd number of tiles
+  auto zero_padding = [=] {
+    if ((rt & 1) && blockIdx.y == 0 && wave >= 2 && wave < 2 + MT * NM) zero_tile((wave - 2) / MT, rt, (wave - 2) % MT);
+  };
+  // Ranks that differ (Section 3.1): a block all of whose tiles lie past their projection's own rank leaves here
+  // (largest rank 1024, every pair at 16, Qwen3 T = 4096: (x A) 674 -> 174 us, (h A2) 210 -> 75).
+  if (uneven) {
+    bool some = false;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int tile = blockIdx.y * T + t, m = tile / rt;
+      some |= tile < tiles && 16 * (tile - m * rt) < __builtin_amdgcn_readfirstlane(d.rank[DUAL ? min(m, 1) : 2]);
+    }
+    if (!some) {
+      // (the FFN kernel reads the columns of the rank steps its expert runs, those of the expert's larger pair)
+      const int rank_e = max(__builtin_amdgcn_readfirstlane(d.rank[DUAL ? 0 : 2]), __builtin_amdgcn_readfirstlane(d.rank[DUAL ? 1 : 2]));
+      const int tile = blockIdx.y * T + wave / MT, m = tile / rt, tl = tile - m * rt;
+      if (wave < T * MT && tile < tiles && 16 * tl < (rank_e + 31) / 32 * 32) zero_tile(m, tl, wave % MT);
+      zero_padding();
+      return;
+    }
+  }
   // factor tile t of this block: 16 columns of projection m.  (The loads are unconditional: what a tile past
   // the projection's own rank or past the last one reads lies inside the factor sections, and its
   // products are dropped.)
@@ -607,7 +636,6 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, c
   const uint32_t* am[T];                     // 3-bit pairs: the tile's metadata, [group of 64 inputs][16 columns]
   bool q3t[T], valid[T];
   float scale[T];
-  const int rt = a.rpad / 16, tiles = NM * rt;
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int tile = min(blockIdx.y * T + t, tiles - 1), m = tile / rt, tl = tile - m * rt, mat = DUAL ? m : 2;
@@ -689,16 +717,11 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, c
       for (int w = 1; w < kXaWaves; ++w) sum += red[w][wave][lane];
       sum *= scale[t];
       if (r + 16 * wave + c < cnt)
-        *reinterpret_cast<half4_t*>(P + size_t(wave ? R[MT - 1] : R[0]) * pitch + m * a.ls * 32 + 16 * (tile - m * rt) + 4 * q) =
+        *reinterpret_cast<half4_t*>(P + size_t(wave ? R_last : R_first) * pitch + m * a.ls * 32 + 16 * (tile - m * rt) + 4 * q) =
             half4_t{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
     }
   }
-  // the padding columns of a rank that is an odd number of tiles
-  if ((rt & 1) && blockIdx.y == 0 && wave >= 2 && wave < 2 + MT * NM) {
-    const int mt = (wave - 2) % MT, m = (wave - 2) / MT;
-    if (r + 16 * mt + c < cnt)
-      *reinterpret_cast<half4_t*>(P + size_t(mt ? R[MT - 1] : R[0]) * pitch + m * a.ls * 32 + 16 * rt + 4 * q) = half4_t{0, 0, 0, 0};
-  }
+  zero_padding();
 }
 
 template <int BITS>
@@ -723,6 +746,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     a.p = buf;
     KArgs ax = a;
     ax.row_list = f.cmp_list;
+    const bool uneven = (DUAL ? f.live13 : f.live2) < (long long)f.n_exp * tiles;    // (ranks that differ)
     // 32 rows per block share the factor units it reads; 16 when that makes too few blocks: W2's longer
     // K wants more of them (Mixtral T = 2048, 2048 rows with the term: fused 28 us with 32 rows, 36 with
     // 16; W2 88 and 67, and 79 with 16 rows and two factor tiles per block, which reads h twice)
@@ -732,7 +756,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     const size_t units = size_t(f.total_rows) * nm * a.ls * 4;
     auto go = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(xitems + unsigned((units + kXaZeroUnits - 1) / kXaZeroUnits), gy), dim3(64 * kXaWaves), 0, s, ax,
-                         xitems, f.cmp_index, (const uint16_t*)f.x_tokens, reinterpret_cast<_Float16*>(buf));
+                         xitems, uneven, f.cmp_index, (const uint16_t*)f.x_tokens, reinterpret_cast<_Float16*>(buf));
     };
     auto pick = [&](auto T_) {
       constexpr int T = decltype(T_)::value;

@@ -71,6 +71,7 @@ struct moe_lrc_layer {
   std::vector<uint8_t> mat_q3;         // [n_total*3] 1: the pair is held at 3 bits (layout.h), in the projection's own
                                        // factor sections, and dequantized by the kernels that consume it
   std::vector<float> mat_inv_mu;       // [n_total*3] 1 / (the power-of-two factors folded into a 3-bit pair's operands)
+  int live13 = 0, live2 = 0;           // 16-column tiles of the A factors of W1 and W3, and of W2, over all experts
   int n_q3 = 0;                        // projections held at 3 bits (0: the launches take the kernels without that path)
   size_t f_total = 0;                  // bytes of d_f (and of h_f)
   int32_t* d_perm = nullptr;           // block counters of the grouping of many pairs by several blocks (kPermuteScratchInts)
@@ -185,6 +186,8 @@ struct FfnArgs {
                               // of by further blocks of the preparing launch
   int keep_partials;          // decode flavour, W2 split into K-blocks: leave the fp32 partial sums in y_part for
                               // the combine instead of adding them into y_rows
+  int live13, live2;          // 16-column factor tiles that hold a pair's columns: those of W1 and W3, those of W2, summed
+                              // over the experts
   int total_rows;
   int n_cu;                   // compute units of the device (the launches size their grids to fill them)
   int q3;                     // some factor pair of the layer is held at 3 bits: the launches take the kernels that

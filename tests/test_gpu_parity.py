@@ -543,7 +543,7 @@ def test_int3_factors(amd, tokens, rank):
 def test_int3_factors_with_a_rank_per_projection(amd, tokens):
     """Factor pairs at 3 bits whose ranks differ from matrix to matrix (Section 3.1 steps 1 and 2
     together): W1 and W3 of an expert run different numbers of rank steps, some projections have no
-    pair at all, and the factor tiles past a projection's own rank are never read.  All three
+    pair at all, and the factor tiles past a projection's own rank add nothing.  All three
     flavour mixes (16, 300, 700 tokens), resident against staged bit for bit."""
     import torch
     cfg = configs.TINY.with_(rank=64, tokens=tokens, bits=2, name=f"int3_ranks_T{tokens}")

@@ -1,0 +1,59 @@
+"""What (x A) and (h A) of the grouped-GEMM flavour cost where their work differs from one layer to the
+next, as ratios of two stage times of one process (the smallest of several runs each): a launch that
+does work it need not do shows as a ratio near the one of the two shapes."""
+import numpy as np
+import pytest
+
+from workload import configs, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def amd():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    import paper_2512_17073_amd as amd
+    amd.lib()
+    return amd
+
+
+def _stage_us(amd, cfg, stage, own_rank=None, int3=False):
+    """Smallest time of `stage` over twelve forwards of a layer whose pairs all have rank own_rank (the layer's
+    rank if None); every expert stores the same artefacts."""
+    import torch
+    r = cfg.rank if own_rank is None else own_rank
+    one = {m: synth.sample_artifacts(cfg.with_(rank=r), 0, m) for m in (0, 1, 2)}
+    L = amd.Layer.from_config(cfg)
+    L.set_gate(*synth.make_gate(cfg))
+    q3 = {m: synth.sample_factor_codes(cfg, 0, m) for m in (0, 1, 2)} if int3 else None
+    for e in range(cfg.n_experts):
+        for m, a in one.items():
+            if int3:
+                L.set_expert(e, m, a["codes"], a["scale"], a["zero"], None, None, 0)
+                L.set_expert_factors_quantized(e, m, r, *q3[m])
+            else:
+                L.set_expert(e, m, a["codes"], a["scale"], a["zero"], a["A"], a["B"], r)
+    x = amd.bf16_tensor(synth.make_tokens(cfg))
+    L.profile_enable(True)
+    best = np.inf
+    for i in range(14):
+        L.forward(x)
+        torch.cuda.synchronize()
+        if i >= 2:
+            best = min(best, L.profile_read()[stage] * 1e3)
+    L.close()
+    print(f"\n[{cfg.name}] {stage} {best:.1f} us", flush=True)
+    return best
+
+
+WIDE = configs.QWEN3.with_(n_experts=64, tokens=2048, ffn=512, zipf_s=0.0)
+
+
+def test_tiles_past_a_pairs_own_rank_cost_little(amd):
+    """A layer whose largest rank is 1024 while its pairs have 16 (Section 3.1 allocates ranks far apart):
+    computing the empty factor tiles takes as long as a layer with all pairs at 1024, leaving
+    them out a quarter of that."""
+    full = _stage_us(amd, WIDE.with_(rank=1024, name="all_1024"), "xa13")
+    dead = _stage_us(amd, WIDE.with_(rank=1024, name="largest_1024_own_16"), "xa13", own_rank=16)
+    assert dead < 0.6 * full
