@@ -632,8 +632,8 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, b
   // factor tile t of this block: 16 columns of projection m.  (The loads are unconditional: what a tile past
   // the projection's own rank or past the last one reads lies inside the factor sections, and its
   // products are dropped.)
-  const uint32_t* af[T];
-  const uint32_t* am[T];                     // 3-bit pairs: the tile's metadata, [group of 64 inputs][16 columns]
+  GlobalPtr<uint32_t> af[T];
+  GlobalPtr<uint32_t> am[T];                 // 3-bit pairs: the tile's metadata, [group of 64 inputs][16 columns]
   bool q3t[T], valid[T];
   float scale[T];
 #pragma unroll
@@ -642,8 +642,8 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, b
     valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d.rank[mat]);
     q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
     scale[t] = d.xa_scale[mat];
-    af[t] = reinterpret_cast<const uint32_t*>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave * (q3t[t] ? 1 : 4);
-    am[t] = q3t[t] ? uniform_ptr(d.afm[mat]) + size_t(valid[t] ? tl : 0) * (a.K / 64) * 16 + c : nullptr;
+    af[t] = as_global<uint32_t>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave * (q3t[t] ? 1 : 4);
+    am[t] = q3t[t] ? as_global<uint32_t>(uniform_ptr(d.afm[mat])) + size_t(valid[t] ? tl : 0) * (a.K / 64) * 16 + c : nullptr;
   }
   float4_t acc[T][MT];
 #pragma unroll
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, b
         o.w[t] = u32x4{af[t][kk * kWave + lane], 0, 0, 0};
         o.mw[t] = am[t][(kk >> 1) * 16];
       } else {
-        o.w[t] = reinterpret_cast<const u32x4*>(af[t])[kk * kWave + lane];
+        o.w[t] = reinterpret_cast<GlobalPtr<u32x4>>(af[t])[kk * kWave + lane];
       }
     }
   };
@@ -750,7 +750,9 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     // 32 rows per block share the factor units it reads; 16 when that makes too few blocks: W2's longer
     // K wants more of them (Mixtral T = 2048, 2048 rows with the term: fused 28 us with 32 rows, 36 with
     // 16; W2 88 and 67, and 79 with 16 rows and two factor tiles per block, which reads h twice)
-    const int per = tiles <= 2 ? tiles : kXaTiles, gy = (tiles + per - 1) / per;
+    // (3-bit pairs: two tiles per block; with four, the dequantized operands do not fit the registers, 9 to 41 of them
+    // spilled: rank 64, K = 4096, T = 1024: 64 us with four tiles, 22 with two)
+    const int per = tiles <= 2 ? tiles : f.q3 ? 2 : kXaTiles, gy = (tiles + per - 1) / per;
     const bool wide = f.T * f.top_n / 32 * gy >= (DUAL ? f.n_cu / 4 : f.n_cu);
     const int xitems = f.T * f.top_n / (wide ? 32 : 16) + f.n_exp;
     const size_t units = size_t(f.total_rows) * nm * a.ls * 4;
@@ -760,8 +762,10 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     };
     auto pick = [&](auto T_) {
       constexpr int T = decltype(T_)::value;
-      if (f.q3) wide ? go(xa_kernel<DUAL, T, 2, true>) : go(xa_kernel<DUAL, T, 1, true>);
-      else wide ? go(xa_kernel<DUAL, T, 2, false>) : go(xa_kernel<DUAL, T, 1, false>);
+      if constexpr (T <= 2) {
+        if (f.q3) return wide ? go(xa_kernel<DUAL, T, 2, true>) : go(xa_kernel<DUAL, T, 1, true>);
+      }
+      wide ? go(xa_kernel<DUAL, T, 2, false>) : go(xa_kernel<DUAL, T, 1, false>);
     };
     if (per == kXaTiles) pick(std::integral_constant<int, kXaTiles>{});
     else if (per == 2) pick(std::integral_constant<int, 2>{});

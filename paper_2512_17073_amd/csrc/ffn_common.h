@@ -123,6 +123,11 @@ __device__ inline void wait_loads() {
 }
 __device__ inline void wait_loads_barrier() { wait_loads(); __syncthreads(); }
 
+// A pointer into global memory whose provenance the compiler cannot see (read from a table): loads through a
+// generic pointer become flat ones, which count in two counters and make every wait one for all loads.
+template <class T> using GlobalPtr = const __attribute__((address_space(1))) T*;
+template <class T, class U> __device__ inline GlobalPtr<T> as_global(const U* p) { return reinterpret_cast<GlobalPtr<T>>(reinterpret_cast<uintptr_t>(p)); }
+
 // A pointer read from memory, moved into scalar registers (a buffer resource must be wave-uniform).
 template <class T> __device__ inline const T* uniform_ptr(const T* p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);

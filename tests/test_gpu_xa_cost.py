@@ -57,3 +57,13 @@ def test_tiles_past_a_pairs_own_rank_cost_little(amd):
     full = _stage_us(amd, WIDE.with_(rank=1024, name="all_1024"), "xa13")
     dead = _stage_us(amd, WIDE.with_(rank=1024, name="largest_1024_own_16"), "xa13", own_rank=16)
     assert dead < 0.6 * full
+
+
+def test_int3_pairs_cost_little_more_than_fp16_ones(amd):
+    """(x A1 | x A3) of pairs held at 3 bits beside the same layer with fp16 pairs: a quarter of the
+    factor bytes and some dequantizing.  A block that holds more operands than its registers and spills them takes
+    more than twice as long."""
+    cfg = configs.MIXTRAL_DECODE.with_(ffn=512, rank=64, tokens=1024, bits=3)
+    plain = _stage_us(amd, cfg.with_(name="fp16_pairs"), "xa13")
+    packed = _stage_us(amd, cfg.with_(name="int3_pairs"), "xa13", int3=True)
+    assert packed < 1.5 * plain
