@@ -77,8 +77,8 @@ Workspace plan_workspace(const moe_lrc_layer* L, int T) {
   w.xh = take((P + kActPadRows) * Hp * 2);
   w.xh_sh = take(c.n_shared ? (size_t(T) + kActPadRows) * Hp * 2 : 0);
   w.h = take((P + kActPadRows) * Fp * 2);
-  // (in A) in fp16, the columns padded to a multiple of 32 (the sizes, which callers may have planned
-  // with, leave room for K-block sums in fp32 behind it)
+  // (in A) in fp16, the columns padded to a multiple of 32, and, for the grouped products that stage their rows,
+  // ksplit K-block sums in fp32 behind it
   w.p13 = take(size_t(L->ksplit13 + 1) * P * 2 * (rpad + 16) * 4 + 256);
   // (the decode flavour keeps one fp16 (h A2) per W2 K-block)
   w.p2 = take(std::max(size_t(L->ksplit2 + 1) * P * (rpad + 16) * 4, size_t(kMaxKBlocks) * P * (rpad + 16) * 2) + 256);
@@ -243,7 +243,7 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   a.y_part = reinterpret_cast<float*>(ws + w.y_part);
   a.plan = reinterpret_cast<int32_t*>(ws + w.plan);
   a.live13 = L->live13; a.live2 = L->live2;
-  a.y_rows = y_rows; a.total_rows = T * c.top_k;
+  a.y_rows = y_rows; a.ksplit13 = L->ksplit13; a.ksplit2 = L->ksplit2; a.total_rows = T * c.top_k;
   a.n_cu = L->n_cu;
   a.q3 = L->n_q3 > 0;
   a.row_exp = reinterpret_cast<int32_t*>(ws + w.row_exp);
@@ -297,7 +297,7 @@ static int run_shared(moe_lrc_layer* L, const void* x, int T, uint8_t* ws, hipSt
   a.h = reinterpret_cast<_Float16*>(ws + w.sh_h);
   a.x_rt = T + kActPadRows; a.h_rt = c.n_shared * T + kActPadRows;
   a.y_part = reinterpret_cast<float*>(ws + w.sh_y_part);
-  a.y_rows = ws + w.sh_y; a.total_rows = T * c.n_shared;
+  a.y_rows = ws + w.sh_y; a.ksplit13 = 1; a.ksplit2 = 1; a.total_rows = T * c.n_shared;
   a.n_cu = L->n_cu;
   a.row_exp = row_exp; a.tok_exp = nullptr;
   LRC_HIP(launch_expert_ffn(a, stream));

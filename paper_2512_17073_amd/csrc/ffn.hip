@@ -26,7 +26,7 @@
 //     double-buffered in LDS: the copy of the next half goes from memory straight to LDS (no
 //     registers) while the current one is multiplied; one barrier per half;
 //   - the rank-r term is extra steps: the B factor's 32-wide units take the place of the codes and
-//     meet (in A), which a small kernel (xa_kernel) has left in global memory; its first fragments are
+//     meet (in A), which xa_kernel (or xa_tile_kernel and xa_join_kernel) has left in global memory; its first fragments are
 //     copied into LDS at the start.
 // Experts with few rows (decode) take the other flavour, ffn_decode.hip.
 #include <algorithm>
@@ -556,9 +556,8 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
 // a block of 16 wavefronts takes 16 MT rows x at most T 16-column factor tiles (grid.y: groups of T
 // tiles), the wavefronts share K and read both operands straight into registers, three or four units of 32
 // inputs ahead; their sums meet in LDS, in wavefront
-// order.  Qwen3 T = 4096: 30 + 19 us for the two products, DeepSeek T = 512: 14 + 9, Mixtral T = 2048:
-// 28 + 67.  Staging 128 rows at a time through LDS, K split over blocks, and a second launch that added
-// the K-blocks took 46 + 37, 20 + 18 and 30 + 54 us.
+// order.  Qwen3 T = 4096: 30 + 22 us for the two products, DeepSeek T = 512: 12 + 10; with the two launches below
+// 43 + 37 and 16 + 16.  Where those are faster instead: xa_staged.
 // Q3: some factor pair of the layer is held at 3 bits (layout.h); such a pair's units are fetched as
 // (codes, metadata) dwords and dequantized.
 constexpr int kXaWaves = 16, kXaTiles = 4;
@@ -724,6 +723,239 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, b
   zero_padding();
 }
 
+// The same product for many factor tiles or a long K, in two launches: with 128 rows staged through LDS,
+// eight row tiles meet every fragment of the factors, and the rows are read once per 32 factor tiles (the
+// kernel above reads the factors once per 16 or 32 rows and the rows once per four tiles).  Which of the
+// two a product takes: xa_staged below.
+// xa_tile_kernel: K-block sums in fp32, [K-block][compact row][NM * ls * 32 columns], already multiplied by
+// the projection's pre-scale.  A block of 8 wavefronts takes 128 compact rows and at most 8 NT factor tiles,
+// wavefront w tiles w, w + 8, ...; the k-steps of activations are double-buffered in LDS; grid.x splits K so
+// that the launch fills the chip, grid.z walks groups of 8 NT tiles.  Tiles past their projection's own rank are
+// neither read, multiplied nor stored, and a block without a tile that counts leaves at once.
+// xa_join_kernel: adds the K-blocks in order and writes every routed row of an expert: fp16 sums, and zeros
+// for the rows without the term and between a projection's rank and the rank steps its expert runs.
+constexpr int kXtWaves = 8;
+constexpr int kXtRowTiles = kBM / 16;
+constexpr int kXtStepUnits = kXtRowTiles * 8 * 64;       // 16-byte units of a k-step of activations (64 KB)
+
+// Copy of the activations of k-step ks for the 128 rows of a chunk into `buf`, as 64 fragments (row tile
+// mt, sub-step s) of 64 units: wavefront w copies the fragments with s = w, each lane its own 16 bytes from
+// global memory straight to LDS; R[mt] is this lane's input row of row tile mt.  A column past the end is
+// clamped to a valid unit (the factor units that meet it are zeros).
+__device__ inline void stage_step_rows(const KArgs& a, uint4* buf, int ks, const int (&R)[kXtRowTiles], int mt_n, int wave, int lane) {
+  const uint4* in_units = reinterpret_cast<const uint4*>(a.in);
+  const int q = lane >> 4, s = wave;
+  const int k8 = min(ks * 32 + q * 8 + s, a.K / 8 - 1);
+#pragma unroll
+  for (int mt = 0; mt < kXtRowTiles; ++mt)
+    if (mt < mt_n)        // (row tiles past the chunk's last row are not read)
+      __builtin_amdgcn_global_load_lds(
+          reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(in_units + act_unit(k8, R[mt], a.in_rt))),
+          reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(buf + (mt * 8 + s) * 64)), 16, 0, 0);
+}
+
+template <bool DUAL, int NT, bool Q3>
+__global__ __launch_bounds__(64 * kXtWaves, 2) void xa_tile_kernel(KArgs a) {
+  extern __shared__ uint4 xs[];
+  constexpr int NM = DUAL ? 2 : 1;
+  constexpr bool kAhead = NT <= 2;                       // registers for the factor units of a whole k-step ahead
+  Chunk ch;
+  if (!find_chunk<kBM>(a, blockIdx.y, ch)) return;
+  const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
+  const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
+  const ExpertDesc& d = a.desc[e];
+  if (!d.has_factors) return;
+  const int th = threadIdx.x, lane = th & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
+  const int q = lane >> 4, c = lane & 15;
+  const int mt_n = min(kXtRowTiles, (cnt - r + 15) >> 4);
+  const int rt = a.rpad / 16, tiles = NM * rt;           // 16-column factor tiles in all
+  const int pitch = NM * a.ls * 32;
+  // K-block blockIdx.x
+  const int steps_all = (a.K + kTileK - 1) / kTileK;
+  const int per = (steps_all + gridDim.x - 1) / gridDim.x;
+  const int step_lo = blockIdx.x * per, steps = min(steps_all, step_lo + per);
+
+  // A fragment of activations (k-step ks, sub-step s) holds, in lane (q, row), the columns
+  // 256 ks + 64 q + 8 s + j: the factor unit that meets it is the one with those K rows, unit
+  // (8 ks + 2 q + s / 4, tile) of the packed factor, lane (s % 4, c) of it.
+  GlobalPtr<half8_t> af[NT];
+  GlobalPtr<uint32_t> am[NT];                // 3-bit pairs: the tile's metadata, [group of 64 inputs][16 columns]
+  bool q3t[NT], valid[NT];
+  const int z0 = blockIdx.z * (kXtWaves * NT), z1 = min(tiles, z0 + kXtWaves * NT);
+  bool some = false;                         // a tile of this block lies below its projection's rank
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    const int first = max(z0 - m * rt, 0);
+    some |= first < min(rt, z1 - m * rt) && 16 * first < __builtin_amdgcn_readfirstlane(d.rank[DUAL ? m : 2]);
+  }
+  if (!some) return;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int tile = z0 + wave + t * kXtWaves;
+    af[t] = nullptr; am[t] = nullptr; q3t[t] = false; valid[t] = false;
+    if (tile < tiles) {
+      const int m = tile / rt, tl = tile - m * rt, mat = DUAL ? m : 2;
+      valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d.rank[mat]);
+      q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
+      if (q3t[t]) {
+        af[t] = reinterpret_cast<GlobalPtr<half8_t>>(as_global<uint32_t>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave + c);
+        am[t] = as_global<uint32_t>(uniform_ptr(d.afm[mat])) + size_t(tl) * (a.K / 64) * 16 + c;
+      } else {
+        af[t] = as_global<half8_t>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave + c;
+      }
+    }
+  }
+  // The chunk's rows are compact rows: row_list names the routed row whose activations each one reads.  A
+  // row past the expert's last compact row reads one of the zero rows at the end of the buffer (its
+  // results are never stored).
+  int Rm[kXtRowTiles];
+#pragma unroll
+  for (int mt = 0; mt < kXtRowTiles; ++mt)
+    Rm[mt] = r + 16 * mt + c < cnt ? a.row_list[r0 + r + 16 * mt + c] : a.in_rt - dec::kZeroRows + c;
+  float4_t acc[NT][kXtRowTiles];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int mt = 0; mt < kXtRowTiles; ++mt) acc[t][mt] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+  // the factor units of sub-step s of k-step `step` for this lane (zero past K)
+  auto load_unit = [&](int step, int s, int t) {
+    const int kk = step * 8 + 2 * q + (s >> 2);          // this lane's 32-row unit of the factor
+    u32x4 v = u32x4{0, 0, 0, 0};
+    if (valid[t] && kk * 32 < a.K) {
+      if (Q3 && q3t[t]) v[0] = reinterpret_cast<GlobalPtr<uint32_t>>(af[t])[size_t(kk) * kWave + (s & 3) * 16];
+      else v = __builtin_bit_cast(u32x4, af[t][size_t(kk) * kWave + (s & 3) * 16]);
+    }
+    return v;
+  };
+  // 3-bit pairs: a lane's eight units of a k-step lie in one group of 64 inputs (rows 256 step + 64 q ..):
+  // one dword of metadata per k-step and tile
+  auto load_meta = [&](int step, int t) {
+    uint32_t mv = 0;
+    if (Q3 && q3t[t] && valid[t] && (step * 4 + q) * 64 < a.K) mv = am[t][(step * 4 + q) * 16];
+    return mv;
+  };
+  // the operand of a fetched unit (a unit that was not fetched is all zeros in either format)
+  auto operand = [&](const u32x4& v, uint32_t mv, int t) {
+    if (Q3 && q3t[t]) return q3_unit_a(v[0], mv);
+    return __builtin_bit_cast(half8_t, v);
+  };
+  u32x4 wnext[kAhead ? 8 : 1][NT];
+  uint32_t mnext[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) mnext[t] = load_meta(step_lo, t);
+  if constexpr (kAhead) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) wnext[s][t] = load_unit(step_lo, s, t);
+  }
+  stage_step_rows(a, xs + (step_lo & 1) * kXtStepUnits, step_lo, Rm, mt_n, wave, lane);
+  wait_loads_barrier();
+  for (int step = step_lo; step < steps; ++step) {
+    stage_step_rows(a, xs + ((step + 1) & 1) * kXtStepUnits, step + 1, Rm, mt_n, wave, lane);
+    const uint4* buf = xs + (step & 1) * kXtStepUnits;
+    half8_t wcur[kAhead ? 8 : 1][NT];
+    uint32_t mcur[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) { mcur[t] = mnext[t]; mnext[t] = load_meta(step + 1, t); }
+    if constexpr (kAhead) {                  // this step's units have arrived; ask for the next step's
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) wcur[s][t] = operand(wnext[s][t], mcur[t], t);
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) wnext[s][t] = load_unit(step + 1, s, t);
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      half8_t wf[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if constexpr (kAhead) wf[t] = wcur[s][t];
+        else wf[t] = operand(load_unit(step, s, t), mcur[t], t);
+      }
+#pragma unroll
+      for (int mt = 0; mt < kXtRowTiles; ++mt)
+        if (mt < mt_n) {
+          const half8_t xf = __builtin_bit_cast(half8_t, buf[(mt * 8 + s) * 64 + lane]);
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            if (valid[t]) acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[t], xf, acc[t][mt], 0, 0, 0);
+        }
+    }
+    // the copy of the next step has landed; everyone is done with this step's half of LDS
+    wait_loads_barrier();
+  }
+
+  // lane holds columns 16 tile + 4 q .. + 3 of row 16 mt + c
+  float* part = a.partial + size_t(blockIdx.x) * a.total_rows * pitch;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if (!valid[t]) continue;
+    const int tile = z0 + wave + t * kXtWaves, m = tile / rt, tl = tile - m * rt;
+    const float lam = d.xa_scale[DUAL ? m : 2];
+#pragma unroll
+    for (int mt = 0; mt < kXtRowTiles; ++mt) {
+      const int row = r + 16 * mt + c;
+      if (mt >= mt_n || row >= cnt) continue;
+      *reinterpret_cast<float4_t*>(part + size_t(r0 + row) * pitch + m * a.ls * 32 + 16 * tl + 4 * q) = acc[t][mt] * lam;
+    }
+  }
+}
+
+// One thread: four columns of a routed row.
+__global__ __launch_bounds__(256) void xa_join_kernel(KArgs a, int kblocks, int nm, bool uneven, const int32_t* __restrict__ comp_index,
+                                                      _Float16* __restrict__ P) {
+  const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;
+  const int ls32 = a.ls * 32, pitch = nm * ls32, per_row = pitch / 4;
+  if (i >= size_t(a.total_rows) * per_row) return;
+  const int row = int(i / per_row), col = int(i - size_t(row) * per_row) * 4;
+  const int m = col / ls32, cm = col - m * ls32;         // projection, column of its (in A)
+  const int ci = comp_index[row];                        // the row's place among those with the term (-1: none)
+  int rank = a.rpad;
+  if (uneven) {
+    int e = 0;                                           // the expert of the row: the last one with offsets[e] <= row
+    for (int step = 128; step > 0; step /= 2)
+      if (e + step < a.n_exp && a.offsets[e + step] <= row) e += step;
+    const int32_t* ranks = a.desc[e].rank;
+    const int rank_e = nm == 2 ? max(ranks[0], ranks[1]) : ranks[2];
+    if (cm / 32 * 32 >= rank_e) return;                  // a rank step this expert does not run
+    rank = ranks[nm == 2 ? m : 2];
+  }
+  float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
+  if (ci >= 0 && cm / 16 * 16 < rank) {
+    const float4_t* part = reinterpret_cast<const float4_t*>(a.partial + size_t(ci) * pitch + col);
+    const size_t kb4 = size_t(a.total_rows) * per_row;
+    sum = part[0];
+    for (int kb = 1; kb < kblocks; ++kb) sum += part[kb * kb4];
+  }
+  *reinterpret_cast<half4_t*>(P + size_t(row) * pitch + col) = half4_t{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
+}
+
+// Whether a product takes the two launches.  What the one launch takes grows with the factor tiles times K; past
+// about 20480 the staged rows win (us, one launch / two):
+//   fused, K = 4096: rank 16 (8192) T = 1024 17 / 25, 4096 22 / 37; rank 32 (16384) 23 / 25 and 28 / 38;
+//     rank 64 (32768) 28 / 27 and 47 / 42; rank 256 49 / 45 and 112 / 87; rank 1024 138 / 91 and 389 / 253
+//   fused, K = 2048, 128 experts, T = 4096: rank 32 (8192) 41 / 46; rank 128 (32768) 94 / 70; rank 1024 663 / 358
+//   W2, K = 14336, T = 2048: rank 16 (14336) 45 / 50; rank 64 (57344) 66 / 54; rank 256 132 / 84
+//   W2, K = 768, T = 4096: rank 128 (6144) 38 / 45; rank 256 (12288) 63 / 55; rank 512 108 / 79
+// (below the line the two launches still win here and there: K = 4096, rank 32, T = 256: 24 / 19; K = 1408, rank 128,
+// T = 1024: 31 / 23.)  With ranks that differ the tiles that hold columns count, averaged over the experts, but at
+// least a fifth of the grid, whose blocks without such tiles are not free (largest rank 1024, the others 16,
+// K = 1216, T = 2048: 93 / 44).  3-bit pairs, two tiles per block: the two launches past 8192 unless the rows are few,
+// tiles times K times rows at most 4e7 (rank 64, K = 4096, T = 1024 22 / 32, 2048 37 / 34, 4096 55 / 52; rank 256,
+// K = 768, T = 4096 91 / 59).
+bool xa_staged(const FfnArgs& f, bool dual) {
+  const long long K = dual ? f.H : f.F, tiles = (dual ? 2 : 1) * f.rpad / 16;
+  const long long cost5 = std::max<long long>(5 * (dual ? f.live13 : f.live2), tiles * f.n_exp) * K / f.n_exp;     // 5 x tiles x K
+  if (f.q3) return cost5 > 5 * 8192 && cost5 * f.T * f.top_n > 5 * 40000000LL;
+  return cost5 > 5 * 20480;
+}
+
 template <int BITS>
 hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   int gs = 0;
@@ -747,9 +979,25 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     KArgs ax = a;
     ax.row_list = f.cmp_list;
     const bool uneven = (DUAL ? f.live13 : f.live2) < (long long)f.n_exp * tiles;    // (ranks that differ)
+    if (xa_staged(f, DUAL)) {
+      const int steps = (a.K + kTileK - 1) / kTileK, ksplit = DUAL ? f.ksplit13 : f.ksplit2;
+      const int per_kb = (steps + ksplit - 1) / ksplit, kblocks = (steps + per_kb - 1) / per_kb;     // no K-block without a k-step
+      const int pitch = nm * a.ls * 32, per_wave = (tiles + kXtWaves - 1) / kXtWaves;               // factor tiles per wavefront
+      ax.partial = buf + (size_t(f.total_rows) * pitch / 2 + 63) / 64 * 64;                         // (behind the fp16 result)
+      auto tile = [&](auto kernel, int nt) {
+        hipLaunchKernelGGL(kernel, dim3(kblocks, f.T * f.top_n / kBM + f.n_exp, (tiles + kXtWaves * nt - 1) / (kXtWaves * nt)), dim3(64 * kXtWaves),
+                           size_t(2) * kXtStepUnits * 16, s, ax);
+      };
+      if (per_wave <= 2) f.q3 ? tile(xa_tile_kernel<DUAL, 2, true>, 2) : tile(xa_tile_kernel<DUAL, 2, false>, 2);
+      else f.q3 ? tile(xa_tile_kernel<DUAL, 4, true>, 4) : tile(xa_tile_kernel<DUAL, 4, false>, 4);
+      const size_t groups = size_t(f.total_rows) * pitch / 4;
+      hipLaunchKernelGGL(xa_join_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, ax, kblocks, nm, uneven, f.cmp_index,
+                         reinterpret_cast<_Float16*>(buf));
+      return;
+    }
     // 32 rows per block share the factor units it reads; 16 when that makes too few blocks: W2's longer
-    // K wants more of them (Mixtral T = 2048, 2048 rows with the term: fused 28 us with 32 rows, 36 with
-    // 16; W2 88 and 67, and 79 with 16 rows and two factor tiles per block, which reads h twice)
+    // K wants more of them (K = 4096, rank 64, 2048 rows with the term: 28 us with 32 rows, 36 with 16; W2 with
+    // K = 14336 88 and 67)
     // (3-bit pairs: two tiles per block; with four, the dequantized operands do not fit the registers, 9 to 41 of them
     // spilled: rank 64, K = 4096, T = 1024: 64 us with four tiles, 22 with two)
     const int per = tiles <= 2 ? tiles : f.q3 ? 2 : kXaTiles, gy = (tiles + per - 1) / per;
@@ -842,6 +1090,14 @@ template <int BITS> static hipError_t tile_init_bits() {
 }
 
 hipError_t ffn_init_device() {
+  const void* fns[8] = {reinterpret_cast<const void*>(&xa_tile_kernel<true, 2, false>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 2, false>),
+                        reinterpret_cast<const void*>(&xa_tile_kernel<true, 4, false>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 4, false>),
+                        reinterpret_cast<const void*>(&xa_tile_kernel<true, 2, true>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 2, true>),
+                        reinterpret_cast<const void*>(&xa_tile_kernel<true, 4, true>), reinterpret_cast<const void*>(&xa_tile_kernel<false, 4, true>)};
+  for (const void* fn : fns) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kXtStepUnits * 16);
+    if (e != hipSuccess) return e;
+  }
   hipError_t e = tile_init_bits<2>();
   if (e == hipSuccess) e = tile_init_bits<3>();
   if (e == hipSuccess) e = tile_init_bits<4>();

@@ -54,7 +54,8 @@ struct KArgs {
   int ls;                    // rank steps of 32 of the B factor: ceil(rank / 32)
   int n_exp;                 // experts of this launch (many-rows flavour: the grid enumerates row chunks)
   int kb_steps;              // decode flavour: k-steps per K-block (grid.z blocks split K; KS if one)
-  float* partial;            // decode flavour, more than one K-block: fp32 partial outputs [kb][rows][N]
+  float* partial;            // decode flavour, more than one K-block: fp32 partial outputs [kb][rows][N]; grouped (in A)
+                             // with staged rows: K-block sums [kb][compact row][projections * ls * 32]
   const int32_t* plan;       // decode flavour: null (grid = blocks per expert x experts), or the block table
                              // (PlanEntry per block, plan.h)
   const int32_t* row_exp;    // per input row: the exponent s of its power-of-two pre-scale (row_exponent below);

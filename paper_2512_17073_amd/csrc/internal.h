@@ -188,6 +188,7 @@ struct FfnArgs {
                               // the combine instead of adding them into y_rows
   int live13, live2;          // 16-column factor tiles that hold a pair's columns: those of W1 and W3, those of W2, summed
                               // over the experts
+  int ksplit13, ksplit2;      // most K-blocks of the staged (in A) products (what p13 and p2 have room for)
   int total_rows;
   int n_cu;                   // compute units of the device (the launches size their grids to fill them)
   int q3;                     // some factor pair of the layer is held at 3 bits: the launches take the kernels that

@@ -660,3 +660,47 @@ def test_ranks_from_the_papers_bucket_up_to_1024(amd, tokens):
     assert err <= TOL and none > 10 * TOL
     assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16))
     Lr.close(); Ls.close()
+
+
+@pytest.mark.parametrize("hidden,ffn,rank,tokens,kind", [
+    (1536, 1600, 120, 300, "same"),        # at most two factor tiles per wavefront; a rank that is no multiple of 16
+    (704, 832, 1024, 300, "same"),         # four, several groups of 32; K no multiple of a k-step
+    (704, 832, 1024, 300, "bucket"),       # ranks far apart, W1 and W3 of an expert differ, some pairs missing
+    (832, 704, 520, 1000, "same"),         # an odd number of factor tiles, several 128-row chunks per expert
+    (704, 832, 256, 2400, "int3"),         # pairs at 3 bits, enough rows
+])
+def test_in_a_with_staged_rows(amd, hidden, ffn, rank, tokens, kind):
+    """(x A) and (h A2) of many factor tiles take the two launches that stage the rows (tiles times K past
+    20480; 3-bit pairs past 8192 and 4e7 with the rows): the sizes at which its splits change, against
+    the oracle, and staged residency bit for bit."""
+    import torch
+    bucket = (1024, 16, 0, 256, 1024, 32, 512)
+    cfg = configs.TINY.with_(hidden=hidden, ffn=ffn, n_experts=4, rank=rank, tokens=tokens, bits=2, name=f"staged_rows_{kind}_{hidden}_r{rank}")
+    layer = fixtures.sample_layer(cfg)
+    for e, ex in enumerate(layer["experts"]):
+        for m in (0, 1, 2):
+            a = ex[m]
+            if kind == "int3":
+                a["Aq"], a["Bq"] = synth.sample_factor_codes(cfg, e, m)
+                a["A"] = a["B"] = None
+            elif kind == "bucket":
+                a["rank"] = r = bucket[(3 * e + 2 * m) % len(bucket)]
+                a["A"] = np.ascontiguousarray(a["A"][:, :r]) if r else None
+                a["B"] = np.ascontiguousarray(a["B"][:r]) if r else None
+    x_bits = synth.make_tokens(cfg)
+    x = amd.bf16_tensor(x_bits)
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    Lr = amd.Layer.from_config(cfg)
+    Ls = amd.Layer.from_config(cfg, residency=amd.STAGED)
+    Lr.load(layer); Ls.load(layer)
+    out_r = Lr.forward(x).clone()
+    torch.cuda.synchronize()
+    assert Lr.stats()["path"] == 3
+    out_s = Ls.forward(x).clone()
+    torch.cuda.synchronize()
+    err = orc.rel_frobenius(_to_np(out_r), ref["out"])
+    none = orc.rel_frobenius(_to_np(out_r), fixtures.oracle_forward(cfg.with_(top_n=0), layer, x_bits)["out"])
+    print(f"\n[{cfg.name}] out rel err {err:.2e} (the rank terms move the output by {none:.2e})", flush=True)
+    assert err <= TOL and none > 5 * TOL
+    assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16))
+    Lr.close(); Ls.close()

@@ -67,3 +67,21 @@ def test_int3_pairs_cost_little_more_than_fp16_ones(amd):
     plain = _stage_us(amd, cfg.with_(name="fp16_pairs"), "xa13")
     packed = _stage_us(amd, cfg.with_(name="int3_pairs"), "xa13", int3=True)
     assert packed < 1.5 * plain
+
+
+def test_large_ranks_read_the_rows_a_few_times_only(amd):
+    """Rank 1024 against rank 64, both at their own size: sixteen times the factor tiles.  With the rows read
+    again for every four tiles that costs ten times the time or more, with the rows staged once per 32 tiles
+    about six times."""
+    small = _stage_us(amd, WIDE.with_(rank=64, tokens=4096, name="rank_64"), "xa13")
+    large = _stage_us(amd, WIDE.with_(rank=1024, tokens=4096, name="rank_1024"), "xa13")
+    assert large < 8.5 * small
+
+
+def test_a_long_k_with_several_tiles_does_not_gather_pieces(amd):
+    """(h A2) over K = 14336 at rank 256 against rank 16: 2.4 times with the rows staged, 3.7 times with each row's
+    16-byte pieces gathered again for every four tiles (82 and 127 us against 34); the line lies between."""
+    cfg = configs.MIXTRAL_PREFILL.with_(hidden=1024, tokens=2048)
+    small = _stage_us(amd, cfg.with_(rank=16, name="long_k_rank_16"), "xa2")
+    large = _stage_us(amd, cfg.with_(rank=256, name="long_k_rank_256"), "xa2")
+    assert large < 3.0 * small
