@@ -286,9 +286,10 @@ __device__ inline Moments join(const Moments& a, const Moments& b) {
   Moments r;
   r.n = n;
   r.mean = a.mean + dn * b.n;
-  r.m2 = a.m2 + b.m2 + d * dn * ab;
-  r.m3 = a.m3 + b.m3 + d * dn * dn * ab * (a.n - b.n) + 3.0 * dn * (a.n * b.m2 - b.n * a.m2);
-  r.m4 = a.m4 + b.m4 + d * dn * dn * dn * ab * (a.n * a.n - ab + b.n * b.n) + 6.0 * dn * dn * (a.n * a.n * b.m2 + b.n * b.n * a.m2) +
+  const double t = d * dn * ab;            // (counts are multiplied in first: no term is smaller on the way than at the end)
+  r.m2 = a.m2 + b.m2 + t;
+  r.m3 = a.m3 + b.m3 + t * (a.n - b.n) * dn + 3.0 * dn * (a.n * b.m2 - b.n * a.m2);
+  r.m4 = a.m4 + b.m4 + t * (a.n * a.n - ab + b.n * b.n) * dn * dn + 6.0 * (a.n * a.n * b.m2 + b.n * b.n * a.m2) * dn * dn +
          4.0 * dn * (a.n * b.m3 - b.n * a.m3);
   return r;
 }
@@ -993,7 +994,9 @@ int moe_lrc_offline_kurtosis(const double* W_dev, size_t n, double* kappa) {
   hipLaunchKernelGGL(moment_kernel, dim3(blocks), dim3(256), 0, nullptr, W_dev, n, d_part);
   hipLaunchKernelGGL(moment_join_kernel, dim3(1), dim3(256), 0, nullptr, d_part, blocks);
   OFF_HIP(hipMemcpy(&m, d_part, sizeof(Moments), hipMemcpyDeviceToHost));
-  *kappa = m.m4 * m.n / (m.m2 * m.m2);
+  m.m2 /= m.n;                             // (the ratio of the means: m2 * m2 of the sums overflows n^2 times earlier)
+  *kappa = m.m4 / m.n / (m.m2 * m.m2);
+  if (*kappa < 1.0) *kappa = 1.0;          // (the least it can be: what a constant matrix leaves is rounding alone)
 done:
   if (d_part) (void)hipFree(d_part);
   return rc;

@@ -131,6 +131,21 @@ def _aligned(A, B, A0, B0):
     return A * sign[None, :], B * sign[:, None]
 
 
+@pytest.mark.parametrize("power,rel", [(247, 1e-12), (-250, 1e-12), (-260, 1e-9)])
+def test_kurtosis_of_very_large_and_very_small_values(amd, power, rel):
+    """A ratio of moments does not change with the scale; while the fourth powers fit fp64 it is finite, whatever
+    the number of entries (2^-1040, the fourth power of 2^-260, is a subnormal with 34 bits: 6e-11 each)."""
+    W = np.random.default_rng(3).standard_normal((1024, 1031))
+    want = compress.kurtosis(W)
+    assert abs(amd.offline_kurtosis(_dev(W * 2.0 ** power)) - want) <= rel * want
+
+
+@pytest.mark.parametrize("K,N", [(96, 70), (64, 129), (256, 130)])
+def test_kurtosis_of_a_constant_matrix(amd, K, N):
+    """0 / 0 up to rounding: never below 1, the least a kurtosis can be (or NaN where the mean is exact)."""
+    assert not amd.offline_kurtosis(_dev(np.full((K, N), 0.3))) < 1.0
+
+
 @pytest.mark.parametrize("K,N,r,bits", [(256, 512, 8, 3), (512, 768, 40, 2), (1024, 640, 16, 2), (384, 384, 128, 4)])
 def test_residual_factors(amd, K, N, r, bits):
     rng = np.random.default_rng(K + N + r)
