@@ -976,7 +976,9 @@ int moe_lrc_offline_quantize_refined(const double* W_dev, int K, int N, int bits
   if (iters < 0 || iters > 1000 || !(p > 0.0 && p <= 1.0) || !(beta > 0.0) || !(kappa >= 1.0))
     return set_error(MOE_LRC_EINVAL, "offline_quantize_refined: need 0 <= iters <= 1000, 0 < p <= 1, beta > 0, kappa >= 1");
   if (K <= 0 || N <= 0 || group <= 0 || K % group) return set_error(MOE_LRC_ESHAPE, "offline_quantize_refined: K must be a positive multiple of group");
-  const double tau = std::pow(beta, -1.0 / (2.0 - p)), tau_step = std::pow(kappa, -1.0 / (2.0 - p));
+  double tau = std::pow(beta, -1.0 / (2.0 - p));
+  const double tau_step = std::pow(kappa, -1.0 / (2.0 - p));
+  if (!(tau < HUGE_VAL)) tau = 0.0;        // (no finite start for the kernel's running threshold: every entry takes the pow())
   auto kernel = group == 32 ? quantize_refined_kernel<32> : group == 64 ? quantize_refined_kernel<64> : quantize_refined_kernel<0>;
   hipLaunchKernelGGL(kernel, dim3((N + 63) / 64, K / group), dim3(64), 0, (hipStream_t)stream, W_dev, K, N, bits, group,
                      iters, p, beta, kappa, tau, tau_step, codes_dev, scale_dev, zero_dev, residual_dev);

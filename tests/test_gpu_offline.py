@@ -118,6 +118,19 @@ def test_refined_quantizer_around_its_threshold(amd, group, beta):
     assert (np.abs(dc) <= 1).all() and (dc != 0).sum() <= 2
 
 
+@pytest.mark.parametrize("group", [32, 48, 64])
+@pytest.mark.parametrize("beta,kappa,iters", [(1e-310, 1e155, 6), (1e-300, 1e100, 5), (1e300, 1.0, 3), (10.0, float("inf"), 3)])
+def test_refined_quantizer_with_extreme_penalties(amd, group, beta, kappa, iters):
+    """p = 1: the threshold is 1 / beta, which fp64 cannot hold for a subnormal beta, also after the penalty has grown
+    to where the threshold matters."""
+    W = np.random.default_rng(group).standard_normal((192, 70)) * 0.02
+    want = compress.quantize_refined(W, 3, group, iters=iters, p=1.0, beta=beta, kappa=kappa)
+    codes, scale, zero, _ = amd.offline_quantize(_dev(W), 3, group, refine={"iters": iters, "p": 1.0, "beta": beta, "kappa": kappa})
+    np.testing.assert_array_equal(_bits(scale), want["scale"])
+    np.testing.assert_array_equal(_bits(zero), want["zero"])
+    np.testing.assert_array_equal(codes.cpu().numpy(), want["codes"])
+
+
 def test_kurtosis(amd):
     rng = np.random.default_rng(3)
     for W in (rng.standard_normal((700, 513)), rng.laplace(size=(300, 1001)) * 0.05 + 0.01, rng.random((257, 129))):
