@@ -47,8 +47,7 @@ SMALL = {
     # several 128-row chunks per expert with a ragged last one; a rank that is no multiple of 16 or 32
     # (padding columns of the factors) at 4 bit
     "tiny_T700_r40": configs.TINY.with_(tokens=700, rank=40, bits=4, name="tiny_T700_r40"),
-    # thousands of rows with the rank-r term: 32 rows per block in both (in A) launches; routing of many
-    # tokens by few experts on the fp64 matrix cores
+    # thousands of rows with the rank-r term: 32 rows per block in both (in A) launches
     "tiny_T8300_r64": configs.TINY.with_(tokens=8300, rank=64, name="tiny_T8300_r64"),
     # heavily skewed routing at decode size: some experts get more than 32 rows (several passes of
     # the decode kernel), others none
@@ -466,6 +465,40 @@ def test_route_with_several_blocks_per_token(amd):
             np.testing.assert_array_equal(_to_np(idx), ref["idx"][:T], err_msg=f"E={E} T={T}")
             np.testing.assert_allclose(_to_np(w), ref["w"][:T], rtol=2e-6, atol=1e-30)
         L.close()
+
+
+@pytest.mark.parametrize("tokens,experts,hidden", [(1001, 60, 1216), (2047, 17, 2112)])
+def test_route_tiled_with_ragged_sizes(amd, tokens, experts, hidden):
+    """Batches that are routed in tiles of 16 tokens x 16 experts (at least 128 tiles and 2^26 products) at sizes that fill
+    neither: a last tile of tokens and of experts, shares of the hidden size that end inside a batch of
+    chunks (hidden / 8 no multiple of 128), a duplicated gate row.  Indices bit-exact; and a forward on tokens
+    of very different magnitudes, which takes the exponents this kernel writes on its way."""
+    import torch
+    cfg = configs.TINY.with_(hidden=hidden, ffn=128, n_experts=experts, top_k=3, top_n=1, rank=16, tokens=tokens, gate_kind="unit", gate_std=1.5,
+                             name=f"route_tiled_{tokens}_{experts}_{hidden}")
+    assert (tokens + 15) // 16 * ((experts + 15) // 16) >= 128 and tokens * experts * hidden >= 1 << 26
+    layer = fixtures.sample_layer(cfg)
+    layer["wg"] = layer["wg"].copy()
+    layer["wg"][3] = layer["wg"][experts - 2]       # equal logits in different tiles: the lower index wins
+    x_bits = synth.make_tokens(cfg)
+    scale = np.array([(-1) ** t * (3 * t % 37) for t in range(tokens)], dtype=np.int64)
+    zero = (x_bits & 0x7fff) == 0
+    x_bits = np.where(zero, x_bits, x_bits.astype(np.int64) + (scale[:, None] << 7)).astype(np.uint16)      # times 2^scale
+    x_bits[tokens - 2] = 0                          # a token of zeros: all logits equal
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    L = amd.Layer.from_config(cfg)
+    L.load(layer)
+    x = amd.bf16_tensor(x_bits)
+    idx, w = L.route(x)
+    np.testing.assert_array_equal(_to_np(idx), ref["route"]["idx"])
+    np.testing.assert_allclose(_to_np(w), ref["route"]["w"], rtol=2e-6, atol=1e-30)
+    out = _to_np(L.forward(x))
+    torch.cuda.synchronize()
+    norm = np.linalg.norm(ref["out"], axis=1)
+    err = np.linalg.norm(out - ref["out"], axis=1)[norm > 0] / norm[norm > 0]
+    print(f"\n[{cfg.name}] worst token {err.max():.2e}", flush=True)
+    assert err.max() <= 4 * TOL and np.abs(out[norm == 0]).max(initial=0.0) == 0.0      # (per token: the worst of thousands)
+    L.close()
 
 
 @pytest.mark.parametrize("tokens", [16, 300])
