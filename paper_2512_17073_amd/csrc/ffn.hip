@@ -12,8 +12,7 @@
 //     waits for on its own (its first loads, the barriers, its epilogue) is time the other one
 //     multiplies in.  With one block of 8 wavefronts per CU that time was lost: the fused launch took
 //     272 us and W2 194 on the Qwen3 shape at T = 4096 (8 and 3 k-steps per block), 248 and 150 so;
-//     a long K (Mixtral, 16 and 56 k-steps) gains 2 %: there the chip's power sets the clock (1.6 GHz
-//     instead of 2.3 with nothing but the products left in the loop);
+//     a long K (Mixtral, 16 and 56 k-steps) gains 2 %;
 //   - the products run on v_mfma_f32_32x32x16_f16 (the same peak rate as the 16x16x32 shape, half
 //     as many MFMA and LDS-read instructions per flop): two streams of 16 output columns that meet
 //     the same activations (W1 and W3 of one n-tile, or two n-tiles of W2) become the 32 rows of one
@@ -21,7 +20,8 @@
 //     streams side by side; the activations are staged as fragments of 32 rows;
 //   - the packed weights never touch LDS: each wavefront loads its tiles HBM -> registers, the next
 //     k-step's into the registers of the current one as soon as its last code is unpacked (a second
-//     set of registers does not fit beside 128 accumulators at 3 and 4 bits);
+//     set of registers does not fit beside 128 accumulators at 3 and 4 bits; at 4 bits the fused kernel and the one
+//     with four n-tiles of W2 per wavefront spill 96 to 108 bytes per lane as it is);
 //   - the activations of half a k-step (128 rows x 128 columns, 32 KB, MFMA operand order) are
 //     double-buffered in LDS: the copy of the next half goes from memory straight to LDS (no
 //     registers) while the current one is multiplied; one barrier per half;

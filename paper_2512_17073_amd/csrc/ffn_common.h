@@ -118,11 +118,11 @@ template <int N> __device__ inline void lds_wait(half8_t& a, half8_t& b) {
 // vmcnt as out of order, and from then on every use of a loaded register waits for vmcnt(0), i.e.
 // for the refills just issued as well (the ring of loads is then one deep instead of two; a Mixtral-shaped forward at T = 64 and 2 bits
 // took 160.5 us with inline asm waits and takes 156.0 with these).
-__device__ inline void wait_loads() {
+__device__ inline void wait_loads_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0), the other counters as they are
+  __syncthreads();
 }
-__device__ inline void wait_loads_barrier() { wait_loads(); __syncthreads(); }
 
 // A pointer into global memory whose provenance the compiler cannot see (read from a table): loads through a
 // generic pointer become flat ones, which count in two counters and make every wait one for all loads.

@@ -106,10 +106,14 @@ hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* i
                         _Float16* xh /*may be null*/, int32_t* tok_exp, hipStream_t s);
 bool route_writes_exponents(const moe_lrc_layer* L, int T);
 // Batches whose routing is tiled on the fp64 matrix cores instead of one block per token: at least 128
-// tiles of 16 tokens x 16 experts and 2^26 products.  Both launches, one block per token -> tiled, us:
-// H = 2048, E = 128: T = 256 27 -> 20, 512 34 -> 26; E = 64: 256 16.2 -> 15.8, 512 20 -> 18, 2048 47 -> 39;
-// H = 4096, E = 8: 2048 24 -> 21, 4096 45 -> 24; just below the line H = 4096, E = 32: 512 17 -> 21;
-// H = 1024, E = 16: 2048 11.5 -> 12.3.
+// tiles of 16 tokens x 16 experts and 2^26 products.  Whole call, one block per token -> tiled, us.  Above the line no
+// shape measured loses: H = 2048, E = 128: T = 256 24.3 -> 17.4, 512 30.7 -> 22.9; E = 64: 512 18.5 -> 16.9,
+// 2048 45 -> 37; H = 4096, E = 8: 2048 29.1 -> 22.2, 4096 56 -> 26; H = 1216, E = 60: 1001 24.3 -> 15.5.  The two cross
+// below it, at no one product of the sizes (a block per token fills the chip in steps of T, a tile takes H in
+// series): H = 2048, E = 128: T = 128 13.8 -> 15.2, 160 23.9 -> 15.5, 255 24.4 -> 17.6; E = 64: 256 14.9 -> 14.7,
+// 511 18.6 -> 17.1; H = 4096, E = 8: 1024 15.9 -> 20.2, 1400 22.2 -> 20.8, 2047 29.1 -> 22.6; E = 32: 512 16.9 -> 21.2,
+// 700 24.8 -> 22.0; H = 5120, E = 16: 512 24.9 -> 23.3, 1800 94 -> 25; H = 512, E = 120: 128 10.7 -> 13.6,
+// 1000 25.6 -> 15.7.  The line is on the safe side of all of these.
 inline bool tiled_gate(int T, int E, int H) {
   return ((T + 15) / 16) * ((E + 15) / 16) >= 128 && (long long)T * E * H >= (1 << 26);
 }

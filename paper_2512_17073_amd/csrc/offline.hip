@@ -78,8 +78,8 @@ __global__ __launch_bounds__(256) void quantize_kernel(const double* __restrict_
 // The same for the usual groups: 64 columns (CPL per lane) x one group per block, the group's rows shared
 // by four wavefronts of R rows each, whose part stays in registers: the matrix is read once, 16 bytes
 // per lane where N is even.  Minimum and maximum do not depend on the order they are taken in.
-// Bound: HBM (read 8, write 9 bytes per entry): 1.0 GB at 4096 x 14336, 170 us at the streaming
-// rate, measured 164 us; reading the group twice, one column per thread, took 333.
+// Bound: HBM (read 8, write 9 bytes per entry): 1.0 GB at 4096 x 14336 in 163 us, 6.1 TB/s (a large streaming read
+// reaches 5.9 here); reading the group twice, one column per thread, took 333.
 template <int R, int CPL>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(const double* __restrict__ W, int K, int N, int bits,
                                                             uint8_t* __restrict__ codes, uint16_t* __restrict__ scale,
@@ -164,7 +164,9 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const double* __rest
 // below it (the usual case: |x| is at most half a step unless the code is clamped) needs no pow(), and
 // (w - 0) / s is the quotient that chose the code, the same in every step.  G > 0: the group has G
 // entries and their quotients stay in registers; a step in which some entry of the group is not far
-// below the threshold is redone with the entries re-read.  G == 0: any group, re-read in every step.
+// below the threshold is redone with the entries re-read.  G == 0: any group, re-read in every step (64 quotients in
+// fp64 already take 346 of a lane's 512 registers: groups of 128 and 256 do not fit and stay here, 2.8 and 3.3 times as
+// fast as before the threshold; 2048 x 1408: 674 and 1169 us).
 // tau: beta^(-1 / (2 - p)), times tau_step = kappa^(-1 / (2 - p)) after every step.
 // 2048 x 1408, 3 bits, 20 steps: 975 us with pow() and two divisions per entry and step, 71 us so (the
 // serial sums of 45000 groups; 0.7 wavefronts per SIMD).
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(256) void moment_join_kernel(Moments* part, int par
 // v_mfma_f64_16x16x4.  The products here are tall and skinny: A is the K x N matrix, read once, and B
 // is a few megabytes, so a block of four wavefronts takes 128 rows of C and all its columns up to
 // 16 CT, a wavefront 32 rows (two tiles that share every B operand read from LDS); the reduction
-// dimension is split over grid.z so that there are about two blocks per CU, each writing its own
+// dimension is split over grid.z so that there are about three blocks per CU, each writing its own
 // partial C (dsum_kernel adds them in order).  k advances in chunks of 32: the next chunk of A (registers) and of B
 // (registers, then the other half of LDS) is requested before the current one is multiplied.  Inside
 // a chunk, MFMA step (h, s) covers k = 16 h + 4 kq + s for lane group kq, so that a lane reads 32
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(256) void moment_join_kernel(Moments* part, int par
 // Bound: HBM (470 MB per product at 4096 x 14336: 80 us at the streaming rate) and the fp64 matrix rate
 // (5.6 GFLOP with 40 columns padded to 48: 80 us) about equally; measured 130-135 us per product, plain
 // or transposed, against 2520 and 730 us with 4 x 4 vector products per thread on a 64 x 64 tile and
-// no split (64 or 224 blocks); more wavefronts per SIMD change nothing.
+// no split (64 or 224 blocks); three wavefronts per SIMD (at which <false, 3> spills 20 bytes per lane) measured like two.
 typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef double double2_t __attribute__((ext_vector_type(2), aligned(8)));
 constexpr int kGemmRows = 128, kGemmK = 32, kGemmBlocks = 768;
@@ -504,7 +506,7 @@ __global__ __launch_bounds__(256) void dsum_kernel(const double* __restrict__ pa
 }
 
 // How a product is cut: column tiles per block, and parts of the reduction (at least 64 long each) so
-// that the blocks number about 512.  (A Gram matrix whose parts the factorisation adds up itself: at
+// that the blocks number about kGemmBlocks.  (A Gram matrix whose parts the factorisation adds up itself: at
 // most kGramParts of them, all in flight at once there.)
 constexpr int kGramParts = 32;
 struct GemmCut { int ct, gx, gy, parts, k_per; };
