@@ -168,8 +168,9 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const double* __rest
 // fp64 already take 346 of a lane's 512 registers: groups of 128 and 256 do not fit and stay here, 2.8 and 3.3 times as
 // fast as before the threshold; 2048 x 1408: 674 and 1169 us).
 // tau: beta^(-1 / (2 - p)), times tau_step = kappa^(-1 / (2 - p)) after every step.
-// 2048 x 1408, 3 bits, 20 steps: 975 us with pow() and two divisions per entry and step, 71 us so (the
-// serial sums of 45000 groups; 0.7 wavefronts per SIMD).
+// Bound: fp64 issue of one wavefront per SIMD (704 of them for 2048 x 1408), six operations per entry and step.
+// 2048 x 1408, 3 bits, 20 steps: 975 us with pow() and two divisions per entry and step, 71 us with twelve
+// operations and four selects in a dependent row, 35 us so (reading and writing the matrices is 8 of them).
 template <int G>
 __global__ __launch_bounds__(64) void quantize_refined_kernel(const double* __restrict__ W, int K, int N, int bits, int group_,
                                                                int iters, double p, double beta, double kappa, double tau, double tau_step,
@@ -213,6 +214,10 @@ __global__ __launch_bounds__(64) void quantize_refined_kernel(const double* __re
     double q = __builtin_rint(r + z);
     return q < 0.0 ? 0.0 : (q > double(levels) ? double(levels) : q);
   };
+  double r_lo = 0.0, r_hi = 0.0;                           // the group's smallest and largest quotient
+  if constexpr (G > 0) {
+    r_lo = lo / s; r_hi = hi / s;                          // (a quotient by one positive number keeps the order)
+  }
   if (!degenerate) {
     double b = beta;
     for (int it = 0; it < iters; ++it) {
@@ -221,11 +226,34 @@ __global__ __launch_bounds__(64) void quantize_refined_kernel(const double* __re
       const double far = tau * (1.0 - 1e-6) / s;
       bool all_far = G > 0;
       if constexpr (G > 0) {
+        // Six fp64 operations per entry.  |r - (q - z)| is at most one half where q is not clamped, and largest at
+        // the group's ends where it is: the threshold is tested once for the group (with the magnitudes that
+        // rounding is relative to), and a group it does not clear is redone entry by entry below, to the same sum.
+        // The clamp is a maximum and a minimum: an entry that is not a number makes the sum, and so the zero
+        // point, not a number whatever its q is, and the codes are chosen by clamped().  kWide entries at a time,
+        // an operation for all of them before the next and an addition of the serial sum in between: a wavefront
+        // has its SIMD to itself, and one entry after the other waits for every operation's result.
+        const double top = double(levels), ends = fmax(r_hi + z - top, -(r_lo + z));
+        all_far = fmax(ends, 0.5) + (fabs(r_lo) + fabs(r_hi) + fabs(z) + top) * 2e-14 < far;
+        constexpr int kWide = 4;
+        double q[kWide], add[kWide] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int i = 0; i < G; ++i) {
-          const double r = ratio[i], q = clamped(r);
-          all_far &= fabs(r - (q - z)) + (fabs(r) + fabs(q - z)) * 1e-14 < far;
-          sum += q - r;
+        for (int i = 0; i <= G; i += kWide) {
+#pragma unroll
+          for (int op = 0; op < 4; ++op) {
+            if (i < G) {
+#pragma unroll
+              for (int u = 0; u < kWide; ++u)
+                q[u] = op == 0 ? ratio[i + u] + z : op == 1 ? __builtin_rint(q[u]) : op == 2 ? fmax(q[u], 0.0) : fmin(q[u], top);
+            }
+            sum += add[op];                                // (those of the entries before, in index order)
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (i < G) {
+#pragma unroll
+            for (int u = 0; u < kWide; ++u) add[u] = q[u] - ratio[i + u];
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
       }
       if (!all_far) {
