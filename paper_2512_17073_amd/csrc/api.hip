@@ -252,6 +252,10 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   // the combine can add the K-block partial sums of a decode-flavour W2 itself
   const int kblocks = (path & 2) ? 1 : decode_w2_kblocks(a);
   a.keep_partials = keep_partials && kblocks > 1;
+  // (the K-block sums that W2 does not write: room for the (h A2) part sums of the decode flavour)
+  const size_t part_bytes = size_t(P) * c.hidden * 4, used = kblocks > 1 ? kblocks : 0;
+  a.ha = reinterpret_cast<float*>(ws + w.y_part + used * part_bytes);
+  a.ha_bytes = (kMaxKBlocks - used) * part_bytes;
   if (kblocks_out) *kblocks_out = a.keep_partials ? kblocks : 1;
   // the launch that converts the activations also makes the block tables of the decode launches
   // and, for the decode flavour of the fused projection, (x A1 | x A3)

@@ -22,6 +22,13 @@ __device__ inline half8_t q3_unit_a(uint32_t codes, uint32_t meta) {
                                                 pk_fma(q3_field<2>(codes), S, C), pk_fma(q3_field<3>(codes), S, C)));
 }
 
+// The lower or upper half of an A-factor unit (elements 0..3 or 4..7)
+__device__ inline uint2 q3_half_unit_a(uint32_t codes, uint32_t meta, bool upper) {
+  const uint32_t S = (meta & 0xffffu) | (meta << 16), C = (meta >> 16) | (meta & 0xffff0000u);
+  const uint32_t v = upper ? codes >> 6 : codes;          // (what crosses from the high half lands outside the fields)
+  return make_uint2(pk_fma(q3_field<0>(v), S, C), pk_fma(q3_field<1>(v), S, C));
+}
+
 // B-factor unit: `own` is the half of the lane group's 32 bytes of metadata that this lane loaded
 // (even lanes the four scale pairs, odd lanes the four offset pairs); the other half comes from
 // the neighbouring lane.  Every lane of the wavefront must be active.

@@ -56,6 +56,8 @@ struct KArgs {
   int kb_steps;              // decode flavour: k-steps per K-block (grid.z blocks split K; KS if one)
   float* partial;            // decode flavour, more than one K-block: fp32 partial outputs [kb][rows][N]; grouped (in A)
                              // with staged rows: K-block sums [kb][compact row][projections * ls * 32]
+  float* ha;                 // decode flavour, or null: part sums of (h A2) [slot][row][ls * 32] that the fused projection's
+                             // blocks leave and the W2 launch adds up (decode_index.h, ha_*), instead of xa_rows_kernel's p
   const int32_t* plan;       // decode flavour: null (grid = blocks per expert x experts), or the block table
                              // (PlanEntry per block, plan.h)
   const int32_t* row_exp;    // per input row: the exponent s of its power-of-two pre-scale (row_exponent below);
@@ -134,6 +136,16 @@ template <class T> __device__ inline const T* uniform_ptr(const T* p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);
   const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v)), hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
   return reinterpret_cast<const T*>((uint64_t(hi) << 32) | lo);
+}
+
+// The argument block of a kernel whose only (or first) argument is a KArgs, read from memory again where it is
+// used: without this every field is loaded at the kernel's start and held in scalar registers, and those
+// that do not fit go to vector register lanes and are fetched back inside the loops.
+typedef const __attribute__((address_space(4))) KArgs* KernArgs;
+__device__ inline KernArgs kern_args() {
+  KernArgs p = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
 }
 
 // Codes and metadata of one k-step of one wavefront (both projections when DUAL), in registers.

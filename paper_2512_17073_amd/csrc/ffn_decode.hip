@@ -16,8 +16,12 @@
 //     zeros, so refills are unconditional and the number of loads in flight is static;
 //   - codes are unpacked in registers (unpack.h) straight into MFMA A-operands; the rank-r term is
 //     ceil(r / 32) more steps per stream on the B factor's fp16 units against (in A), which
-//     xa_rows_kernel has left in global memory; the rank is the projection's own (Section 3.1
+//     the launches before have left in global memory; the rank is the projection's own (Section 3.1
 //     allocates a rank per expert matrix): a stream with fewer rank steps reads zeros past its factor;
+//   - (h A2) of ranks up to 64 is made at the end of the fused projection's blocks, from the h they hold in
+//     registers: each block's columns are a share of its long K, and the W2 blocks add the shares of
+//     their K-block up while their activations arrive.  (A launch between the two reads h and A2 again:
+//     6 to 11 us; the shares cost the two kernels 3 to 4 together.)  Larger ranks keep that launch;
 //   - a long K (W2) is split into K-blocks (grid.z) of one or two phases whose fp32 partial outputs
 //     the combine (or reduce_kernel, for the stand-alone call) adds in a fixed order.
 #include <algorithm>
@@ -47,7 +51,7 @@ using namespace dec;
 // its first four code registers, and is dequantized into the fp16 unit before it is used.
 template <int BITS, bool DUAL, int MT, bool Q3>
 __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int e, const int r0, const int cnt,
-                                            const int b, const int G) {
+                                            const int b, const int G, const int slots) {
   constexpr int NS = kStreams;
   constexpr int TS = DUAL ? 2 : 1;
   constexpr int NC = Extract<BITS>::kClasses;
@@ -83,12 +87,20 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     LSm[m] = lowrank ? (min(rk, a.rank) + 31) / 32 : 0;
   }
   const int LS = max(LSm[0], LSm[1]);
+  const float lam[2] = {d.inv_lambda[DUAL ? 0 : 2], d.inv_lambda[DUAL ? 1 : 2]};
+  // 16-column tiles of (h A2) that this launch makes (fused projection) or adds up (W2)
+  const int ht = lowrank && a.ha != nullptr ? (min(__builtin_amdgcn_readfirstlane(d.rank[2]), a.rank) + 15) / 16 : 0;
   const uint32_t bf_bytes_max = uint32_t(a.NT) * a.ls * 1024;
 
   __amdgpu_buffer_rsrc_t code_rs[NS], meta_rs[NS], bf_rs[NS], bc_rs[NS];
   bool q3m[NS];
 #pragma unroll
   for (int m = 0; m < NS; ++m) {
+    if (!DUAL && m > 0) {                    // (both streams read one projection)
+      q3m[m] = q3m[0]; code_rs[m] = code_rs[0]; meta_rs[m] = meta_rs[0]; bf_rs[m] = bf_rs[0];
+      if constexpr (Q3) bc_rs[m] = bc_rs[0];
+      continue;
+    }
     const int mat = DUAL ? m : 2;
     q3m[m] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
     // (the pointers are read once, into scalar registers: a buffer resource must be wave-uniform)
@@ -110,6 +122,12 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
   const bool p_late = p_frags * 64 > kSpareUnits;
   uint4* p_lds = p_late ? xs : xs + kLdsUnits;
   const int pitch = NP * a.ls * 32;                  // halves per row of (in A): [A1 | A3], or A2
+  // The fused projection's own columns of A2: the packed units (32 inputs each) u0 .. u0 + n_u - 1 of every
+  // factor tile (3-bit pair: their code dwords, then the metadata of the n_q x 4 groups of 64 inputs from g0
+  // on) are copied behind those fragments at the start of the first pass, where they fit; else read when used.
+  const bool q3_a2 = Q3 && ((__builtin_amdgcn_readfirstlane(d.q3) >> 2) & 1) != 0;
+  const int u0 = t0 / 2, n_u = (t1 - 1) / 2 - u0 + 1, g0 = t0 / 4, n_q = ((t1 - 1) / 4 - g0) / 4 + 1;
+  const bool a2_early = DUAL && ht > 0 && !p_late && p_frags * 64 + (q3_a2 ? (n_u + n_q) * 16 : n_u * 64) * ht <= kSpareUnits;
 
   for (int r = 0; r < cnt; r += 16 * MT) {
     // every pass computes all MT row tiles (a last pass with fewer rows computes columns nobody stores)
@@ -179,14 +197,87 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       }
     };
 
+    // (h A2) from the part sums of the fused projection's blocks: TPO threads share four columns of a row.
+    // The first kHaFirst parts of the first rank step are requested before anything else of the pass, the sums go
+    // to LDS as the fragments p_issue would copy.
+    constexpr int TPO = 8 / MT, kHaFirst = BITS == 4 ? 2 : 4;
+    const bool joined = !DUAL && a.ha != nullptr;      // (its fragments always fit behind the activations)
+    float4_t part[kHaFirst];
+    int pair_of_row = 0;
+    float lam2 = 0.f;
+    int hth = th;
+    asm volatile("" : "+v"(hth));            // (nothing of this is kept in registers from pass to pass)
+    const int hj = hth & (TPO - 1), hcol = (hth / TPO) & 7, hrow = hth / (8 * TPO);
+    int ha_lo, ha_hi;
+    ha_share(kb, gridDim.z, slots, ha_lo, ha_hi);
+    if constexpr (!DUAL) {
+      if (joined) {
+        const KernArgs ka = kern_args();
+        const int row = r0 + min(r + hrow, cnt - 1);
+#pragma unroll
+        for (int i = 0; i < kHaFirst; ++i)
+          part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, ka->ls * 32, 4 * hcol));
+        pair_of_row = ka->row_pair[row];
+        lam2 = ka->desc[e].xa_scale[2];
+      }
+    }
+    auto p_join = [&]() {
+      const KernArgs ka = kern_args();
+      const int row = r0 + min(r + hrow, cnt - 1);
+      const bool take = r + hrow < cnt && pair_of_row % ka->top_k < ka->top_n;
+      for (int st = 0; st < LS; ++st) {
+        const int col = 32 * st + 4 * hcol;
+        float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < kHaFirst; ++i) {
+          if (st > 0) part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, ka->ls * 32, col));
+        }
+#pragma unroll
+        for (int i = 0; i < kHaFirst; ++i)
+          if (ha_lo + hj + i * TPO < ha_hi) sum += part[i];
+        for (int sl = ha_lo + hj + kHaFirst * TPO; sl < ha_hi; sl += TPO)
+          sum += *reinterpret_cast<const float4_t*>(ka->ha + ha_part(sl, ka->total_rows, row, ka->ls * 32, col));
+#pragma unroll
+        for (int dlt = 1; dlt < TPO; dlt *= 2)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], dlt);
+        if (hj == 0) {
+          half4_t v = half4_t{0, 0, 0, 0};
+          if (take && col < 16 * ht) v = half4_t{to_f16_sat(sum[0] * lam2), to_f16_sat(sum[1] * lam2), to_f16_sat(sum[2] * lam2), to_f16_sat(sum[3] * lam2)};
+          reinterpret_cast<half4_t*>(p_lds + p_frag_unit(0, st, hrow >> 4, LS, MT) + (hcol >> 1) * 16 + (hrow & 15))[hcol & 1] = v;
+        }
+      }
+    };
+
     // ---- start of a pass: activations of phase 0, the (in A) fragments and the first packed tiles
     //      are all requested before anything is awaited ----
     if (r > 0) __syncthreads();               // everyone is done with the previous pass's LDS
     stage_issue(0, min(KP, KSl));
-    if (!p_late) p_issue();
+    if (!p_late && !joined) p_issue();
+    int row_se[MT];                           // (the rows' exponents for the end of the pass)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) row_se[mt] = a.row_exp[(a.offsets ? r0 : 0) + min(r + 16 * mt + c, cnt - 1)];
+    if (DUAL && a2_early && r == 0) {
+      uint4* dst = p_lds + p_frags * 64;
+      auto lds = [](uint4* p) { return reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p)); };
+      for (int f = wave; f < n_u * ht; f += kWaves) {
+        const int rt = f / n_u, unit = (rt * (a.N / 32) + u0 + f - rt * n_u) * kWave + lane;
+        if (q3_a2) __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d.af[2])) + unit, lds(dst + f * 16), 4, 0, 0);
+        else __builtin_amdgcn_global_load_lds(as_global<u32x4>(uniform_ptr(d.af[2])) + unit, lds(dst + f * 64), 16, 0, 0);
+      }
+      if (q3_a2)
+        for (int f = wave; f < n_q * ht; f += kWaves) {
+          const int rt = f / n_q, g = min(g0 + 4 * (f - rt * n_q) + q, a.N / 64 - 1);
+          __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d.afm[2])) + (rt * (a.N / 64) + g) * 16 + c,
+                                           lds(dst + (n_u * ht + f) * 16), 4, 0, 0);
+        }
+    }
     Slot<BITS, NS> ring[RING];
 #pragma unroll
     for (int i = 0; i < RING; ++i) fetch(ring[i]);
+    if constexpr (!DUAL) {
+      if (joined) p_join();
+    }
     wait_loads_barrier();
 
     float4_t acc[TS][MT][NS];
@@ -334,22 +425,28 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
             for (int m = 0; m < NS; ++m) acc[0][mt][m] += red[(((wave + j) * MT + mt) * NS + m) * 64 + lane];
       }
     }
-    if (kwi != 0) continue;                  // (the next pass starts with a barrier every wavefront reaches)
-
+    const KernArgs ka = kern_args();          // (what the end of a pass needs is read again: it would not fit the scalar registers until here)
+    int ln = lane, tn = th, hn = ht, gn = grp;
+    asm volatile("" : "+v"(ln), "+v"(tn), "+s"(hn), "+s"(gn));    // (addresses and conditions are made here, not kept in registers through the pass)
     // ---- epilogue: lane holds output columns 16*tile + 4*q .. +3 of token column c ----
+    half4_t hs[TS][MT];                       // (this wavefront's h, for (h A2): zero without a unit)
+#pragma unroll
+    for (int ts = 0; ts < TS; ++ts)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) hs[ts][mt] = half4_t{0, 0, 0, 0};
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts) {
-      const int unit = grp + ts * groups;
-      if (unit >= units) continue;
+      const int unit = gn + ts * groups;
+      if (kwi != 0 || unit >= units) continue;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int row = r + 16 * mt + c;
-        if (row >= cnt) continue;
-        const int se = a.row_exp[(a.offsets ? r0 : 0) + row];      // the row's inputs were scaled by 2^se
         if constexpr (DUAL) {
+          // (a column without a row multiplied zeros: its h is zero)
+          const int se = row_se[mt];          // the row's inputs were scaled by 2^se
           const int tile = t0 + unit;
           const float dn = pow2i(-se), up = pow2i(2 * se);
-          const float i1 = d.inv_lambda[0] * dn, i3 = d.inv_lambda[1] * dn;
+          const float i1 = lam[0] * dn, i3 = lam[1] * dn;
           half4_t hv;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -358,24 +455,85 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
           }
           // h in operand order for the W2 kernel: columns f .. f+3 are half of one 16-byte unit
           const int f = tile * kTileN + 4 * q;
-          *reinterpret_cast<half4_t*>(reinterpret_cast<_Float16*>(a.out) + act_unit(f >> 3, r0 + row, a.out_rt) * 8 + (f & 7)) = hv;
+          if (row < cnt) *reinterpret_cast<half4_t*>(reinterpret_cast<_Float16*>(ka->out) + act_unit(f >> 3, r0 + row, ka->out_rt) * 8 + (f & 7)) = hv;
+          hs[ts][mt] = hv;
         } else {
-          const float i2 = d.inv_lambda[2] * pow2i(-2 * se);       // (h was stored times 2^(2 se))
+          if (row >= cnt) continue;
+          const float i2 = lam[0] * pow2i(-2 * row_se[mt]);       // (h was stored times 2^(2 se))
 #pragma unroll
           for (int m = 0; m < NS; ++m) {
             const int tile = t0 + 2 * unit + m;
             if (tile >= t1) continue;
-            const size_t o = size_t(r0 + row) * a.N + tile * kTileN + 4 * q;
-            if (a.partial != nullptr) {          // K-blocks: fp32 partial sums, added up by the combine or by reduce_kernel
-              *reinterpret_cast<float4_t*>(a.partial + size_t(kb) * a.total_rows * a.N + o) = acc[ts][mt][m] * i2;
+            const size_t o = size_t(r0 + row) * ka->N + tile * kTileN + 4 * q;
+            if (ka->partial != nullptr) {          // K-blocks: fp32 partial sums, added up by the combine or by reduce_kernel
+              *reinterpret_cast<float4_t*>(ka->partial + size_t(kb) * ka->total_rows * ka->N + o) = acc[ts][mt][m] * i2;
             } else {
               uint2 yv;
               yv.x = f32x2_to_bf16x2(acc[ts][mt][m][0] * i2, acc[ts][mt][m][1] * i2);
               yv.y = f32x2_to_bf16x2(acc[ts][mt][m][2] * i2, acc[ts][mt][m][3] * i2);
-              *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + o) = yv;
+              *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(ka->out) + o) = yv;
             }
           }
         }
+      }
+    }
+    // (h A2) over the block's columns: the wavefronts' sums meet in LDS, in group order
+    if (DUAL && hn > 0) {
+      float4_t* red = reinterpret_cast<float4_t*>(xs);
+      __syncthreads();                       // (everyone is done with the activations and the fragments)
+      if (kwi == 0) {
+        // (the four columns of h a lane holds are its share of a 16x16x16 product's operand; not unrolled: what a
+        // block runs once is fetched from memory while the wavefront waits)
+#pragma unroll 1
+        for (int rt = 0; rt < hn; ++rt) {
+          uint2 w[TS];
+#pragma unroll
+          for (int ts = 0; ts < TS; ++ts) {
+            const int tile = min(t0 + gn + ts * groups, t1 - 1);       // (without a unit: h is zero)
+            const uint32_t at = ha_operand(rt, tile, ln, ka->N);
+            if (a2_early) {
+              const uint32_t own = at - (rt * (ka->N / 32 - n_u) + u0) * (kWave * 2);
+              if (q3_a2) {
+                const uint32_t* codes = reinterpret_cast<const uint32_t*>(p_lds + p_frags * 64);
+                w[ts] = make_uint2(codes[own >> 1], codes[n_u * hn * kWave + (rt * n_q * 4 + tile / 4 - g0) * 16 + (ln & 15)]);
+              } else {
+                w[ts] = reinterpret_cast<const uint2*>(p_lds + p_frags * 64)[own];
+              }
+            } else if (q3_a2) {                // 3-bit pair: the unit's code dword and its metadata
+              w[ts] = make_uint2(as_global<uint32_t>(uniform_ptr(ka->desc[e].af[2]))[at >> 1],
+                                 as_global<uint32_t>(uniform_ptr(ka->desc[e].afm[2]))[(rt * (ka->N / 64) + tile / 4) * 16 + (ln & 15)]);
+            } else {
+              w[ts] = __builtin_bit_cast(uint2, as_global<u32x2>(uniform_ptr(ka->desc[e].af[2]))[at]);
+            }
+          }
+          float4_t sum[MT];
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) sum[mt] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ts = 0; ts < TS; ++ts) {
+            if (q3_a2) w[ts] = q3_half_unit_a(w[ts].x, w[ts].y, (ln & 16) != 0);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) sum[mt] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(half4_t, w[ts]), hs[ts][mt], sum[mt], 0, 0, 0);
+          }
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) red[((gn * hn + rt) * MT + mt) * 64 + ln] = sum[mt];
+        }
+      }
+      __syncthreads();
+      const int slot = ha_slot(b, t0, G, ka->NT), used = min(groups, units);
+      for (int i = tn; i < hn * MT * 64; i += 64 * kWaves) {
+        float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < used; j += 8) {    // (eight reads in flight)
+          float4_t v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = red[min(j + u, used - 1) * hn * MT * 64 + i];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (j + u < used) sum += v[u];
+        }
+        const int row = r + 16 * ((i >> 6) % MT) + (i & 15), rt = (i >> 6) / MT;
+        if (row < cnt)
+          *reinterpret_cast<float4_t*>(ka->ha + ha_part(slot, ka->total_rows, r0 + row, ka->ls * 32, 16 * rt + 4 * ((i >> 4) & 3))) = sum;
       }
     }
   }
@@ -384,19 +542,20 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
 template <int BITS, bool DUAL, bool Q3>
 __global__ __launch_bounds__(64 * kWaves, 4) void qgemm_decode_kernel(KArgs a) {
   extern __shared__ uint4 xs[];
-  int e = blockIdx.y, b = blockIdx.x, G = gridDim.x, r0, cnt;
+  int e = blockIdx.y, b = blockIdx.x, G = gridDim.x, r0, cnt, slots = 0;
   if (a.plan != nullptr) {                   // shares by table (plan.h): one 32-byte entry per block
     const PlanEntry* pe = reinterpret_cast<const PlanEntry*>(a.plan) + blockIdx.x;
     e = __builtin_amdgcn_readfirstlane(pe->e); b = __builtin_amdgcn_readfirstlane(pe->b); G = __builtin_amdgcn_readfirstlane(pe->G);
     r0 = __builtin_amdgcn_readfirstlane(pe->r0); cnt = __builtin_amdgcn_readfirstlane(pe->cnt);
+    slots = __builtin_amdgcn_readfirstlane(pe->slots);
     if (e < 0) return;
   } else {
     r0 = a.offsets ? a.offsets[e] : e * a.T;
     cnt = a.offsets ? a.offsets[e + 1] - r0 : a.T;
   }
   if (cnt == 0) return;
-  if (cnt <= 16) decode_body<BITS, DUAL, 1, Q3>(a, xs, e, r0, cnt, b, G);
-  else decode_body<BITS, DUAL, 2, Q3>(a, xs, e, r0, cnt, b, G);
+  if (cnt <= 16) decode_body<BITS, DUAL, 1, Q3>(a, xs, e, r0, cnt, b, G, slots);
+  else decode_body<BITS, DUAL, 2, Q3>(a, xs, e, r0, cnt, b, G, slots);
 }
 
 template <bool DUAL>
@@ -426,6 +585,17 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
   y[u] = v;
 }
 
+// Whether the fused launch leaves (h A2) as part sums for W2 (else xa_rows_kernel makes it in between): both
+// projections on this flavour, ranks whose sums of 16 wavefronts fit the LDS of the activations, and room for
+// the parts.  Whole forward, launch in between -> part sums, us: Mixtral T = 64 159.4 -> 153.4, T = 1 71.1 -> 67.5,
+// T = 13 with 3-bit pairs 161.5 -> 159.1; Qwen3 T = 64 110.8 -> 107.0; hidden 256, FFN 512, T = 16 (four calls) 59.6 -> 56.1.
+bool decode_ha(const FfnArgs& f, int which) {
+  if (which != 3 || f.offsets == nullptr || f.plan == nullptr || f.ha == nullptr || f.rank <= 0 || f.rank > dec::kHaRank) return false;
+  const int NT = f.F / kTileN, ls = (f.rank + 31) / 32;
+  const size_t slots = std::min(plan_blocks(f.n_exp, f.T * f.top_k, NT, f.n_cu), NT);
+  return slots * f.total_rows * ls * 128 <= f.ha_bytes;
+}
+
 template <int BITS>
 hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   int gs = 0;
@@ -451,6 +621,9 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   const int pairs = f.T * f.top_k;
   // (the kernels that can dequantize 3-bit factor pairs, where the layer holds any)
   const bool q3 = comp && f.q3;
+  // (h A2) made by the fused launch's blocks themselves
+  const bool ha = comp && decode_ha(f, which);
+  a.ha = ha ? f.ha : nullptr;
   auto k13 = q3 ? qgemm_decode_kernel<BITS, true, true> : qgemm_decode_kernel<BITS, true, false>;
   auto k2 = q3 ? qgemm_decode_kernel<BITS, false, true> : qgemm_decode_kernel<BITS, false, false>;
 
@@ -487,7 +660,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     const int kblocks = decode_w2_kblocks(f);
     a.kb_steps = (a.KS + kblocks - 1) / kblocks;
     a.partial = kblocks > 1 ? f.y_part : nullptr;
-    if (comp) hipLaunchKernelGGL(xa_rows_kernel<false>, dim3(2 * a.ls, f.n_exp, kblocks), dim3(1024), 0, s, a);
+    if (comp && !ha) hipLaunchKernelGGL(xa_rows_kernel<false>, dim3(2 * a.ls, f.n_exp, kblocks), dim3(1024), 0, s, a);
     if (f.marks) (void)hipEventRecord(f.marks[2], s);
     if (by_table) {
       // (second table behind the first; every K-block uses the same shares)

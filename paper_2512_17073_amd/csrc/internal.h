@@ -181,6 +181,8 @@ struct FfnArgs {
   int x_rt, h_rt;
   float* p13;                 // (x A1 | x A3), fp16 [rows][2 * ls * 32] (ffn_common.h, KArgs::p)
   float* p2;                  // (h A2), fp16 [rows][ls * 32]; decode flavour: one per W2 K-block
+  float* ha;                  // decode flavour of both projections: room for ha_bytes of (h A2) part sums (decode_ha)
+  size_t ha_bytes;
   void* y_rows;               // [rows][H] bf16
   float* y_part;              // fp32 partial outputs of the W2 K-blocks (decode flavour), or null
   int32_t* plan;              // decode flavour, routed experts: the block tables (plan.h) of the two projections

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
     return;
   }
   if (plan_block && (int)blockIdx.x == row_blocks + stat_blocks) {         // the block tables (plan.h)
-    if (blockIdx.y == 0 && threadIdx.x < 128) make_plan(offsets, E, threadIdx.x < 64 ? plan0 : plan1, threadIdx.x & 63);
+    if (blockIdx.y == 0 && threadIdx.x < 128) make_plan(offsets, E, threadIdx.x < 64 ? plan0 : plan1, threadIdx.x < 64 ? PlanSpec{0, 0, 0, nullptr} : plan0, threadIdx.x & 63);
     return;
   }
   if ((int)blockIdx.x >= row_blocks) {

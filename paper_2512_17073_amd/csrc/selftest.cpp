@@ -181,6 +181,44 @@ std::string check_shape(const Shape& sh) {
   return "";
 }
 
+// (h A2) made by the fused launch: every block's operand reads, its copy of them in LDS, and the part sums it
+// leaves for the K-blocks of W2
+std::string check_h_a2(int F, int ls, int rank2, const Shape& sh, int kblocks) {
+  const int NT = F / kTileN, ht = (rank2 + 15) / 16, slots = ha_slots(sh.G, NT), pitch = ls * 32;
+  std::vector<int> left(slots, 0), taken(slots, 0);
+  for (int b = 0; b < sh.G; ++b) {
+    int t0, t1;
+    block_tiles(b, sh.G, NT, t0, t1);
+    if (t0 == t1) continue;
+    const int slot = ha_slot(b, t0, sh.G, NT);
+    if (slot < 0 || slot >= slots) SELF_FAIL("block %d of %d leaves its sums in place %d of %d", b, sh.G, slot, slots);
+    ++left[slot];
+    if (ha_part(slot, sh.total_rows, sh.r0 + sh.cnt - 1, pitch, 16 * ht - 4) + 4 > size_t(slots) * sh.total_rows * pitch)
+      SELF_FAIL("block %d stores past its part sums", b);
+    const int u0 = t0 / 2, n_u = (t1 - 1) / 2 - u0 + 1, g0 = t0 / 4, n_q = ((t1 - 1) / 4 - g0) / 4 + 1;
+    for (int rt = 0; rt < ht; ++rt)
+      for (int tile = t0; tile < t1; ++tile) {
+        if ((tile / 4 - g0) / 4 >= n_q) SELF_FAIL("n-tile %d: its metadata is not among the copied groups", tile);
+        for (int lane = 0; lane < 64; ++lane) {
+          const uint32_t at = ha_operand(rt, tile, lane, F);
+          // (packed: [factor tile][unit of 32 inputs][lane][8 inputs])
+          const int q = lane >> 4, c = lane & 15, unit = at / (2 * kWave), l = at / 2 % kWave, f = 32 * (unit - rt * (F / 32)) + 8 * (l >> 4) + 4 * (at & 1);
+          if (unit / (F / 32) != rt || (l & 15) != c || f != 16 * tile + 4 * q) SELF_FAIL("operand of n-tile %d, lane %d reads input %d", tile, lane, f);
+          const uint32_t own = at - (rt * (F / 32 - n_u) + u0) * (kWave * 2);
+          if (own / (2 * kWave) != uint32_t(rt * n_u + tile / 2 - u0) || own >= uint32_t(n_u * ht * kWave * 2)) SELF_FAIL("operand of n-tile %d, lane %d: outside its copy", tile, lane);
+        }
+      }
+  }
+  for (int kb = 0; kb < kblocks; ++kb) {
+    int lo, hi;
+    ha_share(kb, kblocks, slots, lo, hi);
+    for (int s = lo; s < hi; ++s) ++taken[s];
+  }
+  for (int s = 0; s < slots; ++s)
+    if (left[s] != 1 || taken[s] != 1) SELF_FAIL("part sum %d of %d left %d and taken %d times", s, slots, left[s], taken[s]);
+  return "";
+}
+
 }  // namespace
 
 }  // namespace lrc
@@ -203,6 +241,8 @@ extern "C" int moe_lrc_selftest_decode_index(int hidden, int ffn, int bits, int 
   Shape b{ffn, hidden, bits, group, ls, {(rank2 + 31) / 32, (rank2 + 31) / 32}, first_row, rows, total_rows, blocks_w2, kblocks_w2, false};
   err = check_shape(b);
   if (!err.empty()) return set_error(MOE_LRC_ESHAPE, "selftest_decode_index (W2): " + err);
+  if (rank2 > 0 && layer_rank <= kHaRank) err = check_h_a2(ffn, ls, rank2, a, kblocks_w2);
+  if (!err.empty()) return set_error(MOE_LRC_ESHAPE, "selftest_decode_index (h A2): " + err);
   return MOE_LRC_OK;
 }
 

@@ -737,3 +737,47 @@ def test_in_a_with_staged_rows(amd, hidden, ffn, rank, tokens, kind):
     assert err <= TOL and none > 5 * TOL
     assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16))
     Lr.close(); Ls.close()
+
+
+@pytest.mark.parametrize("hidden,ffn,rank,tokens,experts,kind", [
+    (256, 64, 64, 3, 1, "same"),           # four n-tiles for all blocks: most of them own none
+    (256, 64, 8, 1, 2, "int3"),            # one 16-column tile, one row
+    (512, 1088, 40, 70, 4, "same"),        # several passes, an odd number of factor tiles
+    (320, 4160, 56, 37, 2, "int3"),        # W2 in two K-blocks, 260 n-tiles
+    (320, 4160, 64, 21, 2, "bucket"),      # ranks that differ, pairs of W2 missing
+])
+def test_h_a2_from_the_fused_launch(amd, hidden, ffn, rank, tokens, experts, kind):
+    """(h A2) of decode batches with ranks up to 64 is made by the blocks of the fused projection and added up by
+    those of W2: block shares, K-blocks, passes and ranks at which its indices change, against the oracle."""
+    import torch
+    bucket = (64, 0, 16, 40, 0, 8, 64)
+    cfg = configs.TINY.with_(hidden=hidden, ffn=ffn, n_experts=experts, top_k=min(2, experts), rank=rank, tokens=tokens, bits=2,
+                             name=f"h_a2_{kind}_{ffn}_r{rank}")
+    layer = fixtures.sample_layer(cfg)
+    for e, ex in enumerate(layer["experts"]):
+        for m in (0, 1, 2):
+            a = ex[m]
+            if kind == "int3":
+                a["Aq"], a["Bq"] = synth.sample_factor_codes(cfg, e, m)
+                a["A"] = a["B"] = None
+            elif kind == "bucket":
+                a["rank"] = r = bucket[(3 * e + 2 * m) % len(bucket)]
+                a["A"] = np.ascontiguousarray(a["A"][:, :r]) if r else None
+                a["B"] = np.ascontiguousarray(a["B"][:r]) if r else None
+    x_bits = synth.make_tokens(cfg)
+    x = amd.bf16_tensor(x_bits)
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    Lr = amd.Layer.from_config(cfg)
+    Ls = amd.Layer.from_config(cfg, residency=amd.STAGED)
+    Lr.load(layer); Ls.load(layer)
+    out_r = Lr.forward(x).clone()
+    torch.cuda.synchronize()
+    assert Lr.stats()["path"] == 0
+    out_s = Ls.forward(x).clone()
+    torch.cuda.synchronize()
+    err = orc.rel_frobenius(_to_np(out_r), ref["out"])
+    none = orc.rel_frobenius(_to_np(out_r), fixtures.oracle_forward(cfg.with_(top_n=0), layer, x_bits)["out"])
+    print(f"\n[{cfg.name}] out rel err {err:.2e} (the rank terms move the output by {none:.2e})", flush=True)
+    assert err <= TOL and none > 3 * TOL
+    assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16))
+    Lr.close(); Ls.close()
