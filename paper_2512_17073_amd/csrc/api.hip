@@ -226,7 +226,8 @@ static int stage_selected(moe_lrc_layer* L, hipStream_t stream) {
 static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t* offsets,
                           const int32_t* row_pair, void* y_rows, uint8_t* ws, hipStream_t stream,
                           bool mark = false, bool keep_partials = false, int* kblocks_out = nullptr,
-                          const int32_t* tok_exp = nullptr, const PermuteArgs* perm = nullptr, const RouteArgs* route = nullptr) {
+                          const int32_t* tok_exp = nullptr, const PermuteArgs* perm = nullptr, const RouteArgs* route = nullptr,
+                          FfnArgs* ahead_args = nullptr) {
   const moe_lrc_config& c = L->cfg;
   const Workspace w = plan_workspace(L, T);
   _Float16* xh = reinterpret_cast<_Float16*>(ws + w.xh);
@@ -262,7 +263,12 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   PlanSpec plans[2];
   expert_ffn_plan_specs(a, plans[0], plans[1]);
   // ((x A1 | x A3) from the tokens inside the preparing launch needs the exponents beforehand)
-  a.xa13_here = c.residency != MOE_LRC_RESIDENT || tok_exp == nullptr;
+  bool ahead = false;                        // pooled: the FFN is launched before the host has seen the counts
+  if (c.residency == MOE_LRC_POOLED) {
+    const int rc = pool_begin(L, &ahead);
+    if (rc) return rc;
+  }
+  a.xa13_here = (c.residency != MOE_LRC_RESIDENT && !ahead) || tok_exp == nullptr;
   a.x_tokens = x;
   // (the grouped (in A) kernels work on the rows that take the rank-r term only: their compact order)
   const bool comp = c.rank > 0 && c.top_n > 0 && path != 0;
@@ -270,20 +276,28 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   if (comp) { a.cmp_index = cmp.index; a.cmp_list = cmp.list; }
   LRC_HIP(launch_convert_x(L, x, T, xh, P + kActPadRows, offsets, row_pair, L->d_stat, plans,
                            ((path & 1) || a.xa13_here) ? nullptr : &a, tok_exp, a.row_exp, perm, comp ? &cmp : nullptr, route,
-                           ZeroRowsArgs{reinterpret_cast<uint4*>(a.h), a.h_rt, padded_k(c.ffn)}, stream));
+                           ZeroRowsArgs{reinterpret_cast<uint4*>(a.h), a.h_rt, padded_k(c.ffn)}, stream,
+                           c.residency == MOE_LRC_POOLED ? L->h_stat : nullptr));
   L->stats_valid = false;
   L->stats.stage_ms = 0.f;
   if (c.residency == MOE_LRC_STAGED) {
     const int rc = stage_selected(L, stream);
     if (rc) return rc;
   } else if (c.residency == MOE_LRC_POOLED) {
-    const int rc = pool_stage(L, x, T, stream);
+    int rc = pool_counts_written(L, stream);
+    bool complete = false;
+    if (!rc && !ahead) rc = pool_stage(L, T, stream, &complete);
     if (rc) return rc;
   }
   if (mark) LRC_HIP(hipEventRecord(L->marks[MOE_LRC_STAGE_XA13], stream));
   a.marks = mark ? &L->marks[MOE_LRC_STAGE_W13] : nullptr;
   LRC_HIP(launch_expert_ffn(a, stream));
   L->stats.path = path;
+  if (ahead && ahead_args) {                 // (for a second launch, if an expert turns out to be missing)
+    *ahead_args = a;
+    ahead_args->xa13_here = 1;
+    ahead_args->marks = nullptr;
+  }
   return MOE_LRC_OK;
 }
 
@@ -527,6 +541,7 @@ int moe_lrc_set_expert_ranked(moe_lrc_layer* L, int expert, int mat, const uint8
   if (b.f_bytes > 0 && !(pooled && expert < c.n_experts))
     set_factor_ptrs(L, expert, mat, d, L->d_f + L->f_off[expert] + b.off_af[mat], L->d_f + L->f_off[expert] + b.off_bf[mat]);
   LRC_HIP(hipMemcpy(L->d_desc + expert, &d, sizeof(ExpertDesc), hipMemcpyHostToDevice));
+  ++L->desc_gen;
   L->mat_set[expert * 3 + mat] = 1;
   return MOE_LRC_OK;
 }
@@ -582,6 +597,7 @@ int moe_lrc_set_expert_factors_quantized(moe_lrc_layer* L, int expert, int mat, 
   d.q3 |= 1 << mat;
   if (!pooled) set_factor_ptrs(L, expert, mat, d, L->d_f + aoff, L->d_f + L->f_off[expert] + b.off_bf[mat]);
   LRC_HIP(hipMemcpy(L->d_desc + expert, &d, sizeof(ExpertDesc), hipMemcpyHostToDevice));
+  ++L->desc_gen;
   return MOE_LRC_OK;
 }
 
@@ -683,7 +699,10 @@ int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hi
   // a token or two: the blocks of the preparing launch route them as well (another launch fewer)
   const bool fused_route = fused_permute && T * L->cfg.n_experts <= kFusedRoutePairs && tok_exp != nullptr;
   const RouteArgs route{L->d_wg, L->has_bias ? L->d_bias : nullptr, idx, tw, tok_exp, L->cfg.renormalize};
-  if (!fused_route) LRC_HIP(launch_route(L, x, T, idx, tw, nullptr, tok_exp, s));
+  const bool pooled = L->cfg.residency == MOE_LRC_POOLED;
+  const RouteGuess guess = pooled ? pool_guess(L) : RouteGuess{nullptr, nullptr, nullptr};
+  if (!fused_route) LRC_HIP(launch_route(L, x, T, idx, tw, nullptr, tok_exp, s, guess));
+  else if (guess.layer) LRC_HIP(launch_route(guess.layer, x, T, guess.idx, guess.w, nullptr, nullptr, s));
   if (mk) LRC_HIP(hipEventRecord(L->marks[MOE_LRC_STAGE_PERMUTE], s));
   if (!fused_permute)
     LRC_HIP(launch_permute(L, idx, T, (int32_t*)(b + w.counts), offsets, row_pair, pair_row,
@@ -703,13 +722,24 @@ int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hi
   // (the K-block partial sums of a decode-flavour W2 go to the combine as they are: no pass that
   // adds them into bf16 rows first)
   int kblocks = 1;
+  FfnArgs ahead_args{};
   if ((rc = run_expert_ffn(L, x, T, offsets, row_pair, b + w.y_rows, b, s, mk, true, &kblocks, tok_exp,
-                           fused_permute ? &perm : nullptr, fused_route ? &route : nullptr))) return rc;
+                           fused_permute ? &perm : nullptr, fused_route ? &route : nullptr, &ahead_args))) return rc;
   if (fork) LRC_HIP(hipStreamWaitEvent(s, L->ev_join, 0));
   else if (L->cfg.n_shared > 0 && (rc = run_shared(L, x, T, b, s))) return rc;
   if (mk) LRC_HIP(hipEventRecord(L->marks[MOE_LRC_STAGE_COMBINE], s));
-  LRC_HIP(launch_combine(L, b + w.y_rows, kblocks > 1 ? (const float*)(b + w.y_part) : nullptr, kblocks, tw, pair_row, y_shared,
-                         residual, T, out, s));
+  auto combine = [&] {
+    return launch_combine(L, b + w.y_rows, kblocks > 1 ? (const float*)(b + w.y_part) : nullptr, kblocks, tw, pair_row, y_shared, residual, T, out, s);
+  };
+  LRC_HIP(combine());
+  if (ahead_args.desc != nullptr) {            // pooled, launched ahead: now the counts, and once more if something was missing
+    bool complete = false;
+    if ((rc = pool_stage(L, T, s, &complete))) return rc;
+    if (!complete) {
+      LRC_HIP(launch_expert_ffn(ahead_args, s));
+      LRC_HIP(combine());
+    }
+  }
   if (mk) {
     LRC_HIP(hipEventRecord(L->marks[MOE_LRC_N_STAGES], s));
     L->profile_valid = true;

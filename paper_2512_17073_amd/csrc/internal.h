@@ -62,6 +62,7 @@ struct moe_lrc_layer {
   std::vector<size_t> w_off, f_off;    // per-expert offsets into the pools
   lrc::ExpertDesc* d_desc = nullptr;
   std::vector<lrc::ExpertDesc> h_desc;
+  uint64_t desc_gen = 1;               // counts what writes h_desc and d_desc outside a stack's steps
   uint16_t* d_wg = nullptr;
   float* d_bias = nullptr;
   double* d_logits = nullptr;          // [max_tokens][E] gate logits of the routing paths that go through memory (many experts)
@@ -102,8 +103,10 @@ Workspace plan_workspace(const moe_lrc_layer* L, int T);
 // ---- kernel launchers (each returns hipError_t of the launch) ------------------------------
 // tok_exp (may be null): receives every token's pre-scale exponent (ffn_common.h) if
 // route_writes_exponents(L, T), else it is left untouched
+// guess: a second layer of the same hidden size whose gate is applied to the same tokens (layer == null: none)
+struct RouteGuess { const moe_lrc_layer* layer; int32_t* idx; float* w; };
 hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* idx, float* w,
-                        _Float16* xh /*may be null*/, int32_t* tok_exp, hipStream_t s);
+                        _Float16* xh /*may be null*/, int32_t* tok_exp, hipStream_t s, const RouteGuess& guess = RouteGuess{nullptr, nullptr, nullptr});
 bool route_writes_exponents(const moe_lrc_layer* L, int T);
 // Batches whose routing is tiled on the fp64 matrix cores instead of one block per token: at least 128
 // tiles of 16 tokens x 16 experts and 2^26 products.  Whole call, one block per token -> tiled, us.  Above the line no
@@ -157,7 +160,7 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
                             const PermuteArgs* perm /* or null: offsets and row_pair are ready */,
                             const CompactArgs* cmp /* or null */, const RouteArgs* route /* or null: perm->idx is ready */,
                             const ZeroRowsArgs& zr,
-                            hipStream_t s);
+                            hipStream_t s, int32_t* host_stat = nullptr /* pinned: a copy of `stat` for the host */);
 constexpr int kMaxKBlocks = 8;    // most K-blocks the decode W2 kernel splits into
 // blocks (per K-block) of a decode launch that shares its blocks out by a table: `target` (the
 // device's CUs over the K-blocks), or enough for ceil(NT / 32) blocks per expert that can be active
@@ -229,10 +232,15 @@ void set_factor_ptrs(const moe_lrc_layer* L, int e, int mat, ExpertDesc& d, cons
 void fill_algorithmic_stats(moe_lrc_layer* L, const int32_t* stat);
 // moe_lrc_forward after its argument checks; residual as in launch_combine
 int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hipStream_t s, const void* residual);
-// pooled residency, inside the expert FFN after the preparing launch: reads the per-expert counts
-// back, brings the experts that received rows into slots of the stack's pool, points the layer's
-// expert table at them and makes `s` wait for the copies
-int pool_stage(moe_lrc_layer* L, const void* x, int T, hipStream_t s);
+// pooled residency (stack.hip).  pool_begin, before the preparing launch: *ahead if the FFN kernels may be
+// launched before the host knows the counts; pool_counts_written:
+// right after the preparing launch, which has written the counts to L->h_stat; pool_stage: waits for them,
+// brings the experts that received rows into slots of the stack's pool, points the layer's expert table at
+// them and makes `s` wait for the copies; *complete if everything was in place already
+RouteGuess pool_guess(const moe_lrc_layer* L);
+int pool_begin(moe_lrc_layer* L, bool* ahead);
+int pool_counts_written(moe_lrc_layer* L, hipStream_t s);
+int pool_stage(moe_lrc_layer* L, int T, hipStream_t s, bool* complete);
 hipError_t launch_debug_unpack(const uint32_t* packed, const MatLayout& m, uint8_t* codes_dev,
                                hipStream_t s);
 }  // namespace lrc

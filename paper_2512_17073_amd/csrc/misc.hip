@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
                                                    int top_n, int32_t* __restrict__ stat, PlanSpec plan0,
                                                    PlanSpec plan1, int xa_tiles, ffn::KArgs xa,
                                                    const int32_t* tok_exp, int32_t* __restrict__ row_exp,
-                                                   PermuteArgs perm, CompactArgs cmp, RouteArgs route, ZeroRowsArgs zr) {
+                                                   PermuteArgs perm, CompactArgs cmp, RouteArgs route, ZeroRowsArgs zr,
+                                                   int32_t* __restrict__ host_stat) {
   __shared__ ffn::float4_t red[2 * kPrepThreads / 64][64];
   __shared__ uint32_t row_max[16];
   if (route.wg != nullptr) {
@@ -178,6 +179,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
       comp += __popcll(m);
     }
     if (lane == 0) { stat[2 + e] = n; stat[2 + E + e] = comp; }
+    if (lane == 0 && host_stat != nullptr) { host_stat[2 + e] = n; host_stat[2 + E + e] = comp; }
     return;
   }
   const int R = blockIdx.x * 16 + (threadIdx.x & 15);
@@ -263,7 +265,7 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
                             const int32_t* offsets, const int32_t* row_pair, int32_t* stat,
                             const PlanSpec* plans, const FfnArgs* xa13, const int32_t* tok_exp, int32_t* row_exp,
                             const PermuteArgs* perm, const CompactArgs* cmp, const RouteArgs* route, const ZeroRowsArgs& zr,
-                            hipStream_t s) {
+                            hipStream_t s, int32_t* host_stat) {
   const moe_lrc_config& c = L->cfg;
   const int rows = row_pair ? T * c.top_k : T;
   const int row_blocks = (rows + 15) / 16;
@@ -291,7 +293,7 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
                      row_pair, c.n_experts, c.top_k, c.top_n, stat, p0, p1, xa_tiles, xa, tok_exp, row_exp,
                      perm ? *perm : PermuteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0},
                      cmp_block ? *cmp : CompactArgs{nullptr, nullptr},
-                     (route && perm) ? *route : RouteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, 0}, zr);
+                     (route && perm) ? *route : RouteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, 0}, zr, host_stat);
   return hipGetLastError();
 }
 

@@ -20,6 +20,7 @@ namespace {
 // lower index) and the softmax weights of the selected experts.
 
 constexpr int kRouteGroups = 8;     // most blocks that share a token
+struct GuessArgs { const uint16_t* wg; const float* bias; int E, top_k, renorm; int32_t* idx; float* w; };   // blocks T .. 2 T - 1
 
 template <int CH, int NW>
 __global__ __launch_bounds__(64 * NW) void route_kernel(const uint16_t* __restrict__ x,
@@ -27,9 +28,15 @@ __global__ __launch_bounds__(64 * NW) void route_kernel(const uint16_t* __restri
                                                     const float* __restrict__ bias, int T, int H, int E,
                                                     int top_k, int renorm, int32_t* __restrict__ idx,
                                                     float* __restrict__ w, _Float16* __restrict__ xh,
-                                                    int32_t* __restrict__ tok_exp, double* __restrict__ logits_g) {
+                                                    int32_t* __restrict__ tok_exp, double* __restrict__ logits_g, GuessArgs guess) {
   __shared__ double logit[kMaxExperts];
-  const int t = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int t = blockIdx.x;
+  if (t >= T) {                              // a second layer's gate on the same tokens
+    t -= T;
+    wg = guess.wg; bias = guess.bias; E = guess.E; top_k = guess.top_k; renorm = guess.renorm; idx = guess.idx; w = guess.w;
+    tok_exp = nullptr;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // Few tokens and many experts: gridDim.y blocks share a token's gate rows (block g takes experts
   // g * epg .. + epg - 1) and leave their logits (without the bias) in logits_g [T][E]; topk_kernel
   // follows in a launch of its own.
@@ -383,10 +390,14 @@ static bool gate_split(const moe_lrc_layer* L, int T) {
 bool route_writes_exponents(const moe_lrc_layer* L, int T) { return !gate_many(L, T); }
 
 hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* idx, float* w,
-                        _Float16* xh, int32_t* tok_exp, hipStream_t s) {
+                        _Float16* xh, int32_t* tok_exp, hipStream_t s, const RouteGuess& guess) {
   const moe_lrc_config& c = L->cfg;
   // Many (token, expert) products: tiled on the fp64 matrix cores.
   if (xh == nullptr && (gate_many(L, T) || gate_split(L, T))) {
+    if (guess.layer) {
+      const hipError_t e = launch_route(guess.layer, x, T, guess.idx, guess.w, nullptr, nullptr, s);
+      if (e != hipSuccess) return e;
+    }
     const int tt = (T + 15) / 16, et = (c.n_experts + 15) / 16;
     if (gate_many(L, T))
       hipLaunchKernelGGL(gate_logits_many_kernel, dim3(tt, (et + 3) / 4), dim3(256), 0, s, (const uint16_t*)x, L->d_wg, T, c.hidden,
@@ -408,10 +419,24 @@ hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* i
   int G = 1;
   if (wide && c.n_experts >= 128 && L->d_logits != nullptr && T <= c.max_tokens)
     while (G < kRouteGroups && T * G * 2 <= L->n_cu && c.n_experts / (G * 2) >= 16) G *= 2;
+  // (the guess rides the same launch where its layer would take the same kernel)
+  GuessArgs twin{};
+  int blocks = T;
+  if (guess.layer) {
+    const moe_lrc_config& g = guess.layer->cfg;
+    if (xh == nullptr && G == 1 && g.hidden == c.hidden && (g.n_experts >= 64) == (c.n_experts >= 64) && (g.n_experts <= 8) == (c.n_experts <= 8) &&
+        g.n_experts < 128 && !gate_split(guess.layer, T)) {
+      twin = GuessArgs{guess.layer->d_wg, guess.layer->has_bias ? guess.layer->d_bias : nullptr, g.n_experts, g.top_k, g.renormalize, guess.idx, guess.w};
+      blocks = 2 * T;
+    } else {
+      const hipError_t e = launch_route(guess.layer, x, T, guess.idx, guess.w, nullptr, nullptr, s);
+      if (e != hipSuccess) return e;
+    }
+  }
   auto go = [&](auto kernel, int nw) {
-    hipLaunchKernelGGL(kernel, dim3(T, G), dim3(64 * nw), 0, s, (const uint16_t*)x, L->d_wg,
+    hipLaunchKernelGGL(kernel, dim3(blocks, G), dim3(64 * nw), 0, s, (const uint16_t*)x, L->d_wg,
                        L->has_bias ? L->d_bias : nullptr, T, c.hidden, c.n_experts, c.top_k,
-                       c.renormalize, idx, w, xh, tok_exp, L->d_logits);
+                       c.renormalize, idx, w, xh, tok_exp, L->d_logits, twin);
     if (G > 1)
       hipLaunchKernelGGL(topk_kernel, dim3((T + 3) / 4), dim3(256), 0, s, L->d_logits,
                          L->has_bias ? L->d_bias : nullptr, T, c.n_experts, c.top_k, c.renormalize, idx, w);
