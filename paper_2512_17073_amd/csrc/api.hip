@@ -257,18 +257,26 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   const size_t part_bytes = size_t(P) * c.hidden * 4, used = kblocks > 1 ? kblocks : 0;
   a.ha = reinterpret_cast<float*>(ws + w.y_part + used * part_bytes);
   a.ha_bytes = (kMaxKBlocks - used) * part_bytes;
+  bool ahead = false;                        // pooled: the FFN is launched before the host has seen the counts
+  if (c.residency == MOE_LRC_POOLED) {
+    const int rc = pool_begin(L, &ahead);
+    if (rc) return rc;
+  }
+  // (the same room, in front: (x A1 | x A3) of all tokens, where the factors are in place before the preparing launch)
+  const size_t p_bytes = align256(xa_tokens_bytes(c, T)), tokens_bytes = p_bytes + align256(size_t(P) * 4);
+  if (!(path & 1) && (c.residency == MOE_LRC_RESIDENT || ahead) && xa_by_tokens(c, T) && tokens_bytes <= a.ha_bytes) {
+    a.p_tokens = T;
+    a.p13 = a.ha;
+    a.row_tok = reinterpret_cast<int32_t*>(a.ha + p_bytes / 4);
+    a.ha += tokens_bytes / 4; a.ha_bytes -= tokens_bytes;
+  }
   if (kblocks_out) *kblocks_out = a.keep_partials ? kblocks : 1;
   // the launch that converts the activations also makes the block tables of the decode launches
   // and, for the decode flavour of the fused projection, (x A1 | x A3)
   PlanSpec plans[2];
   expert_ffn_plan_specs(a, plans[0], plans[1]);
   // ((x A1 | x A3) from the tokens inside the preparing launch needs the exponents beforehand)
-  bool ahead = false;                        // pooled: the FFN is launched before the host has seen the counts
-  if (c.residency == MOE_LRC_POOLED) {
-    const int rc = pool_begin(L, &ahead);
-    if (rc) return rc;
-  }
-  a.xa13_here = (c.residency != MOE_LRC_RESIDENT && !ahead) || tok_exp == nullptr;
+  a.xa13_here = (c.residency != MOE_LRC_RESIDENT && !ahead) || (tok_exp == nullptr && a.p_tokens == 0);
   a.x_tokens = x;
   // (the grouped (in A) kernels work on the rows that take the rank-r term only: their compact order)
   const bool comp = c.rank > 0 && c.top_n > 0 && path != 0;
@@ -296,6 +304,8 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   if (ahead && ahead_args) {                 // (for a second launch, if an expert turns out to be missing)
     *ahead_args = a;
     ahead_args->xa13_here = 1;
+    ahead_args->p_tokens = 0;
+    ahead_args->p13 = reinterpret_cast<float*>(ws + w.p13);
     ahead_args->marks = nullptr;
   }
   return MOE_LRC_OK;

@@ -50,6 +50,9 @@ struct KArgs {
   int in_rt, out_rt;         // row counts (incl. padding) of the operand-order buffers
   const float* p;            // (in A): fp16 [total_rows][projections * ls * 32], scaled by the projections' pre-scales,
                              // zero for rows without the rank-r term (written by the (in A) kernels)
+  int p_tokens;              // fused projection, decode flavour: p is kept per expert and token, [n_exp][p_tokens][..] and a
+                             // row of zeros behind (0: per routed row) ...
+  const int32_t* row_tok;    // ... per routed row: its token if it takes the rank-r term, else -1
   int K, N, KS, G, NT, group_shift, top_k, top_n, T, rank, rpad, total_rows;
   int ls;                    // rank steps of 32 of the B factor: ceil(rank / 32)
   int n_exp;                 // experts of this launch (many-rows flavour: the grid enumerates row chunks)

@@ -60,6 +60,13 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
   const int th = threadIdx.x, lane = th & 63;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
   const int q = lane >> 4, c = lane & 15, rowl = th & 15;
+  // (x A1 | x A3) kept per token (ranks up to kXaTokensRank: its fragments are at most one per wavefront): the token
+  // of the row whose part of a fragment this lane copies, on its way while the expert's table entry is read
+  int token = -1;
+  if constexpr (DUAL) {
+    const KernArgs ka = kern_args();
+    if (ka->p_tokens > 0) token = ka->row_tok[r0 + min(16 * (wave % MT) + c, cnt - 1)];
+  }
 
   // this block's n-tiles and how their units are dealt to the 16 wavefronts
   int t0, t1;
@@ -252,8 +259,24 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     // ---- start of a pass: activations of phase 0, the (in A) fragments and the first packed tiles
     //      are all requested before anything is awaited ----
     if (r > 0) __syncthreads();               // everyone is done with the previous pass's LDS
+    bool by_rows = true;
+    if constexpr (DUAL) {
+      const KernArgs ka = kern_args();
+      by_rows = ka->p_tokens == 0;
+      if (!by_rows && wave < p_frags) {
+        // (in front of the staging, whose copies a wait for the token would be for as well)
+        const int mt = wave % MT, g = wave / MT, st = g % LS, m = g / LS, pr = r + 16 * mt + c;
+        if (r > 0) token = ka->row_tok[r0 + min(pr, cnt - 1)];
+        // (rows without the term read the row of zeros)
+        const int row = pr < cnt && token >= 0 ? e * ka->p_tokens + token : ka->n_exp * ka->p_tokens;
+        const _Float16* src = reinterpret_cast<const _Float16*>(ka->p) + row * pitch + m * ka->ls * 32 + 32 * st + 8 * q;
+        __builtin_amdgcn_global_load_lds(
+            reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(src)),
+            reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p_lds + p_frag_unit(m, st, mt, LS, MT))), 16, 0, 0);
+      }
+    }
     stage_issue(0, min(KP, KSl));
-    if (!p_late && !joined) p_issue();
+    if (!p_late && !joined && by_rows) p_issue();
     int row_se[MT];                           // (the rows' exponents for the end of the pass)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) row_se[mt] = a.row_exp[(a.offsets ? r0 : 0) + min(r + 16 * mt + c, cnt - 1)];
@@ -632,11 +655,11 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     a.in = f.xh; a.out = f.h; a.K = f.H; a.N = f.F; a.NT = f.F / kTileN;
     a.in_rt = f.x_rt; a.out_rt = f.h_rt;
     a.KS = padded_k(f.H) / kTileK; a.G = padded_k(f.H) / f.group;
-    a.p = f.p13;
+    a.p = f.p13; a.p_tokens = f.p_tokens; a.row_tok = f.row_tok; a.n_exp = f.n_exp;
     a.kb_steps = a.KS; a.partial = nullptr;
     // ((x A1 | x A3) has been made by the launch that prepared the activations, unless it is asked for here)
     if (comp && f.xa13_here)
-      hipLaunchKernelGGL(xa13_tokens_kernel, dim3(4 * a.ls, f.n_exp), dim3(1024), 0, s, a, (const uint16_t*)f.x_tokens);
+      hipLaunchKernelGGL(xa13_tokens_kernel, dim3(2 * a.rpad / 16, f.n_exp), dim3(1024), 0, s, a, (const uint16_t*)f.x_tokens);
     if (f.marks) (void)hipEventRecord(f.marks[0], s);
     if (by_table) {
       a.plan = f.plan;
@@ -652,7 +675,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     a.in = f.h; a.out = f.y_rows; a.K = f.F; a.N = f.H; a.NT = f.H / kTileN;
     a.in_rt = f.h_rt; a.out_rt = 0;
     a.KS = padded_k(f.F) / kTileK; a.G = padded_k(f.F) / f.group;
-    a.p = f.p2;
+    a.p = f.p2; a.p_tokens = 0;
     // a long K (many phases of staged activations) is split into K-blocks of one 16-k-step phase each;
     // their fp32 partial outputs are added by the combine, or by reduce_kernel when y_rows is wanted.
     // The rank-r term is linear in (h A2): every K-block adds B2 times the part of (h A2) over its own
@@ -660,7 +683,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     const int kblocks = decode_w2_kblocks(f);
     a.kb_steps = (a.KS + kblocks - 1) / kblocks;
     a.partial = kblocks > 1 ? f.y_part : nullptr;
-    if (comp && !ha) hipLaunchKernelGGL(xa_rows_kernel<false>, dim3(2 * a.ls, f.n_exp, kblocks), dim3(1024), 0, s, a);
+    if (comp && !ha) hipLaunchKernelGGL(xa_rows_kernel<false>, dim3(a.rpad / 16, f.n_exp, kblocks), dim3(1024), 0, s, a);
     if (f.marks) (void)hipEventRecord(f.marks[2], s);
     if (by_table) {
       // (second table behind the first; every K-block uses the same shares)

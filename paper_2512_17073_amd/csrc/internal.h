@@ -161,6 +161,20 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
                             const CompactArgs* cmp /* or null */, const RouteArgs* route /* or null: perm->idx is ready */,
                             const ZeroRowsArgs& zr,
                             hipStream_t s, int32_t* host_stat = nullptr /* pinned: a copy of `stat` for the host */);
+// (x A1 | x A3) of every expert for every token instead of for the routed rows: it then waits neither for the routing
+// nor for the grouping.  Up to 64 tokens (up to four 16-row passes per factor tile, side by side); ranks whose
+// fragments are one per wavefront of the kernel that copies them.  xa_by_tokens is the part of the rule that does
+// not depend on where the factors are.
+// With many experts to a token's pairs, most of what that computes is not used: 128 experts, top 8, T = 64: 23 us for
+// the launch against 17 by rows (8 experts, top 2, K = 4096, rank 32: 11.2 against 17.2, T = 1 11.8 against 15.3).
+constexpr int kXaTokens = 64, kXaTokensRank = 128, kXaTokensExperts = 8;
+inline bool xa_by_tokens(const moe_lrc_config& c, int T) {
+  return c.rank > 0 && c.rank <= kXaTokensRank && c.top_n > 0 && T <= kXaTokens && c.n_experts <= kXaTokensExperts * c.top_k;
+}
+inline size_t xa_tokens_bytes(const moe_lrc_config& c, int T) {
+  return (size_t(c.n_experts) * T + 1) * ((c.rank + 31) / 32) * 128;
+}
+
 constexpr int kMaxKBlocks = 8;    // most K-blocks the decode W2 kernel splits into
 // blocks (per K-block) of a decode launch that shares its blocks out by a table: `target` (the
 // device's CUs over the K-blocks), or enough for ceil(NT / 32) blocks per expert that can be active
@@ -183,6 +197,8 @@ struct FfnArgs {
   _Float16* h;                // SwiGLU output in operand order, h_rt rows
   int x_rt, h_rt;
   float* p13;                 // (x A1 | x A3), fp16 [rows][2 * ls * 32] (ffn_common.h, KArgs::p)
+  int p_tokens;               // ... or [n_exp][p_tokens tokens][2 * ls * 32] and a row of zeros (KArgs::p_tokens)
+  int32_t* row_tok;           // ... then also [rows]: KArgs::row_tok, written by the preparing launch
   float* p2;                  // (h A2), fp16 [rows][ls * 32]; decode flavour: one per W2 K-block
   float* ha;                  // decode flavour of both projections: room for ha_bytes of (h A2) part sums (decode_ha)
   size_t ha_bytes;

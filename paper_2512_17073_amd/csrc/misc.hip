@@ -109,6 +109,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
 // Then one block makes the block tables of the decode launches (plan.h), and xa_tiles * E further
 // blocks compute (x A1 | x A3) for the decode flavour of the fused projection from the bf16 tokens
 // (xa_rows.h), so that no launch of its own stands between this one and the W1|W3 kernel.
+// Where that is done for every token and expert (KArgs::p_tokens) those blocks run beside the grouping instead of
+// after it, and the row blocks leave, per routed row, which token's result it takes (row_tok).
+// Bound: the longest chain of dependent loads (grouping, then the tokens or the tables; tokens and factors,
+// then a sum over the wavefronts); Mixtral shape T = 64 17.2 -> 11.2 us, T = 1 15.3 -> 11.8, since neither waits for the other
+// and the tables are made without 64-bit divisions from counts read once.
 constexpr int kPrepThreads = 1024;
 // With a token or two every block first routes them itself (route.wg != null).
 // With few pairs, every block first groups the pairs by expert itself (perm.idx != null: the body of
@@ -123,9 +128,20 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
                                                    PlanSpec plan1, int xa_tiles, ffn::KArgs xa,
                                                    const int32_t* tok_exp, int32_t* __restrict__ row_exp,
                                                    PermuteArgs perm, CompactArgs cmp, RouteArgs route, ZeroRowsArgs zr,
-                                                   int32_t* __restrict__ host_stat) {
+                                                   int32_t* __restrict__ host_stat, int32_t* __restrict__ row_tok) {
   __shared__ ffn::float4_t red[2 * kPrepThreads / 64][64];
   __shared__ uint32_t row_max[16];
+  constexpr int kWavesPerBlock = kPrepThreads / 64, kColLanes = kPrepThreads / 16;
+  const int row_blocks = (rows + 15) / 16;
+  const int stat_blocks = stat ? (E + kWavesPerBlock - 1) / kWavesPerBlock : 0, plan_block = plan0.B + plan1.B > 0 ? 1 : 0;
+  const int xa_first = row_blocks + stat_blocks + plan_block;
+  if (xa.p_tokens > 0 && (int)blockIdx.x >= xa_first && (int)blockIdx.x < (int)gridDim.x - 1) {
+    // (x A1 | x A3) of all tokens: nothing to wait for; sixteen at a time where the grid then takes them all at once
+    const int i = (int)blockIdx.x - xa_first, pass = 16 * (int)gridDim.y >= xa.p_tokens ? 16 : 32;
+    ffn::xa_tokens_body<kWavesPerBlock>(xa, x, route.wg != nullptr ? nullptr : tok_exp, i % xa_tiles, i / xa_tiles,
+                                         pass * blockIdx.y, pass * gridDim.y, pass == 32, red);
+    return;
+  }
   if (route.wg != nullptr) {
     // a token or two: every block routes them itself (route_body.h) instead of a launch of its
     // own doing it beforehand; perm.idx and tok_exp are then this block's own writes
@@ -138,9 +154,6 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
     permute_body(pl, perm.idx, perm.P, E, top_k, top_n, perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts);
     __syncthreads();
   }
-  constexpr int kWavesPerBlock = kPrepThreads / 64, kColLanes = kPrepThreads / 16;
-  const int row_blocks = (rows + 15) / 16;
-  const int stat_blocks = stat ? (E + kWavesPerBlock - 1) / kWavesPerBlock : 0, plan_block = plan0.B + plan1.B > 0 ? 1 : 0;
   if ((int)blockIdx.x == (int)gridDim.x - 1) {                              // the zero rows (the last block)
     const int n = blockIdx.y * kPrepThreads + threadIdx.x, step = kPrepThreads * gridDim.y;
     const int xu = (H + kTileK - 1) / kTileK * (kTileK / 8);               // 16-byte units per row
@@ -151,8 +164,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
         zr.h[size_t(i / dec::kZeroRows) * zr.h_rt + zr.h_rt - dec::kZeroRows + i % dec::kZeroRows] = make_uint4(0, 0, 0, 0);
     return;
   }
-  if ((int)blockIdx.x >= row_blocks + stat_blocks + plan_block) {          // (x A1 | x A3)
-    const int i = (int)blockIdx.x - (row_blocks + stat_blocks + plan_block);
+  if ((int)blockIdx.x >= xa_first) {                                        // (x A1 | x A3) of the routed rows
+    const int i = (int)blockIdx.x - xa_first;
     if (blockIdx.y == 0) ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, x, i % xa_tiles, i / xa_tiles, 0, red);
     return;
   }
@@ -206,7 +219,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
     se = ffn::row_exponent(row_max[threadIdx.x & 15]);
   }
   if (R >= rows) return;
-  if (blockIdx.y == 0 && (threadIdx.x >> 4) == 0) row_exp[R] = se;
+  if (blockIdx.y == 0 && (threadIdx.x >> 4) == 0) {
+    row_exp[R] = se;
+    if (row_tok != nullptr) row_tok[R] = row_pair[R] - t * top_k < top_n ? t : -1;
+  }
   const float sc = ffn::pow2i(se);
   // (grid.y splits the columns when there are few rows, so that the launch still fills the chip)
   // (two adjacent units per thread: a wavefront reads 128 contiguous bytes of each of its rows; H / 8 is even)
@@ -283,7 +299,8 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
     xa.rank = f.rank; xa.ls = (f.rank + 31) / 32; xa.K = f.H; xa.p = f.p13; xa.total_rows = f.total_rows;
     xa.kb_steps = (f.H + kTileK - 1) / kTileK;
     xa.tok_exp = tok_exp; xa.row_exp = row_exp;
-    xa_tiles = 4 * xa.ls;
+    xa.rpad = f.rpad; xa.n_exp = f.n_exp; xa.p_tokens = f.p_tokens;
+    xa_tiles = 2 * f.rpad / 16;
   }
   const int stat_blocks = stat ? (c.n_experts + kPrepThreads / 64 - 1) / (kPrepThreads / 64) : 0;
   const int cmp_block = (cmp && row_pair && stat) ? 1 : 0;     // (the compaction rides the per-expert counting)
@@ -293,7 +310,8 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
                      row_pair, c.n_experts, c.top_k, c.top_n, stat, p0, p1, xa_tiles, xa, tok_exp, row_exp,
                      perm ? *perm : PermuteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0},
                      cmp_block ? *cmp : CompactArgs{nullptr, nullptr},
-                     (route && perm) ? *route : RouteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, 0}, zr, host_stat);
+                     (route && perm) ? *route : RouteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, 0}, zr, host_stat,
+                     xa_tiles > 0 && xa.p_tokens > 0 ? xa13->row_tok : nullptr);
   return hipGetLastError();
 }
 

@@ -18,12 +18,15 @@ struct PlanSpec { int B, NT, target; int32_t* plan; };     // B entries for a pr
 struct PlanEntry { int32_t e, b, G, r0, cnt, slots, pad0, pad1; };     // slots: ha_slots of the expert's blocks in the other table
 constexpr int kPlanEntryInts = 8;
 
-// other: the spec of the table whose blocks leave part sums for this table's (null: none)
+// other: the spec of the table whose blocks leave part sums for this table's (null: none).
+// The rest of the preparing launch is short, so this chain sets its length: the experts' rows are read once, 64
+// experts to a register, and nothing is divided in 64 bits (blocks times passes: below 2^31 for any launch of
+// this flavour, whose experts have 128 rows at most on average).
 __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, const PlanSpec sp, const PlanSpec other, int lane) {
   if (sp.plan == nullptr) return;
   int32_t* __restrict__ plan = sp.plan;
-  // what an expert's rows cost: every 32-row pass streams the expert's weights again
-  auto weight = [](int cnt) { return (cnt + 31) / 32; };
+  constexpr int kChunks = 4;                   // (at most 256 experts)
+  const unsigned long long below = (1ull << lane) - 1ull;
   auto scan = [&](int v) {
 #pragma unroll
     for (int dlt = 1; dlt < 64; dlt *= 2) {
@@ -32,69 +35,77 @@ __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, con
     }
     return v;
   };
-  auto rows_of = [&](int e) { return e < E ? offsets[e + 1] - offsets[e] : 0; };
+  int cnt[kChunks], r0[kChunks], weight[kChunks];
+  unsigned long long active[kChunks];
+#pragma unroll
+  for (int i = 0; i < kChunks; ++i) {
+    const int e = min(64 * i + lane, E - 1);
+    r0[i] = offsets[e];
+    cnt[i] = 64 * i + lane < E ? offsets[e + 1] - r0[i] : 0;
+  }
   int n_active = 0, wsum = 0;
-  for (int e0 = 0; e0 < E; e0 += 64) {
-    const int cnt = rows_of(e0 + lane);
-    n_active += __popcll(__ballot(cnt > 0));
-    wsum += __shfl(scan(weight(cnt)), 63);
+#pragma unroll
+  for (int i = 0; i < kChunks; ++i) {
+    // what an expert's rows cost: every 32-row pass streams the expert's weights again
+    weight[i] = (cnt[i] + 31) / 32;
+    active[i] = __ballot(cnt[i] > 0);
+    n_active += __popcll(active[i]);
+    if (64 * i < E) wsum += __shfl(scan(weight[i]), 63);
   }
   // One table's shares: as many blocks as fill the chip (`target`), more only if the experts with rows need
   // them; the rest of the grid exits at once.  Every expert gets its fewest blocks (a block owns at most
   // 32 n-tiles) or its share by weight of all the blocks, whichever is more (the shares by weight are then
-  // scaled down to what is left).
-  struct Shares {
-    int base, total, over, w_before, act_before;
-    long long extra;
-  };
-  auto want_of = [&](const Shares& h, int cnt) {     // an expert's claim on the blocks beyond the fewest
-    const int want = wsum > 0 ? int((long long)h.total * weight(cnt) / wsum) : 0;
-    return max(0, want - (cnt > 0 ? h.base : 0));
-  };
-  auto shares = [&](const PlanSpec& p) {
-    Shares h{};
-    h.base = (p.NT + 31) / 32;
-    h.total = min(p.B, max(p.target, n_active * h.base));
-    h.extra = h.total - n_active * h.base;
-    for (int e0 = 0; e0 < E; e0 += 64) h.over += __shfl(scan(want_of(h, rows_of(e0 + lane))), 63);
-    return h;
-  };
-  // the blocks [lo, hi) of this lane's expert, 64 experts at a time
-  auto step = [&](Shares& h, int cnt, int& lo, int& hi) {
-    const int act = cnt > 0 ? 1 : 0, ai = scan(act), w = want_of(h, cnt), wi = scan(w);
-    lo = hi = 0;
-    if (act) {
-      lo = (h.act_before + ai - 1) * h.base + (h.over > 0 ? int(h.extra * (h.w_before + wi - w) / h.over) : 0);
-      hi = (h.act_before + ai) * h.base + (h.over > 0 ? int(h.extra * (h.w_before + wi) / h.over) : 0);
+  // scaled down to what is left).  Blocks [lo, hi) of the experts of every chunk; returns the blocks used.
+  auto shares = [&](const PlanSpec& p, int (&lo)[kChunks], int (&hi)[kChunks]) {
+    const int base = (p.NT + 31) / 32, total = min(p.B, max(p.target, n_active * base)), extra = total - n_active * base;
+    int claim[kChunks], incl[kChunks], over = 0, act = 0;    // claims on the blocks beyond the fewest, summed up to here
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i) {
+      if (64 * i >= E) continue;
+      claim[i] = max(0, int(uint32_t(total * weight[i]) / uint32_t(max(wsum, 1))) - (cnt[i] > 0 ? base : 0));
+      incl[i] = over + scan(claim[i]);
+      over = __shfl(incl[i], 63);
     }
-    h.act_before += __shfl(ai, 63); h.w_before += __shfl(wi, 63);
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i) {
+      lo[i] = hi[i] = 0;
+      if (64 * i >= E) continue;
+      const int first = (act + __popcll(active[i] & below)) * base;
+      if (cnt[i] > 0) {
+        lo[i] = first + (over > 0 ? int(uint32_t(extra * (incl[i] - claim[i])) / uint32_t(over)) : 0);
+        hi[i] = first + base + (over > 0 ? int(uint32_t(extra * incl[i]) / uint32_t(over)) : 0);
+      }
+      act += __popcll(active[i]);
+    }
+    return n_active > 0 ? n_active * base + (over > 0 ? extra : 0) : 0;
   };
   const int B = sp.B;
-  Shares mine = shares(sp), theirs{};
-  if (other.plan != nullptr) theirs = shares(other);
-  for (int e0 = 0; e0 < E; e0 += 64) {
-    const int e = e0 + lane, cnt = rows_of(e), r0 = e < E ? offsets[e] : 0;
-    int lo, hi, olo = 0, ohi = 0;
-    step(mine, cnt, lo, hi);
-    if (other.plan != nullptr) step(theirs, cnt, olo, ohi);
-    const int slots = min(ohi - olo, other.NT);
-    const unsigned long long with_rows = __ballot(cnt > 0);
-    if (__popcll(with_rows) <= 8) {
+  int lo[kChunks], hi[kChunks], olo[kChunks], ohi[kChunks], slots[kChunks] = {0, 0, 0, 0};
+  const int used = shares(sp, lo, hi);
+  if (other.plan != nullptr) {
+    shares(other, olo, ohi);
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i) slots[i] = min(ohi[i] - olo[i], other.NT);
+  }
+#pragma unroll
+  for (int i = 0; i < kChunks; ++i) {
+    if (64 * i >= E) continue;
+    if (__popcll(active[i]) <= 8) {
       // few experts with many blocks each: the whole wavefront writes one expert's entries after the other's
-      for (unsigned long long todo = with_rows; todo; todo &= todo - 1) {
+      for (unsigned long long todo = active[i]; todo; todo &= todo - 1) {
         const int j = __ffsll(todo) - 1;
-        const int lo_j = __shfl(lo, j), G_j = __shfl(hi, j) - lo_j, hi_j = min(lo_j + G_j, B);
-        const int r0_j = __shfl(r0, j), cnt_j = __shfl(cnt, j), slots_j = __shfl(slots, j);
-        for (int i = lo_j + lane; i < hi_j; i += 64)
-          reinterpret_cast<PlanEntry*>(plan)[i] = PlanEntry{e0 + j, i - lo_j, G_j, r0_j, cnt_j, slots_j, 0, 0};
+        const int lo_j = __shfl(lo[i], j), G_j = __shfl(hi[i], j) - lo_j, hi_j = min(lo_j + G_j, B);
+        const int r0_j = __shfl(r0[i], j), cnt_j = __shfl(cnt[i], j), slots_j = __shfl(slots[i], j);
+        for (int b = lo_j + lane; b < hi_j; b += 64)
+          reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{64 * i + j, b - lo_j, G_j, r0_j, cnt_j, slots_j, 0, 0};
       }
-    } else if (cnt > 0) {
+    } else if (cnt[i] > 0) {
       // many experts with few blocks each: every lane writes its own expert's entries
-      for (int i = lo; i < hi && i < B; ++i) reinterpret_cast<PlanEntry*>(plan)[i] = PlanEntry{e, i - lo, hi - lo, r0, cnt, slots, 0, 0};
+      for (int b = lo[i]; b < hi[i] && b < B; ++b)
+        reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{64 * i + lane, b - lo[i], hi[i] - lo[i], r0[i], cnt[i], slots[i], 0, 0};
     }
   }
-  const int used = n_active > 0 ? n_active * mine.base + (mine.over > 0 ? int(mine.extra) : 0) : 0;
-  for (int i = used + lane; i < B; i += 64) reinterpret_cast<PlanEntry*>(plan)[i] = PlanEntry{-1, 0, 1, 0, 0, 0, 0, 0};
+  for (int b = used + lane; b < B; b += 64) reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{-1, 0, 1, 0, 0, 0, 0, 0};
 }
 
 }  // namespace lrc
