@@ -98,14 +98,17 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
   }
 }
 
-// Blocks 0..ceil(rows/16)-1 write the fp16 copy of sixteen rows' tokens in operand order (the layout
+// ceil(rows/16) blocks write the fp16 copy of sixteen rows' tokens in operand order (the layout
 // the FFN kernels stage from, see act_unit in ffn_common.h): row R of the routed rows is the token
 // of pair row_pair[R]; without row_pair, row R is token R.  Thread (row r = t % 16, column lane
 // t / 16) converts the 16-byte units t / 16, t / 16 + 64, ... of its row: a wavefront reads 64
 // contiguous bytes of each of its rows and writes runs of 256 bytes (sixteen rows of one unit).
-// The blocks after those count, one wavefront per expert, the routed rows and the rows that take
+// The blocks in front of those count, one wavefront per expert, the routed rows and the rows that take
 // the rank-r term (what the router-guided transfer must bring in): stat = [-, -, rows[E], comp rows[E]].
-// (and compact the latter for the grouped (in A) kernels, CompactArgs).
+// (and compact the latter for the grouped (in A) kernels, CompactArgs).  They are first because one of them is the longest
+// chain of a large batch: an expert that nearly every token takes has its rows counted one batch after the other (Qwen3 shape,
+// T = 4096, 4096 rows on one expert: launch 80 -> 50 us with the counting in front and eight batches requested together,
+// and without a pass over the rows for their exponents, which the routing leaves).
 // Then one block makes the block tables of the decode launches (plan.h), and xa_tiles * E further
 // blocks compute (x A1 | x A3) for the decode flavour of the fused projection from the bf16 tokens
 // (xa_rows.h), so that no launch of its own stands between this one and the W1|W3 kernel.
@@ -115,6 +118,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
 // then a sum over the wavefronts); Mixtral shape T = 64 17.2 -> 11.2 us, T = 1 15.3 -> 11.8, since neither waits for the other
 // and the tables are made without 64-bit divisions from counts read once.
 constexpr int kPrepThreads = 1024;
+constexpr int kStatAhead = 8;              // batches of 64 rows whose pairs a counting wavefront asks for together
 // With a token or two every block first routes them itself (route.wg != null).
 // With few pairs, every block first groups the pairs by expert itself (perm.idx != null: the body of
 // the permute kernel, writing the same values from every block) instead of a launch of its own
@@ -173,29 +177,36 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
     if (blockIdx.y == 0 && threadIdx.x < 128) make_plan(offsets, E, threadIdx.x < 64 ? plan0 : plan1, threadIdx.x < 64 ? PlanSpec{0, 0, 0, nullptr} : plan0, threadIdx.x & 63);
     return;
   }
-  if ((int)blockIdx.x >= row_blocks) {
-    const int e = ((int)blockIdx.x - row_blocks) * kWavesPerBlock + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if ((int)blockIdx.x < stat_blocks) {
+    const int e = (int)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (e >= E || blockIdx.y != 0) return;
     const int b = offsets[e], n = offsets[e + 1] - b;
     // the expert's rows that take the rank-r term, counted and (for the grouped (in A) kernels,
     // CompactArgs) compacted in row order by ballot
     int comp = 0;
-    for (int r0 = 0; r0 < n; r0 += 64) {
-      const int r = r0 + lane;
-      const bool f = r < n && (row_pair[b + min(r, n - 1)] % top_k) < top_n;
-      const unsigned long long m = __ballot(f);
-      if (cmp.index != nullptr) {
-        const int at = b + comp + __popcll(m & ((1ull << lane) - 1ull));
-        if (r < n) cmp.index[b + r] = f ? at : -1;
-        if (f) cmp.list[at] = b + r;
+    for (int r0 = 0; r0 < n; r0 += 64 * kStatAhead) {
+      int pair[kStatAhead];
+#pragma unroll
+      for (int u = 0; u < kStatAhead; ++u) pair[u] = row_pair[b + min(r0 + 64 * u + lane, n - 1)];
+#pragma unroll
+      for (int u = 0; u < kStatAhead; ++u) {
+        if (r0 + 64 * u >= n) break;
+        const int r = r0 + 64 * u + lane;
+        const bool f = r < n && pair[u] % top_k < top_n;
+        const unsigned long long m = __ballot(f);
+        if (cmp.index != nullptr) {
+          const int at = b + comp + __popcll(m & ((1ull << lane) - 1ull));
+          if (r < n) cmp.index[b + r] = f ? at : -1;
+          if (f) cmp.list[at] = b + r;
+        }
+        comp += __popcll(m);
       }
-      comp += __popcll(m);
     }
     if (lane == 0) { stat[2 + e] = n; stat[2 + E + e] = comp; }
     if (lane == 0 && host_stat != nullptr) { host_stat[2 + e] = n; host_stat[2 + E + e] = comp; }
     return;
   }
-  const int R = blockIdx.x * 16 + (threadIdx.x & 15);
+  const int R = ((int)blockIdx.x - stat_blocks) * 16 + (threadIdx.x & 15);
   const int t = R < rows ? (row_pair ? row_pair[R] / top_k : R) : 0;
   const uint4* xrow = reinterpret_cast<const uint4*>(x + size_t(t) * H);
   // The row's power-of-two pre-scale (ffn_common.h): from the routing kernel's per-token exponents,
