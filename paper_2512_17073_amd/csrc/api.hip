@@ -700,14 +700,14 @@ int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hi
   const bool mk = L->profile;
   L->profile_valid = false;
   if (mk) LRC_HIP(hipEventRecord(L->marks[MOE_LRC_STAGE_ROUTE], s));
-  int32_t* tok_exp = route_writes_exponents(L, T) ? (int32_t*)(b + w.tok_exp) : nullptr;
+  int32_t* tok_exp = (int32_t*)(b + w.tok_exp);
   // few pairs: every block of the preparing launch groups the pairs itself (one launch fewer)
   const PermuteArgs perm{idx, (int32_t*)(b + w.counts), offsets, row_pair, pair_row, (int32_t*)(b + w.comp_counts), T * L->cfg.top_k};
   // (every block repeats the grouping, so only where the preparing launch is one round of blocks
   // and the tables are small: few experts)
   const bool fused_permute = perm.P <= kFusedPermuteMaxPairs && L->cfg.n_experts <= 32;
   // a token or two: the blocks of the preparing launch route them as well (another launch fewer)
-  const bool fused_route = fused_permute && T * L->cfg.n_experts <= kFusedRoutePairs && tok_exp != nullptr;
+  const bool fused_route = fused_permute && T * L->cfg.n_experts <= kFusedRoutePairs;
   const RouteArgs route{L->d_wg, L->has_bias ? L->d_bias : nullptr, idx, tw, tok_exp, L->cfg.renormalize};
   const bool pooled = L->cfg.residency == MOE_LRC_POOLED;
   const RouteGuess guess = pooled ? pool_guess(L) : RouteGuess{nullptr, nullptr, nullptr};
@@ -719,8 +719,9 @@ int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hi
                            (int32_t*)(b + w.comp_counts), s));
   if (mk) LRC_HIP(hipEventRecord(L->marks[MOE_LRC_STAGE_PREP], s));
   // Shared experts need nothing from the router: with resident weights they run on the layer's side
-  // stream beside the routed experts (forked here, joined before the combine).  In staged mode the
-  // side stream carries the copies and the shared experts follow the routed ones.
+  // stream beside the routed experts (forked here, joined before the combine; forked before the routing instead, the
+  // DeepSeek shape takes 197 us at T = 512 against 191: the grouping's launches wait behind the shared GEMMs).  In staged
+  // mode the side stream carries the copies and the shared experts follow the routed ones.
   const bool fork = L->cfg.n_shared > 0 && L->cfg.residency == MOE_LRC_RESIDENT;
   const void* y_shared = L->cfg.n_shared > 0 ? b + w.sh_y : nullptr;
   if (fork) {

@@ -101,13 +101,11 @@ int set_error(int code, const std::string& msg);
 Workspace plan_workspace(const moe_lrc_layer* L, int T);
 
 // ---- kernel launchers (each returns hipError_t of the launch) ------------------------------
-// tok_exp (may be null): receives every token's pre-scale exponent (ffn_common.h) if
-// route_writes_exponents(L, T), else it is left untouched
+// tok_exp (may be null): receives every token's pre-scale exponent (ffn_common.h)
 // guess: a second layer of the same hidden size whose gate is applied to the same tokens (layer == null: none)
 struct RouteGuess { const moe_lrc_layer* layer; int32_t* idx; float* w; };
 hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* idx, float* w,
                         _Float16* xh /*may be null*/, int32_t* tok_exp, hipStream_t s, const RouteGuess& guess = RouteGuess{nullptr, nullptr, nullptr});
-bool route_writes_exponents(const moe_lrc_layer* L, int T);
 // Batches whose routing is tiled on the fp64 matrix cores instead of one block per token: at least 128
 // tiles of 16 tokens x 16 experts and 2^26 products.  Whole call, one block per token -> tiled, us.  Above the line no
 // shape measured loses: H = 2048, E = 128: T = 256 24.3 -> 17.4, 512 30.7 -> 22.9; E = 64: 512 18.5 -> 16.9,

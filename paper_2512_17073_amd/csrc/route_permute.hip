@@ -125,133 +125,131 @@ __global__ __launch_bounds__(64 * NW) void route_kernel(const uint16_t* __restri
   select_topk(v, lane, E, top_k, renorm, idx + size_t(t) * top_k, w + size_t(t) * top_k);
 }
 
-// Many tokens: the logits of a 16-token x 16-expert tile on the fp64 matrix cores (every wavefront
-// of the other kernel re-reads the whole gate for one token; here a gate row serves 16 tokens).
+// Many tokens: the logits of 16 R tokens x 16 R experts on the fp64 matrix cores (every wavefront
+// of the other kernel re-reads the whole gate for one token; here a gate row serves 16 R tokens).
 // v_mfma_f64_16x16x4: experts are the rows, tokens the columns; lane (i = lane % 16, kq = lane / 16)
-// supplies gate row i and token i at the k index of the step.  The chain of dependent 64-cycle MFMAs is
-// what a tile takes, so the NW wavefronts of a block share the hidden dimension (each lane group kq of
-// each wavefront walks its own contiguous run of 16-byte chunks in order, the next batch of four in
+// supplies gate row i and token i at the k index of the step.  The NW wavefronts of a block share the hidden dimension
+// (each lane group kq of each wavefront walks its own contiguous run of 16-byte chunks in order, the next batch in
 // flight while one is multiplied) and add their parts through LDS in wavefront order.  Products of bf16 values are
 // exact in fp64 and every (expert, token) pair sees the same sequence of operations, so duplicated gate
-// rows give bit-identical logits.  The blocks of the first expert tile also write the tokens' pre-scale
+// rows give bit-identical logits.  The blocks of the first experts also write the tokens' pre-scale
 // exponents.  Grid: (token tiles, expert tiles); logits [T][E].
+// Bound: with few tiles (R = 1, NW = 8) the dependent chain of 64-cycle MFMAs and the loads before it.  With so many that
+// they fill the chip, the issue of MFMAs and of the conversions to fp64, 2 / R per MFMA: E = 128, H = 2048, T = 4096
+// (2.1 GFLOP, 30 us) 52 us with R = 2 and NW = 4; with one 16 x 16 tile per wavefront and K not shared 62, whether the next
+// batch was requested before the products or after them.
 typedef double double4_t __attribute__((ext_vector_type(4)));
-template <int NW>
+template <int NW, int R>
 __global__ __launch_bounds__(64 * NW) void gate_logits_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T,
                                                               int H, int E, double* __restrict__ logits, int32_t* __restrict__ tok_exp) {
-  __shared__ double4_t red[NW][64];
-  __shared__ uint32_t peak[NW][16];
+  constexpr int kBatch = R == 1 ? 4 : 2;                  // 16-byte chunks of every row in a batch
+  __shared__ double4_t red[NW][R * R][64];
+  __shared__ uint32_t peak[NW][16 * R];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int et = blockIdx.y, i = lane & 15, kq = lane >> 4;
-  const int token = min((int)blockIdx.x * 16 + i, T - 1), expert = min(et * 16 + i, E - 1);
+  const int e0 = blockIdx.y * 16 * R, t0 = blockIdx.x * 16 * R, i = lane & 15, kq = lane >> 4;
   const int chunks = H / 8, per = (chunks + 4 * NW - 1) / (4 * NW), lo = (wave * 4 + kq) * per;
-  const uint4* xp = reinterpret_cast<const uint4*>(x + size_t(token) * H);
-  const uint4* wp = reinterpret_cast<const uint4*>(wg + size_t(expert) * H);
-  double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
-  uint32_t top = 0;
-  auto load = [&](int c0, uint4 (&xv)[4], uint4 (&wv)[4]) {
+  const uint4 *xp[R], *wp[R];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+  for (int r = 0; r < R; ++r) {
+    xp[r] = reinterpret_cast<const uint4*>(x + size_t(min(t0 + 16 * r + i, T - 1)) * H);
+    wp[r] = reinterpret_cast<const uint4*>(wg + size_t(min(e0 + 16 * r + i, E - 1)) * H);
+  }
+  double4_t acc[R][R];                                    // [expert tile][token tile]
+  uint32_t top[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    top[r] = 0;
+#pragma unroll
+    for (int s = 0; s < R; ++s) acc[r][s] = double4_t{0.0, 0.0, 0.0, 0.0};
+  }
+  struct Batch { uint4 x[R][kBatch], w[R][kBatch]; };
+  auto load = [&](int c0, Batch& b) {
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
       const int c = min(lo + c0 + u, chunks - 1);
-      xv[u] = xp[c]; wv[u] = wp[c];
+#pragma unroll
+      for (int r = 0; r < R; ++r) { b.x[r][u] = xp[r][c]; b.w[r][u] = wp[r][c]; }
     }
   };
-  const bool whole = chunks == 4 * NW * per && per % 4 == 0, peaks = tok_exp != nullptr && et == 0;
-  auto multiply = [&](auto WHOLE_, int c0, const uint4 (&xv)[4], const uint4 (&wv)[4]) {
+  const bool whole = chunks == 4 * NW * per && per % kBatch == 0, peaks = tok_exp != nullptr && e0 == 0;
+  auto multiply = [&](auto WHOLE_, int c0, const Batch& b) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kBatch; ++u) {
       const bool in = decltype(WHOLE_)::value || (c0 + u < per && lo + c0 + u < chunks);          // (else zeros)
-      const uint32_t xa[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
-      const uint32_t wa[4] = {in ? wv[u].x : 0u, in ? wv[u].y : 0u, in ? wv[u].z : 0u, in ? wv[u].w : 0u};
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (peaks) top = max(top, in ? max(xa[j] & 0x7fffu, (xa[j] >> 16) & 0x7fffu) : 0u);
-        const uint32_t xj = in ? xa[j] : 0u;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf16_to_double(wa[j] & 0xffffu), bf16_to_double(xj & 0xffffu), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf16_to_double(wa[j] >> 16), bf16_to_double(xj >> 16), acc, 0, 0, 0);
+        uint32_t xj[R], wj[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const uint4 xv = b.x[r][u], wv = b.w[r][u];
+          const uint32_t xa[4] = {xv.x, xv.y, xv.z, xv.w}, wa[4] = {wv.x, wv.y, wv.z, wv.w};
+          xj[r] = in ? xa[j] : 0u; wj[r] = in ? wa[j] : 0u;
+          if (peaks) top[r] = max(top[r], max(xj[r] & 0x7fffu, (xj[r] >> 16) & 0x7fffu));
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          double xd[R], wd[R];
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            xd[r] = bf16_to_double(h ? xj[r] >> 16 : xj[r] & 0xffffu);
+            wd[r] = bf16_to_double(h ? wj[r] >> 16 : wj[r] & 0xffffu);
+          }
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int s = 0; s < R; ++s) acc[r][s] = __builtin_amdgcn_mfma_f64_16x16x4f64(wd[r], xd[s], acc[r][s], 0, 0, 0);
+        }
       }
     }
   };
-  uint4 xv[2][4], wv[2][4];
-  load(0, xv[0], wv[0]);
+  Batch ring[2];
+  load(0, ring[0]);
   auto walk = [&](auto WHOLE_) {
-    for (int c0 = 0; c0 < per; c0 += 8) {
-      load(c0 + 4, xv[1], wv[1]);
-      multiply(WHOLE_, c0, xv[0], wv[0]);
-      load(c0 + 8, xv[0], wv[0]);
-      if (c0 + 4 < per) multiply(WHOLE_, c0 + 4, xv[1], wv[1]);
+    for (int c0 = 0; c0 < per; c0 += 2 * kBatch) {
+      load(c0 + kBatch, ring[1]);
+      multiply(WHOLE_, c0, ring[0]);
+      load(c0 + 2 * kBatch, ring[0]);
+      if (c0 + kBatch < per) multiply(WHOLE_, c0 + kBatch, ring[1]);
     }
   };
   if (whole) walk(std::true_type{});
   else walk(std::false_type{});
-  red[wave][lane] = acc;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int s = 0; s < R; ++s) red[wave][r * R + s][lane] = acc[r][s];
   if (peaks) {
-    top = max(top, (uint32_t)__shfl_xor((int)top, 16));
-    top = max(top, (uint32_t)__shfl_xor((int)top, 32));
-    if (kq == 0) peak[wave][i] = top;
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+      top[s] = max(top[s], (uint32_t)__shfl_xor((int)top[s], 16));
+      top[s] = max(top[s], (uint32_t)__shfl_xor((int)top[s], 32));
+      if (kq == 0) peak[wave][16 * s + i] = top[s];
+    }
   }
   __syncthreads();
-  if (wave != 0) return;
-  acc = red[0][lane];
+  // wavefront v takes the tiles v, v + NW, ...
+  for (int v = wave; v < R * R; v += NW) {
+    double4_t sum = red[0][v][lane];
 #pragma unroll
-  for (int w = 1; w < NW; ++w) acc += red[w][lane];
-  // register r of lane (i, kq) holds row kq + 4 r of the tile (the fp64 variant interleaves the
-  // rows by four), i.e. expert 16 et + kq + 4 r, of token 16 tile + i
-  const int t = blockIdx.x * 16 + i;
-  if (t >= T) return;
+    for (int w = 1; w < NW; ++w) sum += red[w][v][lane];
+    // register r of lane (i, kq) holds row kq + 4 r of the tile (the fp64 variant interleaves the
+    // rows by four), i.e. expert e0 + 16 (v / R) + kq + 4 r, of token t0 + 16 (v % R) + i
+    const int t = t0 + 16 * (v % R) + i;
+    if (t < T) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int e = et * 16 + kq + 4 * r;
-    if (e < E) logits[size_t(t) * E + e] = acc[r];
-  }
-  if (peaks && kq == 0) {
-#pragma unroll
-    for (int w = 1; w < NW; ++w) peak[0][i] = max(peak[0][i], peak[w][i]);
-    const int eb = int(peak[0][i] >> 7);
-    tok_exp[t] = eb == 0 ? 0 : min(60, max(-60, 127 - eb));
-  }
-}
-
-// The same with one wavefront per tile, four expert tiles per block (which share the tokens through the
-// L1), for so many tiles that they fill the chip by themselves: E = 128, T = 4096: 63 us with the Top-k, 91 split.
-__global__ __launch_bounds__(256) void gate_logits_many_kernel(const uint16_t* __restrict__ x,
-                                                          const uint16_t* __restrict__ wg, int T, int H, int E,
-                                                          double* __restrict__ logits) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int et = blockIdx.y * 4 + wave;
-  if (et * 16 >= E) return;
-  const int i = lane & 15, kq = lane >> 4, Hq = H / 4;
-  const int token = min((int)blockIdx.x * 16 + i, T - 1), expert = min(et * 16 + i, E - 1);
-  const uint4* xp = reinterpret_cast<const uint4*>(x + size_t(token) * H + kq * Hq);
-  const uint4* wp = reinterpret_cast<const uint4*>(wg + size_t(expert) * H + kq * Hq);
-  double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
-  const int chunks = Hq / 8;
-  for (int c0 = 0; c0 < chunks; c0 += 4) {                  // four loads of each operand in flight
-    uint4 xv[4], wv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      xv[u] = make_uint4(0, 0, 0, 0); wv[u] = make_uint4(0, 0, 0, 0);
-      if (c0 + u < chunks) { xv[u] = xp[c0 + u]; wv[u] = wp[c0 + u]; }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t xa[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w}, wa[4] = {wv[u].x, wv[u].y, wv[u].z, wv[u].w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf16_to_double(wa[j] & 0xffffu), bf16_to_double(xa[j] & 0xffffu), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf16_to_double(wa[j] >> 16), bf16_to_double(xa[j] >> 16), acc, 0, 0, 0);
+      for (int r = 0; r < 4; ++r) {
+        const int e = e0 + 16 * (v / R) + kq + 4 * r;
+        if (e < E) logits[size_t(t) * E + e] = sum[r];
       }
     }
   }
-  // register r of lane (i, kq) holds row kq + 4 r of the tile (the fp64 variant interleaves the
-  // rows by four), i.e. expert 16 et + kq + 4 r, of token 16 tile + i
-  const int t = blockIdx.x * 16 + i;
-  if (t < T)
+  if (peaks && wave == 0 && lane < 16 * R && t0 + lane < T) {
+    uint32_t m = peak[0][lane];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int e = et * 16 + kq + 4 * r;
-      if (e < E) logits[size_t(t) * E + e] = acc[r];
-    }
+    for (int w = 1; w < NW; ++w) m = max(m, peak[w][lane]);
+    const int eb = int(m >> 7);
+    tok_exp[t0 + lane] = eb == 0 ? 0 : min(60, max(-60, 127 - eb));
+  }
 }
 
 // Top-k and softmax weights from stored logits: one wavefront per token.
@@ -387,8 +385,6 @@ static bool gate_split(const moe_lrc_layer* L, int T) {
   return !gate_many(L, T) && tiled_gate(T, L->cfg.n_experts, L->cfg.hidden) && L->d_logits != nullptr;
 }
 
-bool route_writes_exponents(const moe_lrc_layer* L, int T) { return !gate_many(L, T); }
-
 hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* idx, float* w,
                         _Float16* xh, int32_t* tok_exp, hipStream_t s, const RouteGuess& guess) {
   const moe_lrc_config& c = L->cfg;
@@ -398,13 +394,12 @@ hipError_t launch_route(const moe_lrc_layer* L, const void* x, int T, int32_t* i
       const hipError_t e = launch_route(guess.layer, x, T, guess.idx, guess.w, nullptr, nullptr, s);
       if (e != hipSuccess) return e;
     }
-    const int tt = (T + 15) / 16, et = (c.n_experts + 15) / 16;
     if (gate_many(L, T))
-      hipLaunchKernelGGL(gate_logits_many_kernel, dim3(tt, (et + 3) / 4), dim3(256), 0, s, (const uint16_t*)x, L->d_wg, T, c.hidden,
-                         c.n_experts, L->d_logits);
+      hipLaunchKernelGGL((gate_logits_kernel<4, 2>), dim3((T + 31) / 32, (c.n_experts + 31) / 32), dim3(256), 0, s, (const uint16_t*)x, L->d_wg, T,
+                         c.hidden, c.n_experts, L->d_logits, tok_exp);
     else
-      hipLaunchKernelGGL(gate_logits_kernel<8>, dim3(tt, et), dim3(512), 0, s, (const uint16_t*)x, L->d_wg, T, c.hidden, c.n_experts,
-                         L->d_logits, tok_exp);
+      hipLaunchKernelGGL((gate_logits_kernel<8, 1>), dim3((T + 15) / 16, (c.n_experts + 15) / 16), dim3(512), 0, s, (const uint16_t*)x, L->d_wg, T,
+                         c.hidden, c.n_experts, L->d_logits, tok_exp);
     hipLaunchKernelGGL(topk_kernel, dim3((T + 3) / 4), dim3(256), 0, s, L->d_logits,
                        L->has_bias ? L->d_bias : nullptr, T, c.n_experts, c.top_k, c.renormalize, idx, w);
     return hipGetLastError();

@@ -117,3 +117,25 @@ def test_swiglu_output_near_the_top_of_fp16(amd):
     print(f"[range_h] W1, W3 * 2^{k}: max |h| {top:.3g}, error {err:.2e}")
     assert err <= TOL
     L.close()
+
+
+@pytest.mark.parametrize("hidden,experts,tokens,zipf", [
+    (320, 136, 1100, 0.0),       # ragged tiles of tokens and experts, ten chunks per lane group
+    (64, 130, 3001, 1.0),        # two chunks; three registers of experts in the grouped GEMM, one expert with over 512 rows
+])
+def test_exponents_from_the_tiled_routing(amd, hidden, experts, tokens, zipf):
+    """>= 1024 tokens and >= 128 experts: the tiled routing kernel writes the tokens' pre-scale exponents.  Tokens of
+    very different magnitudes and one of zeros, against the oracle (TOL: the bar of the unscaled inputs)."""
+    cfg = configs.TINY.with_(hidden=hidden, ffn=128, n_experts=experts, tokens=tokens, rank=8, gate_kind="unit", gate_std=1.5, zipf_s=zipf,
+                             name=f"range_tiled_{experts}")
+    layer = fixtures.sample_layer(cfg)
+    L = amd.Layer.from_config(cfg)
+    L.load(layer)
+    ks = np.array([(-1) ** t * (3 * t % 37) for t in range(tokens)])
+    x_bits = _scale_bf16(synth.make_tokens(cfg), ks)
+    x_bits[1] = 0
+    err, ref = _run(amd, cfg, layer, L, x_bits)
+    most = np.bincount(ref["route"]["idx"].reshape(-1)).max()
+    print(f"[{cfg.name}] mixed row scales: {err:.2e}, {most} rows on one expert")
+    assert err <= TOL and (zipf == 0.0 or most > 512)
+    L.close()
