@@ -88,6 +88,65 @@ __device__ inline bool find_chunk(const KArgs& a, int item, Chunk& c) {
   return false;
 }
 
+// The same for a grouped GEMM whose launch is a few rounds of blocks: the whole chunks (128 rows) of all experts
+// first, then the experts' last chunks, those with more rows before those with fewer, so that short blocks fill the end
+// (KArgs::by_length).  W2 alone in this order, whole layer (us): Mixtral shape T = 700 660 -> 647, 1024 902 -> 843, 2048 1565 -> 1548, DeepSeek
+// T = 512 and Qwen3 T = 4096 unchanged.  W1|W3 too: Qwen3 T = 1500 285 -> 278, 4096 553 -> 547; not where an expert's weights are
+// far beyond the L2, which its last chunk then reads once more (Mixtral T = 700 647 -> 668, 2048 1498 -> 1513), nor below 64 rows
+// an expert, whose chunks are nearly alike (DeepSeek T = 512 198 -> 202).
+constexpr int kByLengthRows = 64;
+constexpr int kMaxExperts64 = 4;          // up to 256 experts, 64 to a register
+__device__ inline bool find_gemm_chunk(const KArgs& a, int item, Chunk& c) {
+  if (!a.offsets) return find_chunk<kBM>(a, item, c);
+  const int lane = threadIdx.x & 63;
+  int r0[kMaxExperts64], cnt[kMaxExperts64];
+#pragma unroll
+  for (int g = 0; g < kMaxExperts64; ++g) {
+    const int e = 64 * g + lane;
+    r0[g] = cnt[g] = 0;
+    if (64 * g < a.n_exp && e < a.n_exp) { r0[g] = a.offsets[e]; cnt[g] = a.offsets[e + 1] - r0[g]; }
+  }
+  int base = 0;
+#pragma unroll
+  for (int g = 0; g < kMaxExperts64; ++g) {
+    if (64 * g >= a.n_exp) break;
+    const int n = cnt[g] / kBM;
+    int incl = n;
+#pragma unroll
+    for (int dlt = 1; dlt < 64; dlt *= 2) {
+      const int t = __shfl_up(incl, dlt);
+      if (lane >= dlt) incl += t;
+    }
+    const int total = __shfl(incl, 63);
+    if (item < base + total) {
+      const int first = __ffsll(__ballot(base + incl > item)) - 1;
+      c.e = 64 * g + first;
+      c.r0 = __shfl(r0[g], first); c.cnt = __shfl(cnt[g], first);
+      c.r = (item - base - __shfl(incl - n, first)) * kBM;
+      return true;
+    }
+    base += total;
+  }
+  for (int rp = kBM / 32; rp > 0; --rp) {
+#pragma unroll
+    for (int g = 0; g < kMaxExperts64; ++g) {
+      if (64 * g >= a.n_exp) break;
+      unsigned long long hit = __ballot((cnt[g] % kBM + 31) / 32 == rp);
+      const int total = __popcll(hit);
+      if (item < base + total) {
+        for (int i = item - base; i > 0; --i) hit &= hit - 1;
+        const int first = __ffsll(hit) - 1;
+        c.e = 64 * g + first;
+        c.r0 = __shfl(r0[g], first); c.cnt = __shfl(cnt[g], first);
+        c.r = c.cnt / kBM * kBM;
+        return true;
+      }
+      base += total;
+    }
+  }
+  return false;
+}
+
 typedef float float16_t __attribute__((ext_vector_type(16)));
 constexpr int kRP = kBM / 32;             // 32-row fragments ("row pairs") of a chunk
 
@@ -164,7 +223,14 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   constexpr int DW = 2 * BITS;
   constexpr int NC = Extract<BITS>::kClasses;
   Chunk ch;
-  if (!find_chunk<kBM>(a, blockIdx.y, ch)) return;
+  int item = blockIdx.y, bx = blockIdx.x;
+  if (a.by_xcd) {                          // block b runs on XCD b % 8: chunk 8 i + b % 8, its column blocks one after the other
+                                           // (the launch has a multiple of 8 chunks)
+    const int b = blockIdx.y * gridDim.x + blockIdx.x, j = b >> 3, round = j / (int)gridDim.x;
+    bx = j - round * (int)gridDim.x;
+    item = 8 * round + (b & 7);
+  }
+  if (!(a.by_length ? find_gemm_chunk(a, item, ch) : find_chunk<kBM>(a, item, ch))) return;
   // (found by shuffles, the same in every lane: moved into scalar registers, and with them every base address)
   const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
   const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
@@ -173,7 +239,7 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
   const int q = lane >> 4, c = lane & 15;
   const int tdw = kWave * DW;
-  const int tile0 = (blockIdx.x * WAVES + wave) * kNTW;
+  const int tile0 = (bx * WAVES + wave) * kNTW;
 
   const int code_bytes = a.KS * a.NT * tdw * 4, meta_bytes = a.G * a.NT * kTileN * 4;
   const bool lowrank = a.rank > 0 && __builtin_amdgcn_readfirstlane(d.has_factors) != 0 && a.row_pair != nullptr &&
@@ -956,6 +1022,14 @@ bool xa_staged(const FfnArgs& f, bool dual) {
   return cost5 > 5 * 20480;
 }
 
+// Whether the column blocks of a chunk run on one XCD, whose L2 then holds the chunk's rows once for all of them: where the weights that
+// the chunk meets (`mats` matrices of an expert) fit half of that L2.  Otherwise neighbouring blocks share columns of
+// weights, not rows.  Whole layer, columns dealt over the XCDs -> one XCD (us): Qwen3 shape T = 4096 (1.4 and 0.7 MB) 615 -> 600,
+// DeepSeek T = 512 (1.8 and 0.9 MB) 200 -> 195; Mixtral T = 2048 (51 and 26 MB) 1540 -> 1578.
+bool gemm_by_xcd(const FfnArgs& f, int mats) {
+  return (long long)mats * f.H * f.F * (8 * f.bits + 256 / f.group) / 64 <= 2 << 20;     // bits / 8 + 4 / group bytes a weight
+}
+
 template <int BITS>
 hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   int gs = 0;
@@ -966,8 +1040,8 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.group_shift = gs; a.top_k = f.top_k; a.top_n = f.top_n; a.T = f.T;
   a.rank = f.rank; a.rpad = f.rpad; a.ls = (f.rank + 31) / 32; a.total_rows = f.total_rows;
   const bool comp = f.rank > 0 && f.top_n > 0 && f.row_pair != nullptr;
-  // 128-row chunks: at most one partly filled chunk per expert
-  const int items = f.offsets ? f.total_rows / kBM + f.n_exp : f.n_exp * ((f.T + kBM - 1) / kBM);
+  // 128-row chunks: at most one partly filled chunk per expert (a multiple of 8: by_xcd)
+  const int items = ((f.offsets ? f.total_rows / kBM + f.n_exp : f.n_exp * ((f.T + kBM - 1) / kBM)) + 7) / 8 * 8;
   const size_t glds = size_t(kGemmLdsUnits) * 16;
 
   // (in A) of the rows that take the term (T * top_n in all), zeros for the others
@@ -1025,6 +1099,8 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.in_rt = f.x_rt; a.out_rt = f.h_rt;
   a.KS = padded_k(f.H) / kTileK; a.G = padded_k(f.H) / f.group;
   if (comp) xa(std::true_type{}, f.p13);
+  a.by_xcd = gemm_by_xcd(f, 2);
+  a.by_length = a.by_xcd && f.total_rows >= kByLengthRows * f.n_exp;
   if (f.marks) (void)hipEventRecord(f.marks[0], s);
   if (comp && f.q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
   else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
@@ -1036,14 +1112,17 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.in_rt = f.h_rt; a.out_rt = 0;
   a.KS = padded_k(f.F) / kTileK; a.G = padded_k(f.F) / f.group;
   if (comp) xa(std::false_type{}, f.p2);
+  a.by_xcd = gemm_by_xcd(f, 1);
+  a.by_length = 1;
   if (f.marks) (void)hipEventRecord(f.marks[2], s);
-  // four n-tiles per wavefront use a fragment of activations twice as often as two, but make
-  // blocks twice as large: take the one with fewer (weighted) rounds of blocks over the 256 CUs
+  // Four n-tiles per wavefront use a fragment of activations twice as often as two (with two the LDS reads are the
+  // bound), but make blocks twice as large: two only while four make fewer blocks than there are CUs.  Whole layer, four / two
+  // (us): Mixtral shape T = 1024 (320 blocks of four) 840 / 874, 1500 (432) 1167 / 1197, 2048 (576) 1420 / 1461; 700 (240) 650 / 646;
+  // DeepSeek T = 512 (768) 187 / 196; Qwen3 T = 1500 (1264) 283 / 286, 4096 (2560) 532 / 565.
   // (expected number of chunks: about half of the experts end with a partly filled one)
   const int chunks = std::max(1, f.offsets ? f.total_rows / kBM + (f.n_exp + 1) / 2 : f.n_exp * ((f.T + kBM - 1) / kBM));
-  auto rounds = [&](int ntw) { return (chunks * ((a.NT + kGemmWaves * ntw - 1) / (kGemmWaves * ntw)) + 2 * f.n_cu - 1) / (2 * f.n_cu) * ntw; };
   const bool q3 = comp && f.q3;
-  if (rounds(4) * 100 <= rounds(2) * 108) {
+  if (chunks * ((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves)) >= f.n_cu) {
     if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4, true>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
     else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
   } else {

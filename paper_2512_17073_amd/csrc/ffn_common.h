@@ -69,6 +69,8 @@ struct KArgs {
   const int32_t* row_list;   // grouped (in A) kernel: an expert's rows are the first comp_rows[e] of its range, the
                              // compact rows of the pairs that take the rank-r term; row_list names the routed row
                              // of each (CompactArgs); null: the rows are the routed rows
+  int by_xcd;                // grouped GEMM: the column blocks of a chunk run on one XCD (gemm_by_xcd)
+  int by_length;             // grouped GEMM: whole chunks first (find_gemm_chunk)
 };
 
 // Range of the fp16 operands.  The activations cross the ABI as bf16 (8 exponent bits); the matrix
