@@ -207,6 +207,13 @@ __device__ inline void rank_frag_source(int v, int lane, bool dual, int& m, int&
   else { m = 0; grp = v + 2 * h; }
 }
 
+// Waits for all loads of this wavefront but the last N, then for the block.
+template <int N> __device__ inline void wait_loads_barrier_but() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | (N >> 4 << 14));
+  __syncthreads();
+}
+
 // Codes and metadata of one k-step of a wavefront's two n-tiles.
 template <int BITS, int NM, int NTW> struct Slot2 { Slot<BITS, NM> t[NTW]; };
 
@@ -315,12 +322,15 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   // acc[j][rp]: the 32 x 32 result of pair j and row pair rp; register i of lane l holds, of row
   // 32 rp + l % 32, stream i / 8, column 8 ((i / 4) % 2) + 4 (l / 32) + i % 4 of the stream's n-tile
   float16_t acc[NPAIR][kRP];
+  auto clear = [&](auto FROM_) {             // (those of row pairs FROM ..: unused ones are cleared after the k-steps, and take no registers in them)
 #pragma unroll
-  for (int j = 0; j < NPAIR; ++j)
+    for (int j = 0; j < NPAIR; ++j)
 #pragma unroll
-    for (int rp = 0; rp < kRP; ++rp)
+      for (int rp = decltype(FROM_)::value; rp < kRP; ++rp)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[j][rp][i] = 0.f;
+        for (int i = 0; i < 16; ++i) acc[j][rp][i] = 0.f;
+  };
+  clear(std::integral_constant<int, 0>{});
   const int rp_n = min(kRP, (cnt - r + 31) >> 5);         // row pairs that hold rows of this expert
 
   // the two streams of pair j: (tile slot, projection)
@@ -338,6 +348,7 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   uint32_t sc[kNTW][NM][NC];               // the slot's metadata, one dword per field class
   uint32_t v[NPAIR][2][4];                 // operand registers of the next sub-step, before the swap
   constexpr int PIECES = NPAIR * 4;
+  constexpr int kTwoSlots = BITS == 4 ? 2 : 3;     // row pairs up to which the next k-step's tiles have a slot of their own
   auto unpack_piece = [&](const Slot2<BITS, NM, kNTW>& sl, int s, int piece) {
     const int j = piece / 4, i = piece % 4;
 #pragma unroll
@@ -437,6 +448,29 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   const int steps = a.KS;
   auto k_loop = [&](auto RPN_) {
     constexpr int RPN = decltype(RPN_)::value;
+    // Up to kTwoSlots row pairs leave registers for a second slot: the next k-step's tiles are requested a whole k-step ahead
+    // instead of an eighth (which a cold weight's latency exceeds by far), and the wait in the middle of
+    // the k-step leaves them in flight.
+    if constexpr (RPN <= kTwoSlots) {
+      Slot2<BITS, NM, kNTW> nxt;
+      auto one = [&](int step, Slot2<BITS, NM, kNTW>& now, Slot2<BITS, NM, kNTW>& then) {
+        stage_half<RPN>(a, xs + kHalfUnits, step, 1, rin, so, wave, lane);
+        __builtin_amdgcn_sched_barrier(0);               // (in this order: the wait below counts from the last)
+        fetch(min(step + 1, steps - 1), then);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(RPN_, std::integral_constant<int, 0>{}, now, [] {});
+        wait_loads_barrier_but<kNTW * NM * (BITS == 2 ? 2 : 3)>();
+        if (step + 1 < steps) stage_half<RPN>(a, xs, step + 1, 0, rin, so, wave, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(RPN_, std::integral_constant<int, 1>{}, now, [] {});
+        wait_loads_barrier();
+      };
+      for (int step = 0; step < steps; step += 2) {
+        one(step, cur, nxt);
+        if (step + 1 < steps) one(step + 1, nxt, cur);
+      }
+      return;
+    }
     for (int step = 0; step < steps; ++step) {
       stage_half<RPN>(a, xs + kHalfUnits, step, 1, rin, so, wave, lane);
       __builtin_amdgcn_sched_barrier(0);
@@ -451,9 +485,9 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
     }
   };
   if (rp_n == 4) k_loop(std::integral_constant<int, 4>{});
-  else if (rp_n == 3) k_loop(std::integral_constant<int, 3>{});
-  else if (rp_n == 2) k_loop(std::integral_constant<int, 2>{});
-  else k_loop(std::integral_constant<int, 1>{});
+  else if (rp_n == 3) { k_loop(std::integral_constant<int, 3>{}); clear(std::integral_constant<int, 3>{}); }
+  else if (rp_n == 2) { k_loop(std::integral_constant<int, 2>{}); clear(std::integral_constant<int, 2>{}); }
+  else { k_loop(std::integral_constant<int, 1>{}); clear(std::integral_constant<int, 1>{}); }
 
   // ---- rank steps ----
   // 3-bit pairs: the code dword and the lane's half of the metadata (layout.h) of every stream's unit

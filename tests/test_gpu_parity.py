@@ -781,3 +781,80 @@ def test_h_a2_from_the_fused_launch(amd, hidden, ffn, rank, tokens, experts, kin
     assert err <= TOL and none > 3 * TOL
     assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16))
     Lr.close(); Ls.close()
+
+
+@pytest.mark.parametrize("hidden,rank,tokens,experts,top_k,kind", [
+    (256, 8, 16, 8, 1, "same"),            # one pass of 16 tokens, one factor tile, as many experts as the rule takes
+    (320, 40, 17, 3, 2, "int3"),           # one token in the second pass, an odd number of factor tiles
+    (4096, 128, 64, 8, 2, "same"),         # the largest batch and rank
+    (1088, 64, 49, 16, 2, "bucket"),       # more passes than the grid has: 32 tokens at a time; ranks that differ
+])
+def test_x_a13_of_every_token(amd, hidden, rank, tokens, experts, top_k, kind):
+    """(x A1 | x A3) of small decode batches is made for every token and expert beside the grouping: passes, factor
+    tiles and tokens at which its indices change, against the oracle and, bit for bit, against a staged layer (whose
+    factors arrive later: there the products are made of the routed rows)."""
+    import torch
+    bucket = (64, 0, 16, 40, 0, 8, 64)
+    cfg = configs.TINY.with_(hidden=hidden, ffn=128, n_experts=experts, top_k=top_k, rank=rank, tokens=tokens, bits=2,
+                             name=f"x_a13_{kind}_T{tokens}_r{rank}")
+    layer = fixtures.sample_layer(cfg)
+    for e, ex in enumerate(layer["experts"]):
+        for m in (0, 1, 2):
+            a = ex[m]
+            if kind == "int3":
+                a["Aq"], a["Bq"] = synth.sample_factor_codes(cfg, e, m)
+                a["A"] = a["B"] = None
+            elif kind == "bucket":
+                a["rank"] = r = bucket[(3 * e + 2 * m) % len(bucket)]
+                a["A"] = np.ascontiguousarray(a["A"][:, :r]) if r else None
+                a["B"] = np.ascontiguousarray(a["B"][:r]) if r else None
+    x_bits = synth.make_tokens(cfg)
+    x = amd.bf16_tensor(x_bits)
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    Lr = amd.Layer.from_config(cfg)
+    Ls = amd.Layer.from_config(cfg, residency=amd.STAGED)
+    Lr.load(layer); Ls.load(layer)
+    out_r = Lr.forward(x).clone()
+    out_s = Ls.forward(x).clone()
+    torch.cuda.synchronize()
+    err = orc.rel_frobenius(_to_np(out_r), ref["out"])
+    print(f"\n[{cfg.name}] out rel err {err:.2e}", flush=True)
+    assert err <= TOL
+    assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16))
+    Lr.close(); Ls.close()
+
+
+@pytest.mark.parametrize("hidden,ffn,bits,rank,top_n,kind", [
+    (320, 576, 2, 24, 1, "same"),          # odd numbers of k-steps in both products, two n-tiles of W2 per wavefront
+    (2560, 512, 3, 8, 1, "int3"),          # four n-tiles of W2; two k-steps
+    (512, 256, 4, 40, 1, "same"),          # one k-step in W2, 4 bits (a second slot for two row pairs only)
+    (4096, 1024, 3, 0, 0, "same"),         # an expert's weights beyond half an L2: column blocks dealt over the XCDs
+])
+def test_grouped_gemm_chunks_of_every_length(amd, hidden, ffn, bits, rank, top_n, kind):
+    """Rows per expert given by hand: none, one, one short of a fragment or a chunk, exactly one, one more, several.  The
+    grouped GEMM finds its chunks by length and takes the k loop of their number of row pairs; every row against the oracle."""
+    import torch
+    counts = [0, 1, 31, 32, 33, 64, 65, 96, 97, 127, 128, 129, 256, 353, 512, 0, 288]
+    E, T = len(counts), sum(counts)
+    cfg = configs.TINY.with_(hidden=hidden, ffn=ffn, n_experts=E, top_k=1, top_n=top_n, rank=rank, tokens=T, bits=bits, name=f"chunks_{bits}b_{hidden}")
+    layer = fixtures.sample_layer(cfg)
+    if kind == "int3":
+        for e, ex in enumerate(layer["experts"]):
+            for m in (0, 1, 2):
+                ex[m]["Aq"], ex[m]["Bq"] = synth.sample_factor_codes(cfg, e, m)
+                ex[m]["A"] = ex[m]["B"] = None
+    idx = np.random.default_rng(7).permutation(np.repeat(np.arange(E, dtype=np.int32), counts)).reshape(T, 1)
+    x_bits = synth.make_tokens(cfg)
+    perm = orc.permute(idx, E, cfg.top_n)
+    want = orc.expert_ffn(x_bits, perm, layer["experts"], 1, cfg.top_n, cfg.group)
+    L = amd.Layer.from_config(cfg)
+    L.load(layer)
+    x = amd.bf16_tensor(x_bits)
+    got_counts, offsets, row_pair, _, _ = L.permute(torch.from_numpy(idx).cuda())
+    assert _to_np(got_counts).tolist() == counts
+    y = _to_np(L.expert_ffn(x, offsets, row_pair))
+    assert L.stats()["path"] == 3
+    worst = max(orc.rel_frobenius(y[a:b], want[a:b]) for a, b in zip(perm["offsets"][:-1], perm["offsets"][1:]) if b > a)
+    print(f"\n[{cfg.name}] path {L.stats()['path']}, rel err {orc.rel_frobenius(y, want):.2e}, worst expert {worst:.2e}", flush=True)
+    assert orc.rel_frobenius(y, want) <= TOL and worst <= 2 * TOL      # (an expert of one row has no average over rows)
+    L.close()
