@@ -21,7 +21,9 @@
 //   - the packed weights never touch LDS: each wavefront loads its tiles HBM -> registers, the next
 //     k-step's into the registers of the current one as soon as its last code is unpacked (a second
 //     set of registers does not fit beside 128 accumulators at 3 and 4 bits; at 4 bits the fused kernel and the one
-//     with four n-tiles of W2 per wavefront spill 96 to 108 bytes per lane as it is);
+//     with four n-tiles of W2 per wavefront spill 92 to 100 bytes per lane as it is), chunks of fewer rows into a second
+//     set a whole k-step ahead (a dword of every line of the next k-step's tiles requested ahead, for the L2, was
+//     slower instead of faster on full chunks: Mixtral shape T = 2048 1555 -> 1606 us);
 //   - the activations of half a k-step (128 rows x 128 columns, 32 KB, MFMA operand order) are
 //     double-buffered in LDS: the copy of the next half goes from memory straight to LDS (no
 //     registers) while the current one is multiplied; one barrier per half;
