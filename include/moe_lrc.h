@@ -225,8 +225,10 @@ int moe_lrc_stack_destroy(moe_lrc_stack* stack);
 
 /* One decode step: x [T][hidden] bf16 (device) through every layer, result to out [T][hidden] bf16
  * (device).  layer_inputs (device, [n_layers][T][hidden] bf16, or NULL) receives the input of every
- * layer (layer 0's is x).  Synchronises `stream` once per layer (the read-back of the per-expert
- * counts that decides the copies); all kernels run on `stream`, the copies on the stack's own stream.
+ * layer (layer 0's is x).  out may be x (or overlap it, without MOE_LRC_STACK_RESIDUAL).  The host waits once per
+ * layer, for the per-expert counts that decide the copies (an event behind the launch that writes them: with every
+ * expert in its slot the layer's FFN is queued behind it already, and is queued once more if one turns out to be
+ * missing); all kernels run on `stream`, the copies on the stack's own stream.
  * MOE_LRC_ESTATE if a layer's gate or an expert is not uploaded or T exceeds max_tokens. */
 int moe_lrc_stack_step(moe_lrc_stack* stack, const void* x_bf16, int T, void* out_bf16, void* layer_inputs, void* stream);
 

@@ -742,14 +742,17 @@ int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hi
   auto combine = [&] {
     return launch_combine(L, b + w.y_rows, kblocks > 1 ? (const float*)(b + w.y_part) : nullptr, kblocks, tw, pair_row, y_shared, residual, T, out, s);
   };
-  LRC_HIP(combine());
-  if (ahead_args.desc != nullptr) {            // pooled, launched ahead: now the counts, and once more if something was missing
+  // Pooled, launched ahead: now the counts, and once more if something was missing.  Both the FFN and the residual
+  // read x again then, so a combine that writes over x (a stack of one layer stepped in place) waits for the counts.
+  const bool ahead = ahead_args.desc != nullptr;
+  const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), o0 = reinterpret_cast<uintptr_t>(out), bytes = uintptr_t(T) * L->cfg.hidden * 2;
+  const bool over_x = x0 < o0 + bytes && o0 < x0 + bytes;
+  if (!ahead || !over_x) LRC_HIP(combine());
+  if (ahead) {
     bool complete = false;
     if ((rc = pool_stage(L, T, s, &complete))) return rc;
-    if (!complete) {
-      LRC_HIP(launch_expert_ffn(ahead_args, s));
-      LRC_HIP(combine());
-    }
+    if (!complete) LRC_HIP(launch_expert_ffn(ahead_args, s));
+    if (!complete || over_x) LRC_HIP(combine());
   }
   if (mk) {
     LRC_HIP(hipEventRecord(L->marks[MOE_LRC_N_STAGES], s));

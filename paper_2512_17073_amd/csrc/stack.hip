@@ -15,7 +15,8 @@
 // launched behind P before the host waits: they run while the counts travel and the slots are looked up.
 // If an expert (or a factor pair) turns out to be missing after all, the layer goes on as above and the
 // two are launched a second time (what the first ones made of the absent expert's slot is overwritten; they
-// read inside the pool, whatever it holds).
+// read inside the pool, whatever it holds).  The second ones read the layer's input again: where the output lies over it
+// (one layer, stepped in place) the combine is launched once, when the counts are known.
 // Every kernel of the layers before l has finished when the host chooses slots (P follows them on s), and the
 // kernels launched ahead read slots that layer l's hits pin, so a copy never overwrites a slot whose
 // contents count; the copies ahead spare the slots layer l is about to use.

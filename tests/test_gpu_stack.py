@@ -234,3 +234,33 @@ def test_kernels_launched_ahead_are_repeated_when_an_expert_is_missing(amd, stac
     st.close()
     for L in Lp + Lr:
         L.close()
+
+
+@pytest.mark.parametrize("residual,shift", [(False, 0), (True, 0), (False, 1)])
+def test_one_layer_in_place_when_an_expert_is_missing(amd, stack_layers, residual, shift):
+    """A one-layer stack that writes over its own input: a step whose experts are all in their slots, so that the next
+    one's kernels are launched before the counts are known, then a step that lacks some.  The bits of the same steps
+    out of place.  (shift: the output starts one row before the input, in the same buffer.)"""
+    import torch
+    cfgs, layers = stack_layers
+    La, Lb = _make(amd, cfgs[:1], layers[:1], amd.POOLED), _make(amd, cfgs[:1], layers[:1], amd.POOLED)
+    apart = amd.Stack(La, slots=32, prefetch=False, residual=residual)
+    place = amd.Stack(Lb, slots=32, prefetch=False, residual=residual)
+    late = 0                                                   # steps that miss after one that did not
+    for i, T in enumerate((2, 1, 2, 3, 2)):
+        place.reset()
+        apart.reset()
+        for j in (0, 0, 1, 1, 2):
+            x = amd.bf16_tensor(synth.make_tokens(cfgs[0].with_(seed=700 + 10 * i + j), T))
+            before = place.stats()["misses"]
+            want = apart.step(x).clone()
+            buf = torch.zeros((T + 1, cfgs[0].hidden), dtype=torch.bfloat16, device="cuda")
+            buf[1:] = x
+            got = place.step(buf[1:], out=buf[1 - shift:T + 1 - shift])
+            assert torch.equal(got.view(torch.int16), want.view(torch.int16)), (i, j)
+            late += j > 0 and place.stats()["misses"] > before
+    assert late >= 3
+    for st in (apart, place):
+        st.close()
+    for L in La + Lb:
+        L.close()
