@@ -47,9 +47,8 @@ struct moe_lrc_stack {
   hipStream_t copy = nullptr;
   hipEvent_t ev_ready = nullptr, ev_c0 = nullptr, ev_c1 = nullptr;
   hipEvent_t ev_counts = nullptr;          // P above
-  hipEvent_t ev_copied = nullptr;          // after the last copy issued
   bool copying = false;                    // a copy has been issued that is not known to have ended
-  std::vector<uint8_t> missed;             // [layer] its last call lacked an expert or a factor pair (first: yes)
+  std::vector<uint8_t> missed;             // [layer] its last call lacked an expert or a factor pair, or failed (first: yes)
   std::vector<uint64_t> table_gen;         // [layer] the layer's desc_gen when its expert table was last sent (0: never)
   bool copied_this_step = false, c0_recorded = false;
   uint8_t* ws = nullptr;
@@ -94,14 +93,28 @@ hipError_t note_copy(moe_lrc_stack* S) {
   return hipSuccess;
 }
 
+void evict(moe_lrc_stack* S, int slot) {
+  auto& sl = S->slots[slot];
+  if (sl.layer >= 0) S->where[sl.layer][sl.expert] = -1;
+  sl = moe_lrc_stack::Slot{};
+}
+
+int copy_weights(moe_lrc_stack* S, int li, int e, int slot) {
+  moe_lrc_layer* L = S->layers[li];
+  LRC_HIP(note_copy(S));
+  LRC_HIP(hipMemcpyAsync(slot_w_ptr(S, slot), L->h_w + L->w_off[e], L->routed.w_bytes, hipMemcpyHostToDevice, S->copy));
+  S->st.bytes_h2d += L->routed.w_bytes;
+  return MOE_LRC_OK;
+}
+
 // brings (layer li, expert e) into `slot` on the copy stream: the packed weights unless they are there, the factors if wanted
+// (a slot whose weights could not be queued is empty again: no later step may find the expert there)
 int fill_slot(moe_lrc_stack* S, int li, int e, int slot, bool weights, bool factors) {
   moe_lrc_layer* L = S->layers[li];
   const BlobLayout& b = L->routed;
   if (weights) {
-    LRC_HIP(note_copy(S));
-    LRC_HIP(hipMemcpyAsync(slot_w_ptr(S, slot), L->h_w + L->w_off[e], b.w_bytes, hipMemcpyHostToDevice, S->copy));
-    S->st.bytes_h2d += b.w_bytes;
+    const int rc = copy_weights(S, li, e, slot);
+    if (rc) { evict(S, slot); return rc; }
   }
   if (factors && b.f_bytes) {
     LRC_HIP(note_copy(S));
@@ -123,13 +136,6 @@ int fill_slot(moe_lrc_stack* S, int li, int e, int slot, bool weights, bool fact
   }
   return MOE_LRC_OK;
 }
-
-void evict(moe_lrc_stack* S, int slot) {
-  auto& sl = S->slots[slot];
-  if (sl.layer >= 0) S->where[sl.layer][sl.expert] = -1;
-  sl = moe_lrc_stack::Slot{};
-}
-
 
 // Entry e of the layer's expert table as its slots stand (an expert without a slot, which no kernel whose
 // output counts touches, points at slot 0).
@@ -178,7 +184,7 @@ int pool_begin(moe_lrc_layer* L, bool* ahead) {
   if (!S) return set_error(MOE_LRC_ESTATE, "a pooled layer runs through moe_lrc_stack_step only");
   if (S->missed[L->pool_index]) return MOE_LRC_OK;
   if (S->copying) {
-    const hipError_t e = hipEventQuery(S->ev_copied);
+    const hipError_t e = hipStreamQuery(S->copy);
     if (e == hipErrorNotReady) { (void)hipGetLastError(); return MOE_LRC_OK; }
     LRC_HIP(e);
     S->copying = false;
@@ -197,6 +203,7 @@ int pool_stage(moe_lrc_layer* L, int T, hipStream_t s, bool* complete) {
   const moe_lrc_config& c = L->cfg;
   const int E = c.n_experts, li = L->pool_index;
   moe_lrc_layer* next = pool_next(L);
+  S->missed[li] = 1;                         // (until this call has queued everything)
   LRC_HIP(hipEventSynchronize(S->ev_counts));
   fill_algorithmic_stats(L, L->h_stat);
   const int32_t* rows = L->h_stat + 2;
@@ -234,13 +241,13 @@ int pool_stage(moe_lrc_layer* L, int T, hipStream_t s, bool* complete) {
     const int rc = fill_slot(S, li, e, slot, miss, want_f);
     if (rc) return rc;
   }
-  S->missed[li] = !*complete;
   if (S->copying) {                          // (copies of this call, or ahead of it)
     LRC_HIP(hipEventRecord(S->ev_ready, S->copy));
     LRC_HIP(hipStreamWaitEvent(s, S->ev_ready, 0));
   }
   // (the host waited for P: the last upload, before it on s, no longer reads the table's host copy)
   if (!table_sent(S, L)) {
+    S->table_gen[li] = 0;
     for (int e = 0; e < E; ++e) S->h_desc[size_t(li) * S->max_e + e] = table_entry(S, L, e);
     LRC_HIP(hipMemcpyAsync(L->d_desc, S->h_desc + size_t(li) * S->max_e, sizeof(ExpertDesc) * E, hipMemcpyHostToDevice, s));
     S->table_gen[li] = L->desc_gen;
@@ -276,7 +283,7 @@ int pool_stage(moe_lrc_layer* L, int T, hipStream_t s, bool* complete) {
       if (rc) return rc;
     }
   }
-  if (S->copying) LRC_HIP(hipEventRecord(S->ev_copied, S->copy));
+  S->missed[li] = !*complete;
   return MOE_LRC_OK;
 }
 
@@ -299,7 +306,6 @@ int moe_lrc_stack_destroy(moe_lrc_stack* S) {
   if (S->copy) (void)hipStreamDestroy(S->copy);
   if (S->ev_ready) (void)hipEventDestroy(S->ev_ready);
   if (S->ev_counts) (void)hipEventDestroy(S->ev_counts);
-  if (S->ev_copied) (void)hipEventDestroy(S->ev_copied);
   if (S->ev_c0) (void)hipEventDestroy(S->ev_c0);
   if (S->ev_c1) (void)hipEventDestroy(S->ev_c1);
   delete S;
@@ -363,7 +369,6 @@ int moe_lrc_stack_create(moe_lrc_layer* const* layers, int n_layers, int slots, 
   STK_TRY(hipStreamCreateWithFlags(&S->copy, hipStreamNonBlocking));
   STK_TRY(hipEventCreateWithFlags(&S->ev_ready, hipEventDisableTiming));
   STK_TRY(hipEventCreateWithFlags(&S->ev_counts, hipEventDisableTiming));
-  STK_TRY(hipEventCreateWithFlags(&S->ev_copied, hipEventDisableTiming));
   STK_TRY(hipEventCreate(&S->ev_c0));
   STK_TRY(hipEventCreate(&S->ev_c1));
 #undef STK_TRY
