@@ -1061,9 +1061,13 @@ bool xa_staged(const FfnArgs& f, bool dual) {
 // Whether the column blocks of a chunk run on one XCD, whose L2 then holds the chunk's rows once for all of them: where the weights that
 // the chunk meets (`mats` matrices of an expert) fit half of that L2.  Otherwise neighbouring blocks share columns of
 // weights, not rows.  Whole layer, columns dealt over the XCDs -> one XCD (us): Qwen3 shape T = 4096 (1.4 and 0.7 MB) 615 -> 600,
-// DeepSeek T = 512 (1.8 and 0.9 MB) 200 -> 195; Mixtral T = 2048 (51 and 26 MB) 1540 -> 1578.
+// DeepSeek T = 512 (1.8 and 0.9 MB) 200 -> 195; Mixtral T = 2048 (51 and 26 MB) 1540 -> 1578.  Above the line it is no one thing:
+// W1|W3 alone of hidden = FFN = 3072 at 4 bits (10.6 MB), T = 1024 199 -> 221, T = 2048 343 -> 332; 4096 x 7168 at 3 bits (26 MB),
+// T = 2048 780 -> 793; hidden = FFN = 2048 at 3 bits (3.7 MB) 311 -> 301.
+// Routed experts only: shared experts are few chunks, which would leave XCDs without work, and run beside the routed ones.  64 routed experts
+// (Top-1) and one shared, 2048 x 1408, columns dealt / one XCD: T = 128 144 / 156, 256 132 / 144, 768 155 / 155, 1500 171 / 185.
 bool gemm_by_xcd(const FfnArgs& f, int mats) {
-  return (long long)mats * f.H * f.F * (8 * f.bits + 256 / f.group) / 64 <= 2 << 20;     // bits / 8 + 4 / group bytes a weight
+  return f.offsets != nullptr && (long long)mats * f.H * f.F * (8 * f.bits + 256 / f.group) / 64 <= 2 << 20;     // bits / 8 + 4 / group bytes a weight
 }
 
 template <int BITS>
@@ -1076,8 +1080,9 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.group_shift = gs; a.top_k = f.top_k; a.top_n = f.top_n; a.T = f.T;
   a.rank = f.rank; a.rpad = f.rpad; a.ls = (f.rank + 31) / 32; a.total_rows = f.total_rows;
   const bool comp = f.rank > 0 && f.top_n > 0 && f.row_pair != nullptr;
-  // 128-row chunks: at most one partly filled chunk per expert (a multiple of 8: by_xcd)
-  const int items = ((f.offsets ? f.total_rows / kBM + f.n_exp : f.n_exp * ((f.T + kBM - 1) / kBM)) + 7) / 8 * 8;
+  // 128-row chunks: at most one partly filled chunk per expert (by_xcd takes a multiple of 8)
+  const int max_chunks = f.offsets ? f.total_rows / kBM + f.n_exp : f.n_exp * ((f.T + kBM - 1) / kBM);
+  auto items = [&] { return a.by_xcd ? (max_chunks + 7) / 8 * 8 : max_chunks; };
   const size_t glds = size_t(kGemmLdsUnits) * 16;
 
   // (in A) of the rows that take the term (T * top_n in all), zeros for the others
@@ -1138,8 +1143,8 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.by_xcd = gemm_by_xcd(f, 2);
   a.by_length = a.by_xcd && f.total_rows >= kByLengthRows * f.n_exp;
   if (f.marks) (void)hipEventRecord(f.marks[0], s);
-  if (comp && f.q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
-  else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
+  if (comp && f.q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
+  else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
   if (f.marks) (void)hipEventRecord(f.marks[1], s);
   }
   if (which & 2) {
@@ -1159,11 +1164,11 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   const int chunks = std::max(1, f.offsets ? f.total_rows / kBM + (f.n_exp + 1) / 2 : f.n_exp * ((f.T + kBM - 1) / kBM));
   const bool q3 = comp && f.q3;
   if (chunks * ((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves)) >= f.n_cu) {
-    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4, true>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
-    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
+    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4, true>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
+    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 4>), dim3((a.NT + 4 * kGemmWaves - 1) / (4 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
   } else {
-    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
-    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items), dim3(64 * kGemmWaves), glds, s, a);
+    if (q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
+    else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, false, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
   }
   if (f.marks) (void)hipEventRecord(f.marks[3], s);
   }
