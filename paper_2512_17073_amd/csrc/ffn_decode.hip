@@ -49,7 +49,8 @@ using namespace dec;
 // Q3: some factor pair of the layer is held at 3 bits (layout.h): a rank step of such a pair brings
 // the unit's code dword in the slot's metadata register and the lane's half of the unit's metadata in
 // its first four code registers, and is dequantized into the fp16 unit before it is used.
-template <int BITS, bool DUAL, int MT, bool Q3>
+// HA: (h A2) is left by the fused projection's blocks and added up by those of W2 (KArgs::ha).
+template <int BITS, bool DUAL, int MT, bool Q3, bool HA>
 __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int e, const int r0, const int cnt,
                                             const int b, const int G, const int slots) {
   constexpr int NS = kStreams;
@@ -96,7 +97,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
   const int LS = max(LSm[0], LSm[1]);
   const float lam[2] = {d.inv_lambda[DUAL ? 0 : 2], d.inv_lambda[DUAL ? 1 : 2]};
   // 16-column tiles of (h A2) that this launch makes (fused projection) or adds up (W2)
-  const int ht = lowrank && a.ha != nullptr ? (min(__builtin_amdgcn_readfirstlane(d.rank[2]), a.rank) + 15) / 16 : 0;
+  const int ht = HA && lowrank ? (min(__builtin_amdgcn_readfirstlane(d.rank[2]), a.rank) + 15) / 16 : 0;
   const uint32_t bf_bytes_max = uint32_t(a.NT) * a.ls * 1024;
 
   __amdgpu_buffer_rsrc_t code_rs[NS], meta_rs[NS], bf_rs[NS], bc_rs[NS];
@@ -134,7 +135,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
   // on) are copied behind those fragments at the start of the first pass, where they fit; else read when used.
   const bool q3_a2 = Q3 && ((__builtin_amdgcn_readfirstlane(d.q3) >> 2) & 1) != 0;
   const int u0 = t0 / 2, n_u = (t1 - 1) / 2 - u0 + 1, g0 = t0 / 4, n_q = ((t1 - 1) / 4 - g0) / 4 + 1;
-  const bool a2_early = DUAL && ht > 0 && !p_late && p_frags * 64 + (q3_a2 ? (n_u + n_q) * 16 : n_u * 64) * ht <= kSpareUnits;
+  const bool a2_early = HA && DUAL && ht > 0 && !p_late && p_frags * 64 + (q3_a2 ? (n_u + n_q) * 16 : n_u * 64) * ht <= kSpareUnits;
 
   for (int r = 0; r < cnt; r += 16 * MT) {
     // every pass computes all MT row tiles (a last pass with fewer rows computes columns nobody stores)
@@ -208,7 +209,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     // The first kHaFirst parts of the first rank step are requested before anything else of the pass, the sums go
     // to LDS as the fragments p_issue would copy.
     constexpr int TPO = 8 / MT, kHaFirst = BITS == 4 ? 2 : 4;
-    const bool joined = !DUAL && a.ha != nullptr;      // (its fragments always fit behind the activations)
+    constexpr bool joined = HA && !DUAL;      // (its fragments always fit behind the activations)
     float4_t part[kHaFirst];
     int pair_of_row = 0;
     float lam2 = 0.f;
@@ -217,16 +218,14 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     const int hj = hth & (TPO - 1), hcol = (hth / TPO) & 7, hrow = hth / (8 * TPO);
     int ha_lo, ha_hi;
     ha_share(kb, gridDim.z, slots, ha_lo, ha_hi);
-    if constexpr (!DUAL) {
-      if (joined) {
-        const KernArgs ka = kern_args();
-        const int row = r0 + min(r + hrow, cnt - 1);
+    if constexpr (joined) {
+      const KernArgs ka = kern_args();
+      const int row = r0 + min(r + hrow, cnt - 1);
 #pragma unroll
-        for (int i = 0; i < kHaFirst; ++i)
-          part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, ka->ls * 32, 4 * hcol));
-        pair_of_row = ka->row_pair[row];
-        lam2 = ka->desc[e].xa_scale[2];
-      }
+      for (int i = 0; i < kHaFirst; ++i)
+        part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, ka->ls * 32, 4 * hcol));
+      pair_of_row = ka->row_pair[row];
+      lam2 = ka->desc[e].xa_scale[2];
     }
     auto p_join = [&]() {
       const KernArgs ka = kern_args();
@@ -280,7 +279,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     int row_se[MT];                           // (the rows' exponents for the end of the pass)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) row_se[mt] = a.row_exp[(a.offsets ? r0 : 0) + min(r + 16 * mt + c, cnt - 1)];
-    if (DUAL && a2_early && r == 0) {
+    if (a2_early && r == 0) {
       uint4* dst = p_lds + p_frags * 64;
       auto lds = [](uint4* p) { return reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p)); };
       for (int f = wave; f < n_u * ht; f += kWaves) {
@@ -298,9 +297,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     Slot<BITS, NS> ring[RING];
 #pragma unroll
     for (int i = 0; i < RING; ++i) fetch(ring[i]);
-    if constexpr (!DUAL) {
-      if (joined) p_join();
-    }
+    if constexpr (joined) p_join();
     wait_loads_barrier();
 
     float4_t acc[TS][MT][NS];
@@ -451,6 +448,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     const KernArgs ka = kern_args();          // (what the end of a pass needs is read again: it would not fit the scalar registers until here)
     int ln = lane, tn = th, hn = ht, gn = grp;
     asm volatile("" : "+v"(ln), "+v"(tn), "+s"(hn), "+s"(gn));    // (addresses and conditions are made here, not kept in registers through the pass)
+    if (!(HA && DUAL) && kwi != 0) continue;  // (the next pass starts with a barrier every wavefront reaches)
     // ---- epilogue: lane holds output columns 16*tile + 4*q .. +3 of token column c ----
     half4_t hs[TS][MT];                       // (this wavefront's h, for (h A2): zero without a unit)
 #pragma unroll
@@ -501,7 +499,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       }
     }
     // (h A2) over the block's columns: the wavefronts' sums meet in LDS, in group order
-    if (DUAL && hn > 0) {
+    if (HA && DUAL && hn > 0) {
       float4_t* red = reinterpret_cast<float4_t*>(xs);
       __syncthreads();                       // (everyone is done with the activations and the fragments)
       if (kwi == 0) {
@@ -562,7 +560,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
   }
 }
 
-template <int BITS, bool DUAL, bool Q3>
+template <int BITS, bool DUAL, bool Q3, bool HA>
 __global__ __launch_bounds__(64 * kWaves, 4) void qgemm_decode_kernel(KArgs a) {
   extern __shared__ uint4 xs[];
   int e = blockIdx.y, b = blockIdx.x, G = gridDim.x, r0, cnt, slots = 0;
@@ -570,15 +568,15 @@ __global__ __launch_bounds__(64 * kWaves, 4) void qgemm_decode_kernel(KArgs a) {
     const PlanEntry* pe = reinterpret_cast<const PlanEntry*>(a.plan) + blockIdx.x;
     e = __builtin_amdgcn_readfirstlane(pe->e); b = __builtin_amdgcn_readfirstlane(pe->b); G = __builtin_amdgcn_readfirstlane(pe->G);
     r0 = __builtin_amdgcn_readfirstlane(pe->r0); cnt = __builtin_amdgcn_readfirstlane(pe->cnt);
-    slots = __builtin_amdgcn_readfirstlane(pe->slots);
+    if constexpr (HA && !DUAL) slots = __builtin_amdgcn_readfirstlane(pe->slots);
     if (e < 0) return;
   } else {
     r0 = a.offsets ? a.offsets[e] : e * a.T;
     cnt = a.offsets ? a.offsets[e + 1] - r0 : a.T;
   }
   if (cnt == 0) return;
-  if (cnt <= 16) decode_body<BITS, DUAL, 1, Q3>(a, xs, e, r0, cnt, b, G, slots);
-  else decode_body<BITS, DUAL, 2, Q3>(a, xs, e, r0, cnt, b, G, slots);
+  if (cnt <= 16) decode_body<BITS, DUAL, 1, Q3, HA>(a, xs, e, r0, cnt, b, G, slots);
+  else decode_body<BITS, DUAL, 2, Q3, HA>(a, xs, e, r0, cnt, b, G, slots);
 }
 
 template <bool DUAL>
@@ -647,8 +645,12 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   // (h A2) made by the fused launch's blocks themselves
   const bool ha = comp && decode_ha(f, which);
   a.ha = ha ? f.ha : nullptr;
-  auto k13 = q3 ? qgemm_decode_kernel<BITS, true, true> : qgemm_decode_kernel<BITS, true, false>;
-  auto k2 = q3 ? qgemm_decode_kernel<BITS, false, true> : qgemm_decode_kernel<BITS, false, false>;
+  auto pick = [&](auto DUAL_) {
+    constexpr bool DUAL = decltype(DUAL_)::value;
+    if (ha) return q3 ? qgemm_decode_kernel<BITS, DUAL, true, true> : qgemm_decode_kernel<BITS, DUAL, false, true>;
+    return q3 ? qgemm_decode_kernel<BITS, DUAL, true, false> : qgemm_decode_kernel<BITS, DUAL, false, false>;
+  };
+  auto k13 = pick(std::true_type{}), k2 = pick(std::false_type{});
 
   if (which & 1) {
     // W1 | W3 with the SwiGLU epilogue
@@ -726,20 +728,25 @@ void decode_plan_specs(const FfnArgs& f, int which, PlanSpec& p13, PlanSpec& p2)
   }
 }
 
-hipError_t decode_init_device() {
-  // 128 KB of activations + 32 KB of (in A) fragments = all 160 KB of a CU
-  const void* fns[12] = {
-      reinterpret_cast<const void*>(&qgemm_decode_kernel<2, true, false>), reinterpret_cast<const void*>(&qgemm_decode_kernel<2, false, false>),
-      reinterpret_cast<const void*>(&qgemm_decode_kernel<3, true, false>), reinterpret_cast<const void*>(&qgemm_decode_kernel<3, false, false>),
-      reinterpret_cast<const void*>(&qgemm_decode_kernel<4, true, false>), reinterpret_cast<const void*>(&qgemm_decode_kernel<4, false, false>),
-      reinterpret_cast<const void*>(&qgemm_decode_kernel<2, true, true>), reinterpret_cast<const void*>(&qgemm_decode_kernel<2, false, true>),
-      reinterpret_cast<const void*>(&qgemm_decode_kernel<3, true, true>), reinterpret_cast<const void*>(&qgemm_decode_kernel<3, false, true>),
-      reinterpret_cast<const void*>(&qgemm_decode_kernel<4, true, true>), reinterpret_cast<const void*>(&qgemm_decode_kernel<4, false, true>)};
+template <int BITS> static hipError_t decode_init_bits() {
+  const void* fns[8] = {
+      reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, true, false, false>), reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, false, false, false>),
+      reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, true, true, false>), reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, false, true, false>),
+      reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, true, false, true>), reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, false, false, true>),
+      reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, true, true, true>), reinterpret_cast<const void*>(&qgemm_decode_kernel<BITS, false, true, true>)};
   for (const void* fn : fns) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (kLdsUnits + kSpareUnits) * 16);
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (kLdsUnits + kSpareUnits) * 16);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t decode_init_device() {
+  // 128 KB of activations + 32 KB of (in A) fragments = all 160 KB of a CU
+  hipError_t e = decode_init_bits<2>();
+  if (e == hipSuccess) e = decode_init_bits<3>();
+  if (e == hipSuccess) e = decode_init_bits<4>();
+  return e;
 }
 
 hipError_t launch_decode_ffn(const FfnArgs& f, hipStream_t s, int which) {
