@@ -350,7 +350,10 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   uint32_t sc[kNTW][NM][NC];               // the slot's metadata, one dword per field class
   uint32_t v[NPAIR][2][4];                 // operand registers of the next sub-step, before the swap
   constexpr int PIECES = NPAIR * 4;
-  constexpr int kTwoSlots = BITS == 4 ? 2 : 3;     // row pairs up to which the next k-step's tiles have a slot of their own
+  // Row pairs up to which the next k-step's tiles have a slot of their own.  At 4 bits one: with two the registers run out
+  // (whole layer, second slot up to two / one row pairs, us: Mixtral shape T = 200 369 / 354, DeepSeek shape
+  // T = 512 220 / 210, 700 248 / 236, Qwen3 shape T = 4096 575 / 565; with none 352, 206, 234 and 577).
+  constexpr int kTwoSlots = BITS == 4 ? 1 : 3;
   auto unpack_piece = [&](const Slot2<BITS, NM, kNTW>& sl, int s, int piece) {
     const int j = piece / 4, i = piece % 4;
 #pragma unroll
