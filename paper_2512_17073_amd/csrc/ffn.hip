@@ -277,6 +277,9 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
 
   // The packed tiles of a k-step: one 32-bit lane offset per kind of load, everything else scalar.
   // (An n-tile past the last one is clamped: its columns are never stored.)
+  // (kFetchLoads: the loads of one fetch, which the wait in the middle of a k-step with two slots leaves in flight.)
+  constexpr int kCodeLoads = BITS == 2 ? 1 : 2, kTileLoads = kCodeLoads + 1;    // of a tile: codes, then a dword of metadata
+  constexpr int kFetchLoads = kNTW * NM * kTileLoads;
   const int lane16 = lane * 16, lane1 = 1024 + lane * (BITS == 3 ? 8 : 16);
   auto fetch = [&](int step, Slot2<BITS, NM, kNTW>& sl) {
 #pragma unroll
@@ -286,16 +289,18 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         Slot<BITS, NM>& s1 = sl.t[t];
-        const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], lane16, tile_off, 0);
-        s1.cw[m][0] = v0[0]; s1.cw[m][1] = v0[1]; s1.cw[m][2] = v0[2]; s1.cw[m][3] = v0[3];
-        if constexpr (BITS == 3) {
-          const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(code_rs[m], lane1, tile_off, 0);
-          s1.cw[m][4] = v1[0]; s1.cw[m][5] = v1[1];
-        } else if constexpr (BITS == 4) {
-          const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], lane1, tile_off, 0);
-          s1.cw[m][4] = v1[0]; s1.cw[m][5] = v1[1]; s1.cw[m][6] = v1[2]; s1.cw[m][7] = v1[3];
-        }
-        s1.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(meta_rs[m], meta_lane, meta_off, 0);
+        static_for<kTileLoads>([&](auto I) {               // (one load each)
+          constexpr int i = decltype(I)::value;
+          if constexpr (i == kCodeLoads) {
+            s1.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(meta_rs[m], meta_lane, meta_off, 0);
+          } else if constexpr (i == 1 && BITS == 3) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(code_rs[m], lane1, tile_off, 0);
+            s1.cw[m][4] = v[0]; s1.cw[m][5] = v[1];
+          } else {
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], i == 0 ? lane16 : lane1, tile_off, 0);
+            s1.cw[m][4 * i] = v[0]; s1.cw[m][4 * i + 1] = v[1]; s1.cw[m][4 * i + 2] = v[2]; s1.cw[m][4 * i + 3] = v[3];
+          }
+        });
       }
     }
   };
@@ -464,7 +469,7 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
         fetch(min(step + 1, steps - 1), then);
         __builtin_amdgcn_sched_barrier(0);
         compute(RPN_, std::integral_constant<int, 0>{}, now, [] {});
-        wait_loads_barrier_but<kNTW * NM * (BITS == 2 ? 2 : 3)>();
+        wait_loads_barrier_but<kFetchLoads>();
         if (step + 1 < steps) stage_half<RPN>(a, xs, step + 1, 0, rin, so, wave, lane);
         __builtin_amdgcn_sched_barrier(0);
         compute(RPN_, std::integral_constant<int, 1>{}, now, [] {});

@@ -1,0 +1,48 @@
+"""The grouped GEMM's k-steps with two slots of weights wait for the copy of the activations and leave the weights requested
+after it in flight: in the built code the loads between the two are exactly as many as the wait leaves out."""
+import os
+import re
+import struct
+import subprocess
+
+import paper_2512_17073_amd as amd
+from paper_2512_17073_amd import build, binding
+
+LLVM = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build._hipcc()))), "llvm", "bin")
+
+
+def _gfx950_code(tmp_path):
+    amd.lib()                                             # (raises if the library is not built)
+    fat = str(tmp_path / "fat")
+    subprocess.run([os.path.join(LLVM, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat, binding.LIB_PATH, str(tmp_path / "copy")], check=True)
+    data = open(fat, "rb").read()
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data):       # one bundle per translation unit
+        at = m.start() + 32
+        for _ in range(struct.unpack_from("<Q", data, m.start() + 24)[0]):
+            off, size, n = struct.unpack_from("<QQQ", data, at)
+            code = data[m.start() + off:m.start() + off + size]
+            if b"gfx950" in data[at + 24:at + 24 + n] and b"qgemm_tile_kernel" in code:
+                return code
+            at += 24 + n
+    raise AssertionError("no gfx950 code with the grouped GEMM in the library")
+
+
+def test_waits_leave_exactly_the_next_weights_in_flight(tmp_path):
+    co = tmp_path / "ffn.co"
+    co.write_bytes(_gfx950_code(tmp_path))
+    text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(co)], capture_output=True, text=True, check=True).stdout
+    found = {}
+    for name, body in re.findall(r"^[0-9a-f]+ <(\S*qgemm_tile_kernel\S*)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", text, re.S | re.M):
+        loads = None                                      # weight loads since the last copy to LDS (None: not known)
+        lines = [ln.split("//")[0].strip() for ln in body.splitlines()]
+        for i, ln in enumerate(lines):
+            wait = re.fullmatch(r"s_waitcnt vmcnt\((\d+)\)", ln)
+            if re.match(r"buffer_load_.*\blds$", ln):
+                loads = 0
+            elif loads is not None and re.match(r"(buffer|global|flat|scratch)_", ln):
+                loads += 1
+            elif wait and int(wait[1]) > 0 and any(x.startswith("s_barrier") for x in lines[i + 1:i + 3]):
+                assert loads == int(wait[1]), (name, ln, loads)
+                found[name] = found.get(name, 0) + 1
+    # 2, 3 and 4 bits; W1|W3, W2 in two and in four n-tiles; with and without 3-bit factor pairs
+    assert len(found) == 18 and min(found.values()) >= 2, found
