@@ -245,7 +245,7 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   a.plan = reinterpret_cast<int32_t*>(ws + w.plan);
   a.live13 = L->live13; a.live2 = L->live2;
   a.y_rows = y_rows; a.ksplit13 = L->ksplit13; a.ksplit2 = L->ksplit2; a.total_rows = T * c.top_k;
-  a.n_cu = L->n_cu;
+  a.n_cu = L->n_cu; a.n_shared = c.n_shared;
   a.q3 = L->n_q3 > 0;
   a.row_exp = reinterpret_cast<int32_t*>(ws + w.row_exp);
   a.tok_exp = tok_exp;

@@ -174,7 +174,7 @@ LRC_HD int staged_row(int rin, int r, int mt, int rowl, int cnt, int in_rt) {
 // a 16-column factor tile rt of A2 meets the 16 columns of n-tile `tile` as the operand of a 16x16x16
 // product, so lane (q, c) reads inputs 16 tile + 4 q .. + 3 of column 16 rt + c: half (q % 2) of the packed
 // unit (tile / 2) of lane (2 (tile % 2) + q / 2, c).  Index of that half in units of four values.
-constexpr int kHaRank = 64;
+constexpr int kHaRank = 32;                // (one rank step: the part sums of a row are 128 bytes)
 LRC_HD uint32_t ha_operand(int rt, int tile, int lane, int F) {
   const int q = lane >> 4, c = lane & 15;
   return ((uint32_t(rt) * (F / 32) + tile / 2) * kWave + (2 * (tile & 1) + (q >> 1)) * 16 + c) * 2 + (q & 1);
@@ -184,7 +184,7 @@ LRC_HD int ha_slots(int G, int NT) { return G < NT ? G : NT; }
 LRC_HD int ha_slot(int b, int t0, int G, int NT) { return G <= NT ? b : t0; }
 // The part sums K-block kb of kblocks takes: [lo, hi).
 LRC_HD void ha_share(int kb, int kblocks, int slots, int& lo, int& hi) { lo = kb * slots / kblocks; hi = (kb + 1) * slots / kblocks; }
-LRC_HD size_t ha_part(int slot, int total_rows, int row, int pitch, int col) { return (size_t(slot) * total_rows + row) * pitch + col; }
+LRC_HD size_t ha_part(int slot, int total_rows, int row, int col) { return (size_t(slot) * total_rows + row) * kHaRank + col; }
 
 // LDS unit of staged activation fragment (row tile mt, k-step kl of the phase, sub-step s).
 LRC_HD int act_frag_unit(int mt, int kl, int s, int KP) { return ((mt * KP + kl) * 8 + s) * 64; }

@@ -59,7 +59,7 @@ struct KArgs {
   int kb_steps;              // decode flavour: k-steps per K-block (grid.z blocks split K; KS if one)
   float* partial;            // decode flavour, more than one K-block: fp32 partial outputs [kb][rows][N]; grouped (in A)
                              // with staged rows: K-block sums [kb][compact row][projections * ls * 32]
-  float* ha;                 // decode flavour, or null: part sums of (h A2) [slot][row][ls * 32] that the fused projection's
+  float* ha;                 // decode flavour, or null: part sums of (h A2) [slot][row][32] that the fused projection's
                              // blocks leave and the W2 launch adds up (decode_index.h, ha_*), instead of xa_rows_kernel's p
   const int32_t* plan;       // decode flavour: null (grid = blocks per expert x experts), or the block table
                              // (PlanEntry per block, plan.h)

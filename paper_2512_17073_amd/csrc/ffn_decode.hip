@@ -18,10 +18,10 @@
 //     ceil(r / 32) more steps per stream on the B factor's fp16 units against (in A), which
 //     the launches before have left in global memory; the rank is the projection's own (Section 3.1
 //     allocates a rank per expert matrix): a stream with fewer rank steps reads zeros past its factor;
-//   - (h A2) of ranks up to 64 is made at the end of the fused projection's blocks, from the h they hold in
+//   - (h A2) of ranks up to 32 is made at the end of the fused projection's blocks, from the h they hold in
 //     registers: each block's columns are a share of its long K, and the W2 blocks add the shares of
-//     their K-block up while their activations arrive.  (A launch between the two reads h and A2 again:
-//     6 to 11 us; the shares cost the two kernels 3 to 4 together.)  Larger ranks keep that launch;
+//     their K-block up while their activations arrive, where that is less than a launch between the two costs, which
+//     reads h and A2 again (decode_ha).  Larger ranks and many rows over few experts keep that launch;
 //   - a long K (W2) is split into K-blocks (grid.z) of one or two phases whose fp32 partial outputs
 //     the combine (or reduce_kernel, for the stand-alone call) adds in a fixed order.
 #include <algorithm>
@@ -206,7 +206,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     };
 
     // (h A2) from the part sums of the fused projection's blocks: TPO threads share four columns of a row.
-    // The first kHaFirst parts of the first rank step are requested before anything else of the pass, the sums go
+    // The first kHaFirst parts are requested before anything else of the pass, the sums go
     // to LDS as the fragments p_issue would copy.
     constexpr int TPO = 8 / MT, kHaFirst = BITS == 4 ? 2 : 4;
     constexpr bool joined = HA && !DUAL;      // (its fragments always fit behind the activations)
@@ -223,35 +223,29 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       const int row = r0 + min(r + hrow, cnt - 1);
 #pragma unroll
       for (int i = 0; i < kHaFirst; ++i)
-        part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, ka->ls * 32, 4 * hcol));
+        part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, 4 * hcol));
       pair_of_row = ka->row_pair[row];
       lam2 = ka->desc[e].xa_scale[2];
     }
     auto p_join = [&]() {
+      if (LS == 0) return;                     // (ranks up to kHaRank: one rank step)
       const KernArgs ka = kern_args();
-      const int row = r0 + min(r + hrow, cnt - 1);
+      const int row = r0 + min(r + hrow, cnt - 1), col = 4 * hcol;
       const bool take = r + hrow < cnt && pair_of_row % ka->top_k < ka->top_n;
-      for (int st = 0; st < LS; ++st) {
-        const int col = 32 * st + 4 * hcol;
-        float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
+      float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < kHaFirst; ++i) {
-          if (st > 0) part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, ka->ls * 32, col));
-        }
+      for (int i = 0; i < kHaFirst; ++i)
+        if (ha_lo + hj + i * TPO < ha_hi) sum += part[i];
+      for (int sl = ha_lo + hj + kHaFirst * TPO; sl < ha_hi; sl += TPO)
+        sum += *reinterpret_cast<const float4_t*>(ka->ha + ha_part(sl, ka->total_rows, row, col));
 #pragma unroll
-        for (int i = 0; i < kHaFirst; ++i)
-          if (ha_lo + hj + i * TPO < ha_hi) sum += part[i];
-        for (int sl = ha_lo + hj + kHaFirst * TPO; sl < ha_hi; sl += TPO)
-          sum += *reinterpret_cast<const float4_t*>(ka->ha + ha_part(sl, ka->total_rows, row, ka->ls * 32, col));
+      for (int dlt = 1; dlt < TPO; dlt *= 2)
 #pragma unroll
-        for (int dlt = 1; dlt < TPO; dlt *= 2)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], dlt);
-        if (hj == 0) {
-          half4_t v = half4_t{0, 0, 0, 0};
-          if (take && col < 16 * ht) v = half4_t{to_f16_sat(sum[0] * lam2), to_f16_sat(sum[1] * lam2), to_f16_sat(sum[2] * lam2), to_f16_sat(sum[3] * lam2)};
-          reinterpret_cast<half4_t*>(p_lds + p_frag_unit(0, st, hrow >> 4, LS, MT) + (hcol >> 1) * 16 + (hrow & 15))[hcol & 1] = v;
-        }
+        for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], dlt);
+      if (hj == 0) {
+        half4_t v = half4_t{0, 0, 0, 0};
+        if (take && col < 16 * ht) v = half4_t{to_f16_sat(sum[0] * lam2), to_f16_sat(sum[1] * lam2), to_f16_sat(sum[2] * lam2), to_f16_sat(sum[3] * lam2)};
+        reinterpret_cast<half4_t*>(p_lds + p_frag_unit(0, 0, hrow >> 4, LS, MT) + (hcol >> 1) * 16 + (hrow & 15))[hcol & 1] = v;
       }
     };
 
@@ -463,7 +457,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       for (int mt = 0; mt < MT; ++mt) {
         const int row = r + 16 * mt + c;
         if constexpr (DUAL) {
-          // (a column without a row multiplied zeros: its h is zero)
+          // (a column without a row: its inputs are zeros, its (in A) some row's; nothing of it is stored)
           const int se = row_se[mt];          // the row's inputs were scaled by 2^se
           const int tile = t0 + unit;
           const float dn = pow2i(-se), up = pow2i(2 * se);
@@ -554,7 +548,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
         }
         const int row = r + 16 * ((i >> 6) % MT) + (i & 15), rt = (i >> 6) / MT;
         if (row < cnt)
-          *reinterpret_cast<float4_t*>(ka->ha + ha_part(slot, ka->total_rows, r0 + row, ka->ls * 32, 16 * rt + 4 * ((i >> 4) & 3))) = sum;
+          *reinterpret_cast<float4_t*>(ka->ha + ha_part(slot, ka->total_rows, r0 + row, 16 * rt + 4 * ((i >> 4) & 3))) = sum;
       }
     }
   }
@@ -607,14 +601,27 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
 }
 
 // Whether the fused launch leaves (h A2) as part sums for W2 (else xa_rows_kernel makes it in between): both
-// projections on this flavour, ranks whose sums of 16 wavefronts fit the LDS of the activations, and room for
-// the parts.  Whole forward, launch in between -> part sums, us: Mixtral T = 64 159.4 -> 153.4, T = 1 71.1 -> 67.5,
-// T = 13 with 3-bit pairs 161.5 -> 159.1; Qwen3 T = 64 110.8 -> 107.0; hidden 256, FFN 512, T = 16 (four calls) 59.6 -> 56.1.
+// projections on this flavour, ranks up to 32, room for the parts, and few enough of them.  Every W2 block reads the parts of its
+// rows, `slots` of 128 bytes a row: 100 KB cost it about 2 us, the launch in between 3 and 0.25 more per pass of 32 rows and 1000
+// inputs (the FFN width).  The host does not know the counts: the parts are bounded for tokens that select half as many
+// experts as they can (96 KB), and for tokens that all select the same (320 KB), each plus what the passes of the launch
+// would cost.  Whole forward, launch in between -> part sums, us, in bounds: Mixtral T = 1 64.4 -> 60.9, T = 64 151.8 -> 146.3 (all
+// tokens alike 124.0 -> 118.8), T = 160 289.8 -> 285.0; Qwen3 T = 16 72.6 -> 69.3, T = 64 103.4 -> 100.9; hidden 256, FFN 512, 8 experts,
+// Top-2, T = 16 42.4 -> 40.3; 16 experts, Top-2, 2048 x 1024, T = 32 54.8 -> 51.9 (all tokens alike 50.7 -> 53.6).  Out of them: 4 experts, Top-1, 1536 x 896, T = 100 53 -> 63; 32 experts, Top-4, 2048 x 1408, T = 64, all tokens alike
+// 105 -> 112; Qwen3 T = 256 311 -> 315.  At rank 64, with twice the parts and the sums of two steps, most shapes lose (Mixtral
+// T = 32 138.9 -> 140.2, T = 160 299.5 -> 304.6, Qwen3 T = 128 172 -> 179).  Beside shared experts the launch in between is free, the side
+// stream fills it: DeepSeek shape T = 1 80.5 -> 82.8 (without them T = 64 105.9 -> 101.2).
 bool decode_ha(const FfnArgs& f, int which) {
-  if (which != 3 || f.offsets == nullptr || f.plan == nullptr || f.ha == nullptr || f.rank <= 0 || f.rank > dec::kHaRank) return false;
-  const int NT = f.F / kTileN, ls = (f.rank + 31) / 32;
-  const size_t slots = std::min(plan_blocks(f.n_exp, f.T * f.top_k, NT, f.n_cu), NT);
-  return slots * f.total_rows * ls * 128 <= f.ha_bytes;
+  if (which != 3 || f.offsets == nullptr || f.plan == nullptr || f.ha == nullptr || f.rank <= 0 || f.rank > dec::kHaRank || f.n_shared > 0) return false;
+  const int NT = f.F / kTileN, pairs = f.T * f.top_k, kb = decode_w2_kblocks(f);
+  const size_t room = size_t(std::min(plan_blocks(f.n_exp, pairs, NT, f.n_cu), NT)) * f.total_rows * 128;
+  // `experts` of them share the pairs and the blocks of the fused launch: KB of parts that a W2 block reads, within `limit` or not
+  auto within = [&](int experts, int limit) {
+    const int rows = std::min(f.T, (pairs + experts - 1) / experts), passes = (rows + 31) / 32;
+    const int slots = std::min(std::max(f.n_cu / experts, (NT + 31) / 32), NT);
+    return slots * (rows <= 16 ? 16 : 32 * passes) / (8 * kb) <= limit + f.F * passes / 80;
+  };
+  return room <= f.ha_bytes && within(std::max(f.top_k, std::min(f.n_exp, pairs) / 2), 96) && within(f.top_k, 320);
 }
 
 template <int BITS>

@@ -198,6 +198,7 @@ struct FfnArgs {
   int p_tokens;               // ... or [n_exp][p_tokens tokens][2 * ls * 32] and a row of zeros (KArgs::p_tokens)
   int32_t* row_tok;           // ... then also [rows]: KArgs::row_tok, written by the preparing launch
   float* p2;                  // (h A2), fp16 [rows][ls * 32]; decode flavour: one per W2 K-block
+  int n_shared;               // shared experts that the layer runs beside these
   float* ha;                  // decode flavour of both projections: room for ha_bytes of (h A2) part sums (decode_ha)
   size_t ha_bytes;
   void* y_rows;               // [rows][H] bf16

@@ -183,8 +183,8 @@ std::string check_shape(const Shape& sh) {
 
 // (h A2) made by the fused launch: every block's operand reads, its copy of them in LDS, and the part sums it
 // leaves for the K-blocks of W2
-std::string check_h_a2(int F, int ls, int rank2, const Shape& sh, int kblocks) {
-  const int NT = F / kTileN, ht = (rank2 + 15) / 16, slots = ha_slots(sh.G, NT), pitch = ls * 32;
+std::string check_h_a2(int F, int rank2, const Shape& sh, int kblocks) {
+  const int NT = F / kTileN, ht = (rank2 + 15) / 16, slots = ha_slots(sh.G, NT);
   std::vector<int> left(slots, 0), taken(slots, 0);
   for (int b = 0; b < sh.G; ++b) {
     int t0, t1;
@@ -193,7 +193,7 @@ std::string check_h_a2(int F, int ls, int rank2, const Shape& sh, int kblocks) {
     const int slot = ha_slot(b, t0, sh.G, NT);
     if (slot < 0 || slot >= slots) SELF_FAIL("block %d of %d leaves its sums in place %d of %d", b, sh.G, slot, slots);
     ++left[slot];
-    if (ha_part(slot, sh.total_rows, sh.r0 + sh.cnt - 1, pitch, 16 * ht - 4) + 4 > size_t(slots) * sh.total_rows * pitch)
+    if (ha_part(slot, sh.total_rows, sh.r0 + sh.cnt - 1, 16 * ht - 4) + 4 > size_t(slots) * sh.total_rows * kHaRank)
       SELF_FAIL("block %d stores past its part sums", b);
     const int u0 = t0 / 2, n_u = (t1 - 1) / 2 - u0 + 1, g0 = t0 / 4, n_q = ((t1 - 1) / 4 - g0) / 4 + 1;
     for (int rt = 0; rt < ht; ++rt)
@@ -241,7 +241,7 @@ extern "C" int moe_lrc_selftest_decode_index(int hidden, int ffn, int bits, int 
   Shape b{ffn, hidden, bits, group, ls, {(rank2 + 31) / 32, (rank2 + 31) / 32}, first_row, rows, total_rows, blocks_w2, kblocks_w2, false};
   err = check_shape(b);
   if (!err.empty()) return set_error(MOE_LRC_ESHAPE, "selftest_decode_index (W2): " + err);
-  if (rank2 > 0 && layer_rank <= kHaRank) err = check_h_a2(ffn, ls, rank2, a, kblocks_w2);
+  if (rank2 > 0 && layer_rank <= kHaRank) err = check_h_a2(ffn, rank2, a, kblocks_w2);
   if (!err.empty()) return set_error(MOE_LRC_ESHAPE, "selftest_decode_index (h A2): " + err);
   return MOE_LRC_OK;
 }

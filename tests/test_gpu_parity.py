@@ -745,12 +745,17 @@ def test_in_a_with_staged_rows(amd, hidden, ffn, rank, tokens, kind):
     (512, 1088, 40, 70, 4, "same"),        # several passes, an odd number of factor tiles
     (320, 4160, 56, 37, 2, "int3"),        # W2 in two K-blocks, 260 n-tiles
     (320, 4160, 64, 21, 2, "bucket"),      # ranks that differ, pairs of W2 missing
+    # ranks up to 32 and few enough parts: made by the fused launch (the ones above 32 and (512, 1088) by a launch in between)
+    (256, 64, 32, 3, 1, "same"),           # four n-tiles for all blocks: most of them own none
+    (512, 128, 24, 70, 4, "same"),         # several passes, eight parts
+    (320, 4160, 32, 16, 2, "bucket"),      # W2 in two K-blocks, ranks that differ, pairs of W2 missing
+    (320, 8256, 32, 30, 4, "int3"),        # three K-blocks, 128 parts of up to 30 rows
 ])
 def test_h_a2_from_the_fused_launch(amd, hidden, ffn, rank, tokens, experts, kind):
-    """(h A2) of decode batches with ranks up to 64 is made by the blocks of the fused projection and added up by
-    those of W2: block shares, K-blocks, passes and ranks at which its indices change, against the oracle."""
+    """(h A2) of decode batches with ranks up to 32 is made by the blocks of the fused projection and added up by
+    those of W2, where the parts are few: block shares, K-blocks, passes and ranks at which its indices change, against the oracle."""
     import torch
-    bucket = (64, 0, 16, 40, 0, 8, 64)
+    bucket = tuple(min(r, rank) for r in (64, 0, 16, 40, 0, 8, 64))
     cfg = configs.TINY.with_(hidden=hidden, ffn=ffn, n_experts=experts, top_k=min(2, experts), rank=rank, tokens=tokens, bits=2,
                              name=f"h_a2_{kind}_{ffn}_r{rank}")
     layer = fixtures.sample_layer(cfg)
