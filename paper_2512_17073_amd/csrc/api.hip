@@ -264,7 +264,7 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   }
   // (the same room, in front: (x A1 | x A3) of all tokens, where the factors are in place before the preparing launch)
   const size_t p_bytes = align256(xa_tokens_bytes(c, T)), tokens_bytes = p_bytes + align256(size_t(P) * 4);
-  if (!(path & 1) && (c.residency == MOE_LRC_RESIDENT || ahead) && xa_by_tokens(c, T) && tokens_bytes <= a.ha_bytes) {
+  if (!(path & 1) && (c.residency == MOE_LRC_RESIDENT || ahead) && xa_by_tokens(c, T, L->n_cu) && tokens_bytes <= a.ha_bytes) {
     a.p_tokens = T;
     a.p13 = a.ha;
     a.row_tok = reinterpret_cast<int32_t*>(a.ha + p_bytes / 4);

@@ -159,15 +159,28 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
                             const CompactArgs* cmp /* or null */, const RouteArgs* route /* or null: perm->idx is ready */,
                             const ZeroRowsArgs& zr,
                             hipStream_t s, int32_t* host_stat = nullptr /* pinned: a copy of `stat` for the host */);
+// The preparing launch: threads of a block, and blocks side by side (grid.y) per 16 rows: a block covers 1024 columns in one
+// go (two 8-column units per thread), and there are no more blocks than CUs.
+constexpr int kPrepThreads = 1024;
+inline int prep_columns(int hidden, int rows, int n_cu) {
+  const int row_blocks = (rows + 15) / 16, most = n_cu / (row_blocks > 1 ? row_blocks : 1), want = hidden / (16 * (kPrepThreads / 16));
+  return want < 1 || most < 1 ? 1 : want < most ? want : most;
+}
 // (x A1 | x A3) of every expert for every token instead of for the routed rows: it then waits neither for the routing
-// nor for the grouping.  Up to 64 tokens (up to four 16-row passes per factor tile, side by side); ranks whose
-// fragments are one per wavefront of the kernel that copies them.  xa_by_tokens is the part of the rule that does
-// not depend on where the factors are.
-// With many experts to a token's pairs, most of what that computes is not used: 128 experts, top 8, T = 64: 23 us for
-// the launch against 17 by rows (8 experts, top 2, K = 4096, rank 32: 11.2 against 17.2, T = 1 11.8 against 15.3).
-constexpr int kXaTokens = 64, kXaTokensRank = 128, kXaTokensExperts = 8;
-inline bool xa_by_tokens(const moe_lrc_config& c, int T) {
-  return c.rank > 0 && c.rank <= kXaTokensRank && c.top_n > 0 && T <= kXaTokens && c.n_experts <= kXaTokensExperts * c.top_k;
+// nor for the grouping.  Up to 64 tokens in passes of 16 side by side, or of 32 where the grid has no more (xa_tokens_pass); ranks
+// whose fragments are one per wavefront of the kernel that copies them.  xa_by_tokens is the part of the rule that does
+// not depend on where the factors are: what is computed grows with factor tiles x experts x passes, and a CU holds one block of
+// this launch, so only while these blocks leave a quarter of the CUs to the others and no block has a second pass; with more
+// experts than 32, or than eight to a slot of the Top-k, most of it is not used.  Whole forward, by rows -> by tokens, us:
+// 8 experts, Top-2, 2048 x 1024, T = 64, rank 64 (128 blocks) 55.4 -> 53.0, rank 128 (256) 54.0 -> 57.2; rank 128, T = 16 (128) 48.9 -> 47.5; 16
+// experts, rank 32 (128) 52.5 -> 49.8, rank 64 (256) 53.9 -> 57.1; 8 experts, Top-1, 4096 x 1024, rank 64, T = 48 (192) 52.1 -> 50.7, T = 64
+// (256) 53.0 -> 56.9; two passes of 32: hidden 1024, T = 64, rank 8 50.5 -> 52.9; 64 experts, Top-8, rank 16, T = 16 (128) 78.4 -> 79.5.
+constexpr int kXaTokens = 64, kXaTokensRank = 128, kXaTokensExperts = 32;
+LRC_HD int xa_tokens_pass(int T, int columns) { return 16 * columns >= T ? 16 : 32; }
+inline bool xa_by_tokens(const moe_lrc_config& c, int T, int n_cu) {
+  const int columns = prep_columns(c.hidden, T * c.top_k, n_cu), pass = xa_tokens_pass(T, columns), passes = (T + pass - 1) / pass;
+  return c.rank > 0 && c.rank <= kXaTokensRank && c.top_n > 0 && T <= kXaTokens && c.n_experts <= kXaTokensExperts &&
+         c.n_experts <= 8 * c.top_k && passes <= columns && 4 * passes * (2 * ((c.rank + 15) / 16) * c.n_experts) <= 3 * n_cu;
 }
 inline size_t xa_tokens_bytes(const moe_lrc_config& c, int T) {
   return (size_t(c.n_experts) * T + 1) * ((c.rank + 31) / 32) * 128;

@@ -117,7 +117,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
 // Bound: the longest chain of dependent loads (grouping, then the tokens or the tables; tokens and factors,
 // then a sum over the wavefronts); Mixtral shape T = 64 17.2 -> 11.2 us, T = 1 15.3 -> 11.8, since neither waits for the other
 // and the tables are made without 64-bit divisions from counts read once.
-constexpr int kPrepThreads = 1024;
 constexpr int kStatAhead = 8;              // batches of 64 rows whose pairs a counting wavefront asks for together
 // With a token or two every block first routes them itself (route.wg != null).
 // With few pairs, every block first groups the pairs by expert itself (perm.idx != null: the body of
@@ -140,10 +139,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
   const int stat_blocks = stat ? (E + kWavesPerBlock - 1) / kWavesPerBlock : 0, plan_block = plan0.B + plan1.B > 0 ? 1 : 0;
   const int xa_first = row_blocks + stat_blocks + plan_block;
   if (xa.p_tokens > 0 && (int)blockIdx.x >= xa_first && (int)blockIdx.x < (int)gridDim.x - 1) {
-    // (x A1 | x A3) of all tokens: nothing to wait for; sixteen at a time where the grid then takes them all at once
-    const int i = (int)blockIdx.x - xa_first, pass = 16 * (int)gridDim.y >= xa.p_tokens ? 16 : 32;
+    // (x A1 | x A3) of all tokens: nothing to wait for
+    const int i = (int)blockIdx.x - xa_first, pass = xa_tokens_pass(xa.p_tokens, gridDim.y);
     ffn::xa_tokens_body<kWavesPerBlock>(xa, x, route.wg != nullptr ? nullptr : tok_exp, i % xa_tiles, i / xa_tiles,
-                                         pass * blockIdx.y, pass * gridDim.y, pass == 32, red);
+                                         pass * blockIdx.y, pass == 32, red);
     return;
   }
   if (route.wg != nullptr) {
@@ -295,13 +294,11 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
                             hipStream_t s, int32_t* host_stat) {
   const moe_lrc_config& c = L->cfg;
   const int rows = row_pair ? T * c.top_k : T;
-  const int row_blocks = (rows + 15) / 16;
-  // (a block pass covers 16 * kPrepThreads / 16 columns: two 8-column units per thread)
-  const int ky = std::max(1, std::min(c.hidden / (16 * (kPrepThreads / 16)), L->n_cu / std::max(1, row_blocks)));
+  const int row_blocks = (rows + 15) / 16, ky = prep_columns(c.hidden, rows, L->n_cu);
   const PlanSpec none{0, 0, 0, nullptr};
   const PlanSpec p0 = plans ? plans[0] : none, p1 = plans ? plans[1] : none;
   const int plan_block = p0.B + p1.B > 0 ? 1 : 0;
-  // (x A1 | x A3) of the decode flavour: 16-column tiles of both factors, each padded to ls * 32 columns
+  // (x A1 | x A3) of the decode flavour: 16-column tiles of both factors
   ffn::KArgs xa{};
   int xa_tiles = 0;
   if (xa13 && xa13->rank > 0 && xa13->top_n > 0 && row_pair) {

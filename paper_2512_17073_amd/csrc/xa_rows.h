@@ -15,8 +15,8 @@ constexpr int kXaBatch = 4;     // factor and activation units requested togethe
 // (in A)[row][rho] for the rows of the decode flavour, finished in one launch:
 //   P[row][m * ls * 32 + rho] = fp16(lambda_m * sum_k in[row][k] * A_m[k][rho]) for rows that take the
 // rank-r term, 0 for the other rows of an expert that has such rows; lambda_m is the projection's
-// power-of-two pre-scale.  grid = (16-column tiles of [A1 | A3] or of A2, each padded to ls * 32
-// columns; experts); the NW wavefronts of a block split K and add their parts through LDS in a
+// power-of-two pre-scale.  grid = (16-column tiles of [A1 | A3] or of A2, the last of an odd
+// number writing the padding to ls * 32 columns; experts); the NW wavefronts of a block split K and add their parts through LDS in a
 // fixed order.  A tile past the projection's own rank writes zeros (the FFN kernel reads the columns
 // of every rank step its expert runs).  TOKENS: the rows are read from the bf16 tokens through
 // row_pair (the launch that prepares the activations runs this body in further blocks); otherwise
@@ -153,11 +153,11 @@ __device__ __forceinline__ void xa_rows_body(const KArgs& a, const uint16_t* __r
 
 // The same for every token, whatever it is routed to (p_tokens > 0): P[e][token][m * ls * 32 + rho], so that it
 // needs neither the routing nor the grouping.  grid = (16-column tiles of [A1 | A3]; experts; passes of 32 tokens, or
-// of 16 (`wide` false), r0, r0 + r_step, ...).  tok_exp: the tokens' exponents, or null: taken from the rows here.  Per row the
+// of 16 (`wide` false), from token r0 on).  tok_exp: the tokens' exponents, or null: taken from the rows here.  Per row the
 // same products in the same order as above: the same bits.
 template <int NW, int BATCH = kXaBatch>
 __device__ __forceinline__ void xa_tokens_body(const KArgs& a, const uint16_t* __restrict__ x_bf16, const int32_t* tok_exp, int tile, int e,
-                                               int r0, int r_step, bool wide, float4_t (*red)[64] /* [2 * NW][64] */) {
+                                               int r0, bool wide, float4_t (*red)[64] /* [2 * NW][64] */) {
   const ExpertDesc& d = a.desc[e];
   const int lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4, T = a.p_tokens;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -170,7 +170,7 @@ __device__ __forceinline__ void xa_tokens_body(const KArgs& a, const uint16_t* _
     if (pad) *reinterpret_cast<half4_t*>(col + row * pitch + 16) = half4_t{0, 0, 0, 0};
   };
   if (e == 0 && r0 == 0 && wave == NW - 1 && c == 0) store(size_t(a.n_exp) * T, half4_t{0, 0, 0, 0});     // the row of zeros
-  if (!d.has_factors) return;
+  if (!d.has_factors || r0 >= T) return;
   const bool live = 16 * tl < min(d.rank[m], a.rank);
   const float lam = d.xa_scale[m];
   const half8_t* af = reinterpret_cast<const half8_t*>(d.af[m]);
@@ -178,97 +178,94 @@ __device__ __forceinline__ void xa_tokens_body(const KArgs& a, const uint16_t* _
   const uint32_t* aq = reinterpret_cast<const uint32_t*>(d.af[m]);
   const uint32_t* am = d.afm[m];
   const int k32 = a.K / 32, g64 = a.K / 64, per = (k32 + NW - 1) / NW, kk0 = min(k32, wave * per), kk1 = min(k32, kk0 + per);
-  for (int r = r0; r < T; r += r_step) {
-    float4_t acc[2] = {float4_t{0.f, 0.f, 0.f, 0.f}, float4_t{0.f, 0.f, 0.f, 0.f}};
-    if (live) {
-      const uint4* xrow[2];
-      float xs2[2];
+  float4_t acc[2] = {float4_t{0.f, 0.f, 0.f, 0.f}, float4_t{0.f, 0.f, 0.f, 0.f}};
+  if (live) {
+    const uint4* xrow[2];
+    float xs2[2];
 #pragma unroll
-      for (int t = 0; t < 2; ++t) xrow[t] = reinterpret_cast<const uint4*>(x_bf16 + size_t(min(r + 16 * t + c, T - 1)) * a.K);
-      if (tok_exp != nullptr) {
+    for (int t = 0; t < 2; ++t) xrow[t] = reinterpret_cast<const uint4*>(x_bf16 + size_t(min(r0 + 16 * t + c, T - 1)) * a.K);
+    if (tok_exp != nullptr) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) xs2[t] = pow2i(tok_exp[min(r + 16 * t + c, T - 1)]);
-      } else {
-        uint32_t* peak = reinterpret_cast<uint32_t*>(red);           // [NW][2][16]
+      for (int t = 0; t < 2; ++t) xs2[t] = pow2i(tok_exp[min(r0 + 16 * t + c, T - 1)]);
+    } else {
+      uint32_t* peak = reinterpret_cast<uint32_t*>(red);           // [NW][2][16]
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          uint32_t mx = 0;
-          for (int kk = kk0; kk < kk1; ++kk) {
-            const uint4 v = xrow[t][4 * kk + q];
-            const uint32_t in[4] = {v.x, v.y, v.z, v.w};
+      for (int t = 0; t < 2; ++t) {
+        uint32_t mx = 0;
+        for (int kk = kk0; kk < kk1; ++kk) {
+          const uint4 v = xrow[t][4 * kk + q];
+          const uint32_t in[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) mx = max(mx, max(in[i] & 0x7fffu, (in[i] >> 16) & 0x7fffu));
-          }
-          mx = max(mx, (uint32_t)__shfl_xor((int)mx, 16));
-          mx = max(mx, (uint32_t)__shfl_xor((int)mx, 32));
-          if (q == 0) peak[(wave * 2 + t) * 16 + c] = mx;
+          for (int i = 0; i < 4; ++i) mx = max(mx, max(in[i] & 0x7fffu, (in[i] >> 16) & 0x7fffu));
         }
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          uint32_t mx = 0;
-#pragma unroll
-          for (int w = 0; w < NW; ++w) mx = max(mx, peak[(w * 2 + t) * 16 + c]);
-          xs2[t] = pow2i(row_exponent(mx));
-        }
-        __syncthreads();
+        mx = max(mx, (uint32_t)__shfl_xor((int)mx, 16));
+        mx = max(mx, (uint32_t)__shfl_xor((int)mx, 32));
+        if (q == 0) peak[(wave * 2 + t) * 16 + c] = mx;
       }
-      auto k_loop = [&](auto Q3_, auto TWO_) {
-        constexpr bool Q3 = decltype(Q3_)::value, TWO = decltype(TWO_)::value;
-        constexpr int NB = TWO ? BATCH : 2 * BATCH, NT = TWO ? 2 : 1;
-        for (int kk = kk0; kk < kk1; kk += NB) {
-          half8_t wf[NB];
-          uint4 xv[NT][NB];
-          uint32_t cq[NB], mq[NB];
+      __syncthreads();
 #pragma unroll
-          for (int u = 0; u < NB; ++u) {
-            const int ku = min(kk + u, kk1 - 1);
-            if constexpr (Q3) {
-              cq[u] = aq[(size_t(tl) * k32 + ku) * kWave + lane];
-              mq[u] = am[(size_t(tl) * g64 + (ku >> 1)) * 16 + c];
-            } else {
-              wf[u] = af[(size_t(tl) * k32 + ku) * kWave + lane];
-            }
+      for (int t = 0; t < 2; ++t) {
+        uint32_t mx = 0;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) xv[t][u] = xrow[t][4 * ku + q];
-          }
-#pragma unroll
-          for (int u = 0; u < NB; ++u) {
-            if constexpr (Q3) wf[u] = q3_unit_a(cq[u], mq[u]);
-            if (kk + u >= kk1) wf[u] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};       // (a step past this wavefront's share)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-              const uint32_t in[4] = {xv[t][u].x, xv[t][u].y, xv[t][u].z, xv[t][u].w};
-              half8_t xf;
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                xf[2 * i] = (_Float16)(__uint_as_float(in[i] << 16) * xs2[t]);
-                xf[2 * i + 1] = (_Float16)(__uint_as_float(in[i] & 0xffff0000u) * xs2[t]);
-              }
-              acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[u], xf, acc[t], 0, 0, 0);
-            }
-          }
-        }
-      };
-      const bool two = wide && r + 16 < T;
-      if (q3) { if (two) k_loop(std::true_type{}, std::true_type{}); else k_loop(std::true_type{}, std::false_type{}); }
-      else { if (two) k_loop(std::false_type{}, std::true_type{}); else k_loop(std::false_type{}, std::false_type{}); }
-      red[wave][lane] = acc[0];
-      red[NW + wave][lane] = acc[1];
+        for (int w = 0; w < NW; ++w) mx = max(mx, peak[(w * 2 + t) * 16 + c]);
+        xs2[t] = pow2i(row_exponent(mx));
+      }
       __syncthreads();
     }
-    // wavefront t: lane (q, c) columns 16 tl + 4 q .. + 3 of token r + 16 t + c
-    if (wave < (wide ? 2 : 1) && r + 16 * wave + c < T) {
-      half4_t v = half4_t{0, 0, 0, 0};
-      if (live) {
-        float4_t sum = red[wave * NW][lane];
+    auto k_loop = [&](auto Q3_, auto TWO_) {
+      constexpr bool Q3 = decltype(Q3_)::value, TWO = decltype(TWO_)::value;
+      constexpr int NB = TWO ? BATCH : 2 * BATCH, NT = TWO ? 2 : 1;
+      for (int kk = kk0; kk < kk1; kk += NB) {
+        half8_t wf[NB];
+        uint4 xv[NT][NB];
+        uint32_t cq[NB], mq[NB];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) sum += red[wave * NW + w][lane];
-        v = half4_t{to_f16_sat(sum[0] * lam), to_f16_sat(sum[1] * lam), to_f16_sat(sum[2] * lam), to_f16_sat(sum[3] * lam)};
+        for (int u = 0; u < NB; ++u) {
+          const int ku = min(kk + u, kk1 - 1);
+          if constexpr (Q3) {
+            cq[u] = aq[(size_t(tl) * k32 + ku) * kWave + lane];
+            mq[u] = am[(size_t(tl) * g64 + (ku >> 1)) * 16 + c];
+          } else {
+            wf[u] = af[(size_t(tl) * k32 + ku) * kWave + lane];
+          }
+#pragma unroll
+          for (int t = 0; t < NT; ++t) xv[t][u] = xrow[t][4 * ku + q];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+          if constexpr (Q3) wf[u] = q3_unit_a(cq[u], mq[u]);
+          if (kk + u >= kk1) wf[u] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};       // (a step past this wavefront's share)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const uint32_t in[4] = {xv[t][u].x, xv[t][u].y, xv[t][u].z, xv[t][u].w};
+            half8_t xf;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              xf[2 * i] = (_Float16)(__uint_as_float(in[i] << 16) * xs2[t]);
+              xf[2 * i + 1] = (_Float16)(__uint_as_float(in[i] & 0xffff0000u) * xs2[t]);
+            }
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[u], xf, acc[t], 0, 0, 0);
+          }
+        }
       }
-      store(size_t(e) * T + r + 16 * wave + c, v);
+    };
+    const bool two = wide && r0 + 16 < T;
+    if (q3) { if (two) k_loop(std::true_type{}, std::true_type{}); else k_loop(std::true_type{}, std::false_type{}); }
+    else { if (two) k_loop(std::false_type{}, std::true_type{}); else k_loop(std::false_type{}, std::false_type{}); }
+    red[wave][lane] = acc[0];
+    red[NW + wave][lane] = acc[1];
+    __syncthreads();
+  }
+  // wavefront t: lane (q, c) columns 16 tl + 4 q .. + 3 of token r0 + 16 t + c
+  if (wave < (wide ? 2 : 1) && r0 + 16 * wave + c < T) {
+    half4_t v = half4_t{0, 0, 0, 0};
+    if (live) {
+      float4_t sum = red[wave * NW][lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) sum += red[wave * NW + w][lane];
+      v = half4_t{to_f16_sat(sum[0] * lam), to_f16_sat(sum[1] * lam), to_f16_sat(sum[2] * lam), to_f16_sat(sum[3] * lam)};
     }
-    if (live) __syncthreads();
+    store(size_t(e) * T + r0 + 16 * wave + c, v);
   }
 }
 

@@ -791,11 +791,16 @@ def test_h_a2_from_the_fused_launch(amd, hidden, ffn, rank, tokens, experts, kin
 @pytest.mark.parametrize("hidden,rank,tokens,experts,top_k,kind", [
     (256, 8, 16, 8, 1, "same"),            # one pass of 16 tokens, one factor tile, as many experts as the rule takes
     (320, 40, 17, 3, 2, "int3"),           # one token in the second pass, an odd number of factor tiles
-    (4096, 128, 64, 8, 2, "same"),         # the largest batch and rank
-    (1088, 64, 49, 16, 2, "bucket"),       # more passes than the grid has: 32 tokens at a time; ranks that differ
+    (4096, 128, 64, 8, 2, "same"),         # the largest batch and rank (too many blocks: of the routed rows)
+    (1088, 64, 49, 16, 2, "bucket"),       # more passes than the grid has (of the routed rows); ranks that differ
+    (4096, 32, 64, 8, 2, "int3"),          # the largest batch, four passes of 16 side by side
+    (2048, 128, 64, 4, 1, "same"),         # the largest rank, two passes of 32
+    (2112, 64, 49, 6, 1, "bucket"),        # two passes of 32, one token in the last half; ranks that differ
+    (1024, 24, 32, 32, 4, "same"),         # as many experts as the rule takes, one pass of 32, an odd number of factor tiles
 ])
 def test_x_a13_of_every_token(amd, hidden, rank, tokens, experts, top_k, kind):
-    """(x A1 | x A3) of small decode batches is made for every token and expert beside the grouping: passes, factor
+    """(x A1 | x A3) of small decode batches is made for every token and expert beside the grouping (where that is few
+    blocks): passes, factor
     tiles and tokens at which its indices change, against the oracle and, bit for bit, against a staged layer (whose
     factors arrive later: there the products are made of the routed rows)."""
     import torch
