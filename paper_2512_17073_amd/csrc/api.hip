@@ -262,13 +262,14 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
     const int rc = pool_begin(L, &ahead);
     if (rc) return rc;
   }
-  // (the same room, in front: (x A1 | x A3) of all tokens, where the factors are in place before the preparing launch)
+  // (the end of the same room: (x A1 | x A3) of all tokens, where the factors are in place before the preparing launch.  It gives the
+  // same bits as of the routed rows, the part sums of (h A2) do not: whether those fit must not depend on it)
   const size_t p_bytes = align256(xa_tokens_bytes(c, T)), tokens_bytes = p_bytes + align256(size_t(P) * 4);
-  if (!(path & 1) && (c.residency == MOE_LRC_RESIDENT || ahead) && xa_by_tokens(c, T, L->n_cu) && tokens_bytes <= a.ha_bytes) {
+  if (!(path & 1) && (c.residency == MOE_LRC_RESIDENT || ahead) && xa_by_tokens(c, T, L->n_cu) && tokens_bytes + decode_ha_bytes(a) <= a.ha_bytes) {
+    a.ha_bytes -= tokens_bytes;
     a.p_tokens = T;
-    a.p13 = a.ha;
-    a.row_tok = reinterpret_cast<int32_t*>(a.ha + p_bytes / 4);
-    a.ha += tokens_bytes / 4; a.ha_bytes -= tokens_bytes;
+    a.p13 = a.ha + a.ha_bytes / 4;
+    a.row_tok = reinterpret_cast<int32_t*>(a.p13 + p_bytes / 4);
   }
   if (kblocks_out) *kblocks_out = a.keep_partials ? kblocks : 1;
   // the launch that converts the activations also makes the block tables of the decode launches

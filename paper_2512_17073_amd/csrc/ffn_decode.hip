@@ -21,7 +21,7 @@
 //   - (h A2) of ranks up to 32 is made at the end of the fused projection's blocks, from the h they hold in
 //     registers: each block's columns are a share of its long K, and the W2 blocks add the shares of
 //     their K-block up while their activations arrive, where that is less than a launch between the two costs, which
-//     reads h and A2 again (decode_ha).  Larger ranks and many rows over few experts keep that launch;
+//     reads h and A2 again (ha_room).  Larger ranks and many rows over few experts keep that launch;
 //   - a long K (W2) is split into K-blocks (grid.z) of one or two phases whose fp32 partial outputs
 //     the combine (or reduce_kernel, for the stand-alone call) adds in a fixed order.
 #include <algorithm>
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
   y[u] = v;
 }
 
-// Whether the fused launch leaves (h A2) as part sums for W2 (else xa_rows_kernel makes it in between): both
+// Bytes of the part sums of (h A2) where the fused launch leaves them for W2 (0: xa_rows_kernel makes (h A2) in between): both
 // projections on this flavour, ranks up to 32, room for the parts, and few enough of them.  Every W2 block reads the parts of its
 // rows, `slots` of 128 bytes a row: 100 KB cost it about 2 us, the launch in between 3 and 0.25 more per pass of 32 rows and 1000
 // inputs (the FFN width).  The host does not know the counts: the parts are bounded for tokens that select half as many
@@ -611,8 +611,8 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
 // 105 -> 112; Qwen3 T = 256 311 -> 315.  At rank 64, with twice the parts and the sums of two steps, most shapes lose (Mixtral
 // T = 32 138.9 -> 140.2, T = 160 299.5 -> 304.6, Qwen3 T = 128 172 -> 179).  Beside shared experts the launch in between is free, the side
 // stream fills it: DeepSeek shape T = 1 80.5 -> 82.8 (without them T = 64 105.9 -> 101.2).
-bool decode_ha(const FfnArgs& f, int which) {
-  if (which != 3 || f.offsets == nullptr || f.plan == nullptr || f.ha == nullptr || f.rank <= 0 || f.rank > dec::kHaRank || f.n_shared > 0) return false;
+size_t ha_room(const FfnArgs& f) {
+  if (f.offsets == nullptr || f.plan == nullptr || f.ha == nullptr || f.rank <= 0 || f.top_n <= 0 || f.rank > dec::kHaRank || f.n_shared > 0) return 0;
   const int NT = f.F / kTileN, pairs = f.T * f.top_k, kb = decode_w2_kblocks(f);
   const size_t room = size_t(std::min(plan_blocks(f.n_exp, pairs, NT, f.n_cu), NT)) * f.total_rows * 128;
   // `experts` of them share the pairs and the blocks of the fused launch: KB of parts that a W2 block reads, within `limit` or not
@@ -621,7 +621,7 @@ bool decode_ha(const FfnArgs& f, int which) {
     const int slots = std::min(std::max(f.n_cu / experts, (NT + 31) / 32), NT);
     return slots * (rows <= 16 ? 16 : 32 * passes) / (8 * kb) <= limit + f.F * passes / 80;
   };
-  return room <= f.ha_bytes && within(std::max(f.top_k, std::min(f.n_exp, pairs) / 2), 96) && within(f.top_k, 320);
+  return room <= f.ha_bytes && within(std::max(f.top_k, std::min(f.n_exp, pairs) / 2), 96) && within(f.top_k, 320) ? room : 0;
 }
 
 template <int BITS>
@@ -650,7 +650,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   // (the kernels that can dequantize 3-bit factor pairs, where the layer holds any)
   const bool q3 = comp && f.q3;
   // (h A2) made by the fused launch's blocks themselves
-  const bool ha = comp && decode_ha(f, which);
+  const bool ha = comp && which == 3 && ha_room(f) > 0;
   a.ha = ha ? f.ha : nullptr;
   auto pick = [&](auto DUAL_) {
     constexpr bool DUAL = decltype(DUAL_)::value;
@@ -714,6 +714,8 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
 }
 
 }  // namespace
+
+size_t decode_ha_bytes(const FfnArgs& f) { return expert_ffn_path(f) == 0 ? ha_room(f) : 0; }
 
 // K-blocks of the decode flavour's W2 launch: one 16-k-step phase each, at most kMaxKBlocks
 int decode_w2_kblocks(const FfnArgs& f) {

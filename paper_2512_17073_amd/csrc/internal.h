@@ -212,7 +212,7 @@ struct FfnArgs {
   int32_t* row_tok;           // ... then also [rows]: KArgs::row_tok, written by the preparing launch
   float* p2;                  // (h A2), fp16 [rows][ls * 32]; decode flavour: one per W2 K-block
   int n_shared;               // shared experts that the layer runs beside these
-  float* ha;                  // decode flavour of both projections: room for ha_bytes of (h A2) part sums (decode_ha)
+  float* ha;                  // decode flavour of both projections: room for ha_bytes of (h A2) part sums (decode_ha_bytes)
   size_t ha_bytes;
   void* y_rows;               // [rows][H] bf16
   float* y_part;              // fp32 partial outputs of the W2 K-blocks (decode flavour), or null
@@ -240,6 +240,7 @@ hipError_t launch_expert_ffn(const FfnArgs& a, hipStream_t s);
 // K-blocks the decode flavour splits W2 into (1: none); the W2 output of a launch is y_rows, or with
 // keep_partials that many fp32 partial sums [kb][rows][H] in y_part
 int decode_w2_kblocks(const FfnArgs& a);
+size_t decode_ha_bytes(const FfnArgs& a);   // what the part sums of (h A2) take of ha_bytes (0: that form is not taken)
 // bit 0: the fused W1|W3 projection takes the grouped GEMM (else the decode flavour), bit 1: W2 does
 int expert_ffn_path(const FfnArgs& a);
 // once per device, before the first launch: lets the FFN kernels use the whole LDS of a CU

@@ -868,3 +868,20 @@ def test_grouped_gemm_chunks_of_every_length(amd, hidden, ffn, bits, rank, top_n
     print(f"\n[{cfg.name}] path {L.stats()['path']}, rel err {orc.rel_frobenius(y, want):.2e}, worst expert {worst:.2e}", flush=True)
     assert orc.rel_frobenius(y, want) <= TOL and worst <= 2 * TOL      # (an expert of one row has no average over rows)
     L.close()
+
+
+def test_residency_does_not_change_bits_where_the_workspace_is_tight(amd):
+    """FFN width 960, hidden 256, 16 experts: the part sums of (h A2) and (x A1 | x A3) of every token do not fit the same room
+    together.  Which of them is taken must not decide the order of any sum: resident and staged layers, bit for bit."""
+    import torch
+    cfg = configs.TINY.with_(hidden=256, ffn=960, n_experts=16, top_k=2, rank=32, tokens=16, bits=2, name="tight_room")
+    layer = fixtures.sample_layer(cfg)
+    Lr = amd.Layer.from_config(cfg)
+    Ls = amd.Layer.from_config(cfg, residency=amd.STAGED)
+    Lr.load(layer); Ls.load(layer)
+    for seed in range(100):
+        x = amd.bf16_tensor(synth.make_tokens(cfg.with_(seed=3000 + seed)))
+        out_r = Lr.forward(x).clone()
+        out_s = Ls.forward(x).clone()
+        assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16)), seed
+    Lr.close(); Ls.close()
