@@ -614,7 +614,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
 size_t ha_room(const FfnArgs& f) {
   if (f.offsets == nullptr || f.plan == nullptr || f.ha == nullptr || f.rank <= 0 || f.top_n <= 0 || f.rank > dec::kHaRank || f.n_shared > 0) return 0;
   const int NT = f.F / kTileN, pairs = f.T * f.top_k, kb = decode_w2_kblocks(f);
-  const size_t room = size_t(std::min(plan_blocks(f.n_exp, pairs, NT, f.n_cu), NT)) * f.total_rows * 128;
+  const size_t room = size_t(ha_slots(plan_blocks(f.n_exp, pairs, NT, f.n_cu), NT)) * f.total_rows * kHaRank * 4;
   // `experts` of them share the pairs and the blocks of the fused launch: KB of parts that a W2 block reads, within `limit` or not
   auto within = [&](int experts, int limit) {
     const int rows = std::min(f.T, (pairs + experts - 1) / experts), passes = (rows + 31) / 32;

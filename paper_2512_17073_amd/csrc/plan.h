@@ -12,11 +12,31 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "decode_index.h"
+
 namespace lrc {
 
 struct PlanSpec { int B, NT, target; int32_t* plan; };     // B entries for a projection of NT n-tiles; plan == null: no table wanted
 struct PlanEntry { int32_t e, b, G, r0, cnt, slots, pad0, pad1; };     // slots: ha_slots of the expert's blocks in the other table
 constexpr int kPlanEntryInts = 8;
+
+// One table's shares: as many blocks as fill the chip (`target`), more only if the experts with rows need
+// them; the rest of the grid exits at once.  Every expert gets its fewest blocks (a block owns at most
+// 32 n-tiles) or its share by weight of all the blocks, whichever is more (the shares by weight are then
+// scaled down to what is left): its blocks start where the fewest blocks of the experts before it and their part of
+// the rest end.  (Also called on the host, for tests.)
+LRC_HD int plan_least(const PlanSpec& p) { return (p.NT + 31) / 32; }
+LRC_HD int plan_total(const PlanSpec& p, int n_active) {
+  const int least = n_active * plan_least(p), want = p.target > least ? p.target : least;
+  return p.B < want ? p.B : want;
+}
+// ... an expert's claim on the blocks beyond the fewest ...
+LRC_HD int plan_claim(int total, int weight, int wsum, int least) {
+  const int claim = int(uint32_t(total * weight) / uint32_t(wsum > 1 ? wsum : 1)) - least;
+  return claim > 0 ? claim : 0;
+}
+// ... and what `claims` of all the `over` claims get of the `extra` blocks
+LRC_HD int plan_part(int extra, int claims, int over) { return over > 0 ? int(uint32_t(extra * claims) / uint32_t(over)) : 0; }
 
 // other: the spec of the table whose blocks leave part sums for this table's (null: none).
 // The rest of the preparing launch is short, so this chain sets its length: the experts' rows are read once, 64
@@ -52,17 +72,14 @@ __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, con
     n_active += __popcll(active[i]);
     if (64 * i < E) wsum += __shfl(scan(weight[i]), 63);
   }
-  // One table's shares: as many blocks as fill the chip (`target`), more only if the experts with rows need
-  // them; the rest of the grid exits at once.  Every expert gets its fewest blocks (a block owns at most
-  // 32 n-tiles) or its share by weight of all the blocks, whichever is more (the shares by weight are then
-  // scaled down to what is left).  Blocks [lo, hi) of the experts of every chunk; returns the blocks used.
+  // One table's shares: blocks [lo, hi) of the experts of every chunk; returns the blocks used.
   auto shares = [&](const PlanSpec& p, int (&lo)[kChunks], int (&hi)[kChunks]) {
-    const int base = (p.NT + 31) / 32, total = min(p.B, max(p.target, n_active * base)), extra = total - n_active * base;
+    const int base = plan_least(p), total = plan_total(p, n_active), extra = total - n_active * base;
     int claim[kChunks], incl[kChunks], over = 0, act = 0;    // claims on the blocks beyond the fewest, summed up to here
 #pragma unroll
     for (int i = 0; i < kChunks; ++i) {
       if (64 * i >= E) continue;
-      claim[i] = max(0, int(uint32_t(total * weight[i]) / uint32_t(max(wsum, 1))) - (cnt[i] > 0 ? base : 0));
+      claim[i] = plan_claim(total, weight[i], wsum, cnt[i] > 0 ? base : 0);
       incl[i] = over + scan(claim[i]);
       over = __shfl(incl[i], 63);
     }
@@ -72,8 +89,8 @@ __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, con
       if (64 * i >= E) continue;
       const int first = (act + __popcll(active[i] & below)) * base;
       if (cnt[i] > 0) {
-        lo[i] = first + (over > 0 ? int(uint32_t(extra * (incl[i] - claim[i])) / uint32_t(over)) : 0);
-        hi[i] = first + base + (over > 0 ? int(uint32_t(extra * incl[i]) / uint32_t(over)) : 0);
+        lo[i] = first + plan_part(extra, incl[i] - claim[i], over);
+        hi[i] = first + base + plan_part(extra, incl[i], over);
       }
       act += __popcll(active[i]);
     }
@@ -85,7 +102,7 @@ __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, con
   if (other.plan != nullptr) {
     shares(other, olo, ohi);
 #pragma unroll
-    for (int i = 0; i < kChunks; ++i) slots[i] = min(ohi[i] - olo[i], other.NT);
+    for (int i = 0; i < kChunks; ++i) slots[i] = dec::ha_slots(ohi[i] - olo[i], other.NT);
   }
 #pragma unroll
   for (int i = 0; i < kChunks; ++i) {
