@@ -172,6 +172,11 @@ __global__ __launch_bounds__(64 * NW) void gate_logits_kernel(const uint16_t* __
     }
   };
   const bool whole = chunks == 4 * NW * per && per % kBatch == 0, peaks = tok_exp != nullptr && e0 == 0;
+  // The magnitudes' bits, or none.  A test of `peaks` in the loop is a branch between groups of products that nothing moves
+  // across: with one tile two products (route() of E = 64, H = 1024, branches / none: T = 2048 18.3 / 14.9 us, 4096
+  // 30.2 / 24.3), so none there; with four tiles eight, and the batches' loads then stay where they are written (E = 128,
+  // H = 2048: T = 2048 29.9 / 36.5, 4096 52.9 / 57.6), so that form keeps them.
+  const uint32_t peak_lo = peaks ? 0x7fffu : 0u, peak_hi = peaks ? 0x7fff0000u : 0u;
   auto multiply = [&](auto WHOLE_, int c0, const Batch& b) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
@@ -184,7 +189,7 @@ __global__ __launch_bounds__(64 * NW) void gate_logits_kernel(const uint16_t* __
           const uint4 xv = b.x[r][u], wv = b.w[r][u];
           const uint32_t xa[4] = {xv.x, xv.y, xv.z, xv.w}, wa[4] = {wv.x, wv.y, wv.z, wv.w};
           xj[r] = in ? xa[j] : 0u; wj[r] = in ? wa[j] : 0u;
-          if (peaks) top[r] = max(top[r], max(xj[r] & 0x7fffu, (xj[r] >> 16) & 0x7fffu));
+          if (R == 1 || peaks) top[r] = max(top[r], max(xj[r] & peak_lo, (xj[r] & peak_hi) >> 16));
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {

@@ -1,5 +1,6 @@
-"""The grouped GEMM's k-steps with two slots of weights wait for the copy of the activations and leave the weights requested
-after it in flight: in the built code the loads between the two are exactly as many as the wait leaves out."""
+"""What the built code has to show of two kernels.  The grouped GEMM's k-steps with two slots of weights wait for the copy of the
+activations and leave the weights requested after it in flight: the loads between the two are exactly as many as the wait leaves
+out.  The tiled gate's products follow each other without branches."""
 import os
 import re
 import struct
@@ -11,7 +12,16 @@ from paper_2512_17073_amd import build, binding
 LLVM = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build._hipcc()))), "llvm", "bin")
 
 
-def _gfx950_code(tmp_path):
+def _functions(tmp_path, kernel):
+    """(name, instructions) of the kernel's instantiations in the built library."""
+    co = tmp_path / "kernel.co"
+    co.write_bytes(_gfx950_code(tmp_path, kernel))
+    text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(co)], capture_output=True, text=True, check=True).stdout
+    for name, body in re.findall(r"^[0-9a-f]+ <(\S*%s\S*)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)" % kernel, text, re.S | re.M):
+        yield name, [ln.split("//")[0].strip() for ln in body.splitlines()]
+
+
+def _gfx950_code(tmp_path, kernel):
     amd.lib()                                             # (raises if the library is not built)
     fat = str(tmp_path / "fat")
     subprocess.run([os.path.join(LLVM, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat, binding.LIB_PATH, str(tmp_path / "copy")], check=True)
@@ -21,20 +31,16 @@ def _gfx950_code(tmp_path):
         for _ in range(struct.unpack_from("<Q", data, m.start() + 24)[0]):
             off, size, n = struct.unpack_from("<QQQ", data, at)
             code = data[m.start() + off:m.start() + off + size]
-            if b"gfx950" in data[at + 24:at + 24 + n] and b"qgemm_tile_kernel" in code:
+            if b"gfx950" in data[at + 24:at + 24 + n] and kernel.encode() in code:
                 return code
             at += 24 + n
-    raise AssertionError("no gfx950 code with the grouped GEMM in the library")
+    raise AssertionError(f"no gfx950 code with {kernel} in the library")
 
 
 def test_waits_leave_exactly_the_next_weights_in_flight(tmp_path):
-    co = tmp_path / "ffn.co"
-    co.write_bytes(_gfx950_code(tmp_path))
-    text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(co)], capture_output=True, text=True, check=True).stdout
     found = {}
-    for name, body in re.findall(r"^[0-9a-f]+ <(\S*qgemm_tile_kernel\S*)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", text, re.S | re.M):
+    for name, lines in _functions(tmp_path, "qgemm_tile_kernel"):
         loads = None                                      # weight loads since the last copy to LDS (None: not known)
-        lines = [ln.split("//")[0].strip() for ln in body.splitlines()]
         for i, ln in enumerate(lines):
             wait = re.fullmatch(r"s_waitcnt vmcnt\((\d+)\)", ln)
             if re.match(r"buffer_load_.*\blds$", ln):
@@ -46,3 +52,20 @@ def test_waits_leave_exactly_the_next_weights_in_flight(tmp_path):
                 found[name] = found.get(name, 0) + 1
     # 2, 3 and 4 bits; W1|W3, W2 in two and in four n-tiles; with and without 3-bit factor pairs
     assert len(found) == 18 and min(found.values()) >= 2, found
+
+
+def test_products_of_the_tiled_gate_between_branches(tmp_path):
+    found = 0
+    for name, lines in _functions(tmp_path, "gate_logits_kernel"):
+        runs, run = [], 0                                 # matrix instructions between two branches
+        for ln in lines:
+            if ln.startswith("v_mfma"):
+                run += 1
+            elif ln.startswith(("s_cbranch", "s_branch")):
+                runs.append(run)
+                run = 0
+        runs = [r for r in runs + [run] if r > 0]
+        # one 16 x 16 tile: a batch of four 16-byte chunks; four tiles: a pair of values
+        assert runs and min(runs) >= (32 if "ILi8ELi1EE" in name else 8), (name, runs)
+        found += 1
+    assert found == 2
