@@ -241,7 +241,7 @@ typedef struct {
   uint64_t prefetch_hits;   /* hits on a slot that such a copy had filled and nothing had used yet        */
   uint64_t factor_copies;   /* factor pairs copied, on demand or ahead                                    */
   uint64_t bytes_h2d;       /* bytes copied host -> device by all of the above                            */
-  float    last_step_ms;    /* host wall time of the last step, read-backs included                       */
+  float    last_step_ms;    /* host wall time of the last step, the waits for the counts included        */
   float    last_copy_ms;    /* first to last copy of the last step on the copy stream (0: none)           */
 } moe_lrc_stack_stats;
 /* Counters since moe_lrc_stack_create (or the last reset); waits for the last step's copies. */
