@@ -712,6 +712,28 @@ int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hi
   const RouteArgs route{L->d_wg, L->has_bias ? L->d_bias : nullptr, idx, tw, tok_exp, L->cfg.renormalize};
   const bool pooled = L->cfg.residency == MOE_LRC_POOLED;
   const RouteGuess guess = pooled ? pool_guess(L) : RouteGuess{nullptr, nullptr, nullptr};
+  // Shared experts need nothing from the router: with resident weights they run on the layer's side
+  // stream beside the routed experts (joined before the combine).  In staged
+  // mode the side stream carries the copies and the shared experts follow the routed ones.
+  // They are forked before the routing where the routed experts' fused projection takes the decode flavour: its blocks take whole
+  // CUs, and shared experts that start a little later than it wait for its end (two preparing launches decided that by
+  // two microseconds).  Forked after the grouping / before the routing, us: DeepSeek shape, 3 bits, T = 16 120 / 118, 55 149 / 133, 128 168 / 156,
+  // 400 197 / 185, 2 bits T = 1 80 / 74, 55 136 / 119; 60 experts, Top-4, 1024 x 1024, T = 64 114 / 95; 16 experts, 1024 x 3072, T = 512
+  // 141 / 141.  With the grouped GEMM the grouping's launches would wait behind the shared GEMMs: 8 experts, Top-2, hidden =
+  // FFN = 2048, T = 1400 184 / 192, 2048 237 / 268; 60 experts, Top-4, 2048 x 1408, T = 2048 352 / 365.
+  const bool fork = L->cfg.n_shared > 0 && L->cfg.residency == MOE_LRC_RESIDENT;
+  const bool fork_first = (T * L->cfg.top_k + L->cfg.n_experts - 1) / L->cfg.n_experts <= kDecodeMaxRows13;
+  const void* y_shared = L->cfg.n_shared > 0 ? b + w.sh_y : nullptr;
+  auto fork_shared = [&]() -> int {
+    if (!fork) return MOE_LRC_OK;
+    LRC_HIP(hipEventRecord(L->ev_fork, s));
+    LRC_HIP(hipStreamWaitEvent(L->side, L->ev_fork, 0));
+    const int rc = run_shared(L, x, T, b, L->side);
+    if (rc) return rc;
+    LRC_HIP(hipEventRecord(L->ev_join, L->side));
+    return MOE_LRC_OK;
+  };
+  if (fork_first && (rc = fork_shared())) return rc;
   if (!fused_route) LRC_HIP(launch_route(L, x, T, idx, tw, nullptr, tok_exp, s, guess));
   else if (guess.layer) LRC_HIP(launch_route(guess.layer, x, T, guess.idx, guess.w, nullptr, nullptr, s));
   if (mk) LRC_HIP(hipEventRecord(L->marks[MOE_LRC_STAGE_PERMUTE], s));
@@ -719,18 +741,7 @@ int forward_impl(moe_lrc_layer* L, const void* x, int T, void* out, void* ws, hi
     LRC_HIP(launch_permute(L, idx, T, (int32_t*)(b + w.counts), offsets, row_pair, pair_row,
                            (int32_t*)(b + w.comp_counts), s));
   if (mk) LRC_HIP(hipEventRecord(L->marks[MOE_LRC_STAGE_PREP], s));
-  // Shared experts need nothing from the router: with resident weights they run on the layer's side
-  // stream beside the routed experts (forked here, joined before the combine; forked before the routing instead, the
-  // DeepSeek shape takes 197 us at T = 512 against 191: the grouping's launches wait behind the shared GEMMs).  In staged
-  // mode the side stream carries the copies and the shared experts follow the routed ones.
-  const bool fork = L->cfg.n_shared > 0 && L->cfg.residency == MOE_LRC_RESIDENT;
-  const void* y_shared = L->cfg.n_shared > 0 ? b + w.sh_y : nullptr;
-  if (fork) {
-    LRC_HIP(hipEventRecord(L->ev_fork, s));
-    LRC_HIP(hipStreamWaitEvent(L->side, L->ev_fork, 0));
-    if ((rc = run_shared(L, x, T, b, L->side))) return rc;
-    LRC_HIP(hipEventRecord(L->ev_join, L->side));
-  }
+  if (!fork_first && (rc = fork_shared())) return rc;
   // (the K-block partial sums of a decode-flavour W2 go to the combine as they are: no pass that
   // adds them into bf16 rows first)
   int kblocks = 1;

@@ -1189,8 +1189,6 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
 // flavour up to 24 rows per expert; beyond that the grouped GEMM as soon as it is efficient: the
 // fused W1|W3 from about 40 rows per expert on, W2 (whose grid has few column blocks) once its grid
 // of (128-row chunk, 256 columns) blocks covers the 256 CUs.
-constexpr int kDecodeMaxRows13 = 40;
-
 // bit 0: W1|W3 takes the decode flavour, bit 1: W2 does
 static int decode_parts(const FfnArgs& f) {
   // expected rows per expert under uniform routing decides the flavour of each projection

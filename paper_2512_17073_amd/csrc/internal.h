@@ -241,7 +241,8 @@ hipError_t launch_expert_ffn(const FfnArgs& a, hipStream_t s);
 // keep_partials that many fp32 partial sums [kb][rows][H] in y_part
 int decode_w2_kblocks(const FfnArgs& a);
 size_t decode_ha_bytes(const FfnArgs& a);   // what the part sums of (h A2) take of ha_bytes (0: that form is not taken)
-// bit 0: the fused W1|W3 projection takes the grouped GEMM (else the decode flavour), bit 1: W2 does
+// bit 0: the fused W1|W3 projection takes the grouped GEMM (else the decode flavour, up to this many expected rows per expert), bit 1: W2 does
+constexpr int kDecodeMaxRows13 = 40;
 int expert_ffn_path(const FfnArgs& a);
 // once per device, before the first launch: lets the FFN kernels use the whole LDS of a CU
 hipError_t ffn_init_device();
