@@ -1167,7 +1167,9 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   // Four n-tiles per wavefront use a fragment of activations twice as often as two (with two the LDS reads are the
   // bound), but make blocks twice as large: two only while four make fewer blocks than there are CUs.  Whole layer, four / two
   // (us): Mixtral shape T = 1024 (320 blocks of four) 840 / 874, 1500 (432) 1167 / 1197, 2048 (576) 1420 / 1461; 700 (240) 650 / 646;
-  // DeepSeek T = 512 (768) 187 / 196; Qwen3 T = 1500 (1264) 283 / 286, 4096 (2560) 532 / 565.
+  // DeepSeek T = 512 (768) 187 / 196; Qwen3 T = 1500 (1264) 283 / 286, 4096 (2560) 532 / 565.  At 4 bits, where four spill: Mixtral
+  // T = 850 (272) 723 / 727, 960 (304) 802 / 850, 2048 1521 / 1541; DeepSeek T = 512 207 / 212; Qwen3 T = 1500 287 / 301; 3072 x 3072,
+  // 8 experts, T = 1050 (240) 205 / 202, 1400 (300) 259 / 264.  The one loss beyond the line: 2048 x 1408, 16 experts, T = 1600 (264) 142 / 140.
   // (expected number of chunks: about half of the experts end with a partly filled one)
   const int chunks = std::max(1, f.offsets ? f.total_rows / kBM + (f.n_exp + 1) / 2 : f.n_exp * ((f.T + kBM - 1) / kBM));
   const bool q3 = comp && f.q3;
