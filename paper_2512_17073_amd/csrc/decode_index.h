@@ -16,10 +16,11 @@ constexpr int kSpareUnits = 2048;     // 16-byte units behind them (32 KB): (in 
 constexpr int kRing = 2;              // ring slots of a wavefront (each holds one k-step of two streams)
 constexpr int kStreams = 2;           // streams of a slot: (W1, W3) tiles of one n-tile, or two n-tiles of W2
 
-// A block's n-tiles: block b of the G that share an expert owns tiles [t0, t1).
+// A block's n-tiles: block b of the G that share an expert owns tiles [t0, t1).  (G * NT stays far below 2^31: both are at
+// most a few thousand times the 32 n-tiles of a block.)
 LRC_HD void block_tiles(int b, int G, int NT, int& t0, int& t1) {
-  t0 = (int)((long long)b * NT / G);
-  t1 = (int)((long long)(b + 1) * NT / G);
+  t0 = (int)(uint32_t(b) * uint32_t(NT) / uint32_t(G));
+  t1 = (int)(uint32_t(b + 1) * uint32_t(NT) / uint32_t(G));
 }
 
 // Work units of a block: an n-tile of both projections (DUAL) or a pair of adjacent n-tiles (W2).
@@ -29,109 +30,66 @@ LRC_HD int unit_slots(bool dual, int mt) { (void)mt; return dual ? 2 : 1; }
 // n-tiles a block can own
 LRC_HD int max_block_tiles(int mt) { (void)mt; return 32; }
 
-// Wavefronts that share one unit, each taking every kw-th k-step (power of two, 1..16).
-LRC_HD int waves_per_unit(int units) {
-  int kw = 1;
-  while (kw < kWaves && units * kw * 2 <= kWaves) kw *= 2;
-  return kw;
-}
+// Wavefronts that share one unit, each taking every kw-th k-step: the largest power of two kw with units * kw <= 16, at least 1.
+LRC_HD int waves_per_unit_log2(int units) { return units <= 1 ? 4 : units > 8 ? 0 : __builtin_clz(uint32_t(units - 1)) - 28; }
 
 // n-tile of stream m of unit u (block-relative unit index): DUAL: tile t0 + u for both streams;
 // W2: tiles t0 + 2u and t0 + 2u + 1.
 LRC_HD int stream_tile(int t0, int u, int m, bool dual) { return dual ? t0 + u : t0 + 2 * u + m; }
 
-// Steps of a wavefront, in order: [phase][unit slot][own k-step], then [unit slot][own rank step];
-// each innermost segment is padded to a multiple of the ring depth, so that ring slots are indexed
-// statically.
+// A wavefront walks segments: (phase ph, own unit ts), ph = 0 .. n_ph - 1 over the k-steps of a staging phase, then ph = n_ph
+// over the rank steps.  Own step `si` of a segment is its step si * kw + kwi; a segment is walked in whole turns of the
+// ring, so that ring slots are indexed statically, and while a turn is multiplied the next turn, of the same segment or
+// of the one after it, is fetched.  No step is walked that only pads: a segment's turns follow from its own length.
 struct StepPlan {
-  int TS;        // unit slots
   int KP;        // k-steps per phase (16 with one row tile, 8 with two)
   int n_ph;      // phases of this K-block
-  int SP;        // padded own k-steps per (unit slot, phase) segment
-  int n_reg;     // regular steps in all
-  int LSS;       // padded own rank steps per unit slot
-  int LSP;       // padded rank steps in all
 };
-LRC_HD StepPlan step_plan(int KSl, int mt, int kw, int LS, bool dual) {
+LRC_HD StepPlan step_plan(int KSl, int mt) {
   StepPlan p;
-  p.TS = unit_slots(dual, mt);
   p.KP = (kLdsUnits / 512) / mt;
   p.n_ph = (KSl + p.KP - 1) / p.KP;
-  const int spw = (p.KP + kw - 1) / kw;
-  p.SP = (spw + kRing - 1) / kRing * kRing;
-  p.n_reg = p.n_ph * p.TS * p.SP;
-  p.LSS = ((LS + kw - 1) / kw + kRing - 1) / kRing * kRing;
-  p.LSP = p.TS * p.LSS;
   return p;
 }
+// Units of a wavefront of group grp (0, 1 or 2: units grp and grp + groups).
+LRC_HD int own_units(int grp, int groups, int units, bool dual) { return (grp < units ? 1 : 0) + (dual && grp + groups < units ? 1 : 0); }
 
-// What step n of a wavefront (group grp of `groups`, k-share kwi of kw) reads.
+struct Segment {
+  int unit;      // block-relative unit
+  int base;      // absolute k-step of its first step (k-steps)
+  int len;       // steps, shared by kw wavefronts
+  bool lr;       // rank steps of the B factor (else k-steps of packed codes)
+};
+// own: units of the wavefront (own_units); beyond the last segment (ph > n_ph, or no rank steps) the length is zero
+LRC_HD Segment segment(int ph, int ts, int own, const StepPlan& p, int grp, int groups, int ks_lo, int KSl, int LS) {
+  Segment s;
+  const int left = KSl - ph * p.KP;
+  s.unit = grp + ts * groups;
+  s.base = ks_lo + ph * p.KP;
+  s.lr = ph >= p.n_ph;
+  s.len = ts >= own ? 0 : ph < p.n_ph ? (left < p.KP ? left : p.KP) : ph == p.n_ph ? LS : 0;
+  return s;
+}
+// ... and own steps that are walked, whole turns of the ring.
+LRC_HD int segment_steps(int len, int kw_log2) { return ((len + (kRing << kw_log2) - 1) >> (kw_log2 + 1)) * kRing; }
+static_assert(kRing == 2, "the shift above");
+
+// What own step si of a segment reads (k-share kwi of 1 << kw_log2).
 struct StepRef {
   bool reg;      // a k-step of packed codes (else a rank step, or nothing)
   bool lr;       // a rank step of the B factor
-  int ts;        // unit slot
   int unit;      // block-relative unit
   int ks;        // absolute k-step (reg)
-  int kl;        // k-step within the phase (reg)
-  int st;        // rank step (lr)
+  int st;        // step within the segment: k-step within the phase (reg), rank step (lr)
 };
-LRC_HD StepRef step_ref(int n, const StepPlan& p, int grp, int groups, int kwi, int kw, int units, int ks_lo, int KSl,
-                        int LS, bool dual) {
-  StepRef r{};
-  const int TS = p.TS;
-  (void)dual;
-  if (n < p.n_reg) {
-    const int seg = n / p.SP, si = n - seg * p.SP, ph = seg / TS;
-    r.ts = seg - ph * TS;
-    r.unit = grp + r.ts * groups;
-    r.kl = si * kw + kwi;
-    r.ks = ks_lo + ph * p.KP + r.kl;
-    r.reg = r.unit < units && r.kl < p.KP && ph * p.KP + r.kl < KSl;
-  } else {
-    const int l = n - p.n_reg;
-    r.ts = p.LSS > 0 ? l / p.LSS : 0;
-    r.unit = grp + r.ts * groups;
-    r.st = (p.LSS > 0 ? l - r.ts * p.LSS : 0) * kw + kwi;
-    r.lr = l < p.LSP && r.unit < units && r.st < LS;
-  }
+LRC_HD StepRef step_ref(const Segment& s, int si, int kwi, int kw_log2) {
+  StepRef r;
+  r.unit = s.unit;
+  r.st = (si << kw_log2) + kwi;
+  r.ks = s.base + r.st;
+  r.reg = !s.lr && r.st < s.len;
+  r.lr = s.lr && r.st < s.len;
   return r;
-}
-
-// The same sequence walked one step at a time, without divisions: the kernel fetches the steps
-// 0, 1, 2, ... of a pass in order, two of them past the last one.  cursor_ref gives what step_ref
-// gives for the cursor's step (for a step that reads nothing only `reg` and `lr`, both false, are
-// meant to agree).
-struct StepCursor {
-  int part;      // 0: k-steps, 1: rank steps
-  int ph;        // phase (k-steps)
-  int ts;        // unit slot (past the last one: nothing left)
-  int si;        // index within the (phase, unit slot) or (unit slot) segment
-};
-LRC_HD StepCursor cursor_start() { return StepCursor{0, 0, 0, 0}; }
-LRC_HD StepRef cursor_ref(const StepCursor& c, const StepPlan& p, int grp, int groups, int kwi, int kw, int units, int ks_lo,
-                          int KSl, int LS) {
-  StepRef r{};
-  r.ts = c.ts;
-  r.unit = grp + c.ts * groups;
-  const int own = c.si * kw + kwi;
-  if (c.part == 0) {
-    r.kl = own;
-    r.ks = ks_lo + c.ph * p.KP + own;
-    r.reg = r.unit < units && own < p.KP && c.ph * p.KP + own < KSl;
-  } else {
-    r.st = own;
-    r.lr = c.ts < p.TS && c.si < p.LSS && r.unit < units && own < LS;
-  }
-  return r;
-}
-LRC_HD void cursor_advance(StepCursor& c, const StepPlan& p) {
-  ++c.si;
-  if (c.si == (c.part ? p.LSS : p.SP)) { c.si = 0; ++c.ts; }
-  if (c.part == 0 && c.ts == p.TS) {
-    c.ts = 0;
-    ++c.ph;
-    if (c.ph == p.n_ph) c.part = 1;
-  }
 }
 
 // Byte offsets of a lane's loads of one stream of a step (the hardware range-checks offset + size
@@ -169,6 +127,10 @@ constexpr int kZeroRows = 16;
 LRC_HD int staged_row(int rin, int r, int mt, int rowl, int cnt, int in_rt) {
   return r + 16 * mt + rowl < cnt ? rin + 16 * mt + rowl : in_rt - kZeroRows + rowl;
 }
+
+// Lane group (64 inputs) of k-step ks that lane group q stages: its own, or past K (a multiple of 64) the k-step's last one below
+// it (the padded weights there are exact zeros, any finite value will do).
+LRC_HD int staged_group(int ks, int q, int K) { const int left = K / kLaneK - 4 * ks; return q < left ? q : left - 1; }
 
 // (h A2) of the fused projection's own columns, left by every block for the W2 launch (ranks up to kHaRank):
 // a 16-column factor tile rt of A2 meets the 16 columns of n-tile `tile` as the operand of a 16x16x16

@@ -209,13 +209,6 @@ __device__ inline void rank_frag_source(int v, int lane, bool dual, int& m, int&
   else { m = 0; grp = v + 2 * h; }
 }
 
-// Waits for all loads of this wavefront but the last N, then for the block.
-template <int N> __device__ inline void wait_loads_barrier_but() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | (N >> 4 << 14));
-  __syncthreads();
-}
-
 // Codes and metadata of one k-step of a wavefront's two n-tiles.
 template <int BITS, int NM, int NTW> struct Slot2 { Slot<BITS, NM> t[NTW]; };
 

@@ -131,6 +131,13 @@ __device__ inline void wait_loads_barrier() {
   __syncthreads();
 }
 
+// Waits for all loads of this wavefront but the last N, then for the block.
+template <int N> __device__ inline void wait_loads_barrier_but() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | (N >> 4 << 14));
+  __syncthreads();
+}
+
 // A pointer into global memory whose provenance the compiler cannot see (read from a table): loads through a
 // generic pointer become flat ones, which count in two counters and make every wait one for all loads.
 template <class T> using GlobalPtr = const __attribute__((address_space(1))) T*;
@@ -142,6 +149,12 @@ template <class T> __device__ inline const T* uniform_ptr(const T* p) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v)), hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
   return reinterpret_cast<const T*>((uint64_t(hi) << 32) | lo);
 }
+
+// What no kernel writes while it is read, at a wave-uniform address: loads that go to scalar registers, without a wait between them.
+typedef const __attribute__((address_space(4))) ExpertDesc* ConstDesc;
+__device__ inline ConstDesc const_desc(const ExpertDesc* d) { return reinterpret_cast<ConstDesc>(reinterpret_cast<uintptr_t>(d)); }
+typedef const __attribute__((address_space(4))) int32_t* ConstI32;
+__device__ inline ConstI32 const_i32(const int32_t* p) { return reinterpret_cast<ConstI32>(reinterpret_cast<uintptr_t>(p)); }
 
 // The argument block of a kernel whose only (or first) argument is a KArgs, read from memory again where it is
 // used: without this every field is loaded at the kernel's start and held in scalar registers, and those

@@ -50,54 +50,123 @@ using namespace dec;
 // the unit's code dword in the slot's metadata register and the lane's half of the unit's metadata in
 // its first four code registers, and is dequantized into the fp16 unit before it is used.
 // HA: (h A2) is left by the fused projection's blocks and added up by those of W2 (KArgs::ha).
+// A pass's start is what a launch of short streams consists of: with one k-step to multiply, this kernel took 14 us, most of them
+// in five dependent reads of the expert's table entry, 64-bit divisions, and code that every wavefront ran once.  So: one level
+// of loads from the block's entry to the expert's (all of it read at once, into scalar registers), the activations requested
+// before its pointers have arrived, no division, and one copy of the code that multiplies and fetches (a straight-line
+// kilobyte that runs once costs 0.2 us of instruction fetch beside its issue).
 template <int BITS, bool DUAL, int MT, bool Q3, bool HA>
-__device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int e, const int r0, const int cnt,
-                                            const int b, const int G, const int slots) {
+__device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const PlanEntry& pe) {
   constexpr int NS = kStreams;
   constexpr int TS = DUAL ? 2 : 1;
   constexpr int NC = Extract<BITS>::kClasses;
   constexpr int RING = kRing;
-  const ExpertDesc& d = a.desc[e];
+  const int e = pe.e, r0 = pe.r0, cnt = pe.cnt, t0 = pe.t0, t1 = pe.t1;
   const int th = threadIdx.x, lane = th & 63;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
-  const int q = lane >> 4, c = lane & 15, rowl = th & 15;
+  const int q = lane >> 4, c = lane & 15;
+  // the expert's table entry: everything this block needs of it, requested together
+  const ConstDesc d = const_desc(a.desc + e);
+  const int has_factors = d->has_factors, q3 = d->q3, rank2 = d->rank[2];
+  const int comp = *const_i32((a.comp_rows ? a.comp_rows : &a.desc->q3) + (a.comp_rows ? e : 0));
+  const uint32_t* codes[NS] = {d->codes[DUAL ? 0 : 2], d->codes[DUAL ? 1 : 2]};
+  const uint32_t* metas[NS] = {d->meta[DUAL ? 0 : 2], d->meta[DUAL ? 1 : 2]};
+  const _Float16* bfs[NS] = {d->bf[DUAL ? 0 : 2], d->bf[DUAL ? 1 : 2]};
+  const uint32_t* bfcs[NS] = {d->bfc[DUAL ? 0 : 2], d->bfc[DUAL ? 1 : 2]};
+  const int ranks[NS] = {d->rank[DUAL ? 0 : 2], d->rank[DUAL ? 1 : 2]};
+  const float lam[2] = {d->inv_lambda[DUAL ? 0 : 2], d->inv_lambda[DUAL ? 1 : 2]};
   // (x A1 | x A3) kept per token (ranks up to kXaTokensRank: its fragments are at most one per wavefront): the token
   // of the row whose part of a fragment this lane copies, on its way while the expert's table entry is read
   int token = -1;
   if constexpr (DUAL) {
-    const KernArgs ka = kern_args();
-    if (ka->p_tokens > 0) token = ka->row_tok[r0 + min(16 * (wave % MT) + c, cnt - 1)];
+    if (a.p_tokens > 0) token = a.row_tok[r0 + min(16 * (wave % MT) + c, cnt - 1)];
   }
 
-  // this block's n-tiles and how their units are dealt to the 16 wavefronts
-  int t0, t1;
-  block_tiles(b, G, a.NT, t0, t1);
+  // how the block's units are dealt to the 16 wavefronts
   const int nt_b = t1 - t0;
-  if (nt_b == 0) return;
   const int units = block_units(nt_b, DUAL);
-  const int kw = waves_per_unit(units);
-  const int groups = kWaves / kw, grp = wave / kw, kwi = wave % kw;
+  const int kwl = waves_per_unit_log2(units), kw = 1 << kwl;
+  const int groups = kWaves >> kwl, grp = wave >> kwl, kwi = wave & (kw - 1), own = own_units(grp, groups, units, DUAL);
 
   // this block's K-block: k-steps ks_lo .. ks_lo + KSl - 1
   const int kb = blockIdx.z, ks_lo = kb * a.kb_steps, KSl = min(a.KS, ks_lo + a.kb_steps) - ks_lo;
+  const StepPlan sp = step_plan(KSl, MT);
+  const int KP = sp.KP;
   const uint32_t code_bytes = uint32_t(a.KS) * a.NT * (kWave * 2 * BITS * 4), meta_bytes = uint32_t(a.G) * a.NT * kTileN * 4;
+
+  // (what a later pass or phase forms again is formed there, not kept in registers from the start of the block)
+  auto again = [](int v) { asm volatile("" : "+s"(v)); return v; };
+  // A phase is MT * nk * 8 fragments of 64 units (16 rows x 4 column groups of one MFMA sub-step);
+  // four 256-byte runs of the operand-order buffer become 1 KB of LDS, lane-linear.  Rows past the
+  // expert's last one read the zero rows at the end of the buffer (staged_row): their output
+  // columns are never stored.  The copy is asynchronous and takes no registers: each lane's 16 bytes go from
+  // global memory straight to LDS (wave-uniform LDS base + 16 * lane), counted by vmcnt.  A lane's address is a
+  // wave-uniform base (k-step, sub-step) plus a 32-bit offset (column group, row) that is the same for every k-step but one
+  // that K ends in.
+  auto stage_issue = [&](const auto& A, int r, int ph, int nk) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    // first input row of this pass (shared experts all read the token rows 0..T-1)
+    const int rin = ((DUAL && !A.offsets) ? 0 : r0) + r;
+    const int s = wave & 7;                  // fragment (mt, kl, s): wavefront w takes s = w % 8, kl = w / 8, w / 8 + 2, ...
+    const size_t step = size_t(A.in_rt) * 32 * 16;       // bytes of a k-step
+    uint32_t row[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) row[mt] = uint32_t(staged_row(rin, r, mt, ln & 15, cnt, A.in_rt)) * 16u;
+    for (int kl = wave >> 3; kl < nk; kl += 2) {
+      const int ks = ks_lo + ph * KP + kl;
+      const uint8_t* base = reinterpret_cast<const uint8_t*>(A.in) + ks * step + size_t(s * 4) * (uint32_t(A.in_rt) * 16u);
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, 0xffffffffu, 0x00020000);
+      const uint32_t group = uint32_t(staged_group(ks, ln >> 4, A.K)) * (uint32_t(A.in_rt) * 16u);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rs, reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(xs + act_frag_unit(mt, kl, s, KP))), 16,
+            int(group + row[mt]), 0, 0, 0);
+    }
+  };
+  // (h A2) from the part sums of the fused projection's blocks: TPO threads share four columns of a row.
+  // The first kHaFirst parts are requested before anything else of the pass, the sums go
+  // to LDS as the fragments p_issue would copy.
+  constexpr int TPO = 8 / MT, kHaFirst = BITS == 4 ? 2 : 4;
+  constexpr bool joined = HA && !DUAL;      // (its fragments always fit behind the activations)
+  float4_t part[kHaFirst];
+  int pair_of_row = 0, ha_lo = 0, ha_hi = 0;
+  int hj = 0, hcol = 0, hrow = 0;
+  auto part_issue = [&](int r) {
+    const KernArgs ka = kern_args();
+    int ht_ = th;
+    asm volatile("" : "+v"(ht_));
+    hj = ht_ & (TPO - 1); hcol = (ht_ / TPO) & 7; hrow = ht_ / (8 * TPO);
+    const int row = r0 + min(r + hrow, cnt - 1);
+    ha_share(kb, gridDim.z, pe.slots, ha_lo, ha_hi);
+#pragma unroll
+    for (int i = 0; i < kHaFirst; ++i)
+      part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, 4 * hcol));
+    pair_of_row = ka->row_pair[row];
+  };
+  int row_se[MT];                             // the rows' exponents for the end of the pass
+  auto exp_issue = [&](const auto& A, int r) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) row_se[mt] = A.row_exp[(A.offsets ? r0 : 0) + min(r + 16 * mt + c, cnt - 1)];
+  };
+  // (the first pass's, on their way before the table entry's fields are used)
+  if constexpr (joined) part_issue(0);
+  stage_issue(a, 0, 0, min(KP, KSl));
+  exp_issue(a, 0);
+  __builtin_amdgcn_sched_barrier(0);
 
   // The rank-r term rides the same stream (B-factor units in place of packed codes, against (in A)
   // instead of the activations).  With K-blocks, every K-block meets the part of (in A) summed over
   // its own k-steps (the term is linear in it).  Each stream has the rank of its own projection; a
   // resource of the size its rank fills makes later steps read zeros.
-  const bool lowrank = a.rank > 0 && a.row_pair != nullptr && __builtin_amdgcn_readfirstlane(d.has_factors) != 0 &&
-                       __builtin_amdgcn_readfirstlane(a.comp_rows[e]) > 0;
+  const bool lowrank = a.rank > 0 && a.row_pair != nullptr && has_factors != 0 && comp > 0;
   int LSm[NS];
 #pragma unroll
-  for (int m = 0; m < NS; ++m) {
-    const int rk = __builtin_amdgcn_readfirstlane(d.rank[DUAL ? m : 2]);
-    LSm[m] = lowrank ? (min(rk, a.rank) + 31) / 32 : 0;
-  }
+  for (int m = 0; m < NS; ++m) LSm[m] = lowrank ? int(uint32_t(min(ranks[m], a.rank) + 31) / 32) : 0;
   const int LS = max(LSm[0], LSm[1]);
-  const float lam[2] = {d.inv_lambda[DUAL ? 0 : 2], d.inv_lambda[DUAL ? 1 : 2]};
   // 16-column tiles of (h A2) that this launch makes (fused projection) or adds up (W2)
-  const int ht = HA && lowrank ? (min(__builtin_amdgcn_readfirstlane(d.rank[2]), a.rank) + 15) / 16 : 0;
+  const int ht = HA && lowrank ? int(uint32_t(min(rank2, a.rank) + 15) / 16) : 0;
   const uint32_t bf_bytes_max = uint32_t(a.NT) * a.ls * 1024;
 
   __amdgpu_buffer_rsrc_t code_rs[NS], meta_rs[NS], bf_rs[NS], bc_rs[NS];
@@ -109,16 +178,14 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       if constexpr (Q3) bc_rs[m] = bc_rs[0];
       continue;
     }
-    const int mat = DUAL ? m : 2;
-    q3m[m] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
-    // (the pointers are read once, into scalar registers: a buffer resource must be wave-uniform)
-    code_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(uniform_ptr(d.codes[mat])), 0, code_bytes, 0x00020000);
-    meta_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(uniform_ptr(d.meta[mat])), 0, meta_bytes, 0x00020000);
+    q3m[m] = Q3 && ((q3 >> (DUAL ? m : 2)) & 1) != 0;
+    code_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(codes[m]), 0, code_bytes, 0x00020000);
+    meta_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(metas[m]), 0, meta_bytes, 0x00020000);
     // (3-bit pair: the B section's metadata, 128 bytes per rank step and group of four n-tiles)
-    bf_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(uniform_ptr(d.bf[mat])), 0,
+    bf_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(bfs[m]), 0,
                                                  q3m[m] ? uint32_t(a.NT / 4) * LSm[m] * 128 : uint32_t(a.NT) * LSm[m] * 1024, 0x00020000);
     if constexpr (Q3)     // the code dwords of a 3-bit pair's B units (no bytes for an fp16 pair: every read gives zero)
-      bc_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(uniform_ptr(q3m[m] ? d.bfc[mat] : d.codes[mat])), 0,
+      bc_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(q3m[m] ? bfcs[m] : codes[m]), 0,
                                                    q3m[m] ? uint32_t(a.NT) * LSm[m] * 256 : 0u, 0x00020000);
   }
   // (in A) fragments: [projection][rank step][row tile][lane].  Up to 32 of them sit behind the staged
@@ -133,166 +200,124 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
   // The fused projection's own columns of A2: the packed units (32 inputs each) u0 .. u0 + n_u - 1 of every
   // factor tile (3-bit pair: their code dwords, then the metadata of the n_q x 4 groups of 64 inputs from g0
   // on) are copied behind those fragments at the start of the first pass, where they fit; else read when used.
-  const bool q3_a2 = Q3 && ((__builtin_amdgcn_readfirstlane(d.q3) >> 2) & 1) != 0;
+  const bool q3_a2 = Q3 && ((q3 >> 2) & 1) != 0;
   const int u0 = t0 / 2, n_u = (t1 - 1) / 2 - u0 + 1, g0 = t0 / 4, n_q = ((t1 - 1) / 4 - g0) / 4 + 1;
   const bool a2_early = HA && DUAL && ht > 0 && !p_late && p_frags * 64 + (q3_a2 ? (n_u + n_q) * 16 : n_u * 64) * ht <= kSpareUnits;
+  auto as_lds = [](uint4* p) { return reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p)); };
+
+  // (in A) of a pass's rows: fp16 row-major in global memory, already multiplied by the
+  // projection's power-of-two pre-scale and zero for rows without the term.  Fragment
+  // (m, st, mt): lane (q, c) copies columns 32 st + 8 q .. + 7 of row 16 mt + c.  A row past the
+  // expert's last one is clamped to a valid row (its output column is never stored).
+  auto p_issue = [&](const auto& A, int r) {
+    const _Float16* P = reinterpret_cast<const _Float16*>(A.p) + size_t(kb) * A.total_rows * pitch;
+    for (int f = wave; f < p_frags; f += kWaves) {
+      const int mt = f % MT, g = f / MT, m = g >= LS ? 1 : 0, st = g - m * LS;
+      const int row = r0 + min(r + 16 * mt + c, cnt - 1);
+      const _Float16* src = P + size_t(row) * pitch + m * A.ls * 32 + 32 * st + 8 * q;
+      __builtin_amdgcn_global_load_lds(as_global<uint32_t>(src), as_lds(p_lds + p_frag_unit(m, st, mt, LS, MT)), 16, 0, 0);
+    }
+  };
+  // ... or kept per token (the projection's rows of every token, p_tokens > 0)
+  auto p_issue_tokens = [&](const auto& A, int r) {
+    if (wave >= p_frags) return;
+    const int mt = wave % MT, g = wave / MT, m = g >= LS ? 1 : 0, st = g - m * LS, pr = r + 16 * mt + c;
+    if (r > 0) token = A.row_tok[r0 + min(pr, cnt - 1)];
+    // (rows without the term read the row of zeros)
+    const int row = pr < cnt && token >= 0 ? e * A.p_tokens + token : A.n_exp * A.p_tokens;
+    const _Float16* src = reinterpret_cast<const _Float16*>(A.p) + row * pitch + m * A.ls * 32 + 32 * st + 8 * q;
+    __builtin_amdgcn_global_load_lds(as_global<uint32_t>(src), as_lds(p_lds + p_frag_unit(m, st, mt, LS, MT)), 16, 0, 0);
+  };
+  auto p_start = [&](const auto& A, int r) {
+    if (p_late || joined) return;
+    if (DUAL && A.p_tokens > 0) p_issue_tokens(A, r);
+    else p_issue(A, r);
+  };
+  auto p_join = [&](int r) {
+    if (LS == 0) return;                     // (ranks up to kHaRank: one rank step)
+    const KernArgs ka = kern_args();
+    const int row = r0 + min(r + hrow, cnt - 1), col = 4 * hcol;
+    const bool take = r + hrow < cnt && pair_of_row % ka->top_k < ka->top_n;
+    const float lam2 = const_desc(ka->desc + e)->xa_scale[2];
+    float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < kHaFirst; ++i)
+      if (ha_lo + hj + i * TPO < ha_hi) sum += part[i];
+    for (int sl = ha_lo + hj + kHaFirst * TPO; sl < ha_hi; sl += TPO)
+      sum += *reinterpret_cast<const float4_t*>(ka->ha + ha_part(sl, ka->total_rows, row, col));
+#pragma unroll
+    for (int dlt = 1; dlt < TPO; dlt *= 2)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], dlt);
+    if (hj == 0) {
+      half4_t v = half4_t{0, 0, 0, 0};
+      if (take && col < 16 * ht) v = half4_t{to_f16_sat(sum[0] * lam2), to_f16_sat(sum[1] * lam2), to_f16_sat(sum[2] * lam2), to_f16_sat(sum[3] * lam2)};
+      reinterpret_cast<half4_t*>(p_lds + p_frag_unit(0, 0, hrow >> 4, LS, MT) + (hcol >> 1) * 16 + (hrow & 15))[hcol & 1] = v;
+    }
+  };
+
+  // The steps of the wavefront's segments are fetched a turn of the ring ahead of their use (past the last one: zeros).
+  auto fetch = [&](Slot<BITS, NS>& sl, const Segment& seg, int si) {
+    const StepRef ref = step_ref(seg, si, kwi, kwl);
+#pragma unroll
+    for (int m = 0; m < NS; ++m) {
+      const int tile = stream_tile(t0, ref.unit, m, DUAL);
+      const LaneOffsets o = lane_offsets(ref, tile, tile < t1, lane, BITS, a.NT, a.group_shift, code_bytes, meta_bytes, bf_bytes_max,
+                                         Q3 && q3m[m]);
+      const bool lr = ref.lr;
+      const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(lr ? bf_rs[m] : code_rs[m], lr ? o.bf : o.code0, 0, 0);
+      sl.cw[m][0] = v0[0]; sl.cw[m][1] = v0[1]; sl.cw[m][2] = v0[2]; sl.cw[m][3] = v0[3];
+      if constexpr (BITS == 3) {
+        const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(code_rs[m], o.code1, 0, 0);
+        sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1];
+      } else if constexpr (BITS == 4) {
+        const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], o.code1, 0, 0);
+        sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1]; sl.cw[m][6] = v1[2]; sl.cw[m][7] = v1[3];
+      }
+      if constexpr (Q3) sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(lr ? bc_rs[m] : meta_rs[m], lr ? o.bc : o.meta, 0, 0);
+      else sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(meta_rs[m], o.meta, 0, 0);
+    }
+  };
+  const int last_ph = LS > 0 ? sp.n_ph : sp.n_ph - 1;
+  Segment seg = segment(0, 0, own, sp, grp, groups, ks_lo, KSl, LS);
+  Slot<BITS, NS> ring[RING];
+
+  // ---- start of the first pass: everything that is left is requested before anything is awaited ----
+  p_start(a, 0);
+  if (a2_early) {
+    uint4* dst = p_lds + p_frags * 64;
+    for (int f = wave; f < n_u * ht; f += kWaves) {      // (ht: 1 or 2)
+      const int rt = f >= n_u ? 1 : 0, unit = (rt * (a.N / 32) + u0 + f - rt * n_u) * kWave + lane;
+      if (q3_a2) __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d->af[2])) + unit, as_lds(dst + f * 16), 4, 0, 0);
+      else __builtin_amdgcn_global_load_lds(as_global<u32x4>(uniform_ptr(d->af[2])) + unit, as_lds(dst + f * 64), 16, 0, 0);
+    }
+    if (q3_a2)
+      for (int f = wave; f < n_q * ht; f += kWaves) {
+        const int rt = f >= n_q ? 1 : 0, g = min(g0 + 4 * (f - rt * n_q) + q, a.N / 64 - 1);
+        __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d->afm[2])) + (rt * (a.N / 64) + g) * 16 + c,
+                                         as_lds(dst + (n_u * ht + f) * 16), 4, 0, 0);
+      }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < RING; ++i) fetch(ring[i], seg, i);
+  __builtin_amdgcn_sched_barrier(0);
+  constexpr int kFetchLoads = NS * (BITS == 2 ? 2 : 3);
 
   for (int r = 0; r < cnt; r += 16 * MT) {
     // every pass computes all MT row tiles (a last pass with fewer rows computes columns nobody stores)
-    const StepPlan sp = step_plan(KSl, MT, kw, LS, DUAL);
-    const int KP = sp.KP;
-
-    // (the steps are fetched in order, RING of them ahead of their use and RING past the last one)
-    StepCursor cursor = cursor_start();
-    auto fetch = [&](Slot<BITS, NS>& sl) {
-      const StepRef ref = cursor_ref(cursor, sp, grp, groups, kwi, kw, units, ks_lo, KSl, LS);
-      cursor_advance(cursor, sp);
-#pragma unroll
-      for (int m = 0; m < NS; ++m) {
-        const int tile = stream_tile(t0, ref.unit, m, DUAL);
-        const LaneOffsets o = lane_offsets(ref, tile, tile < t1, lane, BITS, a.NT, a.group_shift, code_bytes, meta_bytes, bf_bytes_max,
-                                           Q3 && q3m[m]);
-        const bool lr = ref.lr;
-        const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(lr ? bf_rs[m] : code_rs[m], lr ? o.bf : o.code0, 0, 0);
-        sl.cw[m][0] = v0[0]; sl.cw[m][1] = v0[1]; sl.cw[m][2] = v0[2]; sl.cw[m][3] = v0[3];
-        if constexpr (BITS == 3) {
-          const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(code_rs[m], o.code1, 0, 0);
-          sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1];
-        } else if constexpr (BITS == 4) {
-          const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], o.code1, 0, 0);
-          sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1]; sl.cw[m][6] = v1[2]; sl.cw[m][7] = v1[3];
-        }
-        if constexpr (Q3) sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(lr ? bc_rs[m] : meta_rs[m], lr ? o.bc : o.meta, 0, 0);
-        else sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(meta_rs[m], o.meta, 0, 0);
-      }
-    };
-
-    // first input row of this pass (shared experts all read the token rows 0..T-1)
-    const int rin = ((DUAL && !a.offsets) ? 0 : r0) + r;
-
-    // A phase is MT * nk * 8 fragments of 64 units (16 rows x 4 column groups of one MFMA sub-step);
-    // four 256-byte runs of the operand-order buffer become 1 KB of LDS, lane-linear.  Rows past the
-    // expert's last one read the zero rows at the end of the buffer (staged_row): their output
-    // columns are never stored.  The copy is asynchronous and takes no registers: each lane's 16 bytes go from
-    // global memory straight to LDS (wave-uniform LDS base + 16 * lane), counted by vmcnt.
-    const uint4* in_units = reinterpret_cast<const uint4*>(a.in);
-    auto stage_issue = [&](int ph, int nk) {
-      const int s = wave & 7;                  // fragment (mt, kl, s): wavefront w takes s = w % 8, kl = w / 8, w / 8 + 2, ...
-      for (int mt = 0; mt < MT; ++mt)
-        for (int kl = wave >> 3; kl < nk; kl += 2) {
-          // (columns past K: the padded weights there are exact zeros, any finite value will do)
-          const int k8 = min((ks_lo + ph * KP + kl) * 32 + q * 8 + s, a.K / 8 - 1);
-          uint4* dst = xs + act_frag_unit(mt, kl, s, KP);
-          __builtin_amdgcn_global_load_lds(
-              reinterpret_cast<const __attribute__((address_space(1))) void*>(
-                  reinterpret_cast<uintptr_t>(in_units + act_unit(k8, staged_row(rin, r, mt, rowl, cnt, a.in_rt), a.in_rt))),
-              reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(dst)), 16, 0, 0);
-        }
-    };
-    // (in A) of this pass's rows: fp16 row-major in global memory, already multiplied by the
-    // projection's power-of-two pre-scale and zero for rows without the term.  Fragment
-    // (m, st, mt): lane (q, c) copies columns 32 st + 8 q .. + 7 of row 16 mt + c.  A row past the
-    // expert's last one is clamped to a valid row (its output column is never stored).
-    const _Float16* P = reinterpret_cast<const _Float16*>(a.p) + size_t(kb) * a.total_rows * pitch;
-    auto p_issue = [&]() {
-      for (int f = wave; f < p_frags; f += kWaves) {
-        const int mt = f % MT, g = f / MT, st = g % LS, m = g / LS;
-        const int row = r0 + min(r + 16 * mt + c, cnt - 1);
-        const _Float16* src = P + size_t(row) * pitch + m * a.ls * 32 + 32 * st + 8 * q;
-        __builtin_amdgcn_global_load_lds(
-            reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(src)),
-            reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p_lds + p_frag_unit(m, st, mt, LS, MT))), 16, 0, 0);
-      }
-    };
-
-    // (h A2) from the part sums of the fused projection's blocks: TPO threads share four columns of a row.
-    // The first kHaFirst parts are requested before anything else of the pass, the sums go
-    // to LDS as the fragments p_issue would copy.
-    constexpr int TPO = 8 / MT, kHaFirst = BITS == 4 ? 2 : 4;
-    constexpr bool joined = HA && !DUAL;      // (its fragments always fit behind the activations)
-    float4_t part[kHaFirst];
-    int pair_of_row = 0;
-    float lam2 = 0.f;
-    int hth = th;
-    asm volatile("" : "+v"(hth));            // (nothing of this is kept in registers from pass to pass)
-    const int hj = hth & (TPO - 1), hcol = (hth / TPO) & 7, hrow = hth / (8 * TPO);
-    int ha_lo, ha_hi;
-    ha_share(kb, gridDim.z, slots, ha_lo, ha_hi);
-    if constexpr (joined) {
+    if (r > 0) {
+      __syncthreads();                        // everyone is done with the previous pass's LDS
       const KernArgs ka = kern_args();
-      const int row = r0 + min(r + hrow, cnt - 1);
-#pragma unroll
-      for (int i = 0; i < kHaFirst; ++i)
-        part[i] = *reinterpret_cast<const float4_t*>(ka->ha + ha_part(max(min(ha_lo + hj + i * TPO, ha_hi - 1), 0), ka->total_rows, row, 4 * hcol));
-      pair_of_row = ka->row_pair[row];
-      lam2 = ka->desc[e].xa_scale[2];
+      const int ra = again(r);
+      if constexpr (joined) part_issue(ra);
+      stage_issue(*ka, ra, 0, min(KP, KSl));
+      p_start(*ka, ra);
+      exp_issue(*ka, ra);
     }
-    auto p_join = [&]() {
-      if (LS == 0) return;                     // (ranks up to kHaRank: one rank step)
-      const KernArgs ka = kern_args();
-      const int row = r0 + min(r + hrow, cnt - 1), col = 4 * hcol;
-      const bool take = r + hrow < cnt && pair_of_row % ka->top_k < ka->top_n;
-      float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < kHaFirst; ++i)
-        if (ha_lo + hj + i * TPO < ha_hi) sum += part[i];
-      for (int sl = ha_lo + hj + kHaFirst * TPO; sl < ha_hi; sl += TPO)
-        sum += *reinterpret_cast<const float4_t*>(ka->ha + ha_part(sl, ka->total_rows, row, col));
-#pragma unroll
-      for (int dlt = 1; dlt < TPO; dlt *= 2)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], dlt);
-      if (hj == 0) {
-        half4_t v = half4_t{0, 0, 0, 0};
-        if (take && col < 16 * ht) v = half4_t{to_f16_sat(sum[0] * lam2), to_f16_sat(sum[1] * lam2), to_f16_sat(sum[2] * lam2), to_f16_sat(sum[3] * lam2)};
-        reinterpret_cast<half4_t*>(p_lds + p_frag_unit(0, 0, hrow >> 4, LS, MT) + (hcol >> 1) * 16 + (hrow & 15))[hcol & 1] = v;
-      }
-    };
-
-    // ---- start of a pass: activations of phase 0, the (in A) fragments and the first packed tiles
-    //      are all requested before anything is awaited ----
-    if (r > 0) __syncthreads();               // everyone is done with the previous pass's LDS
-    bool by_rows = true;
-    if constexpr (DUAL) {
-      const KernArgs ka = kern_args();
-      by_rows = ka->p_tokens == 0;
-      if (!by_rows && wave < p_frags) {
-        // (in front of the staging, whose copies a wait for the token would be for as well)
-        const int mt = wave % MT, g = wave / MT, st = g % LS, m = g / LS, pr = r + 16 * mt + c;
-        if (r > 0) token = ka->row_tok[r0 + min(pr, cnt - 1)];
-        // (rows without the term read the row of zeros)
-        const int row = pr < cnt && token >= 0 ? e * ka->p_tokens + token : ka->n_exp * ka->p_tokens;
-        const _Float16* src = reinterpret_cast<const _Float16*>(ka->p) + row * pitch + m * ka->ls * 32 + 32 * st + 8 * q;
-        __builtin_amdgcn_global_load_lds(
-            reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(src)),
-            reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p_lds + p_frag_unit(m, st, mt, LS, MT))), 16, 0, 0);
-      }
-    }
-    stage_issue(0, min(KP, KSl));
-    if (!p_late && !joined && by_rows) p_issue();
-    int row_se[MT];                           // (the rows' exponents for the end of the pass)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) row_se[mt] = a.row_exp[(a.offsets ? r0 : 0) + min(r + 16 * mt + c, cnt - 1)];
-    if (a2_early && r == 0) {
-      uint4* dst = p_lds + p_frags * 64;
-      auto lds = [](uint4* p) { return reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p)); };
-      for (int f = wave; f < n_u * ht; f += kWaves) {
-        const int rt = f / n_u, unit = (rt * (a.N / 32) + u0 + f - rt * n_u) * kWave + lane;
-        if (q3_a2) __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d.af[2])) + unit, lds(dst + f * 16), 4, 0, 0);
-        else __builtin_amdgcn_global_load_lds(as_global<u32x4>(uniform_ptr(d.af[2])) + unit, lds(dst + f * 64), 16, 0, 0);
-      }
-      if (q3_a2)
-        for (int f = wave; f < n_q * ht; f += kWaves) {
-          const int rt = f / n_q, g = min(g0 + 4 * (f - rt * n_q) + q, a.N / 64 - 1);
-          __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d.afm[2])) + (rt * (a.N / 64) + g) * 16 + c,
-                                           lds(dst + (n_u * ht + f) * 16), 4, 0, 0);
-        }
-    }
-    Slot<BITS, NS> ring[RING];
-#pragma unroll
-    for (int i = 0; i < RING; ++i) fetch(ring[i]);
-    if constexpr (joined) p_join();
-    wait_loads_barrier();
+    if constexpr (joined) p_join(again(r));
+    if (r > 0) wait_loads_barrier();
+    else wait_loads_barrier_but<RING * kFetchLoads>();   // (the first turn of the ring stays in flight)
 
     float4_t acc[TS][MT][NS];
 #pragma unroll
@@ -301,7 +326,6 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int m = 0; m < NS; ++m) acc[ts][mt][m] = float4_t{0.f, 0.f, 0.f, 0.f};
-
     // a rank step of one unit: the slot holds B-factor units, which meet (in A) as they are
     auto compute_lr = [&](const Slot<BITS, NS>& cur, int st, float4_t (&ac)[MT][NS]) {
 #pragma unroll
@@ -310,8 +334,8 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
         half8_t bfrag = __builtin_bit_cast(half8_t, make_uint4(cur.cw[m][0], cur.cw[m][1], cur.cw[m][2], cur.cw[m][3]));
         if constexpr (Q3) {
           if (q3m[m]) {
-            const uint32_t own[4] = {cur.cw[m][0], cur.cw[m][1], cur.cw[m][2], cur.cw[m][3]};
-            bfrag = q3_unit_b(cur.mw[m], own, (c & 1) != 0);
+            const uint32_t mine[4] = {cur.cw[m][0], cur.cw[m][1], cur.cw[m][2], cur.cw[m][3]};
+            bfrag = q3_unit_b(cur.mw[m], mine, (c & 1) != 0);
           }
         }
 #pragma unroll
@@ -383,40 +407,48 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
       substep(std::integral_constant<int, 6>{}); substep(std::integral_constant<int, 7>{});
     };
 
+    // Slot i of the ring: consumed, then refilled a turn ahead, from this segment or from the one after it.
+    auto walk = [&](const Segment& next, auto&& use) {
+      const int steps = segment_steps(seg.len, kwl);
+#pragma unroll 1
+      for (int si = 0; si < steps; si += RING) {
+        const bool here = si + RING < steps;
+        const Segment from = {here ? seg.unit : next.unit, here ? seg.base : next.base, here ? seg.len : next.len, here ? seg.lr : next.lr};
+        const int fi = here ? si + RING : 0;
+#pragma unroll
+        for (int i = 0; i < RING; ++i) {
+          const int st = ((si + i) << kwl) + kwi;
+          if (st < seg.len) use(ring[i], st);
+          fetch(ring[i], from, fi + i);
+        }
+      }
+      seg = next;
+    };
+#pragma unroll 1
     for (int ph = 0; ph < sp.n_ph; ++ph) {
-      const int nk = min(KP, KSl - ph * KP);
       if (ph > 0) {
         __syncthreads();                      // everyone is done with the previous phase
-        stage_issue(ph, nk);
+        stage_issue(*kern_args(), again(r), ph, min(KP, KSl - ph * KP));
         wait_loads_barrier();
       }
 #pragma unroll
       for (int ts = 0; ts < TS; ++ts) {
-        const bool unit_ok = grp + ts * groups < units;
-        for (int si = 0; si < sp.SP; si += RING) {
-#pragma unroll
-          for (int i = 0; i < RING; ++i) {   // slot i: consumed, then refilled RING steps ahead
-            if (unit_ok && (si + i) * kw + kwi < nk) compute(ring[i], (si + i) * kw + kwi, acc[ts]);
-            fetch(ring[i]);
-          }
-        }
+        if (ts >= own) continue;
+        const int nts = ts + 1 < own ? ts + 1 : 0, nph = nts > 0 ? ph : ph < last_ph ? ph + 1 : r + 16 * MT < cnt ? 0 : sp.n_ph + 1;
+        walk(segment(nph, nts, own, sp, grp, groups, ks_lo, KSl, LS), [&](const Slot<BITS, NS>& cur, int kl) { compute(cur, kl, acc[ts]); });
       }
     }
-    if (p_late && LS > 0) {                   // many rank steps: their (in A) fragments replace the activations
-      __syncthreads();
-      p_issue();
-      wait_loads_barrier();
-    }
+    if (LS > 0) {                             // the rank steps (none unless this block adds the term)
+      if (p_late) {                           // many of them: their (in A) fragments replace the activations
+        __syncthreads();
+        p_issue(*kern_args(), again(r));
+        wait_loads_barrier();
+      }
 #pragma unroll
-    for (int ts = 0; ts < TS; ++ts) {         // the rank steps (none unless this block adds the term)
-      const bool unit_ok = grp + ts * groups < units;
-      for (int l0 = 0; l0 < sp.LSS; l0 += RING) {
-#pragma unroll
-        for (int i = 0; i < RING; ++i) {
-          const int st = (l0 + i) * kw + kwi;
-          if (unit_ok && st < LS) compute_lr(ring[i], st, acc[ts]);
-          fetch(ring[i]);
-        }
+      for (int ts = 0; ts < TS; ++ts) {
+        if (ts >= own) continue;
+        const int nts = ts + 1 < own ? ts + 1 : 0, nph = nts > 0 ? sp.n_ph : r + 16 * MT < cnt ? 0 : sp.n_ph + 1;
+        walk(segment(nph, nts, own, sp, grp, groups, ks_lo, KSl, LS), [&](const Slot<BITS, NS>& cur, int st) { compute_lr(cur, st, acc[ts]); });
       }
     }
 
@@ -449,10 +481,11 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
     for (int ts = 0; ts < TS; ++ts)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) hs[ts][mt] = half4_t{0, 0, 0, 0};
+    const int mine = kwi == 0 ? own : 0;
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts) {
       const int unit = gn + ts * groups;
-      if (kwi != 0 || unit >= units) continue;
+      if (ts >= mine) continue;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int row = r + 16 * mt + c;
@@ -535,7 +568,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
         }
       }
       __syncthreads();
-      const int slot = ha_slot(b, t0, G, ka->NT), used = min(groups, units);
+      const int slot = pe.own, used = min(groups, units);
       for (int i = tn; i < hn * MT * 64; i += 64 * kWaves) {
         float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
         for (int j = 0; j < used; j += 8) {    // (eight reads in flight)
@@ -557,20 +590,18 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const int
 template <int BITS, bool DUAL, bool Q3, bool HA>
 __global__ __launch_bounds__(64 * kWaves, 4) void qgemm_decode_kernel(KArgs a) {
   extern __shared__ uint4 xs[];
-  int e = blockIdx.y, b = blockIdx.x, G = gridDim.x, r0, cnt, slots = 0;
+  PlanEntry pe;
   if (a.plan != nullptr) {                   // shares by table (plan.h): one 32-byte entry per block
-    const PlanEntry* pe = reinterpret_cast<const PlanEntry*>(a.plan) + blockIdx.x;
-    e = __builtin_amdgcn_readfirstlane(pe->e); b = __builtin_amdgcn_readfirstlane(pe->b); G = __builtin_amdgcn_readfirstlane(pe->G);
-    r0 = __builtin_amdgcn_readfirstlane(pe->r0); cnt = __builtin_amdgcn_readfirstlane(pe->cnt);
-    if constexpr (HA && !DUAL) slots = __builtin_amdgcn_readfirstlane(pe->slots);
-    if (e < 0) return;
+    const auto* src = reinterpret_cast<const __attribute__((address_space(4))) PlanEntry*>(reinterpret_cast<uintptr_t>(a.plan)) + blockIdx.x;
+    pe.e = src->e; pe.t0 = src->t0; pe.t1 = src->t1; pe.r0 = src->r0; pe.cnt = src->cnt; pe.own = src->own; pe.slots = src->slots;
+    if (pe.e < 0) return;
   } else {
-    r0 = a.offsets ? a.offsets[e] : e * a.T;
-    cnt = a.offsets ? a.offsets[e + 1] - r0 : a.T;
+    const int e = blockIdx.y, r0 = a.offsets ? a.offsets[e] : e * a.T;
+    pe = plan_entry(e, blockIdx.x, gridDim.x, a.NT, r0, a.offsets ? a.offsets[e + 1] - r0 : a.T, 0);
   }
-  if (cnt == 0) return;
-  if (cnt <= 16) decode_body<BITS, DUAL, 1, Q3, HA>(a, xs, e, r0, cnt, b, G, slots);
-  else decode_body<BITS, DUAL, 2, Q3, HA>(a, xs, e, r0, cnt, b, G, slots);
+  if (pe.cnt == 0 || pe.t0 == pe.t1) return;
+  if (pe.cnt <= 16) decode_body<BITS, DUAL, 1, Q3, HA>(a, xs, pe);
+  else decode_body<BITS, DUAL, 2, Q3, HA>(a, xs, pe);
 }
 
 template <bool DUAL>

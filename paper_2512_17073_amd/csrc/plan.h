@@ -6,8 +6,9 @@
 // rows gets `base` blocks (enough for 32 n-tiles per block), the rest of `target` blocks go by
 // weight (the number of 32-row passes the expert's rows need: every pass streams its weights
 // again), dealt by the running sum of the weights.  Entry i of the table (PlanEntry, 32 bytes, read by block i with one scalar
-// load): expert (or -1: the block exits), index of the block within the expert, blocks of the expert,
-// first row and number of rows of the expert.
+// load): expert (or -1: the block exits), the block's n-tiles, first row and number of rows of the expert, and where the
+// part sums of (h A2) go and how many there are.  What takes a division is done here, a lane per entry, and not by every wavefront
+// of the launches that read the table.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -17,8 +18,15 @@
 namespace lrc {
 
 struct PlanSpec { int B, NT, target; int32_t* plan; };     // B entries for a projection of NT n-tiles; plan == null: no table wanted
-struct PlanEntry { int32_t e, b, G, r0, cnt, slots, pad0, pad1; };     // slots: ha_slots of the expert's blocks in the other table
+// own: the block's place among the part sums of its expert (ha_slot); slots: ha_slots of the expert's blocks in the other table
+struct PlanEntry { int32_t e, t0, t1, r0, cnt, own, slots, pad; };
 constexpr int kPlanEntryInts = 8;
+LRC_HD PlanEntry plan_entry(int e, int b, int G, int NT, int r0, int cnt, int slots) {
+  PlanEntry p{e, 0, 0, r0, cnt, 0, slots, 0};
+  dec::block_tiles(b, G, NT, p.t0, p.t1);
+  p.own = dec::ha_slot(b, p.t0, G, NT);
+  return p;
+}
 
 // One table's shares: as many blocks as fill the chip (`target`), more only if the experts with rows need
 // them; the rest of the grid exits at once.  Every expert gets its fewest blocks (a block owns at most
@@ -114,15 +122,15 @@ __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, con
         const int lo_j = __shfl(lo[i], j), G_j = __shfl(hi[i], j) - lo_j, hi_j = min(lo_j + G_j, B);
         const int r0_j = __shfl(r0[i], j), cnt_j = __shfl(cnt[i], j), slots_j = __shfl(slots[i], j);
         for (int b = lo_j + lane; b < hi_j; b += 64)
-          reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{64 * i + j, b - lo_j, G_j, r0_j, cnt_j, slots_j, 0, 0};
+          reinterpret_cast<PlanEntry*>(plan)[b] = plan_entry(64 * i + j, b - lo_j, G_j, sp.NT, r0_j, cnt_j, slots_j);
       }
     } else if (cnt[i] > 0) {
       // many experts with few blocks each: every lane writes its own expert's entries
       for (int b = lo[i]; b < hi[i] && b < B; ++b)
-        reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{64 * i + lane, b - lo[i], hi[i] - lo[i], r0[i], cnt[i], slots[i], 0, 0};
+        reinterpret_cast<PlanEntry*>(plan)[b] = plan_entry(64 * i + lane, b - lo[i], hi[i] - lo[i], sp.NT, r0[i], cnt[i], slots[i]);
     }
   }
-  for (int b = used + lane; b < B; b += 64) reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{-1, 0, 1, 0, 0, 0, 0, 0};
+  for (int b = used + lane; b < B; b += 64) reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{-1, 0, 0, 0, 0, 0, 0, 0};
 }
 
 }  // namespace lrc

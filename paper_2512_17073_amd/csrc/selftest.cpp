@@ -58,9 +58,11 @@ std::string check_shape(const Shape& sh) {
       const int nt_b = t1 - t0;
       if (nt_b == 0) continue;
       if (nt_b > max_block_tiles(MT)) SELF_FAIL("block %d of %d owns %d n-tiles (at most %d)", b, sh.G, nt_b, max_block_tiles(MT));
-      const int units = block_units(nt_b, sh.dual), kw = waves_per_unit(units), groups = kWaves / kw;
+      const int units = block_units(nt_b, sh.dual), kwl = waves_per_unit_log2(units), kw = 1 << kwl, groups = kWaves / kw;
+      if ((kw > 1 && units * kw > kWaves) || (kw < kWaves && units * kw * 2 <= kWaves))
+        SELF_FAIL("%d wavefronts per unit for %d units", kw, units);
       if (units > groups * unit_slots(sh.dual, MT)) SELF_FAIL("%d units do not fit %d wavefront groups", units, groups);
-      const StepPlan sp = step_plan(KSl, MT, kw, LS, sh.dual);
+      const StepPlan sp = step_plan(KSl, MT);
       const int p_frags = NP * LS * MT;
       const bool p_late = p_frags * 64 > kSpareUnits;
       if (p_frags * 64 > (p_late ? kLdsUnits : kSpareUnits)) SELF_FAIL("%d (in A) fragments exceed their LDS region", p_frags);
@@ -74,7 +76,9 @@ std::string check_shape(const Shape& sh) {
               for (int kl = wave >> 3; kl < nk; kl += 2)
                 for (int lane = 0; lane < 64; ++lane) {
                   const int q = lane >> 4, rowl = lane & 15, s = wave & 7;
-                  const int k8 = std::min((ks_lo + ph * sp.KP + kl) * 32 + q * 8 + s, sh.K / 8 - 1);
+                  const int ks = ks_lo + ph * sp.KP + kl, k8 = ks * 32 + staged_group(ks, q, sh.K) * 8 + s;
+                  if (k8 >= sh.K / 8) SELF_FAIL("staging reads unit %d of a row of %d", k8, sh.K / 8);
+                  if (ks * 32 + q * 8 + s < sh.K / 8 && k8 != ks * 32 + q * 8 + s) SELF_FAIL("staging of k-step %d, group %d reads unit %d", ks, q, k8);
                   if (act_frag_unit(mt, kl, s, sp.KP) + 64 > kLdsUnits) SELF_FAIL("staged fragment (mt %d, kl %d, s %d) leaves LDS", mt, kl, s);
                   const int row = staged_row(sh.r0 + r, r, mt, rowl, sh.cnt, rt);
                   if (row < 0 || row >= rt) SELF_FAIL("staging reads row %d of %d", row, rt);
@@ -98,19 +102,21 @@ std::string check_shape(const Shape& sh) {
         // the steps of every wavefront (the kernel fetches RING steps past the last one)
         if (r > 0) continue;                  // (the steps do not depend on the pass)
         for (int wave = 0; wave < kWaves; ++wave) {
-          const int grp = wave / kw, kwi = wave % kw;
-          StepCursor cur = cursor_start();
-          for (int n = 0; n < sp.n_reg + sp.LSP + kRing; ++n) {
-            // the kernel walks the steps with the cursor; step_ref is the closed form it must agree with
-            const StepRef want = step_ref(n, sp, grp, groups, kwi, kw, units, ks_lo, KSl, LS, sh.dual);
-            const StepRef ref = cursor_ref(cur, sp, grp, groups, kwi, kw, units, ks_lo, KSl, LS);
-            cursor_advance(cur, sp);
-            if (ref.reg != want.reg || ref.lr != want.lr) SELF_FAIL("step %d: the cursor disagrees on what kind of step it is", n);
-            if (ref.reg && (ref.unit != want.unit || ref.ks != want.ks || ref.kl != want.kl || ref.ts != want.ts))
-              SELF_FAIL("step %d: the cursor is at k-step %d of unit %d, the closed form at %d of %d", n, ref.ks, ref.unit, want.ks, want.unit);
-            if (ref.lr && (ref.unit != want.unit || ref.st != want.st || ref.ts != want.ts))
-              SELF_FAIL("step %d: the cursor is at rank step %d of unit %d, the closed form at %d of %d", n, ref.st, ref.unit, want.st, want.unit);
+          const int grp = wave / kw, kwi = wave % kw, own = own_units(grp, groups, units, sh.dual);
+          // the wavefront's own steps in order, segment by segment, and a turn of the ring past the last one
+          std::vector<StepRef> walk;
+          for (int ph = 0; ph <= sp.n_ph; ++ph)
+            for (int ts = 0; ts < own; ++ts) {
+              const Segment seg = segment(ph, ts, own, sp, grp, groups, ks_lo, KSl, LS);
+              const int steps = segment_steps(seg.len, kwl);
+              if (steps % kRing || steps * kw < seg.len) SELF_FAIL("%d steps for a segment of %d", steps, seg.len);
+              for (int si = 0; si < steps; ++si) walk.push_back(step_ref(seg, si, kwi, kwl));
+            }
+          for (int ph : {sp.n_ph + 1, sp.n_ph + 2}) walk.push_back(step_ref(segment(ph, 0, own, sp, grp, groups, ks_lo, KSl, LS), 0, kwi, kwl));
+          for (int n = 0; n < int(walk.size()); ++n) {
+            const StepRef& ref = walk[n];
             if (ref.reg && ref.lr) SELF_FAIL("step %d is both a k-step and a rank step", n);
+            if ((ref.reg || ref.lr) && ref.unit >= units) SELF_FAIL("step %d is of unit %d of %d", n, ref.unit, units);
             for (int m = 0; m < kStreams; ++m) {
               const int tile = stream_tile(t0, ref.unit, m, sh.dual);
               const bool tile_ok = tile < t1;
