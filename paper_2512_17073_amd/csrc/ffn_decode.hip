@@ -607,7 +607,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void qgemm_decode_kernel(KArgs a) {
 template <bool DUAL>
 __global__ __launch_bounds__(1024) void xa_rows_kernel(KArgs a) {
   __shared__ float4_t red[32][64];
-  xa_rows_body<DUAL, false, 16>(a, nullptr, blockIdx.x, blockIdx.y, blockIdx.z, red);
+  xa_rows_body<DUAL, false, 16>(a, GroupedRows{a.offsets, a.row_pair, a.tok_exp, a.row_exp, a.top_k}, nullptr, blockIdx.x, blockIdx.y, blockIdx.z, 0, 1, red);
 }
 
 // (x A1 | x A3) from the bf16 tokens in a launch of its own: the same body, block size and summation
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(1024) void xa_rows_kernel(KArgs a) {
 // arrive late (staged residency) gets the same bits.
 __global__ __launch_bounds__(1024) void xa13_tokens_kernel(KArgs a, const uint16_t* __restrict__ x_bf16) {
   __shared__ float4_t red[32][64];
-  xa_rows_body<true, true, 16>(a, x_bf16, blockIdx.x, blockIdx.y, 0, red);
+  xa_rows_body<true, true, 16>(a, GroupedRows{a.offsets, a.row_pair, a.tok_exp, a.row_exp, a.top_k}, x_bf16, blockIdx.x, blockIdx.y, 0, 0, 1, red);
 }
 
 // y_rows[R][n] = bf16(sum over K-blocks of partial[kb][R][n]), K-blocks in order (deterministic).

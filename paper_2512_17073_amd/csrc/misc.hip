@@ -119,46 +119,49 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
 // and the tables are made without 64-bit divisions from counts read once.
 constexpr int kStatAhead = 8;              // batches of 64 rows whose pairs a counting wavefront asks for together
 // With a token or two every block first routes them itself (route.wg != null).
-// With few pairs, every block first groups the pairs by expert itself (perm.idx != null: the body of
-// the permute kernel, writing the same values from every block) instead of a launch of its own
-// doing it beforehand; offsets and row_pair are then this block's own writes, read back after a
-// barrier (hence no __restrict__ on them).
-__global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __restrict__ x, int rows, int H,
-                                                   uint4* __restrict__ xg, int rt,
-                                                   const int32_t* offsets,
-                                                   const int32_t* row_pair, int E, int top_k,
-                                                   int top_n, int32_t* __restrict__ stat, PlanSpec plan0,
-                                                   PlanSpec plan1, int xa_tiles, ffn::KArgs xa,
-                                                   const int32_t* tok_exp, int32_t* __restrict__ row_exp,
-                                                   PermuteArgs perm, CompactArgs cmp, RouteArgs route, ZeroRowsArgs zr,
-                                                   int32_t* __restrict__ host_stat, int32_t* __restrict__ row_tok) {
-  __shared__ ffn::float4_t red[2 * kPrepThreads / 64][64];
-  __shared__ uint32_t row_max[16];
+// With few pairs, every block first groups the pairs by expert itself (perm.idx != null) instead of a launch of its own
+// doing it beforehand: by ballots, into its LDS (group_small; the first of the last blocks writes the results out), or, of more pairs and
+// experts, by the body of the permute kernel, writing the same values from every block; offsets and row_pair are then this block's
+// own writes, read back after a barrier (hence no __restrict__ on them).
+struct SmallRows {                         // grouped by this block, in its LDS
+  const SmallGroup& sg;
+  const int32_t* tok_exp;                  // null: the block has routed the tokens itself
+  int top_k;
+  __device__ int offset(int e) const { return sg.offset[e]; }
+  __device__ int pair(int row) const { return sg.pair[row]; }
+  __device__ int exponent(int pair, int) const { return tok_exp ? tok_exp[pair / top_k] : sg.tok_exp[pair / top_k]; }
+};
+
+// The launch's blocks in order: `stat` that count, row blocks x columns, `plan` for the tables, factor tiles x passes of
+// (x A1 | x A3), then `columns` that keep the zero rows.
+struct PrepGrid {
+  int stat, row_blocks, columns, plan, tiles, passes;
+  LRC_HD int rows_at() const { return stat; }
+  LRC_HD int plan_at() const { return stat + row_blocks * columns; }
+  LRC_HD int xa_at() const { return plan_at() + plan; }
+  LRC_HD int zero_at() const { return xa_at() + tiles * passes; }
+  LRC_HD int blocks() const { return zero_at() + columns; }
+};
+// The passes of a factor tile run on one XCD (block b runs on XCD b % 8), whose L2 then holds the tile.
+__device__ inline void xa_block(const PrepGrid& g, int i, int& tile, int& pass) {
+  if (g.tiles % 8 == 0) {
+    const int j = i / (8 * g.passes), in = i - j * 8 * g.passes;
+    pass = in >> 3; tile = 8 * j + (in & 7);
+  } else {
+    pass = i / g.tiles; tile = i - pass * g.tiles;
+  }
+}
+
+// What a block does once the pairs are grouped: its role by its index.
+template <class Rows>
+__device__ inline void prep_roles(const Rows& grouped, const uint16_t* __restrict__ x, int rows, int H, uint4* __restrict__ xg, int rt, bool routed, int E,
+                                  int top_k, int top_n, int32_t* __restrict__ stat, const PlanSpec& plan0, const PlanSpec& plan1, const PrepGrid& g, const ffn::KArgs& xa,
+                                  bool have_exp, int32_t* __restrict__ row_exp, const CompactArgs& cmp, const ZeroRowsArgs& zr,
+                                  int32_t* __restrict__ host_stat, int32_t* __restrict__ row_tok, ffn::float4_t (*red)[64], uint32_t* row_max) {
   constexpr int kWavesPerBlock = kPrepThreads / 64, kColLanes = kPrepThreads / 16;
-  const int row_blocks = (rows + 15) / 16;
-  const int stat_blocks = stat ? (E + kWavesPerBlock - 1) / kWavesPerBlock : 0, plan_block = plan0.B + plan1.B > 0 ? 1 : 0;
-  const int xa_first = row_blocks + stat_blocks + plan_block;
-  if (xa.p_tokens > 0 && (int)blockIdx.x >= xa_first && (int)blockIdx.x < (int)gridDim.x - 1) {
-    // (x A1 | x A3) of all tokens: nothing to wait for
-    const int i = (int)blockIdx.x - xa_first, pass = xa_tokens_pass(xa.p_tokens, gridDim.y);
-    ffn::xa_tokens_body<kWavesPerBlock>(xa, x, route.wg != nullptr ? nullptr : tok_exp, i % xa_tiles, i / xa_tiles,
-                                         pass * blockIdx.y, pass == 32, red);
-    return;
-  }
-  if (route.wg != nullptr) {
-    // a token or two: every block routes them itself (route_body.h) instead of a launch of its
-    // own doing it beforehand; perm.idx and tok_exp are then this block's own writes
-    route_small_body(reinterpret_cast<double*>(&red[0][0]), x, route, perm.P / top_k, H, E, top_k);
-    __syncthreads();
-  }
-  if (perm.idx != nullptr) {
-    PermuteLds& pl = *reinterpret_cast<PermuteLds*>(&red[0][0]);     // (the reduction buffer is not in use yet)
-    static_assert(sizeof(PermuteLds) <= sizeof(red), "the permutation tables must fit the reduction buffer");
-    permute_body(pl, perm.idx, perm.P, E, top_k, top_n, perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts);
-    __syncthreads();
-  }
-  if ((int)blockIdx.x == (int)gridDim.x - 1) {                              // the zero rows (the last block)
-    const int n = blockIdx.y * kPrepThreads + threadIdx.x, step = kPrepThreads * gridDim.y;
+  const int block = blockIdx.x;
+  if (block >= g.zero_at()) {                                               // the zero rows
+    const int n = (block - g.zero_at()) * kPrepThreads + threadIdx.x, step = kPrepThreads * g.columns;
     const int xu = (H + kTileK - 1) / kTileK * (kTileK / 8);               // 16-byte units per row
     for (int i = n; i < xu * dec::kZeroRows; i += step)
       xg[size_t(i / dec::kZeroRows) * rt + rt - dec::kZeroRows + i % dec::kZeroRows] = make_uint4(0, 0, 0, 0);
@@ -167,26 +170,28 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
         zr.h[size_t(i / dec::kZeroRows) * zr.h_rt + zr.h_rt - dec::kZeroRows + i % dec::kZeroRows] = make_uint4(0, 0, 0, 0);
     return;
   }
-  if ((int)blockIdx.x >= xa_first) {                                        // (x A1 | x A3) of the routed rows
-    const int i = (int)blockIdx.x - xa_first;
-    if (blockIdx.y == 0) ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, x, i % xa_tiles, i / xa_tiles, 0, red);
+  if (block >= g.xa_at()) {                                                 // (x A1 | x A3) of the routed rows
+    int tile, pass;
+    xa_block(g, block - g.xa_at(), tile, pass);
+    const int per = g.tiles / E, e = tile / per;
+    ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, grouped, x, tile - e * per, e, 0, pass, g.passes, red);
     return;
   }
-  if (plan_block && (int)blockIdx.x == row_blocks + stat_blocks) {         // the block tables (plan.h)
-    if (blockIdx.y == 0 && threadIdx.x < 128) make_plan(offsets, E, threadIdx.x < 64 ? plan0 : plan1, threadIdx.x < 64 ? PlanSpec{0, 0, 0, nullptr} : plan0, threadIdx.x & 63);
+  if (block >= g.plan_at()) {                                               // the block tables (plan.h)
+    if (threadIdx.x < 128) make_plan([&](int e) { return grouped.offset(e); }, E, threadIdx.x < 64 ? plan0 : plan1, threadIdx.x < 64 ? PlanSpec{0, 0, 0, nullptr} : plan0, threadIdx.x & 63);
     return;
   }
-  if ((int)blockIdx.x < stat_blocks) {
-    const int e = (int)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (e >= E || blockIdx.y != 0) return;
-    const int b = offsets[e], n = offsets[e + 1] - b;
+  if (block < g.rows_at()) {
+    const int e = block * kWavesPerBlock + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (e >= E) return;
+    const int b = grouped.offset(e), n = grouped.offset(e + 1) - b;
     // the expert's rows that take the rank-r term, counted and (for the grouped (in A) kernels,
     // CompactArgs) compacted in row order by ballot
     int comp = 0;
     for (int r0 = 0; r0 < n; r0 += 64 * kStatAhead) {
       int pair[kStatAhead];
 #pragma unroll
-      for (int u = 0; u < kStatAhead; ++u) pair[u] = row_pair[b + min(r0 + 64 * u + lane, n - 1)];
+      for (int u = 0; u < kStatAhead; ++u) pair[u] = grouped.pair(b + min(r0 + 64 * u + lane, n - 1));
 #pragma unroll
       for (int u = 0; u < kStatAhead; ++u) {
         if (r0 + 64 * u >= n) break;
@@ -205,14 +210,15 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
     if (lane == 0 && host_stat != nullptr) { host_stat[2 + e] = n; host_stat[2 + E + e] = comp; }
     return;
   }
-  const int R = ((int)blockIdx.x - stat_blocks) * 16 + (threadIdx.x & 15);
-  const int t = R < rows ? (row_pair ? row_pair[R] / top_k : R) : 0;
+  const int at = block - g.rows_at(), column = at % g.columns;
+  const int R = at / g.columns * 16 + (threadIdx.x & 15);
+  const int pair = routed && R < rows ? grouped.pair(R) : 0, t = routed ? pair / top_k : R < rows ? R : 0;
   const uint4* xrow = reinterpret_cast<const uint4*>(x + size_t(t) * H);
   // The row's power-of-two pre-scale (ffn_common.h): from the routing kernel's per-token exponents,
   // or, without them, from a pass of this block over its sixteen rows.
   int se = 0;
-  if (tok_exp != nullptr) {
-    se = tok_exp[t];
+  if (have_exp) {
+    se = grouped.exponent(pair, R);
   } else {
     if (threadIdx.x < 16) row_max[threadIdx.x] = 0;
     __syncthreads();
@@ -229,29 +235,70 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
     se = ffn::row_exponent(row_max[threadIdx.x & 15]);
   }
   if (R >= rows) return;
-  if (blockIdx.y == 0 && (threadIdx.x >> 4) == 0) {
+  if (column == 0 && (threadIdx.x >> 4) == 0) {
     row_exp[R] = se;
-    if (row_tok != nullptr) row_tok[R] = row_pair[R] - t * top_k < top_n ? t : -1;
+    if (row_tok != nullptr) row_tok[R] = pair - t * top_k < top_n ? t : -1;
   }
   const float sc = ffn::pow2i(se);
-  // (grid.y splits the columns when there are few rows, so that the launch still fills the chip)
+  // (the columns are split when there are few rows, so that the launch still fills the chip)
   // (two adjacent units per thread: a wavefront reads 128 contiguous bytes of each of its rows; H / 8 is even)
-  for (int k8p = 2 * (blockIdx.y * kColLanes + (threadIdx.x >> 4)); k8p < H / 8; k8p += 2 * kColLanes * gridDim.y) {
+  for (int k8p = 2 * (column * kColLanes + (threadIdx.x >> 4)); k8p < H / 8; k8p += 2 * kColLanes * g.columns) {
     const uint4 vv[2] = {xrow[k8p], xrow[k8p + 1]};
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const uint32_t in[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
-      uint32_t o[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const _Float16 lo = (_Float16)(bf16_lo(in[i]) * sc);
-        const _Float16 hi = (_Float16)(bf16_hi(in[i]) * sc);
-        o[i] = uint32_t(__builtin_bit_cast(uint16_t, lo)) | (uint32_t(__builtin_bit_cast(uint16_t, hi)) << 16);
-      }
       const int k8 = k8p + u, ks = k8 >> 5, q = (k8 >> 3) & 3, s = k8 & 7;
-      xg[size_t((ks * 8 + s) * 4 + q) * rt + R] = make_uint4(o[0], o[1], o[2], o[3]);
+      xg[size_t((ks * 8 + s) * 4 + q) * rt + R] = __builtin_bit_cast(uint4, ffn::scaled_unit(vv[u], sc));
     }
   }
+}
+
+__global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __restrict__ x, int rows, int H,
+                                                   uint4* __restrict__ xg, int rt,
+                                                   const int32_t* offsets,
+                                                   const int32_t* row_pair, int E, int top_k,
+                                                   int top_n, int32_t* __restrict__ stat, PlanSpec plan0,
+                                                   PlanSpec plan1, PrepGrid g, ffn::KArgs xa,
+                                                   const int32_t* tok_exp, int32_t* __restrict__ row_exp,
+                                                   PermuteArgs perm, CompactArgs cmp, RouteArgs route, ZeroRowsArgs zr,
+                                                   int32_t* __restrict__ host_stat, int32_t* __restrict__ row_tok) {
+  __shared__ ffn::float4_t red[2 * kPrepThreads / 64][64];
+  __shared__ uint32_t row_max[16];
+  __shared__ SmallGroup sg;
+  constexpr int kWavesPerBlock = kPrepThreads / 64;
+  const int block = blockIdx.x;
+  if (xa.p_tokens > 0 && block >= g.xa_at() && block < g.zero_at()) {
+    // (x A1 | x A3) of all tokens: nothing to wait for
+    int tile, p;
+    xa_block(g, block - g.xa_at(), tile, p);
+    const int pass = xa_tokens_pass(xa.p_tokens, g.columns), per = g.tiles / E, e = tile / per;
+    ffn::xa_tokens_body<kWavesPerBlock>(xa, x, route.wg != nullptr ? nullptr : tok_exp, tile - e * per, e, pass * p, pass == 32, red);
+    return;
+  }
+  const bool routed = row_pair != nullptr;
+  auto roles = [&](const auto& grouped, bool have_exp) {
+    prep_roles(grouped, x, rows, H, xg, rt, routed, E, top_k, top_n, stat, plan0, plan1, g, xa, have_exp, row_exp, cmp, zr, host_stat, row_tok, red, row_max);
+  };
+  if (perm.idx != nullptr && group_small_fits(perm.P, E)) {
+    const bool out = block == g.zero_at();     // the block that writes the results
+    const PermuteOut o{perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts};
+    if (route.wg != nullptr) {
+      // a token or two: every block routes them itself (route_body.h) instead of a launch of its own doing it beforehand
+      route_small_body(reinterpret_cast<double*>(&red[0][0]), sg.idx, sg.tok_exp, x, route, perm.P / top_k, H, E, top_k, out);
+      __syncthreads();
+      group_small(sg, [&](int i) { return sg.idx[i]; }, perm.P, E, top_k, top_n, out, o);
+    } else {
+      group_small(sg, [&](int i) { return perm.idx[i]; }, perm.P, E, top_k, top_n, out, o);
+    }
+    roles(SmallRows{sg, route.wg != nullptr ? nullptr : tok_exp, top_k}, true);
+    return;
+  }
+  if (perm.idx != nullptr) {
+    PermuteLds& pl = *reinterpret_cast<PermuteLds*>(&red[0][0]);     // (the reduction buffer is not in use yet)
+    static_assert(sizeof(PermuteLds) <= sizeof(red), "the permutation tables must fit the reduction buffer");
+    permute_body(pl, perm.idx, perm.P, E, top_k, top_n, perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts);
+    __syncthreads();
+  }
+  roles(ffn::GroupedRows{offsets, row_pair, tok_exp, row_exp, top_k}, tok_exp != nullptr);
 }
 
 // One wavefront per packed tile: runs the same field extraction as the FFN kernels and writes the
@@ -311,11 +358,19 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
     xa_tiles = 2 * f.rpad / 16;
   }
   const int stat_blocks = stat ? (c.n_experts + kPrepThreads / 64 - 1) / (kPrepThreads / 64) : 0;
+  PrepGrid g{stat_blocks, row_blocks, ky, plan_block, xa_tiles * c.n_experts, 1};
+  if (xa.p_tokens > 0) {
+    const int pass = xa_tokens_pass(xa.p_tokens, ky);
+    g.passes = (xa.p_tokens + pass - 1) / pass;
+  } else if (xa_tiles > 0) {
+    // By rows, 32 a pass, up to four side by side: an expert with many must not be one block's chain of passes (Qwen3 shape, T = 64, 60
+    // rows on one of 128 experts: launch 17.2 -> 14.0 us; the blocks of experts with fewer rows leave at once, 2 us for all of them).
+    g.passes = std::max(1, std::min({4, (T + 31) / 32, 4 * L->n_cu / g.tiles}));
+  }
   const int cmp_block = (cmp && row_pair && stat) ? 1 : 0;     // (the compaction rides the per-expert counting)
-  // (+ 1: the block that keeps the zero rows)
-  hipLaunchKernelGGL(prep_kernel, dim3(row_blocks + stat_blocks + plan_block + xa_tiles * c.n_experts + 1, ky),
+  hipLaunchKernelGGL(prep_kernel, dim3(g.blocks()),
                      dim3(kPrepThreads), 0, s, (const uint16_t*)x_bf16, rows, c.hidden, reinterpret_cast<uint4*>(xg), rt, offsets,
-                     row_pair, c.n_experts, c.top_k, c.top_n, stat, p0, p1, xa_tiles, xa, tok_exp, row_exp,
+                     row_pair, c.n_experts, c.top_k, c.top_n, stat, p0, p1, g, xa, tok_exp, row_exp,
                      perm ? *perm : PermuteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0},
                      cmp_block ? *cmp : CompactArgs{nullptr, nullptr},
                      (route && perm) ? *route : RouteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, 0}, zr, host_stat,

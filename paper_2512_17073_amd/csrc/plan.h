@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "decode_index.h"
+#include "wave.h"
 
 namespace lrc {
 
@@ -50,35 +51,32 @@ LRC_HD int plan_part(int extra, int claims, int over) { return over > 0 ? int(ui
 // The rest of the preparing launch is short, so this chain sets its length: the experts' rows are read once, 64
 // experts to a register, and nothing is divided in 64 bits (blocks times passes: below 2^31 for any launch of
 // this flavour, whose experts have 128 rows at most on average).
-__device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, const PlanSpec sp, const PlanSpec other, int lane) {
+// offset(e): first row of expert e, of E that of all rows.
+template <class Offset>
+__device__ inline void make_plan(const Offset& offset, int E, const PlanSpec sp, const PlanSpec other, int lane) {
   if (sp.plan == nullptr) return;
   int32_t* __restrict__ plan = sp.plan;
   constexpr int kChunks = 4;                   // (at most 256 experts)
   const unsigned long long below = (1ull << lane) - 1ull;
-  auto scan = [&](int v) {
-#pragma unroll
-    for (int dlt = 1; dlt < 64; dlt *= 2) {
-      const int t = __shfl_up(v, dlt);
-      if (lane >= dlt) v += t;
-    }
-    return v;
-  };
   int cnt[kChunks], r0[kChunks], weight[kChunks];
   unsigned long long active[kChunks];
 #pragma unroll
   for (int i = 0; i < kChunks; ++i) {
     const int e = min(64 * i + lane, E - 1);
-    r0[i] = offsets[e];
-    cnt[i] = 64 * i + lane < E ? offsets[e + 1] - r0[i] : 0;
+    r0[i] = cnt[i] = 0;
+    if (64 * i >= E) continue;
+    r0[i] = offset(e);
+    cnt[i] = offset(e + 1);
   }
   int n_active = 0, wsum = 0;
 #pragma unroll
   for (int i = 0; i < kChunks; ++i) {
+    cnt[i] = 64 * i + lane < E ? cnt[i] - r0[i] : 0;
     // what an expert's rows cost: every 32-row pass streams the expert's weights again
     weight[i] = (cnt[i] + 31) / 32;
     active[i] = __ballot(cnt[i] > 0);
     n_active += __popcll(active[i]);
-    if (64 * i < E) wsum += __shfl(scan(weight[i]), 63);
+    if (64 * i < E) wsum += lane_value(wave_scan(weight[i]), 63);
   }
   // One table's shares: blocks [lo, hi) of the experts of every chunk; returns the blocks used.
   auto shares = [&](const PlanSpec& p, int (&lo)[kChunks], int (&hi)[kChunks]) {
@@ -88,8 +86,8 @@ __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, con
     for (int i = 0; i < kChunks; ++i) {
       if (64 * i >= E) continue;
       claim[i] = plan_claim(total, weight[i], wsum, cnt[i] > 0 ? base : 0);
-      incl[i] = over + scan(claim[i]);
-      over = __shfl(incl[i], 63);
+      incl[i] = over + wave_scan(claim[i]);
+      over = lane_value(incl[i], 63);
     }
 #pragma unroll
     for (int i = 0; i < kChunks; ++i) {
@@ -119,8 +117,8 @@ __device__ inline void make_plan(const int32_t* __restrict__ offsets, int E, con
       // few experts with many blocks each: the whole wavefront writes one expert's entries after the other's
       for (unsigned long long todo = active[i]; todo; todo &= todo - 1) {
         const int j = __ffsll(todo) - 1;
-        const int lo_j = __shfl(lo[i], j), G_j = __shfl(hi[i], j) - lo_j, hi_j = min(lo_j + G_j, B);
-        const int r0_j = __shfl(r0[i], j), cnt_j = __shfl(cnt[i], j), slots_j = __shfl(slots[i], j);
+        const int lo_j = lane_value(lo[i], j), G_j = lane_value(hi[i], j) - lo_j, hi_j = min(lo_j + G_j, B);
+        const int r0_j = lane_value(r0[i], j), cnt_j = lane_value(cnt[i], j), slots_j = lane_value(slots[i], j);
         for (int b = lo_j + lane; b < hi_j; b += 64)
           reinterpret_cast<PlanEntry*>(plan)[b] = plan_entry(64 * i + j, b - lo_j, G_j, sp.NT, r0_j, cnt_j, slots_j);
       }

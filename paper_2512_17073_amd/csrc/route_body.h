@@ -50,7 +50,7 @@ __device__ inline double wave_max(double v) { return wave_reduce(v, [](double a,
 // (Top-8 of 128, T = 4096: 17.0 -> 10.3 us, shuffles with the index beside the value and an exponential per selection before;
 // Top-6 of 64, T = 512: 8.3 -> 6.0).
 __device__ inline void select_topk(const double (&v)[4], int lane, int E, int top_k, int renorm,
-                                   int32_t* __restrict__ idx_t, float* __restrict__ w_t) {
+                                   int32_t* __restrict__ idx_t, float* __restrict__ w_t, int32_t* idx_l = nullptr) {
   uint32_t taken = 0;
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -81,6 +81,10 @@ __device__ inline void select_topk(const double (&v)[4], int lane, int E, int to
     if (j == 0) vmax = best;
     if (lane == j) { my_v = best; my_idx = bi; }
   }
+  if (idx_l != nullptr) {                  // (a second place for the experts, and no weights wanted without the first)
+    if (lane < top_k) idx_l[lane] = my_idx;
+    if (idx_t == nullptr) return;
+  }
   double part = 0.0;
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -100,27 +104,28 @@ __device__ inline void select_topk(const double (&v)[4], int lane, int E, int to
 // 1024-thread block: every (token, expert) gate dot product by one wavefront, with the lanes walking
 // the 16-byte chunks of the rows and adding the exact bf16 x bf16 products in fp64 in the order the
 // per-token routing kernel uses (the logits are bit-identical to that kernel's); then one wavefront
-// per token takes the Top-k and the softmax weights and writes the token's pre-scale exponent.
-// `logit` is LDS, T * E doubles.  Every block that runs this writes the same values; a block reads
-// them back after the __syncthreads() the caller follows this with.
-__device__ inline void route_small_body(double* logit, const uint16_t* __restrict__ x, const RouteArgs& ra, int T, int H, int E,
-                                        int top_k) {
+// per token takes the Top-k and the softmax weights and the token's pre-scale exponent.
+// `logit` is LDS, T * E doubles; the selected experts and the exponents are left in LDS (idx_l, exp_l) for the
+// __syncthreads() the caller follows this with, and written out by the one block that is asked to (`out`).
+__device__ inline void route_small_body(double* logit, int32_t* idx_l, int32_t* exp_l, const uint16_t* __restrict__ x, const RouteArgs& ra,
+                                        int T, int H, int E, int top_k, bool out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, chunks = H / 8;
   for (int p = wave; p < T * E; p += 16) {
     const int t = p / E, e = p - t * E;
     const uint4* xrow = reinterpret_cast<const uint4*>(x + size_t(t) * H);
     const uint4* wrow = reinterpret_cast<const uint4*>(ra.wg + size_t(e) * H);
     double acc = 0.0;
-    for (int c0 = lane; c0 < chunks; c0 += 64 * 4) {      // four chunks of both rows in flight
-      uint4 xv[4], wv[4];
+    constexpr int kAhead = 8;
+    for (int c0 = lane; c0 < chunks; c0 += 64 * kAhead) {      // eight chunks of both rows in flight
+      uint4 xv[kAhead], wv[kAhead];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < kAhead; ++u) {
         const int c = c0 + 64 * u;
         xv[u] = c < chunks ? xrow[c] : make_uint4(0, 0, 0, 0);
         wv[u] = c < chunks ? wrow[c] : make_uint4(0, 0, 0, 0);
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {                        // (chunks in increasing order; a chunk of zeros adds nothing)
+      for (int u = 0; u < kAhead; ++u) {                   // (chunks in increasing order; a chunk of zeros adds nothing)
         const uint32_t xa[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w}, wa[4] = {wv[u].x, wv[u].y, wv[u].z, wv[u].w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -132,19 +137,28 @@ __device__ inline void route_small_body(double* logit, const uint16_t* __restric
     acc = wave_sum(acc);
     if (lane == 0) logit[p] = acc + (ra.bias ? (double)ra.bias[e] : 0.0);
   }
-  if (wave < T && ra.tok_exp != nullptr) {       // the token's pre-scale exponent (ffn_common.h)
-    const uint4* xrow = reinterpret_cast<const uint4*>(x + size_t(wave) * H);
+  // the tokens' pre-scale exponents (ffn_common.h), by the last wavefronts, which have no product where there are fewer than 16
+  if (15 - wave < T) {
+    const int t = 15 - wave;
+    const uint4* xrow = reinterpret_cast<const uint4*>(x + size_t(t) * H);
     uint32_t m = 0;
-    for (int c = lane; c < chunks; c += 64) {
-      const uint4 xv = xrow[c];
-      const uint32_t xa[4] = {xv.x, xv.y, xv.z, xv.w};
+    for (int c0 = lane; c0 < chunks; c0 += 64 * 8) {
+      uint4 xv[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) m = max(m, max(xa[i] & 0x7fffu, (xa[i] >> 16) & 0x7fffu));
+      for (int u = 0; u < 8; ++u) xv[u] = xrow[min(c0 + 64 * u, chunks - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t xa[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = max(m, max(xa[i] & 0x7fffu, (xa[i] >> 16) & 0x7fffu));
+      }
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d));
     const int eb = int(m >> 7);
-    if (lane == 0) ra.tok_exp[wave] = eb == 0 ? 0 : min(60, max(-60, 127 - eb));
+    const int se = eb == 0 ? 0 : min(60, max(-60, 127 - eb));
+    if (lane == 0) exp_l[t] = se;
+    if (lane == 0 && out) ra.tok_exp[t] = se;
   }
   __syncthreads();
   if (wave < T) {
@@ -154,7 +168,8 @@ __device__ inline void route_small_body(double* logit, const uint16_t* __restric
       const int e = lane + 64 * m;
       v[m] = e < E ? logit[wave * E + e] : 0.0;
     }
-    select_topk(v, lane, E, top_k, ra.renorm, ra.idx + size_t(wave) * top_k, ra.w + size_t(wave) * top_k);
+    select_topk(v, lane, E, top_k, ra.renorm, out ? ra.idx + size_t(wave) * top_k : nullptr, out ? ra.w + size_t(wave) * top_k : nullptr,
+                idx_l + wave * top_k);
   }
 }
 
