@@ -89,7 +89,10 @@ Workspace plan_workspace(const moe_lrc_layer* L, int T) {
   w.tok_exp = take(size_t(T) * 4);
   w.row_exp = take((P + kActPadRows) * 4);
   w.row_exp_sh = take(c.n_shared ? (size_t(T) + kActPadRows) * 4 : 0);
-  w.plan = take(size_t(plan_blocks(c.n_experts, int(P), c.ffn / 16, L->n_cu) + plan_blocks(c.n_experts, int(P), c.hidden / 16, L->n_cu)) * kPlanEntryInts * 4);
+  // (a projection has one table, of blocks or of chunks, whichever flavour it takes)
+  const size_t chunks = size_t(chunk_items(int(P), c.n_experts)) * kChunkEntryInts * 4;
+  w.plan = take(std::max(chunks, size_t(plan_blocks(c.n_experts, int(P), c.ffn / 16, L->n_cu)) * kPlanEntryInts * 4));
+  w.plan2 = take(std::max(chunks, size_t(plan_blocks(c.n_experts, int(P), c.hidden / 16, L->n_cu)) * kPlanEntryInts * 4));
   w.cmp_index = take(P * 4);  w.cmp_list = take(P * 4);
   w.total = o;
   return w;
@@ -243,6 +246,7 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   a.p13 = reinterpret_cast<float*>(ws + w.p13); a.p2 = reinterpret_cast<float*>(ws + w.p2);
   a.y_part = reinterpret_cast<float*>(ws + w.y_part);
   a.plan = reinterpret_cast<int32_t*>(ws + w.plan);
+  a.plan2 = reinterpret_cast<int32_t*>(ws + w.plan2);
   a.live13 = L->live13; a.live2 = L->live2;
   a.y_rows = y_rows; a.ksplit13 = L->ksplit13; a.ksplit2 = L->ksplit2; a.total_rows = T * c.top_k;
   a.n_cu = L->n_cu; a.n_shared = c.n_shared;
@@ -274,8 +278,7 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   if (kblocks_out) *kblocks_out = a.keep_partials ? kblocks : 1;
   // the launch that converts the activations also makes the block tables of the decode launches
   // and, for the decode flavour of the fused projection, (x A1 | x A3)
-  PlanSpec plans[2];
-  expert_ffn_plan_specs(a, plans[0], plans[1]);
+  const FfnTables tables = expert_ffn_tables(a);
   // ((x A1 | x A3) from the tokens inside the preparing launch needs the exponents beforehand)
   a.xa13_here = (c.residency != MOE_LRC_RESIDENT && !ahead) || (tok_exp == nullptr && a.p_tokens == 0);
   a.x_tokens = x;
@@ -283,7 +286,7 @@ static int run_expert_ffn(moe_lrc_layer* L, const void* x, int T, const int32_t*
   const bool comp = c.rank > 0 && c.top_n > 0 && path != 0;
   const CompactArgs cmp{reinterpret_cast<int32_t*>(ws + w.cmp_index), reinterpret_cast<int32_t*>(ws + w.cmp_list)};
   if (comp) { a.cmp_index = cmp.index; a.cmp_list = cmp.list; }
-  LRC_HIP(launch_convert_x(L, x, T, xh, P + kActPadRows, offsets, row_pair, L->d_stat, plans,
+  LRC_HIP(launch_convert_x(L, x, T, xh, P + kActPadRows, offsets, row_pair, L->d_stat, &tables,
                            ((path & 1) || a.xa13_here) ? nullptr : &a, tok_exp, a.row_exp, perm, comp ? &cmp : nullptr, route,
                            ZeroRowsArgs{reinterpret_cast<uint4*>(a.h), a.h_rt, padded_k(c.ffn)}, stream,
                            c.residency == MOE_LRC_POOLED ? L->h_stat : nullptr));

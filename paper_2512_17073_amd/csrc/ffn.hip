@@ -46,43 +46,38 @@ namespace {
 
 using namespace ffn;
 
+constexpr int kByLengthRows = 64;         // rows an expert from which W1|W3 takes the chunks by length (plan.h)
 constexpr int kGemmWaves = 4;             // wavefronts per block of the grouped GEMM (two blocks per CU)
 constexpr int kBM = 128;                  // rows of an expert per block
 constexpr int kHalfUnits = kBM / 16 * 4 * 64;   // 16-byte units of half a k-step of activations (32 KB)
 constexpr int kGemmLdsUnits = 5120;       // LDS of a grouped-GEMM block: 80 KB, half of a CU's
-// Work item `item` of a launch -> (expert, first row of its chunk of ROWS rows).  Routed experts: the
-// items enumerate the chunks of the experts in order (an expert with cnt rows has ceil(cnt / ROWS));
-// shared experts: every expert has the same T rows.
 struct Chunk { int e, r0, cnt, r; };
+// Work item `item` of an (in A) launch -> (expert, first row of its chunk of ROWS compact rows): the items enumerate the chunks of the
+// experts in order.  (How many compact rows an expert has is counted by the launch that makes the tables of plan.h, so these
+// items are found here.)  64 experts at a time, read together: every lane counts the chunks of one expert, a prefix sum
+// over the wavefront finds the one that holds the item (every wavefront of the block does the same).
 template <int ROWS>
 __device__ inline bool find_chunk(const KArgs& a, int item, Chunk& c) {
-  if (!a.offsets) {
-    const int per = (a.T + ROWS - 1) / ROWS;
-    c.e = item / per; c.r = (item - c.e * per) * ROWS; c.r0 = c.e * a.T; c.cnt = a.T;
-    return c.e < a.n_exp;
-  }
-  // 64 experts at a time: every lane counts the chunks of one expert, a prefix sum over the
-  // wavefront finds the one that holds the item (every wavefront of the block does the same)
+  constexpr int kGroups = 4;                // (at most 256 experts)
   const int lane = threadIdx.x & 63;
-  int base = 0;
-  for (int e0 = 0; e0 < a.n_exp; e0 += 64) {
-    const int e = e0 + lane;
-    int r0 = 0, cnt = 0;
-    if (e < a.n_exp) { r0 = a.offsets[e]; cnt = a.row_list ? a.comp_rows[e] : a.offsets[e + 1] - r0; }
-    const int n = (cnt + ROWS - 1) / ROWS;
-    int incl = n;
+  int r0[kGroups], cnt[kGroups];
 #pragma unroll
-    for (int dlt = 1; dlt < 64; dlt *= 2) {
-      const int t = __shfl_up(incl, dlt);
-      if (lane >= dlt) incl += t;
-    }
-    const int total = __shfl(incl, 63);
+  for (int g = 0; g < kGroups; ++g) {
+    r0[g] = cnt[g] = 0;
+    if (64 * g >= a.n_exp) continue;
+    const int e = min(64 * g + lane, a.n_exp - 1);
+    r0[g] = a.offsets[e]; cnt[g] = a.comp_rows[e];
+  }
+  int base = 0;
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    if (64 * g >= a.n_exp) continue;
+    const int n = 64 * g + lane < a.n_exp ? (cnt[g] + ROWS - 1) / ROWS : 0, incl = wave_scan(n), total = lane_value(incl, 63);
     if (item < base + total) {
-      const unsigned long long hit = __ballot(base + incl > item);
-      const int first = __ffsll(hit) - 1;
-      c.e = e0 + first;
-      c.r0 = __shfl(r0, first); c.cnt = __shfl(cnt, first);
-      c.r = (item - base - __shfl(incl - n, first)) * ROWS;
+      const int first = __ffsll(__ballot(base + incl > item)) - 1;
+      c.e = 64 * g + first;
+      c.r0 = lane_value(r0[g], first); c.cnt = lane_value(cnt[g], first);
+      c.r = (item - base - lane_value(incl - n, first)) * ROWS;
       return true;
     }
     base += total;
@@ -90,64 +85,7 @@ __device__ inline bool find_chunk(const KArgs& a, int item, Chunk& c) {
   return false;
 }
 
-// The same for a grouped GEMM whose launch is a few rounds of blocks: the whole chunks (128 rows) of all experts
-// first, then the experts' last chunks, those with more rows before those with fewer, so that short blocks fill the end
-// (KArgs::by_length).  W2 alone in this order, whole layer (us): Mixtral shape T = 700 660 -> 647, 1024 902 -> 843, 2048 1565 -> 1548, DeepSeek
-// T = 512 and Qwen3 T = 4096 unchanged.  W1|W3 too: Qwen3 T = 1500 285 -> 278, 4096 553 -> 547; not where an expert's weights are
-// far beyond the L2, which its last chunk then reads once more (Mixtral T = 700 647 -> 668, 2048 1498 -> 1513), nor below 64 rows
-// an expert, whose chunks are nearly alike (DeepSeek T = 512 198 -> 202).
-constexpr int kByLengthRows = 64;
-constexpr int kMaxExperts64 = 4;          // up to 256 experts, 64 to a register
-__device__ inline bool find_gemm_chunk(const KArgs& a, int item, Chunk& c) {
-  if (!a.offsets) return find_chunk<kBM>(a, item, c);
-  const int lane = threadIdx.x & 63;
-  int r0[kMaxExperts64], cnt[kMaxExperts64];
-#pragma unroll
-  for (int g = 0; g < kMaxExperts64; ++g) {
-    const int e = 64 * g + lane;
-    r0[g] = cnt[g] = 0;
-    if (64 * g < a.n_exp && e < a.n_exp) { r0[g] = a.offsets[e]; cnt[g] = a.offsets[e + 1] - r0[g]; }
-  }
-  int base = 0;
-#pragma unroll
-  for (int g = 0; g < kMaxExperts64; ++g) {
-    if (64 * g >= a.n_exp) break;
-    const int n = cnt[g] / kBM;
-    int incl = n;
-#pragma unroll
-    for (int dlt = 1; dlt < 64; dlt *= 2) {
-      const int t = __shfl_up(incl, dlt);
-      if (lane >= dlt) incl += t;
-    }
-    const int total = __shfl(incl, 63);
-    if (item < base + total) {
-      const int first = __ffsll(__ballot(base + incl > item)) - 1;
-      c.e = 64 * g + first;
-      c.r0 = __shfl(r0[g], first); c.cnt = __shfl(cnt[g], first);
-      c.r = (item - base - __shfl(incl - n, first)) * kBM;
-      return true;
-    }
-    base += total;
-  }
-  for (int rp = kBM / 32; rp > 0; --rp) {
-#pragma unroll
-    for (int g = 0; g < kMaxExperts64; ++g) {
-      if (64 * g >= a.n_exp) break;
-      unsigned long long hit = __ballot((cnt[g] % kBM + 31) / 32 == rp);
-      const int total = __popcll(hit);
-      if (item < base + total) {
-        for (int i = item - base; i > 0; --i) hit &= hit - 1;
-        const int first = __ffsll(hit) - 1;
-        c.e = 64 * g + first;
-        c.r0 = __shfl(r0[g], first); c.cnt = __shfl(cnt[g], first);
-        c.r = c.cnt / kBM * kBM;
-        return true;
-      }
-      base += total;
-    }
-  }
-  return false;
-}
+static_assert(kBM == kChunkRows, "the chunk tables' rows");
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
 constexpr int kRP = kBM / 32;             // 32-row fragments ("row pairs") of a chunk
@@ -232,11 +170,20 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
     bx = j - round * (int)gridDim.x;
     item = 8 * round + (b & 7);
   }
-  if (!(a.by_length ? find_gemm_chunk(a, item, ch) : find_chunk<kBM>(a, item, ch))) return;
-  // (found by shuffles, the same in every lane: moved into scalar registers, and with them every base address)
-  const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
-  const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
-  const ExpertDesc& d = a.desc[e];
+  if (a.plan != nullptr) {                 // (one scalar load: the preparing launch has made the table)
+    const auto* at = reinterpret_cast<const __attribute__((address_space(4))) ChunkEntry*>(reinterpret_cast<uintptr_t>(a.plan)) + item;
+    ch.e = at->e; ch.r0 = at->r0; ch.cnt = at->cnt; ch.r = at->r;
+    if (ch.e < 0) return;
+  } else {                                 // shared experts: every one has the same rows
+    const int per = (a.T + kBM - 1) / kBM;
+    ch.e = item / per; ch.r = (item - ch.e * per) * kBM; ch.r0 = ch.e * a.T; ch.cnt = a.T;
+    if (ch.e >= a.n_exp) return;
+  }
+  const int e = ch.e, r0 = ch.r0, cnt = ch.cnt, r = ch.r;
+  // the expert's table entry: everything of it that the block needs, requested together
+  const ConstDesc d = const_desc(a.desc + e);
+  const int has_factors = d->has_factors, q3 = d->q3;
+  const int comp = *const_i32((a.comp_rows ? a.comp_rows : &a.desc->q3) + (a.comp_rows ? e : 0));
   const int th = threadIdx.x, lane = th & 63;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
   const int q = lane >> 4, c = lane & 15;
@@ -244,25 +191,30 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
   const int tile0 = (bx * WAVES + wave) * kNTW;
 
   const int code_bytes = a.KS * a.NT * tdw * 4, meta_bytes = a.G * a.NT * kTileN * 4;
-  const bool lowrank = a.rank > 0 && __builtin_amdgcn_readfirstlane(d.has_factors) != 0 && a.row_pair != nullptr &&
-                       __builtin_amdgcn_readfirstlane(a.comp_rows[e]) > 0;
+  const uint32_t* codes[NM];
+  const uint32_t* metas[NM];
+  const _Float16* bfs[NM];
+  int ranks[NM];
+  float lam[NM];
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    const int mat = DUAL ? m : 2;
+    codes[m] = d->codes[mat]; metas[m] = d->meta[mat]; bfs[m] = d->bf[mat]; ranks[m] = d->rank[mat]; lam[m] = d->inv_lambda[mat];
+  }
+  const bool lowrank = a.rank > 0 && has_factors != 0 && a.row_pair != nullptr && comp > 0;
   // every projection has the rank of its own factor pair (Section 3.1): the expert runs the rank
   // steps of the larger one, a resource of the size its rank fills makes the other read zeros
   int LSm[NM];
   __amdgpu_buffer_rsrc_t code_rs[NM], meta_rs[NM], bf_rs[NM];
   bool q3m[NM];
-  float lam[NM];
 #pragma unroll
   for (int m = 0; m < NM; ++m) {
-    const int mat = DUAL ? m : 2;
-    LSm[m] = lowrank ? (min(__builtin_amdgcn_readfirstlane(d.rank[mat]), a.rank) + 31) / 32 : 0;
-    q3m[m] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
-    code_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(uniform_ptr(d.codes[mat])), 0, code_bytes, 0x00020000);
-    meta_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(uniform_ptr(d.meta[mat])), 0, meta_bytes, 0x00020000);
+    LSm[m] = lowrank ? int(uint32_t(min(ranks[m], a.rank) + 31) / 32) : 0;
+    q3m[m] = Q3 && ((q3 >> (DUAL ? m : 2)) & 1) != 0;
+    code_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(codes[m]), 0, code_bytes, 0x00020000);
+    meta_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(metas[m]), 0, meta_bytes, 0x00020000);
     // (a 3-bit pair's rank steps read zeros here and fetch their units themselves)
-    bf_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(uniform_ptr(d.bf[mat])), 0,
-                                                 q3m[m] ? 0 : a.NT * LSm[m] * 1024, 0x00020000);
-    lam[m] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(d.inv_lambda[mat])));
+    bf_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(bfs[m]), 0, q3m[m] ? 0 : a.NT * LSm[m] * 1024, 0x00020000);
   }
   const int LS = max(LSm[0], LSm[NM - 1]);
   const int gps = kTileK >> a.group_shift;               // groups per k-step
@@ -435,12 +387,16 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
     }
   };
   const StageOffsets so = stage_offsets(a, rin, cnt - r, rp_n, lane);
-  Slot2<BITS, NM, kNTW> cur;
-  fetch(0, cur);
+  // (the activations need nothing of the expert's table entry)
   if (rp_n == 4) stage_half<4>(a, xs, 0, 0, rin, so, wave, lane);
   else if (rp_n == 3) stage_half<3>(a, xs, 0, 0, rin, so, wave, lane);
   else if (rp_n == 2) stage_half<2>(a, xs, 0, 0, rin, so, wave, lane);
   else stage_half<1>(a, xs, 0, 0, rin, so, wave, lane);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int m = 0; m < NM; ++m) asm volatile("" : "+s"(lam[m]));       // (read here, with the rest: not again in front of the k-steps, whose waits count loads)
+  Slot2<BITS, NM, kNTW> cur;
+  fetch(0, cur);
   if (LS > 0) stage_rank(xs + 2 * kHalfUnits, 0, min(LS, kRankFirst));
   wait_loads_barrier();
 
@@ -508,8 +464,8 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void qgemm_tile_kernel(KArgs a)
           const int tile = tile0 + t;
           if (q3m[m] && st < LSm[m] && tile < a.NT) {
             const int mat = DUAL ? m : 2;
-            qu.codes[t][m] = uniform_ptr(d.bfc[mat])[(size_t(st) * a.NT + tile) * kWave + lane];
-            const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(uniform_ptr(d.bf[mat])) +
+            qu.codes[t][m] = uniform_ptr(d->bfc[mat])[(size_t(st) * a.NT + tile) * kWave + lane];
+            const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(uniform_ptr(d->bf[mat])) +
                                                             ((size_t(st) * (a.NT / 4) + (tile >> 2)) * 4 + q) * 32 + (c & 1) * 16);
             qu.meta[t][m][0] = v.x; qu.meta[t][m][1] = v.y; qu.meta[t][m][2] = v.z; qu.meta[t][m][3] = v.w;
           }
@@ -685,8 +641,8 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, b
   if (!find_chunk<16 * MT>(a, blockIdx.x, ch)) return;
   const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
   const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
-  const ExpertDesc& d = a.desc[e];
-  if (!d.has_factors) return;
+  const ConstDesc d = const_desc(a.desc + e);
+  if (!d->has_factors) return;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
   const int q = lane >> 4, c = lane & 15;
   // The chunk's rows are compact rows: row_list names the routed row of each (past the last one: the
@@ -720,11 +676,11 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, b
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       const int tile = blockIdx.y * T + t, m = tile / rt;
-      some |= tile < tiles && 16 * (tile - m * rt) < __builtin_amdgcn_readfirstlane(d.rank[DUAL ? min(m, 1) : 2]);
+      some |= tile < tiles && 16 * (tile - m * rt) < __builtin_amdgcn_readfirstlane(d->rank[DUAL ? min(m, 1) : 2]);
     }
     if (!some) {
       // (the FFN kernel reads the columns of the rank steps its expert runs, those of the expert's larger pair)
-      const int rank_e = max(__builtin_amdgcn_readfirstlane(d.rank[DUAL ? 0 : 2]), __builtin_amdgcn_readfirstlane(d.rank[DUAL ? 1 : 2]));
+      const int rank_e = max(__builtin_amdgcn_readfirstlane(d->rank[DUAL ? 0 : 2]), __builtin_amdgcn_readfirstlane(d->rank[DUAL ? 1 : 2]));
       const int tile = blockIdx.y * T + wave / MT, m = tile / rt, tl = tile - m * rt;
       if (wave < T * MT && tile < tiles && 16 * tl < (rank_e + 31) / 32 * 32) zero_tile(m, tl, wave % MT);
       zero_padding();
@@ -741,11 +697,11 @@ __global__ __launch_bounds__(64 * kXaWaves) void xa_kernel(KArgs a, int items, b
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int tile = min(blockIdx.y * T + t, tiles - 1), m = tile / rt, tl = tile - m * rt, mat = DUAL ? m : 2;
-    valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d.rank[mat]);
-    q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
-    scale[t] = d.xa_scale[mat];
-    af[t] = as_global<uint32_t>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave * (q3t[t] ? 1 : 4);
-    am[t] = q3t[t] ? as_global<uint32_t>(uniform_ptr(d.afm[mat])) + size_t(valid[t] ? tl : 0) * (a.K / 64) * 16 + c : nullptr;
+    valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d->rank[mat]);
+    q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d->q3 >> mat) & 1) != 0;
+    scale[t] = d->xa_scale[mat];
+    af[t] = as_global<uint32_t>(uniform_ptr(d->af[mat])) + size_t(tl) * (a.K / 32) * kWave * (q3t[t] ? 1 : 4);
+    am[t] = q3t[t] ? as_global<uint32_t>(uniform_ptr(d->afm[mat])) + size_t(valid[t] ? tl : 0) * (a.K / 64) * 16 + c : nullptr;
   }
   float4_t acc[T][MT];
 #pragma unroll
@@ -866,8 +822,8 @@ __global__ __launch_bounds__(64 * kXtWaves, 2) void xa_tile_kernel(KArgs a) {
   if (!find_chunk<kBM>(a, blockIdx.y, ch)) return;
   const int e = __builtin_amdgcn_readfirstlane(ch.e), r0 = __builtin_amdgcn_readfirstlane(ch.r0);
   const int cnt = __builtin_amdgcn_readfirstlane(ch.cnt), r = __builtin_amdgcn_readfirstlane(ch.r);
-  const ExpertDesc& d = a.desc[e];
-  if (!d.has_factors) return;
+  const ConstDesc d = const_desc(a.desc + e);
+  if (!d->has_factors) return;
   const int th = threadIdx.x, lane = th & 63;
   const int wave = __builtin_amdgcn_readfirstlane(th >> 6);
   const int q = lane >> 4, c = lane & 15;
@@ -890,7 +846,7 @@ __global__ __launch_bounds__(64 * kXtWaves, 2) void xa_tile_kernel(KArgs a) {
 #pragma unroll
   for (int m = 0; m < NM; ++m) {
     const int first = max(z0 - m * rt, 0);
-    some |= first < min(rt, z1 - m * rt) && 16 * first < __builtin_amdgcn_readfirstlane(d.rank[DUAL ? m : 2]);
+    some |= first < min(rt, z1 - m * rt) && 16 * first < __builtin_amdgcn_readfirstlane(d->rank[DUAL ? m : 2]);
   }
   if (!some) return;
 #pragma unroll
@@ -899,13 +855,13 @@ __global__ __launch_bounds__(64 * kXtWaves, 2) void xa_tile_kernel(KArgs a) {
     af[t] = nullptr; am[t] = nullptr; q3t[t] = false; valid[t] = false;
     if (tile < tiles) {
       const int m = tile / rt, tl = tile - m * rt, mat = DUAL ? m : 2;
-      valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d.rank[mat]);
-      q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d.q3 >> mat) & 1) != 0;
+      valid[t] = 16 * tl < __builtin_amdgcn_readfirstlane(d->rank[mat]);
+      q3t[t] = Q3 && __builtin_amdgcn_readfirstlane((d->q3 >> mat) & 1) != 0;
       if (q3t[t]) {
-        af[t] = reinterpret_cast<GlobalPtr<half8_t>>(as_global<uint32_t>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave + c);
-        am[t] = as_global<uint32_t>(uniform_ptr(d.afm[mat])) + size_t(tl) * (a.K / 64) * 16 + c;
+        af[t] = reinterpret_cast<GlobalPtr<half8_t>>(as_global<uint32_t>(uniform_ptr(d->af[mat])) + size_t(tl) * (a.K / 32) * kWave + c);
+        am[t] = as_global<uint32_t>(uniform_ptr(d->afm[mat])) + size_t(tl) * (a.K / 64) * 16 + c;
       } else {
-        af[t] = as_global<half8_t>(uniform_ptr(d.af[mat])) + size_t(tl) * (a.K / 32) * kWave + c;
+        af[t] = as_global<half8_t>(uniform_ptr(d->af[mat])) + size_t(tl) * (a.K / 32) * kWave + c;
       }
     }
   }
@@ -1000,7 +956,7 @@ __global__ __launch_bounds__(64 * kXtWaves, 2) void xa_tile_kernel(KArgs a) {
   for (int t = 0; t < NT; ++t) {
     if (!valid[t]) continue;
     const int tile = z0 + wave + t * kXtWaves, m = tile / rt, tl = tile - m * rt;
-    const float lam = d.xa_scale[DUAL ? m : 2];
+    const float lam = d->xa_scale[DUAL ? m : 2];
 #pragma unroll
     for (int mt = 0; mt < kXtRowTiles; ++mt) {
       const int row = r + 16 * mt + c;
@@ -1081,9 +1037,8 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.group_shift = gs; a.top_k = f.top_k; a.top_n = f.top_n; a.T = f.T;
   a.rank = f.rank; a.rpad = f.rpad; a.ls = (f.rank + 31) / 32; a.total_rows = f.total_rows;
   const bool comp = f.rank > 0 && f.top_n > 0 && f.row_pair != nullptr;
-  // 128-row chunks: at most one partly filled chunk per expert (by_xcd takes a multiple of 8)
-  const int max_chunks = f.offsets ? f.total_rows / kBM + f.n_exp : f.n_exp * ((f.T + kBM - 1) / kBM);
-  auto items = [&] { return a.by_xcd ? (max_chunks + 7) / 8 * 8 : max_chunks; };
+  const int items_n = f.offsets ? chunk_items(f.total_rows, f.n_exp) : f.n_exp * ((f.T + kBM - 1) / kBM);
+  auto items = [&] { return items_n; };
   const size_t glds = size_t(kGemmLdsUnits) * 16;
 
   // (in A) of the rows that take the term (T * top_n in all), zeros for the others
@@ -1142,7 +1097,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.KS = padded_k(f.H) / kTileK; a.G = padded_k(f.H) / f.group;
   if (comp) xa(std::true_type{}, f.p13);
   a.by_xcd = gemm_by_xcd(f, 2);
-  a.by_length = a.by_xcd && f.total_rows >= kByLengthRows * f.n_exp;
+  a.plan = f.offsets ? f.plan : nullptr;
   if (f.marks) (void)hipEventRecord(f.marks[0], s);
   if (comp && f.q3) hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2, true>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
   else hipLaunchKernelGGL((qgemm_tile_kernel<BITS, true, 2>), dim3((a.NT + 2 * kGemmWaves - 1) / (2 * kGemmWaves), items()), dim3(64 * kGemmWaves), glds, s, a);
@@ -1155,7 +1110,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
   a.KS = padded_k(f.F) / kTileK; a.G = padded_k(f.F) / f.group;
   if (comp) xa(std::false_type{}, f.p2);
   a.by_xcd = gemm_by_xcd(f, 1);
-  a.by_length = 1;
+  a.plan = f.offsets ? f.plan2 : nullptr;
   if (f.marks) (void)hipEventRecord(f.marks[2], s);
   // Four n-tiles per wavefront use a fragment of activations twice as often as two (with two the LDS reads are the
   // bound), but make blocks twice as large: two only while four make fewer blocks than there are CUs.  Whole layer, four / two
@@ -1228,7 +1183,16 @@ hipError_t ffn_init_device() {
 
 int expert_ffn_path(const FfnArgs& f) { return 3 & ~decode_parts(f); }
 
-void expert_ffn_plan_specs(const FfnArgs& f, PlanSpec& p13, PlanSpec& p2) { decode_plan_specs(f, decode_parts(f), p13, p2); }
+FfnTables expert_ffn_tables(const FfnArgs& f) {
+  FfnTables t{};
+  if (f.offsets == nullptr) return t;
+  const int dp = decode_parts(f), items = chunk_items(f.total_rows, f.n_exp);
+  decode_plan_specs(f, dp, t.plan[0], t.plan[1]);
+  // (the order of the chunks: plan.h)
+  if (!(dp & 1)) t.chunk[0] = ChunkSpec{items, gemm_by_xcd(f, 2) && f.total_rows >= kByLengthRows * f.n_exp, f.plan};
+  if (!(dp & 2)) t.chunk[1] = ChunkSpec{items, true, f.plan2};
+  return t;
+}
 
 hipError_t launch_expert_ffn(const FfnArgs& f, hipStream_t s) {
   auto tile = [&](int which) {

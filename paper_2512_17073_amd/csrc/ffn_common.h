@@ -61,8 +61,8 @@ struct KArgs {
                              // with staged rows: K-block sums [kb][compact row][projections * ls * 32]
   float* ha;                 // decode flavour, or null: part sums of (h A2) [slot][row][32] that the fused projection's
                              // blocks leave and the W2 launch adds up (decode_index.h, ha_*), instead of xa_rows_kernel's p
-  const int32_t* plan;       // decode flavour: null (grid = blocks per expert x experts), or the block table
-                             // (PlanEntry per block, plan.h)
+  const int32_t* plan;       // null (shared experts), or the block table (decode flavour: PlanEntry per block, plan.h) or the
+                             // chunk table (grouped GEMM: ChunkEntry per item)
   const int32_t* row_exp;    // per input row: the exponent s of its power-of-two pre-scale (row_exponent below);
                              // routed launches: one per routed row; shared experts: one per token
   const int32_t* tok_exp;    // the same per token, where a kernel reads the bf16 tokens itself (or null)
@@ -70,7 +70,6 @@ struct KArgs {
                              // compact rows of the pairs that take the rank-r term; row_list names the routed row
                              // of each (CompactArgs); null: the rows are the routed rows
   int by_xcd;                // grouped GEMM: the column blocks of a chunk run on one XCD (gemm_by_xcd)
-  int by_length;             // grouped GEMM: whole chunks first (find_gemm_chunk)
 };
 
 // Range of the fp16 operands.  The activations cross the ABI as bf16 (8 exponent bits); the matrix

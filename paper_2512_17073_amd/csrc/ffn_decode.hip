@@ -726,8 +726,7 @@ hipError_t launch_bits(const FfnArgs& f, hipStream_t s, int which) {
     if (comp && !ha) hipLaunchKernelGGL(xa_rows_kernel<false>, dim3(a.rpad / 16, f.n_exp, kblocks), dim3(1024), 0, s, a);
     if (f.marks) (void)hipEventRecord(f.marks[2], s);
     if (by_table) {
-      // (second table behind the first; every K-block uses the same shares)
-      a.plan = f.plan + kPlanEntryInts * plan_blocks(f.n_exp, pairs, f.F / kTileN, f.n_cu);
+      a.plan = f.plan2;                      // (every K-block uses the same shares)
       const int B = plan_blocks(f.n_exp, pairs, a.NT, (f.n_cu + kblocks - 1) / kblocks);
       hipLaunchKernelGGL(k2, dim3(B, 1, kblocks), dim3(64 * kWaves), lds, s, a);
       a.plan = nullptr;
@@ -755,16 +754,12 @@ int decode_w2_kblocks(const FfnArgs& f) {
 }
 
 void decode_plan_specs(const FfnArgs& f, int which, PlanSpec& p13, PlanSpec& p2) {
-  p13 = PlanSpec{0, 0, 0, nullptr};
-  p2 = PlanSpec{0, 0, 0, nullptr};
-  if (f.offsets == nullptr || f.plan == nullptr) return;
   const int pairs = f.T * f.top_k, NT13 = f.F / kTileN, NT2 = f.H / kTileN;
-  const int B13 = plan_blocks(f.n_exp, pairs, NT13, f.n_cu);
-  if (which & 1) p13 = PlanSpec{B13, NT13, f.n_cu, f.plan};
+  if (which & 1) p13 = PlanSpec{plan_blocks(f.n_exp, pairs, NT13, f.n_cu), NT13, f.n_cu, f.plan};
   if (which & 2) {
     const int kb2 = decode_w2_kblocks(f);
     const int target2 = (f.n_cu + kb2 - 1) / kb2;
-    p2 = PlanSpec{plan_blocks(f.n_exp, pairs, NT2, target2), NT2, target2, f.plan + kPlanEntryInts * B13};
+    p2 = PlanSpec{plan_blocks(f.n_exp, pairs, NT2, target2), NT2, target2, f.plan2};
   }
 }
 

@@ -37,7 +37,7 @@ struct BlobLayout {
 
 struct Workspace {       // carved out of the caller's buffer; all offsets 256-byte aligned
   size_t topk_idx, topk_w, counts, offsets, comp_counts, row_pair, pair_row;
-  size_t y_rows, xh, xh_sh, h, p13, p2, y_part, sh_y_part, sh_h, sh_y, plan, tok_exp, row_exp, row_exp_sh;
+  size_t y_rows, xh, xh_sh, h, p13, p2, y_part, sh_y_part, sh_h, sh_y, plan, plan2, tok_exp, row_exp, row_exp_sh;
   size_t cmp_index, cmp_list, total;
 };
 
@@ -122,6 +122,7 @@ hipError_t launch_permute(const moe_lrc_layer* L, const int32_t* idx, int T, int
                           int32_t* offsets, int32_t* row_pair, int32_t* pair_row,
                           int32_t* comp_counts, hipStream_t s);
 struct PlanSpec;   // plan.h
+struct FfnTables;
 // the grouping of the pairs by expert run inside the preparing launch (few pairs): the routing
 // kernel's indices in, the five arrays of moe_lrc_permute out
 struct PermuteArgs { const int32_t* idx; int32_t *counts, *offsets, *row_pair, *pair_row, *comp_counts; int P; };
@@ -153,7 +154,7 @@ struct FfnArgs;
 // the decode flavour and wants (x A1 | x A3) made by further blocks of this launch; else null
 hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _Float16* xg, int rt,
                             const int32_t* offsets, const int32_t* row_pair, int32_t* stat,
-                            const PlanSpec* plans /* two, or null */, const FfnArgs* xa13,
+                            const FfnTables* tables /* or null */, const FfnArgs* xa13,
                             const int32_t* tok_exp /* or null */, int32_t* row_exp,
                             const PermuteArgs* perm /* or null: offsets and row_pair are ready */,
                             const CompactArgs* cmp /* or null */, const RouteArgs* route /* or null: perm->idx is ready */,
@@ -216,7 +217,7 @@ struct FfnArgs {
   size_t ha_bytes;
   void* y_rows;               // [rows][H] bf16
   float* y_part;              // fp32 partial outputs of the W2 K-blocks (decode flavour), or null
-  int32_t* plan;              // decode flavour, routed experts: the block tables (plan.h) of the two projections
+  int32_t *plan, *plan2;      // routed experts: the block or chunk tables (plan.h) of W1|W3 and of W2
   const void* x_tokens;       // the bf16 tokens [T][H] (routed launches)
   int xa13_here;              // decode flavour of W1|W3: (x A1 | x A3) is made by a launch of its own in front of the
                               // FFN kernel (staged layers: the factors arrive after the preparing launch) instead
@@ -247,8 +248,8 @@ int expert_ffn_path(const FfnArgs& a);
 // once per device, before the first launch: lets the FFN kernels use the whole LDS of a CU
 hipError_t ffn_init_device();
 hipError_t decode_init_device();
-// the block tables (plan.h) that launch_expert_ffn(a) will read: to be made by launch_convert_x
-void expert_ffn_plan_specs(const FfnArgs& a, PlanSpec& p13, PlanSpec& p2);
+// the tables (plan.h) that launch_expert_ffn(a) will read: to be made by launch_convert_x
+FfnTables expert_ffn_tables(const FfnArgs& a);
 // y_part != null: the expert outputs are the sums over `kblocks` fp32 partial sums [kb][T*k][H]
 // (the decode flavour's W2 K-blocks) instead of the bf16 rows y_rows
 // residual != null: out = residual + (the weighted sum), rounded once

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
 // chain of a large batch: an expert that nearly every token takes has its rows counted one batch after the other (Qwen3 shape,
 // T = 4096, 4096 rows on one expert: launch 80 -> 50 us with the counting in front and eight batches requested together,
 // and without a pass over the rows for their exponents, which the routing leaves).
-// Then one block makes the block tables of the decode launches (plan.h), and xa_tiles * E further
+// Then one block makes the tables of the FFN launches (plan.h), and xa_tiles * E further
 // blocks compute (x A1 | x A3) for the decode flavour of the fused projection from the bf16 tokens
 // (xa_rows.h), so that no launch of its own stands between this one and the W1|W3 kernel.
 // Where that is done for every token and expert (KArgs::p_tokens) those blocks run beside the grouping instead of
@@ -155,7 +155,7 @@ __device__ inline void xa_block(const PrepGrid& g, int i, int& tile, int& pass) 
 // What a block does once the pairs are grouped: its role by its index.
 template <class Rows>
 __device__ inline void prep_roles(const Rows& grouped, const uint16_t* __restrict__ x, int rows, int H, uint4* __restrict__ xg, int rt, bool routed, int E,
-                                  int top_k, int top_n, int32_t* __restrict__ stat, const PlanSpec& plan0, const PlanSpec& plan1, const PrepGrid& g, const ffn::KArgs& xa,
+                                  int top_k, int top_n, int32_t* __restrict__ stat, const FfnTables& tables, const PrepGrid& g, const ffn::KArgs& xa,
                                   bool have_exp, int32_t* __restrict__ row_exp, const CompactArgs& cmp, const ZeroRowsArgs& zr,
                                   int32_t* __restrict__ host_stat, int32_t* __restrict__ row_tok, ffn::float4_t (*red)[64], uint32_t* row_max) {
   constexpr int kWavesPerBlock = kPrepThreads / 64, kColLanes = kPrepThreads / 16;
@@ -177,8 +177,11 @@ __device__ inline void prep_roles(const Rows& grouped, const uint16_t* __restric
     ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, grouped, x, tile - e * per, e, 0, pass, g.passes, red);
     return;
   }
-  if (block >= g.plan_at()) {                                               // the block tables (plan.h)
-    if (threadIdx.x < 128) make_plan([&](int e) { return grouped.offset(e); }, E, threadIdx.x < 64 ? plan0 : plan1, threadIdx.x < 64 ? PlanSpec{0, 0, 0, nullptr} : plan0, threadIdx.x & 63);
+  if (block >= g.plan_at()) {                                               // the tables of the FFN launches (plan.h)
+    const auto offset = [&](int e) { return grouped.offset(e); };
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (part < 2) make_plan(offset, E, part == 0 ? tables.plan[0] : tables.plan[1], part == 0 ? PlanSpec{0, 0, 0, nullptr} : tables.plan[0], lane);
+    else if (part < 4) make_chunks(offset, E, part == 2 ? tables.chunk[0] : tables.chunk[1], lane);
     return;
   }
   if (block < g.rows_at()) {
@@ -256,8 +259,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
                                                    uint4* __restrict__ xg, int rt,
                                                    const int32_t* offsets,
                                                    const int32_t* row_pair, int E, int top_k,
-                                                   int top_n, int32_t* __restrict__ stat, PlanSpec plan0,
-                                                   PlanSpec plan1, PrepGrid g, ffn::KArgs xa,
+                                                   int top_n, int32_t* __restrict__ stat, FfnTables tables, PrepGrid g, ffn::KArgs xa,
                                                    const int32_t* tok_exp, int32_t* __restrict__ row_exp,
                                                    PermuteArgs perm, CompactArgs cmp, RouteArgs route, ZeroRowsArgs zr,
                                                    int32_t* __restrict__ host_stat, int32_t* __restrict__ row_tok) {
@@ -276,7 +278,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
   }
   const bool routed = row_pair != nullptr;
   auto roles = [&](const auto& grouped, bool have_exp) {
-    prep_roles(grouped, x, rows, H, xg, rt, routed, E, top_k, top_n, stat, plan0, plan1, g, xa, have_exp, row_exp, cmp, zr, host_stat, row_tok, red, row_max);
+    prep_roles(grouped, x, rows, H, xg, rt, routed, E, top_k, top_n, stat, tables, g, xa, have_exp, row_exp, cmp, zr, host_stat, row_tok, red, row_max);
   };
   if (perm.idx != nullptr && group_small_fits(perm.P, E)) {
     const bool out = block == g.zero_at();     // the block that writes the results
@@ -336,15 +338,14 @@ hipError_t launch_combine(const moe_lrc_layer* L, const void* y_rows, const floa
 
 hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _Float16* xg, int rt,
                             const int32_t* offsets, const int32_t* row_pair, int32_t* stat,
-                            const PlanSpec* plans, const FfnArgs* xa13, const int32_t* tok_exp, int32_t* row_exp,
+                            const FfnTables* tables, const FfnArgs* xa13, const int32_t* tok_exp, int32_t* row_exp,
                             const PermuteArgs* perm, const CompactArgs* cmp, const RouteArgs* route, const ZeroRowsArgs& zr,
                             hipStream_t s, int32_t* host_stat) {
   const moe_lrc_config& c = L->cfg;
   const int rows = row_pair ? T * c.top_k : T;
   const int row_blocks = (rows + 15) / 16, ky = prep_columns(c.hidden, rows, L->n_cu);
-  const PlanSpec none{0, 0, 0, nullptr};
-  const PlanSpec p0 = plans ? plans[0] : none, p1 = plans ? plans[1] : none;
-  const int plan_block = p0.B + p1.B > 0 ? 1 : 0;
+  const FfnTables t = tables ? *tables : FfnTables{};
+  const int plan_block = t.plan[0].plan || t.plan[1].plan || t.chunk[0].table || t.chunk[1].table ? 1 : 0;
   // (x A1 | x A3) of the decode flavour: 16-column tiles of both factors
   ffn::KArgs xa{};
   int xa_tiles = 0;
@@ -370,7 +371,7 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
   const int cmp_block = (cmp && row_pair && stat) ? 1 : 0;     // (the compaction rides the per-expert counting)
   hipLaunchKernelGGL(prep_kernel, dim3(g.blocks()),
                      dim3(kPrepThreads), 0, s, (const uint16_t*)x_bf16, rows, c.hidden, reinterpret_cast<uint4*>(xg), rt, offsets,
-                     row_pair, c.n_experts, c.top_k, c.top_n, stat, p0, p1, g, xa, tok_exp, row_exp,
+                     row_pair, c.n_experts, c.top_k, c.top_n, stat, t, g, xa, tok_exp, row_exp,
                      perm ? *perm : PermuteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0},
                      cmp_block ? *cmp : CompactArgs{nullptr, nullptr},
                      (route && perm) ? *route : RouteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, 0}, zr, host_stat,

@@ -131,4 +131,64 @@ __device__ inline void make_plan(const Offset& offset, int E, const PlanSpec sp,
   for (int b = used + lane; b < B; b += 64) reinterpret_cast<PlanEntry*>(plan)[b] = PlanEntry{-1, 0, 0, 0, 0, 0, 0, 0};
 }
 
+// The grouped GEMM's work items: chunks of kChunkRows rows of one expert.  Item i of a launch reads entry i (expert, or -1: nothing
+// to do; the expert's first row and number of rows; the chunk's first row within them) with one scalar load, instead of counting
+// every expert's chunks in every block.  By expert, or (by_length) the whole chunks of all experts first, then the experts' last
+// chunks, those with more row pairs (32 rows) before those with fewer, so that short blocks fill the end of a launch that is a few
+// rounds of blocks.  W2 alone in this order, whole layer (us): Mixtral shape T = 700 660 -> 647, 1024 902 -> 843, 2048 1565 -> 1548, DeepSeek
+// T = 512 and Qwen3 T = 4096 unchanged.  W1|W3 too: Qwen3 T = 1500 285 -> 278, 4096 553 -> 547; not where an expert's weights are
+// far beyond the L2, which its last chunk then reads once more (Mixtral T = 700 647 -> 668, 2048 1498 -> 1513), nor below 64 rows
+// an expert, whose chunks are nearly alike (DeepSeek T = 512 198 -> 202).
+constexpr int kChunkRows = 128;
+struct ChunkEntry { int32_t e, r0, cnt, r; };
+constexpr int kChunkEntryInts = 4;
+struct ChunkSpec { int items; bool by_length; int32_t* table; };       // table == null: none wanted
+LRC_HD int chunk_count(int rows) { return (rows + kChunkRows - 1) / kChunkRows; }
+LRC_HD int chunk_tail_pairs(int rows) { return (rows % kChunkRows + 31) / 32; }       // row pairs of the last, partly filled chunk (0: none)
+// most items of a launch: every expert but the whole chunks' has at most one partly filled chunk; a multiple of 8 for the XCD order
+LRC_HD int chunk_items(int total_rows, int n_exp) { return (total_rows / kChunkRows + n_exp + 7) / 8 * 8; }
+
+template <class Offset>
+__device__ inline void make_chunks(const Offset& offset, int E, const ChunkSpec sp, int lane) {
+  if (sp.table == nullptr) return;
+  ChunkEntry* table = reinterpret_cast<ChunkEntry*>(sp.table);
+  constexpr int kChunks = 4;                   // (at most 256 experts)
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int r0[kChunks], cnt[kChunks];
+#pragma unroll
+  for (int i = 0; i < kChunks; ++i) {
+    r0[i] = cnt[i] = 0;
+    if (64 * i >= E) continue;
+    const int e = min(64 * i + lane, E - 1);
+    r0[i] = offset(e);
+    cnt[i] = offset(e + 1);
+  }
+  int base = 0;
+#pragma unroll
+  for (int i = 0; i < kChunks; ++i) {
+    if (64 * i >= E) continue;
+    cnt[i] = 64 * i + lane < E ? cnt[i] - r0[i] : 0;
+    const int n = sp.by_length ? cnt[i] / kChunkRows : chunk_count(cnt[i]);
+    const int incl = wave_scan(n), first = base + incl - n;
+    for (int j = 0; j < n; ++j)
+      if (first + j < sp.items) table[first + j] = ChunkEntry{64 * i + lane, r0[i], cnt[i], j * kChunkRows};
+    base += lane_value(incl, 63);
+  }
+  if (sp.by_length)
+    for (int rp = kChunkRows / 32; rp > 0; --rp)
+#pragma unroll
+      for (int i = 0; i < kChunks; ++i) {
+        if (64 * i >= E) continue;
+        const bool mine = chunk_tail_pairs(cnt[i]) == rp;
+        const unsigned long long m = __ballot(mine);
+        const int at = base + __popcll(m & below);
+        if (mine && at < sp.items) table[at] = ChunkEntry{64 * i + lane, r0[i], cnt[i], cnt[i] / kChunkRows * kChunkRows};
+        base += __popcll(m);
+      }
+  for (int i = base + lane; i < sp.items; i += 64) table[i] = ChunkEntry{-1, 0, 0, 0};
+}
+
+// What the preparing launch makes for the FFN launches: per projection (W1|W3, W2) the one table its flavour reads.
+struct FfnTables { PlanSpec plan[2]; ChunkSpec chunk[2]; };
+
 }  // namespace lrc
