@@ -37,10 +37,9 @@ LRC_HD int waves_per_unit_log2(int units) { return units <= 1 ? 4 : units > 8 ? 
 // W2: tiles t0 + 2u and t0 + 2u + 1.
 LRC_HD int stream_tile(int t0, int u, int m, bool dual) { return dual ? t0 + u : t0 + 2 * u + m; }
 
-// A wavefront walks segments: (phase ph, own unit ts), ph = 0 .. n_ph - 1 over the k-steps of a staging phase, then ph = n_ph
-// over the rank steps.  Own step `si` of a segment is its step si * kw + kwi; a segment is walked in whole turns of the
-// ring, so that ring slots are indexed statically, and while a turn is multiplied the next turn, of the same segment or
-// of the one after it, is fetched.  No step is walked that only pads: a segment's turns follow from its own length.
+// A wavefront walks segments: (phase ph, own unit ts), the k-steps of a staging phase.  Its own step k of a segment is step
+// (k << kw_log2) + kwi; a segment is walked in whole turns of the ring, so that ring slots are indexed statically, and while
+// a turn is multiplied the next turn, of the same segment or of the one after it, is fetched.  The rank steps of the units follow.
 struct StepPlan {
   int KP;        // k-steps per phase (16 with one row tile, 8 with two)
   int n_ph;      // phases of this K-block
@@ -53,69 +52,54 @@ LRC_HD StepPlan step_plan(int KSl, int mt) {
 }
 // Units of a wavefront of group grp (0, 1 or 2: units grp and grp + groups).
 LRC_HD int own_units(int grp, int groups, int units, bool dual) { return (grp < units ? 1 : 0) + (dual && grp + groups < units ? 1 : 0); }
+LRC_HD int phase_steps(const StepPlan& p, int ph, int KSl) { return KSl - ph * p.KP < p.KP ? KSl - ph * p.KP : p.KP; }
+// Own steps of a segment of len steps.
+LRC_HD int own_steps(int len, int kwi, int kw_log2) { return len > kwi ? (len - kwi + (1 << kw_log2) - 1) >> kw_log2 : 0; }
 
-struct Segment {
-  int unit;      // block-relative unit
-  int base;      // absolute k-step of its first step (k-steps)
-  int len;       // steps, shared by kw wavefronts
-  bool lr;       // rank steps of the B factor (else k-steps of packed codes)
+// Where the own steps of a segment lie: byte offsets (wave-uniform) of n-tile `tile`'s codes and metadata at the first and at the last
+// of them.  From one to the next both move by a fixed stride and stop at the last: what is fetched beyond it is not multiplied.  A
+// wavefront without a step of its own in the segment stays at the segment's last step.
+struct Walk {
+  uint32_t code, meta, code_last, meta_last;
+  int n;         // own steps
 };
-// own: units of the wavefront (own_units); beyond the last segment (ph > n_ph, or no rank steps) the length is zero
-LRC_HD Segment segment(int ph, int ts, int own, const StepPlan& p, int grp, int groups, int ks_lo, int KSl, int LS) {
-  Segment s;
-  const int left = KSl - ph * p.KP;
-  s.unit = grp + ts * groups;
-  s.base = ks_lo + ph * p.KP;
-  s.lr = ph >= p.n_ph;
-  s.len = ts >= own ? 0 : ph < p.n_ph ? (left < p.KP ? left : p.KP) : ph == p.n_ph ? LS : 0;
-  return s;
+struct Strides { uint32_t code, meta; };
+LRC_HD Strides walk_strides(int kw_log2, int bits, int NT, int gps) {
+  return Strides{uint32_t(NT << kw_log2) * (kWave * 2 * bits * 4), uint32_t((NT * gps) << kw_log2) * (kTileN * 4)};
 }
-// ... and own steps that are walked, whole turns of the ring.
-LRC_HD int segment_steps(int len, int kw_log2) { return ((len + (kRing << kw_log2) - 1) >> (kw_log2 + 1)) * kRing; }
-static_assert(kRing == 2, "the shift above");
-
-// What own step si of a segment reads (k-share kwi of 1 << kw_log2).
-struct StepRef {
-  bool reg;      // a k-step of packed codes (else a rank step, or nothing)
-  bool lr;       // a rank step of the B factor
-  int unit;      // block-relative unit
-  int ks;        // absolute k-step (reg)
-  int st;        // step within the segment: k-step within the phase (reg), rank step (lr)
-};
-LRC_HD StepRef step_ref(const Segment& s, int si, int kwi, int kw_log2) {
-  StepRef r;
-  r.unit = s.unit;
-  r.st = (si << kw_log2) + kwi;
-  r.ks = s.base + r.st;
-  r.reg = !s.lr && r.st < s.len;
-  r.lr = s.lr && r.st < s.len;
-  return r;
+// first: absolute k-step of the segment's first step
+LRC_HD Walk walk_start(int first, int len, int tile, int kwi, int kw_log2, int bits, int NT, int gps, const Strides& st) {
+  Walk w;
+  w.n = own_steps(len, kwi, kw_log2);
+  const uint32_t ks = first + (kwi < len ? kwi : len - 1), more = w.n > 1 ? w.n - 1 : 0;
+  w.code = (ks * NT + tile) * (kWave * 2 * bits * 4);
+  w.meta = (ks * gps * NT + tile) * (kTileN * 4);
+  w.code_last = w.code + more * st.code;
+  w.meta_last = w.meta + more * st.meta;
+  return w;
 }
-
-// Byte offsets of a lane's loads of one stream of a step (the hardware range-checks offset + size
-// against the resource; a step that reads nothing gets an offset at the end of every resource).
-// q3: the stream's factor pair is held at 3 bits (layout.h).  A rank step then reads, through `bf`,
-// the lane's half of the 32 bytes of metadata of (rank step, group of four n-tiles, lane group) from
-// a resource of (NT / 4) * LS * 128 bytes, and through `bc` the unit's code dword from a resource of
-// NT * LS * 256 bytes; `bc` of any other step lies past every resource.
-struct LaneOffsets { uint32_t code0, code1, meta, bf, bc; };
-LRC_HD LaneOffsets lane_offsets(const StepRef& r, int tile, bool tile_ok, int lane, int bits, int NT, int group_shift,
-                                uint32_t code_bytes, uint32_t meta_bytes, uint32_t bf_bytes_max, bool q3 = false) {
-  const uint32_t tdw = kWave * 2 * bits, q = lane >> 4, c = lane & 15;
-  const uint32_t gps = kTileK >> group_shift;
-  const uint32_t meta_lane = ((q * kLaneK) >> group_shift) * (uint32_t(NT) * kTileN * 4) + c * 4;
-  LaneOffsets o;
-  const bool ok = r.reg && tile_ok, lr = r.lr && tile_ok;
-  const uint32_t past = code_bytes > bf_bytes_max ? code_bytes : bf_bytes_max;
-  const uint32_t tile_base = (uint32_t(r.ks) * NT + tile) * (tdw * 4);
-  o.code0 = (ok ? tile_base : past) + lane * 16;
-  o.code1 = (ok ? tile_base : code_bytes) + 1024 + lane * (bits == 3 ? 8 : 16);
-  o.meta = (ok ? (uint32_t(r.ks) * gps * NT + tile) * (kTileN * 4) : meta_bytes) + meta_lane;
-  // (selects on wave-uniform conditions rather than branches: the loads of a step stay in one block)
-  const bool lq = q3 && lr;
-  const uint32_t unit = uint32_t(r.st) * NT + tile, group4 = uint32_t(r.st) * (NT / 4) + (tile >> 2);
-  o.bf = (lq ? group4 * 128 : lr ? unit * 1024 : past) + (lq ? q * 32 + (c & 1) * 16 : lane * 16);
-  o.bc = (lq ? unit * 256 : 0xfffffe00u) + lane * 4;
+LRC_HD void walk_on(Walk& w, const Strides& st) {
+  w.code = w.code + st.code < w.code_last ? w.code + st.code : w.code_last;
+  w.meta = w.meta + st.meta < w.meta_last ? w.meta + st.meta : w.meta_last;
+}
+// A lane's part of the offsets of a k-step's loads: the first 16 bytes of its codes, the rest, its metadata.  A stream without a tile
+// adds kNoTile, which lies past every resource (the hardware then reads zeros without touching memory).
+constexpr uint32_t kNoTile = 0x80000000u;
+struct LaneOffsets { uint32_t code0, code1, meta; };
+LRC_HD LaneOffsets lane_offsets(int lane, int bits, int NT, int group_shift, bool tile_ok) {
+  const uint32_t q = lane >> 4, c = lane & 15, past = tile_ok ? 0u : kNoTile;
+  return LaneOffsets{past + lane * 16, past + 1024 + lane * (bits == 3 ? 8 : 16), past + ((q * kLaneK) >> group_shift) * (uint32_t(NT) * kTileN * 4) + c * 4};
+}
+// Byte offsets of a lane's loads of rank step st of one stream (range-checked: a step past the stream's own rank, or without a tile,
+// lies past the resource): the B factor's unit; or, of a pair held at 3 bits (layout.h), through `bf` the lane's half of the 32
+// bytes of metadata of (rank step, group of four n-tiles, lane group) from a resource of (NT / 4) * LS * 128 bytes, and through `bc` the
+// unit's code dword from a resource of NT * LS * 256 bytes.
+struct RankOffsets { uint32_t bf, bc; };
+LRC_HD RankOffsets rank_offsets(int st, int tile, bool ok, int lane, int NT, bool q3) {
+  const uint32_t q = lane >> 4, c = lane & 15, unit = uint32_t(st) * NT + tile, group4 = uint32_t(st) * (NT / 4) + (tile >> 2);
+  RankOffsets o;
+  o.bf = ok ? (q3 ? group4 * 128 + q * 32 + (c & 1) * 16 : unit * 1024 + lane * 16) : kNoTile;
+  o.bc = ok ? unit * 256 + lane * 4 : kNoTile;
   return o;
 }
 

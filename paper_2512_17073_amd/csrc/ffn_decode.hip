@@ -71,8 +71,6 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
   const int comp = *const_i32((a.comp_rows ? a.comp_rows : &a.desc->q3) + (a.comp_rows ? e : 0));
   const uint32_t* codes[NS] = {d->codes[DUAL ? 0 : 2], d->codes[DUAL ? 1 : 2]};
   const uint32_t* metas[NS] = {d->meta[DUAL ? 0 : 2], d->meta[DUAL ? 1 : 2]};
-  const _Float16* bfs[NS] = {d->bf[DUAL ? 0 : 2], d->bf[DUAL ? 1 : 2]};
-  const uint32_t* bfcs[NS] = {d->bfc[DUAL ? 0 : 2], d->bfc[DUAL ? 1 : 2]};
   const int ranks[NS] = {d->rank[DUAL ? 0 : 2], d->rank[DUAL ? 1 : 2]};
   const float lam[2] = {d->inv_lambda[DUAL ? 0 : 2], d->inv_lambda[DUAL ? 1 : 2]};
   // (x A1 | x A3) kept per token (ranks up to kXaTokensRank: its fragments are at most one per wavefront): the token
@@ -167,26 +165,14 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
   const int LS = max(LSm[0], LSm[1]);
   // 16-column tiles of (h A2) that this launch makes (fused projection) or adds up (W2)
   const int ht = HA && lowrank ? int(uint32_t(min(rank2, a.rank) + 15) / 16) : 0;
-  const uint32_t bf_bytes_max = uint32_t(a.NT) * a.ls * 1024;
 
-  __amdgpu_buffer_rsrc_t code_rs[NS], meta_rs[NS], bf_rs[NS], bc_rs[NS];
+  __amdgpu_buffer_rsrc_t code_rs[NS], meta_rs[NS];
   bool q3m[NS];
 #pragma unroll
   for (int m = 0; m < NS; ++m) {
-    if (!DUAL && m > 0) {                    // (both streams read one projection)
-      q3m[m] = q3m[0]; code_rs[m] = code_rs[0]; meta_rs[m] = meta_rs[0]; bf_rs[m] = bf_rs[0];
-      if constexpr (Q3) bc_rs[m] = bc_rs[0];
-      continue;
-    }
     q3m[m] = Q3 && ((q3 >> (DUAL ? m : 2)) & 1) != 0;
     code_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(codes[m]), 0, code_bytes, 0x00020000);
     meta_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(metas[m]), 0, meta_bytes, 0x00020000);
-    // (3-bit pair: the B section's metadata, 128 bytes per rank step and group of four n-tiles)
-    bf_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(bfs[m]), 0,
-                                                 q3m[m] ? uint32_t(a.NT / 4) * LSm[m] * 128 : uint32_t(a.NT) * LSm[m] * 1024, 0x00020000);
-    if constexpr (Q3)     // the code dwords of a 3-bit pair's B units (no bytes for an fp16 pair: every read gives zero)
-      bc_rs[m] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(q3m[m] ? bfcs[m] : codes[m]), 0,
-                                                   q3m[m] ? uint32_t(a.NT) * LSm[m] * 256 : 0u, 0x00020000);
   }
   // (in A) fragments: [projection][rank step][row tile][lane].  Up to 32 of them sit behind the staged
   // activations from the start of a pass; more (ranks above 256) take the place of the activations
@@ -256,31 +242,101 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
     }
   };
 
-  // The steps of the wavefront's segments are fetched a turn of the ring ahead of their use (past the last one: zeros).
-  auto fetch = [&](Slot<BITS, NS>& sl, const Segment& seg, int si) {
-    const StepRef ref = step_ref(seg, si, kwi, kwl);
+  // The own steps of the wavefront's segments are fetched a turn of the ring ahead of their use: wave-uniform offsets that move by a
+  // stride, beside lane offsets that stay (a scalar instruction of each of the sixteen wavefronts goes through the one scalar unit
+  // of the CU: sixty a step, with the offsets formed anew, were a good part of a step; about 25 now.  W2 alone, before and with this:
+  // Mixtral T = 64 48 -> 46 us, T = 13 at 3 bits 52 -> 46, T = 1 17.1 -> 16.2; W1|W3 at T = 13, 3 bits 87 -> 81).
+  // The same loads bring the units' first rank steps at the end: other resources and lane offsets, no branch between two
+  // kinds of loads, behind which the compiler's waits would be for all of them.
+  const int gps = kTileK >> a.group_shift;
+  const Strides strides = walk_strides(kwl, BITS, a.NT, gps);
+  constexpr int NLO = DUAL && !Q3 ? 1 : NS;    // W1 and W3 are laid out alike: one set of offsets serves both (registers: the kernel is at its 128)
+  struct Source {
+    Walk at;                                  // of the next fetch
+    Strides by;
+    uint32_t code2, meta2;                    // W2: from the first stream's tile to the second's
+    LaneOffsets lo[NLO];
+    __amdgpu_buffer_rsrc_t code[NS], meta[NS];
+  } src;
+  auto fetch = [&](Slot<BITS, NS>& sl) {
 #pragma unroll
     for (int m = 0; m < NS; ++m) {
-      const int tile = stream_tile(t0, ref.unit, m, DUAL);
-      const LaneOffsets o = lane_offsets(ref, tile, tile < t1, lane, BITS, a.NT, a.group_shift, code_bytes, meta_bytes, bf_bytes_max,
-                                         Q3 && q3m[m]);
-      const bool lr = ref.lr;
-      const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(lr ? bf_rs[m] : code_rs[m], lr ? o.bf : o.code0, 0, 0);
+      const uint32_t code = src.at.code + (m > 0 && !DUAL ? src.code2 : 0), meta = src.at.meta + (m > 0 && !DUAL ? src.meta2 : 0);
+      const LaneOffsets& lo = src.lo[m < NLO ? m : 0];
+      const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(src.code[m], lo.code0, code, 0);
       sl.cw[m][0] = v0[0]; sl.cw[m][1] = v0[1]; sl.cw[m][2] = v0[2]; sl.cw[m][3] = v0[3];
       if constexpr (BITS == 3) {
-        const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(code_rs[m], o.code1, 0, 0);
+        const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(src.code[m], lo.code1, code, 0);
         sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1];
       } else if constexpr (BITS == 4) {
-        const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(code_rs[m], o.code1, 0, 0);
+        // (code1 by the instruction's own offset, a register less: with 128 in use the kernel spilled.  A rank step reads the next unit's
+        // 16 bytes with it and leaves them)
+        const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(src.code[m], lo.code0 + 1024, code, 0);
         sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1]; sl.cw[m][6] = v1[2]; sl.cw[m][7] = v1[3];
       }
-      if constexpr (Q3) sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(lr ? bc_rs[m] : meta_rs[m], lr ? o.bc : o.meta, 0, 0);
-      else sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(meta_rs[m], o.meta, 0, 0);
+      sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(src.meta[m], lo.meta, meta, 0);
+    }
+    walk_on(src.at, src.by);
+  };
+  // fetches from here on: the steps of (phase ph, own unit ts), or nothing
+  auto fetch_from = [&](int ph, int ts, bool some) {
+    const int tile = stream_tile(again(t0), again(grp) + ts * groups, 0, DUAL);
+    src.by = strides;
+    src.at = walk_start(again(ks_lo) + ph * KP, some ? phase_steps(sp, ph, KSl) : 1, some ? tile : 0, again(kwi), kwl, BITS, a.NT, gps, strides);
+    src.code2 = kWave * 2 * BITS * 4; src.meta2 = kTileN * 4;
+#pragma unroll
+    for (int m = 0; m < NS; ++m) {
+      if (m < NLO) src.lo[m] = lane_offsets(lane, BITS, a.NT, a.group_shift, some && (DUAL ? tile : tile + m) < t1);
+      src.code[m] = code_rs[m]; src.meta[m] = meta_rs[m];
     }
   };
-  const int last_ph = LS > 0 ? sp.n_ph : sp.n_ph - 1;
-  Segment seg = segment(0, 0, own, sp, grp, groups, ks_lo, KSl, LS);
+  // The B factor of stream m's projection, of the size its rank fills (3-bit pair: the B section's metadata, 128 bytes per rank step and
+  // group of four n-tiles, and the code dwords of its units; no bytes of these for an fp16 pair: every read gives zero).  Read from
+  // the table again where it is used: it would not fit the scalar registers through the k-steps.
+  auto rank_rsrc = [&](int m, __amdgpu_buffer_rsrc_t& bf, __amdgpu_buffer_rsrc_t& bc) {
+    const KernArgs ka = kern_args();
+    const ConstDesc dd = const_desc(ka->desc + e);
+    const int mat = DUAL ? m : 2, NT = ka->NT;
+    bf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(dd->bf[mat]), 0, q3m[m] ? uint32_t(NT / 4) * LSm[m] * 128 : uint32_t(NT) * LSm[m] * 1024, 0x00020000);
+    if constexpr (Q3) bc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(dd->bfc[mat]), 0, q3m[m] ? uint32_t(NT) * LSm[m] * 256 : 0u, 0x00020000);
+  };
+  // ... or the first rank step of own unit ts (a stream past its own rank, or without a unit, reads nothing)
+  auto fetch_rank_from = [&](int ts) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));              // (the offsets are made here, not kept in registers through the k-steps)
+    const int first = again(t0), g = again(grp), k = again(kwi);
+    src.by = Strides{0, 0};
+    src.at = Walk{0, 0, 0, 0, 0};
+    src.code2 = src.meta2 = 0;
+#pragma unroll
+    for (int m = 0; m < NS; ++m) {
+      const int tile = stream_tile(first, g + ts * groups, m, DUAL);
+      if (m < NLO) {
+        // (a step past the stream's rank lies past its resource)
+        const RankOffsets o = rank_offsets(k, tile, ts < own && tile < t1, ln, a.NT, Q3 && q3m[m]);
+        src.lo[m] = LaneOffsets{o.bf, kNoTile, Q3 ? o.bc : kNoTile};
+      }
+      if (ts == 0) {
+        if constexpr (Q3) rank_rsrc(m, src.code[m], src.meta[m]);
+        else rank_rsrc(m, src.code[m], src.code[m]);
+      }
+    }
+  };
+  // rank step st of own unit ts, beyond the first
+  auto fetch_rank = [&](Slot<BITS, NS>& sl, int ts, int st) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int m = 0; m < NS; ++m) {
+      const int tile = stream_tile(t0, grp + ts * groups, m, DUAL);
+      const RankOffsets o = rank_offsets(st, tile, ts < own && tile < t1, ln, a.NT, Q3 && q3m[m]);
+      const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(src.code[m], o.bf, 0, 0);
+      sl.cw[m][0] = v0[0]; sl.cw[m][1] = v0[1]; sl.cw[m][2] = v0[2]; sl.cw[m][3] = v0[3];
+      if constexpr (Q3) sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(src.meta[m], o.bc, 0, 0);
+    }
+  };
   Slot<BITS, NS> ring[RING];
+  static_assert(RING >= TS, "the last turn leaves a slot to every unit's first rank step");
 
   // ---- start of the first pass: everything that is left is requested before anything is awaited ----
   p_start(a, 0);
@@ -299,10 +355,11 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
       }
   }
   __builtin_amdgcn_sched_barrier(0);
+  fetch_from(0, 0, own > 0);
 #pragma unroll
-  for (int i = 0; i < RING; ++i) fetch(ring[i], seg, i);
+  for (int i = 0; i < RING; ++i) fetch(ring[i]);
   __builtin_amdgcn_sched_barrier(0);
-  constexpr int kFetchLoads = NS * (BITS == 2 ? 2 : 3);
+  constexpr int kAheadLoads = RING * NS * (BITS == 2 ? 2 : 3);
 
   for (int r = 0; r < cnt; r += 16 * MT) {
     // every pass computes all MT row tiles (a last pass with fewer rows computes columns nobody stores)
@@ -314,10 +371,13 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
       stage_issue(*ka, ra, 0, min(KP, KSl));
       p_start(*ka, ra);
       exp_issue(*ka, ra);
+      fetch_from(0, 0, own > 0);
+#pragma unroll
+      for (int i = 0; i < RING; ++i) fetch(ring[i]);
     }
     if constexpr (joined) p_join(again(r));
     if (r > 0) wait_loads_barrier();
-    else wait_loads_barrier_but<RING * kFetchLoads>();   // (the first turn of the ring stays in flight)
+    else wait_loads_barrier_but<kAheadLoads>();          // (the first turn of the ring stays in flight)
 
     float4_t acc[TS][MT][NS];
 #pragma unroll
@@ -407,23 +467,6 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
       substep(std::integral_constant<int, 6>{}); substep(std::integral_constant<int, 7>{});
     };
 
-    // Slot i of the ring: consumed, then refilled a turn ahead, from this segment or from the one after it.
-    auto walk = [&](const Segment& next, auto&& use) {
-      const int steps = segment_steps(seg.len, kwl);
-#pragma unroll 1
-      for (int si = 0; si < steps; si += RING) {
-        const bool here = si + RING < steps;
-        const Segment from = {here ? seg.unit : next.unit, here ? seg.base : next.base, here ? seg.len : next.len, here ? seg.lr : next.lr};
-        const int fi = here ? si + RING : 0;
-#pragma unroll
-        for (int i = 0; i < RING; ++i) {
-          const int st = ((si + i) << kwl) + kwi;
-          if (st < seg.len) use(ring[i], st);
-          fetch(ring[i], from, fi + i);
-        }
-      }
-      seg = next;
-    };
 #pragma unroll 1
     for (int ph = 0; ph < sp.n_ph; ++ph) {
       if (ph > 0) {
@@ -431,11 +474,25 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
         stage_issue(*kern_args(), again(r), ph, min(KP, KSl - ph * KP));
         wait_loads_barrier();
       }
+      const int n = own_steps(phase_steps(sp, ph, KSl), kwi, kwl);
 #pragma unroll
       for (int ts = 0; ts < TS; ++ts) {
         if (ts >= own) continue;
-        const int nts = ts + 1 < own ? ts + 1 : 0, nph = nts > 0 ? ph : ph < last_ph ? ph + 1 : r + 16 * MT < cnt ? 0 : sp.n_ph + 1;
-        walk(segment(nph, nts, own, sp, grp, groups, ks_lo, KSl, LS), [&](const Slot<BITS, NS>& cur, int kl) { compute(cur, kl, acc[ts]); });
+        // the segment after this one: the next unit's or the next phase's; after the last one the units' first rank steps
+        const int nts = ts + 1 < own ? ts + 1 : 0, nph = nts > 0 ? ph : ph + 1;
+        const bool last = nph == sp.n_ph;
+        // slot i of the ring: consumed, then refilled a turn ahead (without an own step, one turn to refill it)
+#pragma unroll 1
+        for (int si = 0; si < n || si == 0; si += RING) {
+          const bool over = si + RING >= n;
+          if (over && !last) fetch_from(nph, nts, true);
+#pragma unroll
+          for (int i = 0; i < RING; ++i) {
+            if (si + i < n) compute(ring[i], ((si + i) << kwl) + kwi, acc[ts]);
+            if (over && last) fetch_rank_from(i);
+            fetch(ring[i]);
+          }
+        }
       }
     }
     if (LS > 0) {                             // the rank steps (none unless this block adds the term)
@@ -446,9 +503,20 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
       }
 #pragma unroll
       for (int ts = 0; ts < TS; ++ts) {
-        if (ts >= own) continue;
-        const int nts = ts + 1 < own ? ts + 1 : 0, nph = nts > 0 ? sp.n_ph : r + 16 * MT < cnt ? 0 : sp.n_ph + 1;
-        walk(segment(nph, nts, own, sp, grp, groups, ks_lo, KSl, LS), [&](const Slot<BITS, NS>& cur, int st) { compute_lr(cur, st, acc[ts]); });
+        if (ts >= own || kwi >= LS) continue;
+        compute_lr(ring[ts], kwi, acc[ts]);
+        if (kwi + kw < LS) {                  // (two at a time: one is multiplied, the other on its way)
+          Slot<BITS, NS> sl[2];
+          fetch_rank(sl[0], ts, kwi + kw);
+          fetch_rank(sl[1], ts, kwi + 2 * kw);
+#pragma unroll 1
+          for (int st = kwi + kw; st < LS; st += 2 * kw) {
+            compute_lr(sl[0], st, acc[ts]);
+            fetch_rank(sl[0], ts, st + 2 * kw);
+            if (st + kw < LS) compute_lr(sl[1], st + kw, acc[ts]);
+            fetch_rank(sl[1], ts, st + 3 * kw);
+          }
+        }
       }
     }
 

@@ -40,7 +40,6 @@ std::string check_shape(const Shape& sh) {
   int gs = 0;
   while ((1 << gs) < sh.group) ++gs;
   const uint32_t code_bytes = uint32_t(KS) * NT * (kWave * 2 * sh.bits * 4), meta_bytes = uint32_t(Gr) * NT * kTileN * 4;
-  const uint32_t bf_bytes_max = uint32_t(NT) * sh.ls_max * 1024;
   const int rt = sh.total_rows + kActPadRows;                       // rows of the operand-order activation buffers
   const size_t in_units = size_t(rt) * Kp / 8;
   const int kb_steps = (KS + sh.kblocks - 1) / sh.kblocks;
@@ -103,70 +102,60 @@ std::string check_shape(const Shape& sh) {
         if (r > 0) continue;                  // (the steps do not depend on the pass)
         for (int wave = 0; wave < kWaves; ++wave) {
           const int grp = wave / kw, kwi = wave % kw, own = own_units(grp, groups, units, sh.dual);
-          // the wavefront's own steps in order, segment by segment, and a turn of the ring past the last one
-          std::vector<StepRef> walk;
-          for (int ph = 0; ph <= sp.n_ph; ++ph)
+          const int gps = kTileK >> gs, tb = kWave * 2 * sh.bits * 4;
+          const Strides strides = walk_strides(kwl, sh.bits, NT, gps);
+          for (int ph = 0; ph < sp.n_ph; ++ph)
             for (int ts = 0; ts < own; ++ts) {
-              const Segment seg = segment(ph, ts, own, sp, grp, groups, ks_lo, KSl, LS);
-              const int steps = segment_steps(seg.len, kwl);
-              if (steps % kRing || steps * kw < seg.len) SELF_FAIL("%d steps for a segment of %d", steps, seg.len);
-              for (int si = 0; si < steps; ++si) walk.push_back(step_ref(seg, si, kwi, kwl));
-            }
-          for (int ph : {sp.n_ph + 1, sp.n_ph + 2}) walk.push_back(step_ref(segment(ph, 0, own, sp, grp, groups, ks_lo, KSl, LS), 0, kwi, kwl));
-          for (int n = 0; n < int(walk.size()); ++n) {
-            const StepRef& ref = walk[n];
-            if (ref.reg && ref.lr) SELF_FAIL("step %d is both a k-step and a rank step", n);
-            if ((ref.reg || ref.lr) && ref.unit >= units) SELF_FAIL("step %d is of unit %d of %d", n, ref.unit, units);
-            for (int m = 0; m < kStreams; ++m) {
-              const int tile = stream_tile(t0, ref.unit, m, sh.dual);
-              const bool tile_ok = tile < t1;
-              const uint32_t bf_size = uint32_t(NT) * (lowrank ? sh.LSm[sh.dual ? m : 0] : 0) * 1024;
-              for (int lane = 0; lane < 64; ++lane) {
-                const LaneOffsets o = lane_offsets(ref, tile, tile_ok, lane, sh.bits, NT, gs, code_bytes, meta_bytes, bf_bytes_max);
-                const uint32_t w1 = sh.bits == 3 ? 8 : 16;
-                if (ref.reg && tile_ok) {
-                  if (ref.ks < ks_lo || ref.ks >= ks_lo + KSl || tile < t0) SELF_FAIL("step %d reads k-step %d tile %d outside the block's share", n, ref.ks, tile);
-                  if (o.code0 + 16 > code_bytes) SELF_FAIL("code load at %u + 16 > %u", o.code0, code_bytes);
-                  if (sh.bits > 2 && o.code1 + w1 > code_bytes) SELF_FAIL("second code load at %u > %u", o.code1, code_bytes);
-                  if (o.meta + 4 > meta_bytes) SELF_FAIL("metadata load at %u + 4 > %u", o.meta, meta_bytes);
-                  const uint32_t tdw = kWave * 2 * sh.bits * 4;
-                  if (o.code0 != (uint32_t(ref.ks) * NT + tile) * tdw + lane * 16) SELF_FAIL("code offset does not address tile (%d, %d)", ref.ks, tile);
-                  if (lane == 0) ++seen[(size_t(ref.ks - ks_lo) * NT + tile) * 2 + (sh.dual ? m : 0)];
-                } else {
-                  // (the kernel takes the first load from the B factor's resource on a rank step, else from the codes')
-                  const uint32_t off1 = ref.lr ? o.bf : o.code0, size1 = ref.lr ? bf_size : code_bytes;
-                  if (!(ref.lr && tile_ok) && off1 < size1) SELF_FAIL("idle step %d loads inside a resource (offset %u of %u)", n, off1, size1);
-                  if (o.code1 < code_bytes) SELF_FAIL("idle step %d: second code load inside the resource", n);
-                  if (o.meta < meta_bytes) SELF_FAIL("idle step %d: metadata load inside the resource", n);
-                }
-                if (ref.lr && tile_ok) {
-                  // inside the stream's own factor, or wholly past it (zeros): never astride its end
-                  const bool inside = o.bf + 16 <= bf_size, outside = o.bf >= bf_size;
-                  if (!inside && !outside) SELF_FAIL("rank step %d straddles the end of the B factor", ref.st);
-                  if ((ref.st < (lowrank ? sh.LSm[sh.dual ? m : 0] : 0)) != inside) SELF_FAIL("rank step %d of stream %d: wrong side of the factor's end", ref.st, m);
-                  if (inside && lane == 0) ++seen_lr[(size_t(ref.st) * NT + tile) * 2 + (sh.dual ? m : 0)];
-                }
-                // the same step of a stream whose pair is held at 3 bits: metadata through `bf`, codes through `bc`
-                {
-                  const int LSq = lowrank ? sh.LSm[sh.dual ? m : 0] : 0;
-                  const uint32_t bm_size = uint32_t(NT / 4) * LSq * 128, bc_size = uint32_t(NT) * LSq * 256;
-                  const LaneOffsets oq = lane_offsets(ref, tile, tile_ok, lane, sh.bits, NT, gs, code_bytes, meta_bytes, bf_bytes_max, true);
-                  if (oq.code0 != o.code0 || oq.code1 != o.code1 || oq.meta != o.meta) SELF_FAIL("3-bit pairs change the k-step offsets of step %d", n);
-                  if (ref.lr && tile_ok && ref.st < LSq) {
-                    const uint32_t q = lane >> 4, c = lane & 15;
-                    if (oq.bf != ((uint32_t(ref.st) * (NT / 4) + tile / 4) * 4 + q) * 32 + (c & 1) * 16 || oq.bf + 16 > bm_size)
-                      SELF_FAIL("rank step %d: metadata of a 3-bit unit at %u of %u", ref.st, oq.bf, bm_size);
-                    if (oq.bc != (uint32_t(ref.st) * NT + tile) * 256 + lane * 4 || oq.bc + 4 > bc_size)
-                      SELF_FAIL("rank step %d: codes of a 3-bit unit at %u of %u", ref.st, oq.bc, bc_size);
-                  } else {
-                    if (ref.lr && oq.bf < bm_size) SELF_FAIL("step %d reads 3-bit metadata it should not (offset %u of %u)", n, oq.bf, bm_size);
-                    // (the kernel reads through `bc` on rank steps only, from the codes' resource)
-                    if (ref.lr && oq.bc < bc_size) SELF_FAIL("step %d reads 3-bit codes it should not (offset %u of %u)", n, oq.bc, bc_size);
+              const int unit = grp + ts * groups, first = ks_lo + ph * sp.KP, len = phase_steps(sp, ph, KSl), tile0 = stream_tile(t0, unit, 0, sh.dual);
+              if (unit >= units || len <= 0 || len > sp.KP) SELF_FAIL("segment of unit %d of %d, %d steps", unit, units, len);
+              Walk at = walk_start(first, len, tile0, kwi, kwl, sh.bits, NT, gps, strides);
+              // (the kernel fetches a turn of the ring past the last own step: the last one again)
+              for (int k = 0; k < at.n + 2 * kRing; ++k, walk_on(at, strides)) {
+                const int st = std::min(at.n > 0 ? (std::min(k, at.n - 1) << kwl) + kwi : len - 1, len - 1), ks = first + st;
+                if (k < at.n && (k << kwl) + kwi >= len) SELF_FAIL("own step %d of a segment of %d", k, len);
+                for (int m = 0; m < kStreams; ++m) {
+                  const int tile = stream_tile(t0, unit, m, sh.dual), next_tile = sh.dual ? 0 : m;
+                  const bool ok = tile < t1;
+                  const uint32_t code = at.code + next_tile * tb, meta = at.meta + next_tile * (kTileN * 4);
+                  if (ok && k < at.n) ++seen[(size_t(ks - ks_lo) * NT + tile) * 2 + (sh.dual ? m : 0)];
+                  for (int lane = 0; lane < 64; ++lane) {
+                    const LaneOffsets o = lane_offsets(lane, sh.bits, NT, gs, ok);
+                    const uint32_t q = lane >> 4, c = lane & 15, w1 = sh.bits == 3 ? 8 : 16;
+                    if (!ok) {
+                      if (o.code0 < kNoTile || o.code1 < kNoTile || o.meta < kNoTile || code_bytes > kNoTile || meta_bytes > kNoTile) SELF_FAIL("a stream without a tile reads inside its resource");
+                      if (((uint64_t(o.code1) + code + 16) >> 32) != 0 || ((uint64_t(o.meta) + meta + 4) >> 32) != 0) SELF_FAIL("an offset past every resource wraps round");
+                      continue;
+                    }
+                    if (code + o.code0 != (uint32_t(ks) * NT + tile) * tb + lane * 16) SELF_FAIL("code offset does not address tile (%d, %d)", ks, tile);
+                    if (code + o.code0 + 16 > code_bytes) SELF_FAIL("code load at %u + 16 > %u", code + o.code0, code_bytes);
+                    if (sh.bits > 2 && code + o.code1 + w1 > (uint32_t(ks) * NT + tile + 1) * tb) SELF_FAIL("second code load at %u leaves tile (%d, %d)", code + o.code1, ks, tile);
+                    if (meta + o.meta != ((uint32_t(ks) * gps + ((q * kLaneK) >> gs)) * NT + tile) * (kTileN * 4) + c * 4 || meta + o.meta + 4 > meta_bytes)
+                      SELF_FAIL("metadata load at %u of %u", meta + o.meta, meta_bytes);
                   }
                 }
               }
             }
-          }
+          // rank steps, and the ones fetched past the last
+          for (int ts = 0; ts < own; ++ts)
+            for (int st = kwi; LS > 0 && st < LS + 3 * kw; st += kw)
+              for (int m = 0; m < kStreams; ++m) {
+                const int tile = stream_tile(t0, grp + ts * groups, m, sh.dual), LSq = lowrank ? sh.LSm[sh.dual ? m : 0] : 0;
+                const bool ok = tile < t1;
+                const uint32_t bf_size = uint32_t(NT) * LSq * 1024, bm_size = uint32_t(NT / 4) * LSq * 128, bc_size = uint32_t(NT) * LSq * 256;
+                if (ok && st < LSq) ++seen_lr[(size_t(st) * NT + tile) * 2 + (sh.dual ? m : 0)];
+                for (int lane = 0; lane < 64; ++lane) {
+                  const uint32_t q = lane >> 4, c = lane & 15;
+                  const RankOffsets o = rank_offsets(st, tile, ok, lane, NT, false), oq = rank_offsets(st, tile, ok, lane, NT, true);
+                  if (ok && st < LSq) {
+                    if (o.bf != (uint32_t(st) * NT + tile) * 1024 + lane * 16 || o.bf + 16 > bf_size) SELF_FAIL("rank step %d reads the B factor at %u of %u", st, o.bf, bf_size);
+                    if (oq.bf != ((uint32_t(st) * (NT / 4) + tile / 4) * 4 + q) * 32 + (c & 1) * 16 || oq.bf + 16 > bm_size)
+                      SELF_FAIL("rank step %d: metadata of a 3-bit unit at %u of %u", st, oq.bf, bm_size);
+                    if (oq.bc != (uint32_t(st) * NT + tile) * 256 + lane * 4 || oq.bc + 4 > bc_size) SELF_FAIL("rank step %d: codes of a 3-bit unit at %u of %u", st, oq.bc, bc_size);
+                  } else if (o.bf < bf_size || oq.bf < bm_size || oq.bc < bc_size) {
+                    SELF_FAIL("rank step %d of stream %d reads inside a resource it should not", st, m);
+                  }
+                }
+              }
         }
       }
     }
