@@ -379,188 +379,234 @@ __global__ __launch_bounds__(256) void moment_join_kernel(Moments* part, int par
 // C[M][Nc] = op(A) B with op(A)[i][k] = TRANS ? A[k * lda + i] : A[i * lda + k] and B[k * ldb + j], on
 // v_mfma_f64_16x16x4.  The products here are tall and skinny: A is the K x N matrix, read once, and B
 // is a few megabytes, so a block of four wavefronts takes 128 rows of C and all its columns up to
-// 16 CT, a wavefront 32 rows (two tiles that share every B operand read from LDS); the reduction
-// dimension is split over grid.z so that there are about three blocks per CU, each writing its own
-// partial C (dsum_kernel adds them in order).  k advances in chunks of 32: the next chunk of A (registers) and of B
-// (registers, then the other half of LDS) is requested before the current one is multiplied.  Inside
+// 16 CT, a wavefront 32 rows (two tiles that share every B operand read from LDS).  The reduction dimension, in chunks of 32, is split
+// so that there are two blocks per CU (GemmCut), each writing its own partial C (dsum_kernel adds them in order).  The chunks of A
+// come through a ring of registers, two chunks ahead, those of B through another and then the other half of LDS; all are requested
+// before the current chunk is multiplied.  Inside
 // a chunk, MFMA step (h, s) covers k = 16 h + 4 kq + s for lane group kq, so that a lane reads 32
 // contiguous bytes of a row of A.  TRANS: a lane reads two adjacent entries of a row of A, which are
 // rows 2 i and 2 i + 1 of the wavefront's 32: tile rt holds the rows of parity rt.
 // Bound: HBM (470 MB per product at 4096 x 14336: 80 us at the streaming rate) and the fp64 matrix rate
-// (5.6 GFLOP with 40 columns padded to 48: 80 us) about equally; measured 130-135 us per product, plain
-// or transposed, against 2520 and 730 us with 4 x 4 vector products per thread on a 64 x 64 tile and
-// no split (64 or 224 blocks); three wavefronts per SIMD (at which <false, 3> spills 20 bytes per lane) measured like two.
+// (5.6 GFLOP with 40 columns padded to 48: 80 us) about equally.  Measured, plain / transposed: 133 / 130 us with three
+// blocks per CU that asked for one chunk ahead and had up to 14 % unequal work, 126 / 123 us so (512 equal blocks); without the products
+// the loads took 101 / 97 us, without A's loads the products 99 / 112.  4096 x 14336 with 56 columns: a call of 2470 -> 2256 us, 14336 x
+// 4096 with 72 (two column groups) 4140 -> 3595.
 typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef double double2_t __attribute__((ext_vector_type(2), aligned(8)));
-constexpr int kGemmRows = 128, kGemmK = 32, kGemmBlocks = 768;
+constexpr int kGemmRows = 128, kGemmK = 32, kGemmBlocks = 512, kRing = 3;
 
-// The loop over whole chunks has no branch in it (a guarded load is a branch, and the compiler then
-// waits for every load in flight before the next): the last chunk's prefetch repeats that chunk, rows
+// How a product is cut.  The blocks of a column group (ct tiles of 16 columns) share out the chunks of all row blocks in order,
+// `per_block` each, whatever row block they belong to, so that every block has the same work: part z of row block y is that of the
+// z-th block that has chunks of it (at most `parts`).  Row blocks cut alike instead (shared == false), into `parts` of per_block chunks,
+// the last one shorter: where whoever reads the parts counts on the same number for every row, and where there are more row blocks
+// than twice the blocks that fill the chip.
+struct GemmCut {
+  int ct, gx, gy, chunks, parts, per_block;           // chunks: of one row block
+  bool shared;
+  LRC_HD int first_block(int y) const { return int((long long)y * chunks / per_block); }                       // shared: that has chunks of row block y
+  LRC_HD int parts_of(int y) const { return shared ? first_block(y + 1) - first_block(y) + ((long long)(y + 1) * chunks % per_block != 0) : parts; }
+  LRC_HD int blocks() const { return shared ? int(((long long)gy * chunks + per_block - 1) / per_block) : gy * parts; }
+};
+
+// The loop over whole chunks has no branch around a load in it (a guarded load is a branch, and the compiler then
+// waits for every load in flight before the next): the last chunks' prefetches repeat the last chunk, rows
 // of a wavefront that would end past M start earlier (PAIR; for M < 32 the entries are read one by one,
 // clamped), what lies past the edges of B becomes zero on its way into LDS, and a last partial chunk is
 // read with clamped indices after the loop.
 template <bool TRANS, int CT, bool PAIR = true>
-__global__ __launch_bounds__(256, CT <= 3 ? 3 : 2) void dgemm_kernel(int M, int Nc, int Kd, int k_per, const double* __restrict__ A, int lda,
+__global__ __launch_bounds__(256, 2) void dgemm_kernel(GemmCut cut, int M, int Nc, int Kd, const double* __restrict__ A, int lda,
                                                     const double* __restrict__ B, int ldb, double* __restrict__ C, int ldc,
                                                     size_t c_stride) {
   constexpr int kPitch = 16 * CT + 4;                  // (lane groups 4 rows apart then sit in different halves of the banks)
   constexpr int kLoadsB = kGemmK * 16 * CT / 256;
   __shared__ double Bs[2][kGemmK * kPitch];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), i = lane & 15, kq = lane >> 4;
-  const int m_first = blockIdx.y * kGemmRows + wave * 32, j0 = blockIdx.x * (16 * CT);
-  const int m0 = TRANS && PAIR ? max(0, min(m_first, M - 32)) : m_first;
-  const int k_lo = blockIdx.z * k_per, k_hi = min(Kd, k_lo + k_per);
-  double4_t acc[2][CT];
+  const int j0 = blockIdx.x * (16 * CT), block = blockIdx.y;
+  // this block's chunks, counted over all row blocks
+  const long long lo = cut.shared ? (long long)block * cut.per_block : (long long)(block / cut.parts) * cut.chunks + block % cut.parts * cut.per_block;
+  const long long end = cut.shared ? (long long)cut.gy * cut.chunks : (long long)(block / cut.parts + 1) * cut.chunks;
+  const long long hi = min(lo + cut.per_block, end);
+  for (long long at = lo; at < hi;) {                  // the row blocks among them
+    const int y = int(at / cut.chunks), first = int(at - (long long)y * cut.chunks), last = int(min((long long)cut.chunks, first + (hi - at)));
+    const int z = cut.shared ? block - cut.first_block(y) : block % cut.parts;
+    at += last - first;
+    const int m_first = y * kGemmRows + wave * 32;
+    const int m0 = TRANS && PAIR ? max(0, min(m_first, M - 32)) : m_first;
+    const int k_lo = first * kGemmK, k_hi = min(Kd, last * kGemmK);
+    double4_t acc[2][CT];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = double4_t{0.0, 0.0, 0.0, 0.0};
-  // a[rt][4 h + s]: this lane's A operand of step (h, s)
-  const double* a_row[2] = {A + size_t(min(m0 + i, M - 1)) * lda + 4 * kq, A + size_t(min(m0 + 16 + i, M - 1)) * lda + 4 * kq};   // !TRANS
-  const double* a_col = A + size_t(4 * kq) * lda + (PAIR ? m0 + 2 * i : 0);                                                  // TRANS
-  const int c0 = min(m0 + 2 * i, M - 1), c1 = min(m0 + 2 * i + 1, M - 1);
-  auto load_a = [&](int k0, double (&a)[2][8]) {           // a whole chunk
+      for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = double4_t{0.0, 0.0, 0.0, 0.0};
+    // a[rt][4 h + s]: this lane's A operand of step (h, s)
+    const double* a_row[2] = {A + size_t(min(m0 + i, M - 1)) * lda + 4 * kq, A + size_t(min(m0 + 16 + i, M - 1)) * lda + 4 * kq};   // !TRANS
+    const double* a_col = A + size_t(4 * kq) * lda + (PAIR ? m0 + 2 * i : 0);                                                  // TRANS
+    const int c0 = min(m0 + 2 * i, M - 1), c1 = min(m0 + 2 * i + 1, M - 1);
+    auto load_a = [&](int k0, double (&a)[2][8]) {           // a whole chunk
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if constexpr (TRANS) {
+      for (int h = 0; h < 2; ++h)
+        if constexpr (TRANS) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const double* row = a_col + size_t(k0 + 16 * h + u) * lda;
-          if constexpr (PAIR) {
-            const double2_t v = *reinterpret_cast<const double2_t*>(row);
-            a[0][4 * h + u] = v[0]; a[1][4 * h + u] = v[1];
-          } else {
-            a[0][4 * h + u] = row[c0]; a[1][4 * h + u] = row[c1];
+          for (int u = 0; u < 4; ++u) {
+            const double* row = a_col + size_t(k0 + 16 * h + u) * lda;
+            if constexpr (PAIR) {
+              const double2_t v = *reinterpret_cast<const double2_t*>(row);
+              a[0][4 * h + u] = v[0]; a[1][4 * h + u] = v[1];
+            } else {
+              a[0][4 * h + u] = row[c0]; a[1][4 * h + u] = row[c1];
+            }
+          }
+        } else {
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt) {
+            const double* p = a_row[rt] + k0 + 16 * h;
+            const double2_t v = *reinterpret_cast<const double2_t*>(p), w = *reinterpret_cast<const double2_t*>(p + 2);
+            a[rt][4 * h] = v[0]; a[rt][4 * h + 1] = v[1]; a[rt][4 * h + 2] = w[0]; a[rt][4 * h + 3] = w[1];
           }
         }
-      } else {
+    };
+    auto load_a_edge = [&](int k0, double (&a)[2][8]) {      // past k_hi: any finite value, B is zero there
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-          const double* p = a_row[rt] + k0 + 16 * h;
-          const double2_t v = *reinterpret_cast<const double2_t*>(p), w = *reinterpret_cast<const double2_t*>(p + 2);
-          a[rt][4 * h] = v[0]; a[rt][4 * h + 1] = v[1]; a[rt][4 * h + 2] = w[0]; a[rt][4 * h + 3] = w[1];
-        }
+      for (int u = 0; u < 8; ++u) {
+        const int k = min(k0 + 16 * (u >> 2) + 4 * kq + (u & 3), k_hi - 1);
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+          a[rt][u] = TRANS ? A[size_t(k) * lda + (rt ? c1 : c0)] : A[size_t(min(m0 + 16 * rt + i, M - 1)) * lda + k];
       }
-  };
-  auto load_a_edge = [&](int k0, double (&a)[2][8]) {      // past k_hi: any finite value, B is zero there
+    };
+    auto load_b = [&](int k0, double (&b)[kLoadsB]) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = min(k0 + 16 * (u >> 2) + 4 * kq + (u & 3), k_hi - 1);
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
-        a[rt][u] = TRANS ? A[size_t(k) * lda + (rt ? c1 : c0)] : A[size_t(min(m0 + 16 * rt + i, M - 1)) * lda + k];
-    }
-  };
-  auto load_b = [&](int k0, double (&b)[kLoadsB]) {
-#pragma unroll
-    for (int u = 0; u < kLoadsB; ++u) {
-      const int x = t + 256 * u, kk = x / (16 * CT), j = j0 + x % (16 * CT);
-      b[u] = B[size_t(min(k0 + kk, k_hi - 1)) * ldb + min(j, Nc - 1)];
-    }
-  };
-  auto store_b = [&](double* bs, int k0, const double (&b)[kLoadsB]) {
-#pragma unroll
-    for (int u = 0; u < kLoadsB; ++u) {
-      const int x = t + 256 * u, kk = x / (16 * CT), j = j0 + x % (16 * CT);
-      bs[kk * kPitch + x % (16 * CT)] = (k0 + kk < k_hi && j < Nc) ? b[u] : 0.0;
-    }
-  };
-  auto multiply = [&](const double (&a)[2][8], const double* buf) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const double* bs = buf + (16 * (u >> 2) + 4 * kq + (u & 3)) * kPitch + i;
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const double b = bs[16 * ct];
-        acc[0][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][u], b, acc[0][ct], 0, 0, 0);
-        acc[1][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][u], b, acc[1][ct], 0, 0, 0);
+      for (int u = 0; u < kLoadsB; ++u) {
+        const int x = t + 256 * u, kk = x / (16 * CT), j = j0 + x % (16 * CT);
+        b[u] = B[size_t(min(k0 + kk, k_hi - 1)) * ldb + min(j, Nc - 1)];
       }
-    }
-  };
-  const int whole = (k_hi - k_lo) / kGemmK;
-  double a[2][8], b[kLoadsB];
-  if (whole > 0) {
-    load_a(k_lo, a);
-    load_b(k_lo, b);
-    store_b(Bs[0], k_lo, b);
-    __syncthreads();
-    for (int ch = 0; ch < whole; ++ch) {
-      const int k_next = k_lo + min(ch + 1, whole - 1) * kGemmK;
-      double a_next[2][8];
-      load_a(k_next, a_next);
-      load_b(k_next, b);
-      __builtin_amdgcn_sched_barrier(0);                 // (the requests stay in front of the products)
-      multiply(a, Bs[ch & 1]);
-      __builtin_amdgcn_sched_barrier(0);
-      store_b(Bs[(ch + 1) & 1], k_next, b);
+    };
+    auto store_b = [&](double* bs, int k0, const double (&b)[kLoadsB]) {
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int u = 0; u < kLoadsB; ++u) {
+        const int x = t + 256 * u, kk = x / (16 * CT), j = j0 + x % (16 * CT);
+        bs[kk * kPitch + x % (16 * CT)] = (k0 + kk < k_hi && j < Nc) ? b[u] : 0.0;
+      }
+    };
+    auto multiply = [&](const double (&a)[2][8], const double* buf) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a[rt][u] = a_next[rt][u];
-      __syncthreads();
-    }
-  }
-  const int k_tail = k_lo + whole * kGemmK;
-  if (k_tail < k_hi) {
-    load_a_edge(k_tail, a);
-    load_b(k_tail, b);
-    store_b(Bs[whole & 1], k_tail, b);
-    __syncthreads();
-    multiply(a, Bs[whole & 1]);
-  }
-  // register r of lane (i, kq): row kq + 4 r, column i of the tile
-  double* Cz = C + blockIdx.z * c_stride;
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int rho = kq + 4 * r, m = TRANS ? m0 + 2 * rho + rt : m0 + 16 * rt + rho;
-      if (m >= m_first && m < M)
+      for (int u = 0; u < 8; ++u) {
+        const double* bs = buf + (16 * (u >> 2) + 4 * kq + (u & 3)) * kPitch + i;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-          const int j = j0 + 16 * ct + i;
-          if (j < Nc) Cz[size_t(m) * ldc + j] = acc[rt][ct][r];
+          const double b = bs[16 * ct];
+          acc[0][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][u], b, acc[0][ct], 0, 0, 0);
+          acc[1][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][u], b, acc[1][ct], 0, 0, 0);
         }
+      }
+    };
+    const int whole = (k_hi - k_lo) / kGemmK;
+    double a[kRing][2][8], b[kRing][kLoadsB];
+    __syncthreads();                                       // (the row block before this one has been multiplied)
+    if (whole > 0) {
+      const int k_last = k_lo + (whole - 1) * kGemmK;
+#pragma unroll
+      for (int u = 0; u < kRing - 1; ++u) {
+        load_b(min(k_lo + u * kGemmK, k_last), b[u]);
+        __builtin_amdgcn_sched_barrier(0);                 // (loads return in order: B's, wanted first, are in front)
+        load_a(min(k_lo + u * kGemmK, k_last), a[u]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      store_b(Bs[0], k_lo, b[0]);
+      __syncthreads();
+      // chunk ch, in slot u of the rings
+      auto step = [&](int ch, auto U) {
+        constexpr int u = decltype(U)::value, slot = (u + kRing - 1) % kRing;
+        const int ahead = min(k_lo + (ch + kRing - 1) * kGemmK, k_last);
+        load_b(ahead, b[slot]);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(ahead, a[slot]);
+        __builtin_amdgcn_sched_barrier(0);                 // (the requests stay in front of the products)
+        multiply(a[u], Bs[ch & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        store_b(Bs[(ch + 1) & 1], min(k_lo + (ch + 1) * kGemmK, k_last), b[(u + 1) % kRing]);
+        __syncthreads();
+      };
+      int ch = 0;
+      for (; ch + kRing <= whole; ch += kRing) {           // (no way out of its middle: the waits at its head would be for that, too)
+        step(ch, std::integral_constant<int, 0>{});
+        step(ch + 1, std::integral_constant<int, 1>{});
+        step(ch + 2, std::integral_constant<int, 2>{});
+      }
+      if (ch < whole) step(ch, std::integral_constant<int, 0>{});
+      if (ch + 1 < whole) step(ch + 1, std::integral_constant<int, 1>{});
     }
+    const int k_tail = k_lo + whole * kGemmK;
+    if (k_tail < k_hi) {
+      load_a_edge(k_tail, a[0]);
+      load_b(k_tail, b[0]);
+      store_b(Bs[whole & 1], k_tail, b[0]);
+      __syncthreads();
+      multiply(a[0], Bs[whole & 1]);
+    }
+    // register r of lane (i, kq): row kq + 4 r, column i of the tile
+    double* Cz = C + z * c_stride;
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int rho = kq + 4 * r, m = TRANS ? m0 + 2 * rho + rt : m0 + 16 * rt + rho;
+        if (m >= m_first && m < M)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const int j = j0 + 16 * ct + i;
+            if (j < Nc) Cz[size_t(m) * ldc + j] = acc[rt][ct][r];
+          }
+      }
+  }
 }
 
-// C[x] = sum over z (in order) of part[z][x]
-__global__ __launch_bounds__(256) void dsum_kernel(const double* __restrict__ part, int parts, size_t n, double* __restrict__ C) {
+// C[x] = sum over z (in order) of part[z][x], of the parts that row x / Nc has
+__global__ __launch_bounds__(256) void dsum_kernel(GemmCut cut, const double* __restrict__ part, int Nc, size_t n, double* __restrict__ C) {
   const size_t x = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (x >= n) return;
+  const int parts = cut.parts_of(int(x / Nc) / kGemmRows);
   double v = part[x];
   for (int z = 1; z < parts; ++z) v += part[size_t(z) * n + x];
   C[x] = v;
 }
 
-// How a product is cut: column tiles per block, and parts of the reduction (at least 64 long each) so
-// that the blocks number about kGemmBlocks.  (A Gram matrix whose parts the factorisation adds up itself: at
-// most kGramParts of them, all in flight at once there.)
+// kGemmBlocks blocks, a chunk or two at least in each.  max_parts > 0 (a Gram matrix whose parts the factorisation adds up itself: at
+// most kGramParts of them, all in flight at once there): every row block cut alike.
 constexpr int kGramParts = 32;
-struct GemmCut { int ct, gx, gy, parts, k_per; };
-GemmCut gemm_cut(int M, int Nc, int Kd, int max_parts = 512) {
+GemmCut gemm_cut(int M, int Nc, int Kd, int max_parts = 0) {
   GemmCut c;
   c.ct = std::min(4, (Nc + 15) / 16);
   c.gx = (Nc + 16 * c.ct - 1) / (16 * c.ct);
   c.gy = (M + kGemmRows - 1) / kGemmRows;
-  const long long blocks = (long long)c.gx * c.gy;
-  const int parts = int(std::max(1LL, std::min<long long>(std::min<long long>(kGemmBlocks / std::max(1LL, blocks), max_parts), Kd / 64)));
-  c.k_per = ((Kd + parts - 1) / parts + kGemmK - 1) / kGemmK * kGemmK;
-  c.parts = (Kd + c.k_per - 1) / c.k_per;
+  c.chunks = (Kd + kGemmK - 1) / kGemmK;
+  const long long all = (long long)c.gy * c.chunks, blocks = std::max(1, kGemmBlocks / c.gx);
+  c.shared = max_parts == 0 && c.gy < 2 * blocks;
+  if (c.shared) {
+    c.per_block = int(std::max(2LL, (all + blocks - 1) / blocks));
+    c.parts = 1;
+    for (int y = 0; y < c.gy; ++y) c.parts = std::max(c.parts, c.parts_of(y));
+  } else {
+    const int parts = max_parts == 0 ? 1 : int(std::max(1LL, std::min({std::max(1LL, 768 / std::max(1LL, (long long)c.gx * c.gy)), (long long)max_parts, (long long)Kd / 64})));
+    c.per_block = (c.chunks + parts - 1) / parts;
+    c.parts = (c.chunks + c.per_block - 1) / c.per_block;
+  }
   return c;
 }
-size_t gemm_part_doubles(int M, int Nc, int Kd) { return size_t(gemm_cut(M, Nc, Kd).parts) * M * Nc; }
+size_t gemm_part_doubles(int M, int Nc, int Kd) {
+  return size_t(std::max(gemm_cut(M, Nc, Kd).parts, gemm_cut(M, Nc, Kd, kGramParts).parts)) * M * Nc;
+}
 
 // part: room for gemm_part_doubles doubles.  keep_parts: leaves the partial sums there (returns their
 // number); else C (ldc == Nc when the reduction is split) holds the product.
 template <bool TRANS>
 int dgemm(int M, int Nc, int Kd, const double* A, int lda, const double* B, int ldb, double* C, double* part, bool keep_parts = false) {
-  const GemmCut g = gemm_cut(M, Nc, Kd, keep_parts ? kGramParts : 512);
+  const GemmCut g = gemm_cut(M, Nc, Kd, keep_parts ? kGramParts : 0);
   const bool direct = g.parts == 1 && !keep_parts;
   double* out = direct ? C : part;
-  const dim3 grid(g.gx, g.gy, g.parts);
+  const dim3 grid(g.gx, g.blocks());
   const size_t cs = size_t(M) * Nc;
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, nullptr, M, Nc, Kd, g.k_per, A, lda, B, ldb, out, Nc, cs); };
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, nullptr, g, M, Nc, Kd, A, lda, B, ldb, out, Nc, cs); };
   auto pick = [&](auto CT_) {
     constexpr int CT = decltype(CT_)::value;
     if constexpr (TRANS) {
@@ -575,7 +621,7 @@ int dgemm(int M, int Nc, int Kd, const double* A, int lda, const double* B, int 
     default: pick(std::integral_constant<int, 4>{}); break;
   }
   if (!direct && !keep_parts)
-    hipLaunchKernelGGL(dsum_kernel, dim3((unsigned)((cs + 255) / 256)), dim3(256), 0, nullptr, part, g.parts, cs, C);
+    hipLaunchKernelGGL(dsum_kernel, dim3((unsigned)((cs + 255) / 256)), dim3(256), 0, nullptr, g, part, Nc, cs, C);
   return g.parts;
 }
 
