@@ -209,6 +209,14 @@ def test_residual_factors_at_the_edges(amd, K, N, r, over, iters):
     assert orc.rel_frobenius(A.cpu().numpy() @ B.cpu().numpy(), (Q @ U[:, :r] * S[:r]) @ Vt[:r]) <= 1e-8
 
 
+# shares of the reduction that run over the end of a row block: two, three and thirteen chunks of 32 to a block, a last chunk that is
+# partial, two groups of columns, fewer rows than a block takes, and so many row blocks that they are not cut at all
+@pytest.mark.parametrize("K,N,r,over,iters", [(4100, 129, 8, 8, 1), (1700, 3300, 24, 8, 1), (520, 3000, 40, 30, 1), (31, 8192, 16, 8, 1),
+                                              (6500, 5000, 60, 20, 0), (131200, 40, 8, 4, 0)])
+def test_residual_factors_cut_across_row_blocks(amd, K, N, r, over, iters):
+    test_residual_factors_at_the_edges(amd, K, N, r, over, iters)
+
+
 def test_residual_factors_of_a_matrix_whose_gram_matrix_is_singular(amd):
     # ten singular values near 1, ten near 1e-12, and a test matrix that weighs them alike: Y is well
     # conditioned, Bm Bm^T is not positive definite in fp64

@@ -788,6 +788,34 @@ def test_h_a2_from_the_fused_launch(amd, hidden, ffn, rank, tokens, experts, kin
     Lr.close(); Ls.close()
 
 
+@pytest.mark.parametrize("experts,top_k,tokens", [
+    (32, 2, 32), (32, 2, 33),              # 64 pairs and the most experts; a 65th pair, which is too many steps for 32 experts
+    (16, 2, 64), (16, 3, 43),              # two steps; 129 pairs
+    (8, 2, 128), (8, 1, 129), (8, 2, 129), # the most pairs; three steps; 258 pairs
+    (33, 1, 5), (3, 3, 85), (1, 1, 256),   # an expert too many; every token has every expert; one expert
+])
+def test_forward_of_few_pairs_groups_them_as_permute_does(amd, experts, top_k, tokens):
+    """forward() groups few pairs by ballots in the launch that prepares the activations, permute() by the histogram: sizes on both
+    sides of the line between them, against the oracle (bf16 rounding: TOL) and the four calls (which may round the expert rows to
+    bf16 once more, 2^-9)."""
+    cfg = configs.TINY.with_(n_experts=experts, top_k=top_k, top_n=min(top_k, 2), tokens=tokens, ffn=128, rank=16, name=f"few_E{experts}_T{tokens}")
+    layer = fixtures.sample_layer(cfg)
+    x_bits = synth.make_tokens(cfg)
+    x = amd.bf16_tensor(x_bits)
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    L = amd.Layer.from_config(cfg)
+    L.load(layer)
+    idx, w = L.route(x)
+    counts, offsets, row_pair, pair_row, comp = L.permute(idx)
+    for g, key in zip((counts, offsets, row_pair, pair_row, comp), ("counts", "offsets", "row_pair", "pair_row", "comp_counts")):
+        np.testing.assert_array_equal(_to_np(g), ref["perm"][key], err_msg=key)
+    four = L.combine(L.expert_ffn(x, offsets, row_pair), w, pair_row, x).clone()
+    out = L.forward(x)
+    assert orc.rel_frobenius(_to_np(out), ref["out"]) <= TOL
+    assert orc.rel_frobenius(_to_np(out), _to_np(four)) <= 2.5e-3
+    L.close()
+
+
 @pytest.mark.parametrize("hidden,rank,tokens,experts,top_k,kind", [
     (256, 8, 16, 8, 1, "same"),            # one pass of 16 tokens, one factor tile, as many experts as the rule takes
     (320, 40, 17, 3, 2, "int3"),           # one token in the second pass, an odd number of factor tiles
