@@ -152,8 +152,8 @@ __device__ inline void xa_block(const PrepGrid& g, int i, int& tile, int& pass) 
   }
 }
 
-// What a block does once the pairs are grouped: its role by its index.
-template <class Rows>
+// What a block does once the pairs are grouped: its role by its index (XA: some have (x A1 | x A3) to make).
+template <bool XA, class Rows>
 __device__ inline void prep_roles(const Rows& grouped, const uint16_t* __restrict__ x, int rows, int H, uint4* __restrict__ xg, int rt, bool routed, int E,
                                   int top_k, int top_n, int32_t* __restrict__ stat, const FfnTables& tables, const PrepGrid& g, const ffn::KArgs& xa,
                                   bool have_exp, int32_t* __restrict__ row_exp, const CompactArgs& cmp, const ZeroRowsArgs& zr,
@@ -170,12 +170,14 @@ __device__ inline void prep_roles(const Rows& grouped, const uint16_t* __restric
         zr.h[size_t(i / dec::kZeroRows) * zr.h_rt + zr.h_rt - dec::kZeroRows + i % dec::kZeroRows] = make_uint4(0, 0, 0, 0);
     return;
   }
-  if (block >= g.xa_at()) {                                                 // (x A1 | x A3) of the routed rows
-    int tile, pass;
-    xa_block(g, block - g.xa_at(), tile, pass);
-    const int per = g.tiles / E, e = tile / per;
-    ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, grouped, x, tile - e * per, e, 0, pass, g.passes, red);
-    return;
+  if constexpr (XA) {
+    if (block >= g.xa_at()) {                                               // of the routed rows
+      int tile, pass;
+      xa_block(g, block - g.xa_at(), tile, pass);
+      const int per = g.tiles / E, e = tile / per;
+      ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, grouped, x, tile - e * per, e, 0, pass, g.passes, red);
+      return;
+    }
   }
   if (block >= g.plan_at()) {                                               // the tables of the FFN launches (plan.h)
     const auto offset = [&](int e) { return grouped.offset(e); };
@@ -255,7 +257,11 @@ __device__ inline void prep_roles(const Rows& grouped, const uint16_t* __restric
   }
 }
 
-__global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __restrict__ x, int rows, int H,
+// FULL: with the blocks of (x A1 | x A3) and the grouping, whose registers leave a CU one block.  Without either (batches beyond the decode
+// flavour) the launch is the gather, many rounds of blocks, and a CU holds two
+// (47 registers instead of 106).  Qwen3 shape, T = 4096: 52 -> 43 us (134 MB written); Mixtral, T = 2048: 20 -> 17.
+template <bool FULL>
+__global__ __launch_bounds__(kPrepThreads, FULL ? 4 : 8) void prep_kernel(const uint16_t* __restrict__ x, int rows, int H,
                                                    uint4* __restrict__ xg, int rt,
                                                    const int32_t* offsets,
                                                    const int32_t* row_pair, int E, int top_k,
@@ -263,44 +269,50 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint16_t* __re
                                                    const int32_t* tok_exp, int32_t* __restrict__ row_exp,
                                                    PermuteArgs perm, CompactArgs cmp, RouteArgs route, ZeroRowsArgs zr,
                                                    int32_t* __restrict__ host_stat, int32_t* __restrict__ row_tok) {
-  __shared__ ffn::float4_t red[2 * kPrepThreads / 64][64];
   __shared__ uint32_t row_max[16];
-  __shared__ SmallGroup sg;
-  constexpr int kWavesPerBlock = kPrepThreads / 64;
-  const int block = blockIdx.x;
-  if (xa.p_tokens > 0 && block >= g.xa_at() && block < g.zero_at()) {
-    // (x A1 | x A3) of all tokens: nothing to wait for
-    int tile, p;
-    xa_block(g, block - g.xa_at(), tile, p);
-    const int pass = xa_tokens_pass(xa.p_tokens, g.columns), per = g.tiles / E, e = tile / per;
-    ffn::xa_tokens_body<kWavesPerBlock>(xa, x, route.wg != nullptr ? nullptr : tok_exp, tile - e * per, e, pass * p, pass == 32, red);
-    return;
-  }
   const bool routed = row_pair != nullptr;
-  auto roles = [&](const auto& grouped, bool have_exp) {
-    prep_roles(grouped, x, rows, H, xg, rt, routed, E, top_k, top_n, stat, tables, g, xa, have_exp, row_exp, cmp, zr, host_stat, row_tok, red, row_max);
-  };
-  if (perm.idx != nullptr && group_small_fits(perm.P, E)) {
-    const bool out = block == g.zero_at();     // the block that writes the results
-    const PermuteOut o{perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts};
-    if (route.wg != nullptr) {
-      // a token or two: every block routes them itself (route_body.h) instead of a launch of its own doing it beforehand
-      route_small_body(reinterpret_cast<double*>(&red[0][0]), sg.idx, sg.tok_exp, x, route, perm.P / top_k, H, E, top_k, out);
-      __syncthreads();
-      group_small(sg, [&](int i) { return sg.idx[i]; }, perm.P, E, top_k, top_n, out, o);
-    } else {
-      group_small(sg, [&](int i) { return perm.idx[i]; }, perm.P, E, top_k, top_n, out, o);
-    }
-    roles(SmallRows{sg, route.wg != nullptr ? nullptr : tok_exp, top_k}, true);
+  if constexpr (!FULL) {
+    prep_roles<false>(ffn::GroupedRows{offsets, row_pair, tok_exp, row_exp, top_k}, x, rows, H, xg, rt, routed, E, top_k, top_n, stat, tables, g, xa,
+                      tok_exp != nullptr, row_exp, cmp, zr, host_stat, row_tok, nullptr, row_max);
     return;
+  } else {
+    __shared__ ffn::float4_t red[2 * kPrepThreads / 64][64];
+    __shared__ SmallGroup sg;
+    constexpr int kWavesPerBlock = kPrepThreads / 64;
+    const int block = blockIdx.x;
+    if (xa.p_tokens > 0 && block >= g.xa_at() && block < g.zero_at()) {
+      // (x A1 | x A3) of all tokens: nothing to wait for
+      int tile, p;
+      xa_block(g, block - g.xa_at(), tile, p);
+      const int pass = xa_tokens_pass(xa.p_tokens, g.columns), per = g.tiles / E, e = tile / per;
+      ffn::xa_tokens_body<kWavesPerBlock>(xa, x, route.wg != nullptr ? nullptr : tok_exp, tile - e * per, e, pass * p, pass == 32, red);
+      return;
+    }
+    auto roles = [&](const auto& grouped, bool have_exp) {
+      prep_roles<true>(grouped, x, rows, H, xg, rt, routed, E, top_k, top_n, stat, tables, g, xa, have_exp, row_exp, cmp, zr, host_stat, row_tok, red, row_max);
+    };
+    if (perm.idx != nullptr && group_small_fits(perm.P, E)) {
+      const bool out = block == g.zero_at();     // the block that writes the results
+      const PermuteOut o{perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts};
+      if (route.wg != nullptr) {
+        // a token or two: every block routes them itself (route_body.h) instead of a launch of its own doing it beforehand
+        route_small_body(reinterpret_cast<double*>(&red[0][0]), sg.idx, sg.tok_exp, x, route, perm.P / top_k, H, E, top_k, out);
+        __syncthreads();
+        group_small(sg, [&](int i) { return sg.idx[i]; }, perm.P, E, top_k, top_n, out, o);
+      } else {
+        group_small(sg, [&](int i) { return perm.idx[i]; }, perm.P, E, top_k, top_n, out, o);
+      }
+      roles(SmallRows{sg, route.wg != nullptr ? nullptr : tok_exp, top_k}, true);
+      return;
+    }
+    if (perm.idx != nullptr) {
+      PermuteLds& pl = *reinterpret_cast<PermuteLds*>(&red[0][0]);     // (the reduction buffer is not in use yet)
+      static_assert(sizeof(PermuteLds) <= sizeof(red), "the permutation tables must fit the reduction buffer");
+      permute_body(pl, perm.idx, perm.P, E, top_k, top_n, perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts);
+      __syncthreads();
+    }
+    roles(ffn::GroupedRows{offsets, row_pair, tok_exp, row_exp, top_k}, tok_exp != nullptr);
   }
-  if (perm.idx != nullptr) {
-    PermuteLds& pl = *reinterpret_cast<PermuteLds*>(&red[0][0]);     // (the reduction buffer is not in use yet)
-    static_assert(sizeof(PermuteLds) <= sizeof(red), "the permutation tables must fit the reduction buffer");
-    permute_body(pl, perm.idx, perm.P, E, top_k, top_n, perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts);
-    __syncthreads();
-  }
-  roles(ffn::GroupedRows{offsets, row_pair, tok_exp, row_exp, top_k}, tok_exp != nullptr);
 }
 
 // One wavefront per packed tile: runs the same field extraction as the FFN kernels and writes the
@@ -369,7 +381,8 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
     g.passes = std::max(1, std::min({4, (T + 31) / 32, 4 * L->n_cu / g.tiles}));
   }
   const int cmp_block = (cmp && row_pair && stat) ? 1 : 0;     // (the compaction rides the per-expert counting)
-  hipLaunchKernelGGL(prep_kernel, dim3(g.blocks()),
+  const bool full = xa_tiles > 0 || perm != nullptr;
+  hipLaunchKernelGGL(full ? prep_kernel<true> : prep_kernel<false>, dim3(g.blocks()),
                      dim3(kPrepThreads), 0, s, (const uint16_t*)x_bf16, rows, c.hidden, reinterpret_cast<uint4*>(xg), rt, offsets,
                      row_pair, c.n_experts, c.top_k, c.top_n, stat, t, g, xa, tok_exp, row_exp,
                      perm ? *perm : PermuteArgs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0},
