@@ -90,6 +90,13 @@ LRC_HD LaneOffsets lane_offsets(int lane, int bits, int NT, int group_shift, boo
   const uint32_t q = lane >> 4, c = lane & 15, past = tile_ok ? 0u : kNoTile;
   return LaneOffsets{past + lane * 16, past + 1024 + lane * (bits == 3 ? 8 : 16), past + ((q * kLaneK) >> group_shift) * (uint32_t(NT) * kTileN * 4) + c * 4};
 }
+// The rank steps of a wavefront come in turns of the ring, too: turn t brings, in slot i, rank_slot_step of own unit rank_slot_unit (both
+// own units' steps side by side in the fused projection, two steps of the one unit of W2).
+LRC_HD int rank_slot_unit(bool dual, int i) { return dual ? i : 0; }
+LRC_HD int rank_slot_step(bool dual, int t, int i, int kwi, int kw_log2) { return kwi + ((dual ? t : kRing * t + i) << kw_log2); }
+// Turns of a wavefront that has a unit, of LS rank steps (0: none of its own).
+LRC_HD int rank_turns(bool dual, int LS, int kwi, int kw_log2) { const int n = own_steps(LS, kwi, kw_log2); return dual ? n : (n + kRing - 1) / kRing; }
+
 // Byte offsets of a lane's loads of rank step st of one stream (range-checked: a step past the stream's own rank, or without a tile,
 // lies past the resource): the B factor's unit; or, of a pair held at 3 bits (layout.h), through `bf` the lane's half of the 32
 // bytes of metadata of (rank step, group of four n-tiles, lane group) from a resource of (NT / 4) * LS * 128 bytes, and through `bc` the

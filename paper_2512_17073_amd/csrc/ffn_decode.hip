@@ -246,7 +246,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
   // stride, beside lane offsets that stay (a scalar instruction of each of the sixteen wavefronts goes through the one scalar unit
   // of the CU: sixty a step, with the offsets formed anew, were a good part of a step; about 25 now.  W2 alone, before and with this:
   // Mixtral T = 64 48 -> 46 us, T = 13 at 3 bits 52 -> 46, T = 1 17.1 -> 16.2; W1|W3 at T = 13, 3 bits 87 -> 81).
-  // The same loads bring the units' first rank steps at the end: other resources and lane offsets, no branch between two
+  // The same loads bring the first turn of rank steps at the end: other resources and lane offsets, no branch between two
   // kinds of loads, behind which the compiler's waits would be for all of them.
   const int gps = kTileK >> a.group_shift;
   const Strides strides = walk_strides(kwl, BITS, a.NT, gps);
@@ -300,43 +300,44 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
     bf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(dd->bf[mat]), 0, q3m[m] ? uint32_t(NT / 4) * LSm[m] * 128 : uint32_t(NT) * LSm[m] * 1024, 0x00020000);
     if constexpr (Q3) bc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(dd->bfc[mat]), 0, q3m[m] ? uint32_t(NT) * LSm[m] * 256 : 0u, 0x00020000);
   };
-  // ... or the first rank step of own unit ts (a stream past its own rank, or without a unit, reads nothing)
-  auto fetch_rank_from = [&](int ts) {
+  // Offsets of slot i of rank turn t (a stream past its own rank, or without a unit, reads nothing: past its resource)
+  auto rank_at = [&](int t, int i, int m, int ln) {
+    const int ts = rank_slot_unit(DUAL, i), tile = stream_tile(again(t0), again(grp) + ts * groups, m, DUAL);
+    return rank_offsets(rank_slot_step(DUAL, t, i, again(kwi), kwl), tile, ts < own && tile < t1, ln, a.NT, Q3 && q3m[m]);
+  };
+  // ... the first turn, by the fetch that ends the k-steps: slot i from here on
+  auto fetch_rank_from = [&](int i) {
     int ln = lane;
     asm volatile("" : "+v"(ln));              // (the offsets are made here, not kept in registers through the k-steps)
-    const int first = again(t0), g = again(grp), k = again(kwi);
     src.by = Strides{0, 0};
     src.at = Walk{0, 0, 0, 0, 0};
     src.code2 = src.meta2 = 0;
 #pragma unroll
     for (int m = 0; m < NS; ++m) {
-      const int tile = stream_tile(first, g + ts * groups, m, DUAL);
       if (m < NLO) {
-        // (a step past the stream's rank lies past its resource)
-        const RankOffsets o = rank_offsets(k, tile, ts < own && tile < t1, ln, a.NT, Q3 && q3m[m]);
+        const RankOffsets o = rank_at(0, i, m, ln);
         src.lo[m] = LaneOffsets{o.bf, kNoTile, Q3 ? o.bc : kNoTile};
       }
-      if (ts == 0) {
+      if (i == 0) {
         if constexpr (Q3) rank_rsrc(m, src.code[m], src.meta[m]);
         else rank_rsrc(m, src.code[m], src.code[m]);
       }
     }
   };
-  // rank step st of own unit ts, beyond the first
-  auto fetch_rank = [&](Slot<BITS, NS>& sl, int ts, int st) {
+  // ... and slot i of a turn beyond the first
+  auto fetch_rank = [&](Slot<BITS, NS>& sl, int t, int i) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
 #pragma unroll
     for (int m = 0; m < NS; ++m) {
-      const int tile = stream_tile(t0, grp + ts * groups, m, DUAL);
-      const RankOffsets o = rank_offsets(st, tile, ts < own && tile < t1, ln, a.NT, Q3 && q3m[m]);
+      const RankOffsets o = rank_at(t, i, m, ln);
       const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(src.code[m], o.bf, 0, 0);
       sl.cw[m][0] = v0[0]; sl.cw[m][1] = v0[1]; sl.cw[m][2] = v0[2]; sl.cw[m][3] = v0[3];
       if constexpr (Q3) sl.mw[m] = __builtin_amdgcn_raw_buffer_load_b32(src.meta[m], o.bc, 0, 0);
     }
   };
   Slot<BITS, NS> ring[RING];
-  static_assert(RING >= TS, "the last turn leaves a slot to every unit's first rank step");
+  static_assert(RING == 2 && TS <= RING, "a rank turn's slots: a unit each, or two steps of one unit");
 
   // ---- start of the first pass: everything that is left is requested before anything is awaited ----
   p_start(a, 0);
@@ -478,7 +479,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
 #pragma unroll
       for (int ts = 0; ts < TS; ++ts) {
         if (ts >= own) continue;
-        // the segment after this one: the next unit's or the next phase's; after the last one the units' first rank steps
+        // the segment after this one: the next unit's or the next phase's; after the last one the first turn of rank steps
         const int nts = ts + 1 < own ? ts + 1 : 0, nph = nts > 0 ? ph : ph + 1;
         const bool last = nph == sp.n_ph;
         // slot i of the ring: consumed, then refilled a turn ahead (without an own step, one turn to refill it)
@@ -501,23 +502,25 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
         p_issue(*kern_args(), again(r));
         wait_loads_barrier();
       }
-#pragma unroll
-      for (int ts = 0; ts < TS; ++ts) {
-        if (ts >= own || kwi >= LS) continue;
-        compute_lr(ring[ts], kwi, acc[ts]);
-        if (kwi + kw < LS) {                  // (two at a time: one is multiplied, the other on its way)
-          Slot<BITS, NS> sl[2];
-          fetch_rank(sl[0], ts, kwi + kw);
-          fetch_rank(sl[1], ts, kwi + 2 * kw);
+      // The last fetch of the k-steps has brought the first turn, one slot is refilled while the other's step is on its way.  (Requests
+      // after the first turn's products had nothing in flight beside them: a memory round trip more a unit and pass.  Whole forward,
+      // Mixtral shape, so -> with this, us: rank 64 T = 8 118.4 -> 116.0, T = 160 281.3 -> 279.9; rank 128 T = 8 123 -> 120, T = 64
+      // 161.3 -> 159.9; 3 bits with 3-bit pairs, rank 64, T = 8 145.3 -> 138.4, T = 160 326 -> 316.6; rank 32 the same.)
+      const int turns = own > 0 ? rank_turns(DUAL, LS, kwi, kwl) : 0;
+      auto slot_lr = [&](int t, int i) {
+        const int ts = rank_slot_unit(DUAL, i), st = rank_slot_step(DUAL, t, i, kwi, kwl);
+        if (ts < own && st < LS) compute_lr(ring[i], st, acc[ts]);
+      };
+      int t = 0;
 #pragma unroll 1
-          for (int st = kwi + kw; st < LS; st += 2 * kw) {
-            compute_lr(sl[0], st, acc[ts]);
-            fetch_rank(sl[0], ts, st + 2 * kw);
-            if (st + kw < LS) compute_lr(sl[1], st + kw, acc[ts]);
-            fetch_rank(sl[1], ts, st + 3 * kw);
-          }
+      for (; t + 1 < turns; ++t)
+#pragma unroll
+        for (int i = 0; i < RING; ++i) {
+          slot_lr(t, i);
+          fetch_rank(ring[i], t + 1, i);
         }
-      }
+#pragma unroll
+      for (int i = 0; i < RING; ++i) slot_lr(t, i);
     }
 
     // ---- wavefronts that shared a unit add up their partial sums through LDS ----

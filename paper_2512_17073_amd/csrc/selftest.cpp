@@ -135,12 +135,14 @@ std::string check_shape(const Shape& sh) {
                 }
               }
             }
-          // rank steps, and the ones fetched past the last
-          for (int ts = 0; ts < own; ++ts)
-            for (int st = kwi; LS > 0 && st < LS + 3 * kw; st += kw)
+          // rank steps, by turns of the ring (the first turn is fetched whether it holds a step or not)
+          const int turns = own > 0 ? rank_turns(sh.dual, LS, kwi, kwl) : 0;
+          for (int t = 0; t < std::max(turns, 1); ++t)
+            for (int i = 0; i < kRing; ++i)
               for (int m = 0; m < kStreams; ++m) {
+                const int ts = rank_slot_unit(sh.dual, i), st = rank_slot_step(sh.dual, t, i, kwi, kwl);
                 const int tile = stream_tile(t0, grp + ts * groups, m, sh.dual), LSq = lowrank ? sh.LSm[sh.dual ? m : 0] : 0;
-                const bool ok = tile < t1;
+                const bool ok = ts < own && tile < t1;
                 const uint32_t bf_size = uint32_t(NT) * LSq * 1024, bm_size = uint32_t(NT / 4) * LSq * 128, bc_size = uint32_t(NT) * LSq * 256;
                 if (ok && st < LSq) ++seen_lr[(size_t(st) * NT + tile) * 2 + (sh.dual ? m : 0)];
                 for (int lane = 0; lane < 64; ++lane) {

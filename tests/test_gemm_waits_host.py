@@ -1,6 +1,6 @@
-"""What the built code has to show of two kernels.  The grouped GEMM's k-steps with two slots of weights wait for the copy of the
+"""What the built code has to show of three kernels.  The grouped GEMM's k-steps with two slots of weights wait for the copy of the
 activations and leave the weights requested after it in flight: the loads between the two are exactly as many as the wait leaves
-out.  The tiled gate's products follow each other without branches."""
+out.  The decode kernels request a rank step while another is on its way.  The tiled gate's products follow each other without branches."""
 import os
 import re
 import struct
@@ -52,6 +52,33 @@ def test_waits_leave_exactly_the_next_weights_in_flight(tmp_path):
                 found[name] = found.get(name, 0) + 1
     # 2, 3 and 4 bits; W1|W3, W2 in two and in four n-tiles; with and without 3-bit factor pairs
     assert len(found) == 18 and min(found.values()) >= 2, found
+
+
+def _decode_functions(tmp_path):
+    """(name, bits, dual, q3, instructions) of the 24 decode kernels."""
+    found = list(_functions(tmp_path, "qgemm_decode_kernel"))
+    assert len(found) == 24, [n for n, _ in found]
+    for name, lines in found:
+        bits, dual, q3, _ = re.search(r"qgemm_decode_kernelILi(\d)ELb(\d)ELb(\d)ELb(\d)", name).groups()
+        yield name, int(bits), int(dual), int(q3), lines
+
+
+def test_decode_kernels_refill_a_slot_while_the_other_rank_step_is_on_its_way(tmp_path):
+    # Between two barriers (the k-steps have 16 products a row tile and more): a loop that multiplies a slot's step of two streams and
+    # requests the next into it, for either slot, then the last turn's products.  A request anywhere else is one whose product
+    # comes next, with nothing else in flight.
+    for name, bits, dual, q3, lines in _decode_functions(tmp_path):
+        events = ""
+        for ln in lines:
+            if ln.startswith("s_barrier"):
+                events += "B"
+            elif ln.startswith("buffer_load_dwordx4") and not ln.endswith("lds"):
+                events += "L"
+            elif ln.startswith("v_mfma_f32_16x16x32"):
+                events += "P"
+        parts = [part for part in events.split("B") if part.strip("L") and part.count("P") < 32]
+        assert sorted(part.count("P") for part in parts) == [8, 16], (name, parts)         # one row tile, two
+        assert all(part.count("L") == 4 and "LLL" not in part for part in parts), (name, parts)
 
 
 def test_products_of_the_tiled_gate_between_branches(tmp_path):

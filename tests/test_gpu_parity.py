@@ -788,6 +788,37 @@ def test_h_a2_from_the_fused_launch(amd, hidden, ffn, rank, tokens, experts, kin
     Lr.close(); Ls.close()
 
 
+@pytest.mark.parametrize("hidden,ffn", [(256, 2176), (2176, 256)])      # 17 n-tiles a block of W1|W3, or of W2: no wavefront shares a unit
+@pytest.mark.parametrize("rank,kind,bits", [(40, "same", 4), (72, "int3", 3), (104, "int3", 2), (104, "int3", 4), (136, "same", 2), (200, "bucket", 3)])
+def test_rank_steps_of_unshared_units(amd, hidden, ffn, rank, kind, bits):
+    """Two to seven rank steps that all are one wavefront's (odd and even numbers, ranks that differ or are 0), of one unit and of two,
+    with one row tile and with two, against the oracle."""
+    cfg = configs.TINY.with_(hidden=hidden, ffn=ffn, n_experts=32, top_k=4, top_n=2, rank=rank, tokens=160, bits=bits, name=f"unshared_{hidden}_r{rank}_b{bits}")
+    layer = fixtures.sample_layer(cfg)
+    bucket = (200, 8, 0, 104, 200, 32, 64)
+    for e, ex in enumerate(layer["experts"]):
+        for m in (0, 1, 2):
+            a = ex[m]
+            if kind == "int3":
+                a["Aq"], a["Bq"] = synth.sample_factor_codes(cfg, e, m)
+                a["A"] = a["B"] = None
+            elif kind == "bucket":
+                a["rank"] = r = bucket[(3 * e + 2 * m) % len(bucket)]
+                a["A"] = np.ascontiguousarray(a["A"][:, :r]) if r else None
+                a["B"] = np.ascontiguousarray(a["B"][:r]) if r else None
+    x_bits = synth.make_tokens(cfg)
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    rows = np.diff(ref["perm"]["offsets"])
+    assert (rows > 16).any() and ((rows > 0) & (rows <= 16)).any()
+    L = amd.Layer.from_config(cfg)
+    L.load(layer)
+    out = _to_np(L.forward(amd.bf16_tensor(x_bits)))
+    assert L.stats()["path"] == 0
+    none = orc.rel_frobenius(out, fixtures.oracle_forward(cfg.with_(top_n=0), layer, x_bits)["out"])
+    assert orc.rel_frobenius(out, ref["out"]) <= TOL and none > 3 * TOL
+    L.close()
+
+
 @pytest.mark.parametrize("experts,top_k,tokens", [
     (32, 2, 32), (32, 2, 33),              # 64 pairs and the most experts; a 65th pair, which is too many steps for 32 experts
     (16, 2, 64), (16, 3, 43),              # two steps; 129 pairs
