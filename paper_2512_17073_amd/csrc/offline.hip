@@ -26,6 +26,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "gemm_cut.h"
 #include "internal.h"
 #include "offline_round.h"
 
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(256) void moment_join_kernel(Moments* part, int par
 // v_mfma_f64_16x16x4.  The products here are tall and skinny: A is the K x N matrix, read once, and B
 // is a few megabytes, so a block of four wavefronts takes 128 rows of C and all its columns up to
 // 16 CT, a wavefront 32 rows (two tiles that share every B operand read from LDS).  The reduction dimension, in chunks of 32, is split
-// so that there are two blocks per CU (GemmCut), each writing its own partial C (dsum_kernel adds them in order).  The chunks of A
+// over the blocks (gemm_cut.h), each writing its own partial C (dsum_kernel adds them in order).  The chunks of A
 // come through a ring of registers, two chunks ahead, those of B through another and then the other half of LDS; all are requested
 // before the current chunk is multiplied.  Inside
 // a chunk, MFMA step (h, s) covers k = 16 h + 4 kq + s for lane group kq, so that a lane reads 32
@@ -393,20 +394,7 @@ __global__ __launch_bounds__(256) void moment_join_kernel(Moments* part, int par
 // 4096 with 72 (two column groups) 4140 -> 3595.
 typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef double double2_t __attribute__((ext_vector_type(2), aligned(8)));
-constexpr int kGemmRows = 128, kGemmK = 32, kGemmBlocks = 512, kRing = 3;
-
-// How a product is cut.  The blocks of a column group (ct tiles of 16 columns) share out the chunks of all row blocks in order,
-// `per_block` each, whatever row block they belong to, so that every block has the same work: part z of row block y is that of the
-// z-th block that has chunks of it (at most `parts`).  Row blocks cut alike instead (shared == false), into `parts` of per_block chunks,
-// the last one shorter: where whoever reads the parts counts on the same number for every row, and where there are more row blocks
-// than twice the blocks that fill the chip.
-struct GemmCut {
-  int ct, gx, gy, chunks, parts, per_block;           // chunks: of one row block
-  bool shared;
-  LRC_HD int first_block(int y) const { return int((long long)y * chunks / per_block); }                       // shared: that has chunks of row block y
-  LRC_HD int parts_of(int y) const { return shared ? first_block(y + 1) - first_block(y) + ((long long)(y + 1) * chunks % per_block != 0) : parts; }
-  LRC_HD int blocks() const { return shared ? int(((long long)gy * chunks + per_block - 1) / per_block) : gy * parts; }
-};
+constexpr int kRing = 3;
 
 // The loop over whole chunks has no branch around a load in it (a guarded load is a branch, and the compiler then
 // waits for every load in flight before the next): the last chunks' prefetches repeat the last chunk, rows
@@ -423,12 +411,10 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(GemmCut cut, int M, int N
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), i = lane & 15, kq = lane >> 4;
   const int j0 = blockIdx.x * (16 * CT), block = blockIdx.y;
   // this block's chunks, counted over all row blocks
-  const long long lo = cut.shared ? (long long)block * cut.per_block : (long long)(block / cut.parts) * cut.chunks + block % cut.parts * cut.per_block;
-  const long long end = cut.shared ? (long long)cut.gy * cut.chunks : (long long)(block / cut.parts + 1) * cut.chunks;
-  const long long hi = min(lo + cut.per_block, end);
-  for (long long at = lo; at < hi;) {                  // the row blocks among them
+  const long long hi = cut.end(block);
+  for (long long at = cut.begin(block); at < hi;) {    // the row blocks among them
     const int y = int(at / cut.chunks), first = int(at - (long long)y * cut.chunks), last = int(min((long long)cut.chunks, first + (hi - at)));
-    const int z = cut.shared ? block - cut.first_block(y) : block % cut.parts;
+    const int z = cut.part_of(block, y);
     at += last - first;
     const int m_first = y * kGemmRows + wave * 32;
     const int m0 = TRANS && PAIR ? max(0, min(m_first, M - 32)) : m_first;
@@ -569,32 +555,6 @@ __global__ __launch_bounds__(256) void dsum_kernel(GemmCut cut, const double* __
   double v = part[x];
   for (int z = 1; z < parts; ++z) v += part[size_t(z) * n + x];
   C[x] = v;
-}
-
-// kGemmBlocks blocks, a chunk or two at least in each.  max_parts > 0 (a Gram matrix whose parts the factorisation adds up itself: at
-// most kGramParts of them, all in flight at once there): every row block cut alike.
-constexpr int kGramParts = 32;
-GemmCut gemm_cut(int M, int Nc, int Kd, int max_parts = 0) {
-  GemmCut c;
-  c.ct = std::min(4, (Nc + 15) / 16);
-  c.gx = (Nc + 16 * c.ct - 1) / (16 * c.ct);
-  c.gy = (M + kGemmRows - 1) / kGemmRows;
-  c.chunks = (Kd + kGemmK - 1) / kGemmK;
-  const long long all = (long long)c.gy * c.chunks, blocks = std::max(1, kGemmBlocks / c.gx);
-  c.shared = max_parts == 0 && c.gy < 2 * blocks;
-  if (c.shared) {
-    c.per_block = int(std::max(2LL, (all + blocks - 1) / blocks));
-    c.parts = 1;
-    for (int y = 0; y < c.gy; ++y) c.parts = std::max(c.parts, c.parts_of(y));
-  } else {
-    const int parts = max_parts == 0 ? 1 : int(std::max(1LL, std::min({std::max(1LL, 768 / std::max(1LL, (long long)c.gx * c.gy)), (long long)max_parts, (long long)Kd / 64})));
-    c.per_block = (c.chunks + parts - 1) / parts;
-    c.parts = (c.chunks + c.per_block - 1) / c.per_block;
-  }
-  return c;
-}
-size_t gemm_part_doubles(int M, int Nc, int Kd) {
-  return size_t(std::max(gemm_cut(M, Nc, Kd).parts, gemm_cut(M, Nc, Kd, kGramParts).parts)) * M * Nc;
 }
 
 // part: room for gemm_part_doubles doubles.  keep_parts: leaves the partial sums there (returns their

@@ -1,6 +1,6 @@
 """Host code of csrc/ that needs no device, compiled into small programs of its own: the layer stack's bookkeeping after a
 copy that HIP refuses (stack_host.cpp, against a HIP of plain host memory: nothing of a failed step may be taken for granted by the
-next ones), and the shares of the decode launches' blocks (plan_host.cpp)."""
+next ones), the shares of the decode launches' blocks (plan_host.cpp), and the cut of the offline half's products (gemm_cut_host.cpp)."""
 import os
 import subprocess
 
@@ -27,3 +27,7 @@ def test_steps_after_a_refused_copy(tmp_path):
 
 def test_shares_of_the_decode_blocks(tmp_path):
     _run(tmp_path, os.path.join(HERE, "plan_host.cpp"))
+
+
+def test_cut_of_the_fp64_products(tmp_path):
+    _run(tmp_path, os.path.join(HERE, "gemm_cut_host.cpp"))
