@@ -1,4 +1,4 @@
-// How the offline half's dense fp64 products are cut into blocks.
+// How the offline half's dense fp64 products are cut into blocks, and the room that a factors call keeps for their parts.
 #pragma once
 #include <stddef.h>
 
@@ -68,8 +68,17 @@ inline GemmCut gemm_cut(int M, int Nc, int Kd, int max_parts = 0) {
   return c;
 }
 
-inline size_t gemm_part_doubles(int M, int Nc, int Kd) {
-  return size_t(std::max(gemm_cut(M, Nc, Kd).parts, gemm_cut(M, Nc, Kd, kGramParts).parts)) * M * Nc;
+// Room for a product's parts, in doubles: all but the first, which lies where the product will be; of a Gram matrix all of them.
+inline size_t gemm_part_doubles(int M, int Nc, int Kd) { return size_t(gemm_cut(M, Nc, Kd).parts - 1) * M * Nc; }
+inline size_t gram_part_doubles(int l, int Kd) { return size_t(gemm_cut(l, l, Kd, kGramParts).parts) * l * l; }
+
+// What a factors call of a K x N matrix with l columns keeps beside its two panels, in doubles: N x l for Bm, or its orthonormalised copy, and
+// (small: l columns fit one block's LDS) the parts of a Gram matrix behind it; the parts of all other products, which are done when
+// that is written, lie in the same place.  (An allocation above 64 MB costs a call 280 us more than one below: with a place of their own for
+// all parts 70000 x 512, rank 32, took 1800 us instead of 1520, 131072 x 256 2150 instead of 1810.)
+inline size_t factors_room(int K, int N, int rank, int l, bool small) {
+  const size_t panel = size_t(N) * l, gram = small ? std::max(gram_part_doubles(l, K), gram_part_doubles(l, N)) : gemm_part_doubles(l, l, K);
+  return std::max({panel + (small ? gram : 0), gram, gemm_part_doubles(K, l, N), gemm_part_doubles(N, l, K), gemm_part_doubles(K, rank, l)});
 }
 
 }  // namespace lrc

@@ -404,7 +404,7 @@ constexpr int kRing = 3;
 template <bool TRANS, int CT, bool PAIR = true>
 __global__ __launch_bounds__(256, 2) void dgemm_kernel(GemmCut cut, int M, int Nc, int Kd, const double* __restrict__ A, int lda,
                                                     const double* __restrict__ B, int ldb, double* __restrict__ C, int ldc,
-                                                    size_t c_stride) {
+                                                    double* __restrict__ part, size_t part_stride) {
   constexpr int kPitch = 16 * CT + 4;                  // (lane groups 4 rows apart then sit in different halves of the banks)
   constexpr int kLoadsB = kGemmK * 16 * CT / 256;
   __shared__ double Bs[2][kGemmK * kPitch];
@@ -531,7 +531,7 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(GemmCut cut, int M, int N
       multiply(a[0], Bs[whole & 1]);
     }
     // register r of lane (i, kq): row kq + 4 r, column i of the tile
-    double* Cz = C + z * c_stride;
+    double* Cz = z == 0 ? C : part + (z - 1) * part_stride;
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
@@ -547,13 +547,13 @@ __global__ __launch_bounds__(256, 2) void dgemm_kernel(GemmCut cut, int M, int N
   }
 }
 
-// C[x] = sum over z (in order) of part[z][x], of the parts that row x / Nc has
+// C[x] += the sum over z >= 1 (in order) of part[z - 1][x], of the parts that row x / Nc has: C holds part 0
 __global__ __launch_bounds__(256) void dsum_kernel(GemmCut cut, const double* __restrict__ part, int Nc, size_t n, double* __restrict__ C) {
   const size_t x = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (x >= n) return;
   const int parts = cut.parts_of(int(x / Nc) / kGemmRows);
-  double v = part[x];
-  for (int z = 1; z < parts; ++z) v += part[size_t(z) * n + x];
+  double v = C[x];
+  for (int z = 1; z < parts; ++z) v += part[size_t(z - 1) * n + x];
   C[x] = v;
 }
 
@@ -562,11 +562,11 @@ __global__ __launch_bounds__(256) void dsum_kernel(GemmCut cut, const double* __
 template <bool TRANS>
 int dgemm(int M, int Nc, int Kd, const double* A, int lda, const double* B, int ldb, double* C, double* part, bool keep_parts = false) {
   const GemmCut g = gemm_cut(M, Nc, Kd, keep_parts ? kGramParts : 0);
-  const bool direct = g.parts == 1 && !keep_parts;
-  double* out = direct ? C : part;
   const dim3 grid(g.gx, g.blocks());
   const size_t cs = size_t(M) * Nc;
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, nullptr, g, M, Nc, Kd, A, lda, B, ldb, out, Nc, cs); };
+  double* out = keep_parts ? part : C;
+  double* more = keep_parts ? part + cs : part;
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, nullptr, g, M, Nc, Kd, A, lda, B, ldb, out, Nc, more, cs); };
   auto pick = [&](auto CT_) {
     constexpr int CT = decltype(CT_)::value;
     if constexpr (TRANS) {
@@ -580,7 +580,7 @@ int dgemm(int M, int Nc, int Kd, const double* A, int lda, const double* B, int 
     case 3: pick(std::integral_constant<int, 3>{}); break;
     default: pick(std::integral_constant<int, 4>{}); break;
   }
-  if (!direct && !keep_parts)
+  if (g.parts > 1 && !keep_parts)
     hipLaunchKernelGGL(dsum_kernel, dim3((unsigned)((cs + 255) / 256)), dim3(256), 0, nullptr, g, part, Nc, cs, C);
   return g.parts;
 }
@@ -1053,10 +1053,7 @@ int moe_lrc_offline_factors(const double* E_dev, int K, int N, int rank, const d
   size_t bytes = 0;
   auto take = [&](size_t n) { const size_t at = bytes; bytes += (n + 255) & ~size_t(255); return at; };
   const size_t oY = take(size_t(K) * l * 8), oZ = take(size_t(N) * l * 8);
-  const size_t oZ2 = take(size_t(N) * l * 8);       // small l: the orthonormalised copy of Z; else (and as the fallback) Bm
-  const size_t part_n = std::max({gemm_part_doubles(K, l, N), gemm_part_doubles(N, l, K), gemm_part_doubles(l, l, K), gemm_part_doubles(l, l, N),
-                                  gemm_part_doubles(K, rank, l)});
-  const size_t oPart = take(part_n * 8);
+  const size_t oZ2 = take(factors_room(K, N, rank, l, small) * 8);
   const size_t oL1 = take(size_t(l) * l * 8), oL2 = take(size_t(l) * l * 8), oLi = take(size_t(l) * l * 8);
   const size_t oM = take(size_t(l) * rank * 8), oMi = take(size_t(l) * rank * 8);
   const size_t oGt = take(size_t(l) * l * 8), oNorm = take(size_t(l) * 8), oMul = take(size_t(rank) * 8), oSig = take(size_t(rank) * 8);
@@ -1065,15 +1062,15 @@ int moe_lrc_offline_factors(const double* E_dev, int K, int N, int rank, const d
   std::vector<int> h_pairs, order(l), h_sel(rank);
   std::vector<double> h_norm2(l), h_Gt, h_M, h_mul(rank), h_sig(rank);
   int h_status[4] = {0, 0, 0, 0};                   // sketch lost rank; Gram matrix of Bm not positive; rotations unconverged; scratch
-  double *Y, *Z, *Z2, *part, *L1, *L2, *Li, *M, *Mi, *Gt, *norm2, *mul, *sig;
+  double *Y, *Z, *Z2, *part, *gram, *L1, *L2, *Li, *M, *Mi, *Gt, *norm2, *mul, *sig;
   int *pairs, *sel, *status;
   unsigned* off;
   size_t small_lds = 0, rmul_lds = 0;
   void (*jacobi)(const double*, const double*, int, int, double*, double*, double*, const int*, int*) = nullptr;
   // one Cholesky QR of X [rows][l] (in place, or into `to`); factor and its inverse in L, Li
   auto qr_once = [&](double* X, int rows, double* to, double* L, int* bad) {
-    const int parts = dgemm<true>(l, l, rows, X, l, X, l, nullptr, part, true);
-    hipLaunchKernelGGL(cholesky_small_kernel, dim3(1), dim3(kCholThreads), small_lds, nullptr, part, parts, l, L, Li, bad);
+    const int parts = dgemm<true>(l, l, rows, X, l, X, l, nullptr, gram, true);
+    hipLaunchKernelGGL(cholesky_small_kernel, dim3(1), dim3(kCholThreads), small_lds, nullptr, gram, parts, l, L, Li, bad);
     if (to) hipLaunchKernelGGL(rmul_kernel<true>, dim3((rows + 63) / 64), dim3(256), rmul_lds, nullptr, X, rows, l, Li, l, to, (const int*)nullptr);
   };
   auto orth = [&](int reps) {
@@ -1088,7 +1085,7 @@ int moe_lrc_offline_factors(const double* E_dev, int K, int N, int rank, const d
     }
   };
   OFF_HIP(hipMalloc((void**)&base, bytes));
-  Y = (double*)(base + oY); Z = (double*)(base + oZ); Z2 = (double*)(base + oZ2); part = (double*)(base + oPart);
+  Y = (double*)(base + oY); Z = (double*)(base + oZ); Z2 = part = (double*)(base + oZ2); gram = Z2 + size_t(N) * l;
   L1 = (double*)(base + oL1); L2 = (double*)(base + oL2); Li = (double*)(base + oLi); M = (double*)(base + oM); Mi = (double*)(base + oMi);
   Gt = (double*)(base + oGt); norm2 = (double*)(base + oNorm); mul = (double*)(base + oMul); sig = (double*)(base + oSig);
   pairs = (int*)(base + oPairs); sel = (int*)(base + oSel); status = (int*)(base + oStatus);
@@ -1179,8 +1176,8 @@ int moe_lrc_offline_factors(const double* E_dev, int K, int N, int rank, const d
     OFF_HIP(hipMemcpy(M, h_M.data(), h_M.size() * 8, hipMemcpyHostToDevice));
     OFF_HIP(hipMemcpy(mul, h_mul.data(), size_t(rank) * 8, hipMemcpyHostToDevice));
     OFF_HIP(hipMemcpy(sel, h_sel.data(), size_t(rank) * sizeof(int), hipMemcpyHostToDevice));
-    dgemm<false>(K, rank, l, Y, l, M, rank, A_dev, part);
     hipLaunchKernelGGL(pick_rows_kernel, dim3((N + 255) / 256, rank), dim3(256), 0, nullptr, Bm, N, sel, mul, B_dev);
+    dgemm<false>(K, rank, l, Y, l, M, rank, A_dev, part);               // (Bm is done with)
   }
   if (A_bf16_dev) hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((size_t(K) * rank + 255) / 256)), dim3(256), 0, nullptr, A_dev, size_t(K) * rank, A_bf16_dev);
   if (B_bf16_dev) hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((size_t(rank) * N + 255) / 256)), dim3(256), 0, nullptr, B_dev, size_t(rank) * N, B_bf16_dev);

@@ -1,6 +1,7 @@
 // The cut of the offline half's dense fp64 products (csrc/gemm_cut.h), over sizes from one chunk up: every chunk of the reduction
 // in one part of its row block, the parts numbered from 0 without a gap, and no more of them than there is room for; small products
-// in one block per CU at most, none of them with chunks of two row blocks, large ones in as many as the chip holds.
+// in one block per CU at most, none of them with chunks of two row blocks, large ones in as many as the chip holds.  And the room
+// that a factors call keeps: not above 64 MB where a place for every part of a cut of three blocks per CU is below.
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -36,6 +37,14 @@ static void check_cut(int M, int Nc, int Kd, int max_parts) {
     REQUIRE(next_chunk[y] == c.chunks && next_part[y] == c.parts_of(y), "%d x %d x %d: row block %d ends at chunk %d of %d, part %d of %d", M, Nc, Kd, y, next_chunk[y], c.chunks, next_part[y], c.parts_of(y));
 }
 
+// ... three blocks per CU, row blocks alike, a place for every part
+static size_t all_parts(int M, int Nc, int Kd) {
+  const int ct = std::min(4, (Nc + 15) / 16), gx = (Nc + 16 * ct - 1) / (16 * ct), gy = (M + 127) / 128;
+  const int parts = std::max(1, std::min({std::max(1, 768 / (gx * gy)), 512, Kd / 64}));
+  const int k_per = ((Kd + parts - 1) / parts + 31) / 32 * 32;
+  return size_t((Kd + k_per - 1) / k_per) * M * Nc;
+}
+
 int main() {
   std::mt19937 rng(11);
   auto upto = [&](int n) { return int(rng() % unsigned(n)) + 1; };
@@ -44,5 +53,19 @@ int main() {
     check_cut(M, Nc, Kd, 0);
     check_cut(std::min(Nc, 96), std::min(Nc, 96), Kd, kGramParts);
   }
+  const int sizes[] = {300, 512, 700, 1024, 1408, 2048, 2944, 4096, 6000, 8192, 11008, 14336, 20000, 28672, 40000, 50000, 57344, 70000, 98304, 110000, 131072};
+  int below = 0;
+  for (int K : sizes)
+    for (int N : sizes)
+      for (int r : {1, 8, 16, 24, 32, 48, 64, 88, 128, 256}) {
+        const int l = r + 8;
+        if (l > std::min(K, N) || (long long)K * N > 1500000000LL) continue;
+        const size_t was = size_t(K) * l + 2 * size_t(N) * l + std::max({all_parts(K, l, N), all_parts(N, l, K), all_parts(l, l, K), all_parts(l, l, N), all_parts(K, r, l)});
+        const size_t is = size_t(K) * l + size_t(N) * l + factors_room(K, N, r, l, l <= 96);
+        if (was * 8 > size_t(64) << 20) continue;
+        ++below;
+        REQUIRE(is * 8 <= size_t(64) << 20, "%d x %d, rank %d: %.1f MB, %.1f before", K, N, r, is / 131072.0, was / 131072.0);
+      }
+  REQUIRE(below > 500, "%d shapes", below);
   return 0;
 }

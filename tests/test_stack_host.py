@@ -1,6 +1,7 @@
 """Host code of csrc/ that needs no device, compiled into small programs of its own: the layer stack's bookkeeping after a
 copy that HIP refuses (stack_host.cpp, against a HIP of plain host memory: nothing of a failed step may be taken for granted by the
-next ones), the shares of the decode launches' blocks (plan_host.cpp), and the cut of the offline half's products (gemm_cut_host.cpp)."""
+next ones), the shares of the decode launches' blocks (plan_host.cpp), and the cut of the offline half's products with the room they
+take (gemm_cut_host.cpp)."""
 import os
 import subprocess
 
