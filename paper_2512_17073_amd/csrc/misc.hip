@@ -117,6 +117,12 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
 // Bound: the longest chain of dependent loads (grouping, then the tokens or the tables; tokens and factors,
 // then a sum over the wavefronts); Mixtral shape T = 64 17.2 -> 11.2 us, T = 1 15.3 -> 11.8, since neither waits for the other
 // and the tables are made without 64-bit divisions from counts read once.
+// At most this many blocks for the passes of (x A1 | x A3) beyond the experts' first ones.  Whole forward, us, with 0 / 32 / 64 / 128 / 256: Qwen3
+// shape T = 64 87.2 / 86.2 / 86.1 / 86.2 / 86.1, T = 128 145.9 / 139.8 / 134.5 / 134.4 / 134.4, T = 256 263 / 243 / 236 / 230 / 230, rank 64
+// T = 64 94.7 / 99.6 / 96.4 / 96.3 / 96.3, T = 128 151.5 / 166.1 / 155.7 / 149.2 / 145.3; Mixtral rank 64 T = 160 271.6 / 268.7 / 266.7 / 265.6 /
+// 265.9; where no expert has more than 32 rows the same with any of them, while up to four blocks a tile, one a pass, cost 16 experts, rank 64,
+// Top-1, T = 100 37.8 -> 50.6, 32 experts, Top-4, T = 128 51.9 -> 64.7.
+constexpr int kMorePassBlocks = 128;
 constexpr int kStatAhead = 8;              // batches of 64 rows whose pairs a counting wavefront asks for together
 // With a token or two every block first routes them itself (route.wg != null).
 // With few pairs, every block first groups the pairs by expert itself (perm.idx != null) instead of a launch of its own
@@ -133,13 +139,13 @@ struct SmallRows {                         // grouped by this block, in its LDS
 };
 
 // The launch's blocks in order: `stat` that count, row blocks x columns, `plan` for the tables, factor tiles x passes of
-// (x A1 | x A3), then `columns` that keep the zero rows.
+// (x A1 | x A3) and `more` for the passes that only some experts have, then `columns` that keep the zero rows.
 struct PrepGrid {
-  int stat, row_blocks, columns, plan, tiles, passes;
+  int stat, row_blocks, columns, plan, tiles, passes, more;
   LRC_HD int rows_at() const { return stat; }
   LRC_HD int plan_at() const { return stat + row_blocks * columns; }
   LRC_HD int xa_at() const { return plan_at() + plan; }
-  LRC_HD int zero_at() const { return xa_at() + tiles * passes; }
+  LRC_HD int zero_at() const { return xa_at() + tiles * passes + more; }
   LRC_HD int blocks() const { return zero_at() + columns; }
 };
 // The passes of a factor tile run on one XCD (block b runs on XCD b % 8), whose L2 then holds the tile.
@@ -172,10 +178,22 @@ __device__ inline void prep_roles(const Rows& grouped, const uint16_t* __restric
   }
   if constexpr (XA) {
     if (block >= g.xa_at()) {                                               // of the routed rows
-      int tile, pass;
-      xa_block(g, block - g.xa_at(), tile, pass);
-      const int per = g.tiles / E, e = tile / per;
-      ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, grouped, x, tile - e * per, e, 0, pass, g.passes, red);
+      // Every tile has a block for its expert's first pass of 32 rows, which takes the others too where the launch has no blocks for them;
+      // these deal out the passes beyond the first of the experts that have any (an expert with many rows must not be one block's chain
+      // of passes, nor every tile have blocks for rows that only a few experts have: each block groups the pairs and takes a CU).
+      constexpr int kOnly = 1 << 20;
+      const int per = g.tiles / E, i = block - g.xa_at();
+      if (i < g.tiles) {
+        const int e = i / per;
+        ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, grouped, x, i - e * per, e, 0, 0, g.more > 0 ? kOnly : 1, red);
+        return;
+      }
+      const auto offset = [&](int e) { return grouped.offset(e); };
+      int e, pass;
+      for (int item = i - g.tiles; further_pass(offset, E, item / per, threadIdx.x & 63, e, pass); item += g.more) {
+        if (item >= g.more) __syncthreads();           // (the item before this one is done with the sums)
+        ffn::xa_rows_body<true, true, kWavesPerBlock>(xa, grouped, x, item % per, e, 0, pass, kOnly, red);
+      }
       return;
     }
   }
@@ -371,14 +389,13 @@ hipError_t launch_convert_x(const moe_lrc_layer* L, const void* x_bf16, int T, _
     xa_tiles = 2 * f.rpad / 16;
   }
   const int stat_blocks = stat ? (c.n_experts + kPrepThreads / 64 - 1) / (kPrepThreads / 64) : 0;
-  PrepGrid g{stat_blocks, row_blocks, ky, plan_block, xa_tiles * c.n_experts, 1};
+  PrepGrid g{stat_blocks, row_blocks, ky, plan_block, xa_tiles * c.n_experts, 1, 0};
   if (xa.p_tokens > 0) {
     const int pass = xa_tokens_pass(xa.p_tokens, ky);
     g.passes = (xa.p_tokens + pass - 1) / pass;
-  } else if (xa_tiles > 0) {
-    // By rows, 32 a pass, up to four side by side: an expert with many must not be one block's chain of passes (Qwen3 shape, T = 64, 60
-    // rows on one of 128 experts: launch 17.2 -> 14.0 us; the blocks of experts with fewer rows leave at once, 2 us for all of them).
-    g.passes = std::max(1, std::min({4, (T + 31) / 32, 4 * L->n_cu / g.tiles}));
+  } else if (xa_tiles > 0 && T > 32) {
+    // (experts with more than 32 rows have at most rows / 32 passes beyond their first ones)
+    g.more = std::min(kMorePassBlocks, xa_tiles * (rows / 32));
   }
   const int cmp_block = (cmp && row_pair && stat) ? 1 : 0;     // (the compaction rides the per-expert counting)
   const bool full = xa_tiles > 0 || perm != nullptr;

@@ -188,6 +188,23 @@ __device__ inline void make_chunks(const Offset& offset, int E, const ChunkSpec 
   for (int i = base + lane; i < sp.items; i += 64) table[i] = ChunkEntry{-1, 0, 0, 0};
 }
 
+// The n-th pass of 32 rows beyond the experts' first ones, counted over the experts in order: its expert, and the pass within it (from 1).
+template <class Offset>
+__device__ inline bool further_pass(const Offset& offset, int E, int n, int lane, int& e, int& pass) {
+  for (int g = 0, base = 0; g < E; g += 64) {
+    const int x = min(g + lane, E - 1), cnt = g + lane < E ? offset(x + 1) - offset(x) : 0;
+    const int more = max((cnt + 31) / 32 - 1, 0), incl = wave_scan(more), total = lane_value(incl, 63);
+    if (n < base + total) {
+      const int first = __ffsll(__ballot(base + incl > n)) - 1;
+      e = g + first;
+      pass = 1 + n - base - lane_value(incl - more, first);
+      return true;
+    }
+    base += total;
+  }
+  return false;
+}
+
 // What the preparing launch makes for the FFN launches: per projection (W1|W3, W2) the one table its flavour reads.
 struct FfnTables { PlanSpec plan[2]; ChunkSpec chunk[2]; };
 

@@ -819,6 +819,46 @@ def test_rank_steps_of_unshared_units(amd, hidden, ffn, rank, kind, bits):
     L.close()
 
 
+@pytest.mark.parametrize("experts,top_k,busy,tokens,rank,kind", [
+    (8, 2, 2, 160, 256, "same"),           # passes beyond the first: 8, of 32 tiles each, dealt to 128 blocks twice
+    (20, 2, 2, 33, 8, "same"),             # one row beyond the first pass of either expert
+    (130, 3, 3, 100, 24, "int3"),          # experts of the third group of 64 have them all; an odd number of tiles
+    (16, 1, 1, 65, 40, "bucket"),          # one expert has every row; ranks that differ, pairs missing
+    (12, 1, 12, 32, 16, "same"),           # no expert can have more than one pass
+])
+def test_x_a13_of_experts_with_several_passes(amd, experts, top_k, busy, tokens, rank, kind):
+    """(x A1 | x A3) of the routed rows where the last `busy` experts take every token: the passes of 32 rows beyond an expert's first
+    one, which blocks of their own share, against the oracle and, bit for bit, staged residency, where one block makes them all."""
+    import torch
+    cfg = configs.TINY.with_(hidden=320, ffn=256, n_experts=experts, top_k=top_k, top_n=top_k, tokens=tokens, bits=2, rank=rank, name=f"busy_{experts}_{tokens}_r{rank}")
+    layer = fixtures.sample_layer(cfg)
+    layer["bias"] = np.where(np.arange(experts) >= experts - busy, 100.0, 0.0).astype(np.float32)
+    bucket = (rank, 0, 16, rank, 8)
+    for e, ex in enumerate(layer["experts"]):
+        for m in (0, 1, 2):
+            a = ex[m]
+            if kind == "int3":
+                a["Aq"], a["Bq"] = synth.sample_factor_codes(cfg, e, m)
+                a["A"] = a["B"] = None
+            elif kind == "bucket":
+                a["rank"] = r = bucket[(3 * e + 2 * m) % len(bucket)]
+                a["A"] = np.ascontiguousarray(a["A"][:, :r]) if r else None
+                a["B"] = np.ascontiguousarray(a["B"][:r]) if r else None
+    x_bits = synth.make_tokens(cfg)
+    x = amd.bf16_tensor(x_bits)
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    assert (np.diff(ref["perm"]["offsets"])[:experts - busy] == 0).all()
+    Lr, Ls = amd.Layer.from_config(cfg), amd.Layer.from_config(cfg, residency=amd.STAGED)
+    Lr.load(layer); Ls.load(layer)
+    out_r = Lr.forward(x).clone()
+    assert Lr.stats()["path"] == 0
+    out_s = Ls.forward(x).clone()
+    torch.cuda.synchronize()
+    assert orc.rel_frobenius(_to_np(out_r), ref["out"]) <= TOL
+    assert torch.equal(out_r.view(torch.int16), out_s.view(torch.int16))
+    Lr.close(); Ls.close()
+
+
 @pytest.mark.parametrize("experts,top_k,tokens", [
     (32, 2, 32), (32, 2, 33),              # 64 pairs and the most experts; a 65th pair, which is too many steps for 32 experts
     (16, 2, 64), (16, 3, 43),              # two steps; 129 pairs
