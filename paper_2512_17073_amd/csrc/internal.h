@@ -130,7 +130,7 @@ constexpr int kFusedPermuteMaxPairs = 1024;
 // the routing of a token or two run inside the preparing launch as well (forward only): gate
 // [E][H] bf16 and bias (or null) in, the outputs of moe_lrc_route and the tokens' pre-scale exponents out
 struct RouteArgs { const uint16_t* wg; const float* bias; int32_t* idx; float* w; int32_t* tok_exp; int renorm; };
-constexpr int kFusedRoutePairs = 16;      // (token, expert) gate products: one per wavefront of a block (its pairs always fit group_small)
+constexpr int kFusedRoutePairs = 16;      // (token, expert) gate products: one per wavefront of a block (always grouped by ballots, group_small)
 // above this many pairs several blocks group them (two launches); their counters live in the layer
 constexpr int kPermuteOneBlockPairs = 8192, kPermuteMaxBlocks = 64;
 constexpr int kPermuteScratchInts = kPermuteMaxBlocks * 2 * 256 + 64;

@@ -309,7 +309,8 @@ __global__ __launch_bounds__(kPrepThreads, FULL ? 4 : 8) void prep_kernel(const 
     auto roles = [&](const auto& grouped, bool have_exp) {
       prep_roles<true>(grouped, x, rows, H, xg, rt, routed, E, top_k, top_n, stat, tables, g, xa, have_exp, row_exp, cmp, zr, host_stat, row_tok, red, row_max);
     };
-    if (perm.idx != nullptr && group_small_fits(perm.P, E)) {
+    static_assert(kFusedRoutePairs <= kSmallExperts, "the pairs that this launch routes itself are grouped by ballots");
+    if (perm.idx != nullptr && (route.wg != nullptr || group_small_fits(perm.P, E))) {
       const bool out = block == g.zero_at();     // the block that writes the results
       const PermuteOut o{perm.counts, perm.offsets, perm.row_pair, perm.pair_row, perm.comp_counts};
       if (route.wg != nullptr) {

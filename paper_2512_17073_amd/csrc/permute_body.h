@@ -91,13 +91,16 @@ __device__ inline void permute_body(PermuteLds& L, const int32_t* idx, int P, in
   }
 }
 
-// The same for few pairs and experts by ballots alone (group_small_fits): every wavefront groups all pairs for itself, without a
+// The same for few pairs and experts by ballots alone (where group_small_fits): every wavefront groups all pairs for itself, without a
 // barrier or a read back of what it has stored, and leaves the offsets and the rows' pairs in the block's LDS (all wavefronts write
 // the same values there).  idx may be in LDS.  With `out` wavefront 0 writes the five arrays of the permute kernel.
-// Mixtral shape, T = 64: the launch that prepares the activations, which every block of groups first, spends 0.8 us on it
-// instead of 2.7.
-constexpr int kSmallPairs = 256, kSmallExperts = 32;
-LRC_HD bool group_small_fits(int P, int E) { return P <= kSmallPairs && E <= kSmallExperts && (P + 63) / 64 * E <= 32; }
+// Every block of the launch that prepares the activations does this first, so its length counts once a round of blocks: two ballots and
+// their counts per 64 pairs and expert, against the five barriers and the LDS tables of the kernel's body.  Whole forward, the body ->
+// ballots, us, hidden 1024, by (steps of 64 pairs) x experts, no factors / rank 128: 2 30.7 -> 29.5 / 38.7 -> 38.0, 8 30.8 -> 29.4 / 37.0 -> 35.6, 9
+// 1.2 less / 1.2 less, 12 0.9 less / 0.6 less with one step, 0.4 less / 0.1 more with two or more; 14 0.7 less / 0.4 more, 16 0.3 less / 1.9
+// more with 16 experts, 24 34.2 -> 33.4 / 42.9 -> 43.4, 32 37.9 -> 39.9 / 55.0 -> 65.6 with 32 experts.
+constexpr int kSmallPairs = 256, kSmallExperts = 16;      // (what it can take: the experts of a token that the launch routes itself)
+LRC_HD bool group_small_fits(int P, int E) { return P <= kSmallPairs && (P + 63) / 64 * E <= 12; }
 struct SmallGroup {
   int32_t offset[kSmallExperts + 1];
   int32_t pair[kSmallPairs];             // pair of every row
