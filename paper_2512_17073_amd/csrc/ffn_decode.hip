@@ -151,7 +151,6 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
   // (the first pass's, on their way before the table entry's fields are used)
   if constexpr (joined) part_issue(0);
   stage_issue(a, 0, 0, min(KP, KSl));
-  exp_issue(a, 0);
   __builtin_amdgcn_sched_barrier(0);
 
   // The rank-r term rides the same stream (B-factor units in place of packed codes, against (in A)
@@ -189,7 +188,16 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
   const bool q3_a2 = Q3 && ((q3 >> 2) & 1) != 0;
   const int u0 = t0 / 2, n_u = (t1 - 1) / 2 - u0 + 1, g0 = t0 / 4, n_q = ((t1 - 1) / 4 - g0) / 4 + 1;
   const bool a2_early = HA && DUAL && ht > 0 && !p_late && p_frags * 64 + (q3_a2 ? (n_u + n_q) * 16 : n_u * 64) * ht <= kSpareUnits;
-  auto as_lds = [](uint4* p) { return reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(p)); };
+  // Copies to LDS of 16 (or 4) bytes a lane, byte offset `at` from a wave-uniform base.  (By a buffer resource: with a global_load_lds in flight
+  // the compiler waits for every load at the next barrier.  Rows of this flavour are at most 128 an expert on average: `at` is below 2^27.)
+  auto copy16 = [](const void* from, int at, uint4* to) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(from), 0, 0xffffffffu, 0x00020000),
+        reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(to)), 16, at, 0, 0, 0);
+  };
+  auto copy4 = [](const void* from, int at, uint4* to) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(from), 0, 0xffffffffu, 0x00020000),
+        reinterpret_cast<__attribute__((address_space(3))) void*>(reinterpret_cast<uintptr_t>(to)), 4, at, 0, 0, 0);
+  };
 
   // (in A) of a pass's rows: fp16 row-major in global memory, already multiplied by the
   // projection's power-of-two pre-scale and zero for rows without the term.  Fragment
@@ -200,8 +208,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
     for (int f = wave; f < p_frags; f += kWaves) {
       const int mt = f % MT, g = f / MT, m = g >= LS ? 1 : 0, st = g - m * LS;
       const int row = r0 + min(r + 16 * mt + c, cnt - 1);
-      const _Float16* src = P + size_t(row) * pitch + m * A.ls * 32 + 32 * st + 8 * q;
-      __builtin_amdgcn_global_load_lds(as_global<uint32_t>(src), as_lds(p_lds + p_frag_unit(m, st, mt, LS, MT)), 16, 0, 0);
+      copy16(P, (row * pitch + m * A.ls * 32 + 32 * st + 8 * q) * 2, p_lds + p_frag_unit(m, st, mt, LS, MT));
     }
   };
   // ... or kept per token (the projection's rows of every token, p_tokens > 0)
@@ -211,8 +218,7 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
     if (r > 0) token = A.row_tok[r0 + min(pr, cnt - 1)];
     // (rows without the term read the row of zeros)
     const int row = pr < cnt && token >= 0 ? e * A.p_tokens + token : A.n_exp * A.p_tokens;
-    const _Float16* src = reinterpret_cast<const _Float16*>(A.p) + row * pitch + m * A.ls * 32 + 32 * st + 8 * q;
-    __builtin_amdgcn_global_load_lds(as_global<uint32_t>(src), as_lds(p_lds + p_frag_unit(m, st, mt, LS, MT)), 16, 0, 0);
+    copy16(A.p, (row * pitch + m * A.ls * 32 + 32 * st + 8 * q) * 2, p_lds + p_frag_unit(m, st, mt, LS, MT));
   };
   auto p_start = [&](const auto& A, int r) {
     if (p_late || joined) return;
@@ -269,8 +275,8 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
         const u32x2 v1 = __builtin_amdgcn_raw_buffer_load_b64(src.code[m], lo.code1, code, 0);
         sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1];
       } else if constexpr (BITS == 4) {
-        // (code1 by the instruction's own offset, a register less: with 128 in use the kernel spilled.  A rank step reads the next unit's
-        // 16 bytes with it and leaves them)
+        // (code1 by the instruction's own offset, a register less of the kernel's 128.  A rank step reads the next unit's 16 bytes with it and
+        // leaves them)
         const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(src.code[m], lo.code0 + 1024, code, 0);
         sl.cw[m][4] = v1[0]; sl.cw[m][5] = v1[1]; sl.cw[m][6] = v1[2]; sl.cw[m][7] = v1[3];
       }
@@ -339,26 +345,21 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
   Slot<BITS, NS> ring[RING];
   static_assert(RING == 2 && TS <= RING, "a rank turn's slots: a unit each, or two steps of one unit");
 
-  // ---- start of the first pass: everything that is left is requested before anything is awaited ----
+  // ---- start of the first pass: the copies that are left ----
   p_start(a, 0);
   if (a2_early) {
     uint4* dst = p_lds + p_frags * 64;
     for (int f = wave; f < n_u * ht; f += kWaves) {      // (ht: 1 or 2)
       const int rt = f >= n_u ? 1 : 0, unit = (rt * (a.N / 32) + u0 + f - rt * n_u) * kWave + lane;
-      if (q3_a2) __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d->af[2])) + unit, as_lds(dst + f * 16), 4, 0, 0);
-      else __builtin_amdgcn_global_load_lds(as_global<u32x4>(uniform_ptr(d->af[2])) + unit, as_lds(dst + f * 64), 16, 0, 0);
+      if (q3_a2) copy4(d->af[2], unit * 4, dst + f * 16);
+      else copy16(d->af[2], unit * 16, dst + f * 64);
     }
     if (q3_a2)
       for (int f = wave; f < n_q * ht; f += kWaves) {
         const int rt = f >= n_q ? 1 : 0, g = min(g0 + 4 * (f - rt * n_q) + q, a.N / 64 - 1);
-        __builtin_amdgcn_global_load_lds(as_global<uint32_t>(uniform_ptr(d->afm[2])) + (rt * (a.N / 64) + g) * 16 + c,
-                                         as_lds(dst + (n_u * ht + f) * 16), 4, 0, 0);
+        copy4(d->afm[2], ((rt * (a.N / 64) + g) * 16 + c) * 4, dst + (n_u * ht + f) * 16);
       }
   }
-  __builtin_amdgcn_sched_barrier(0);
-  fetch_from(0, 0, own > 0);
-#pragma unroll
-  for (int i = 0; i < RING; ++i) fetch(ring[i]);
   __builtin_amdgcn_sched_barrier(0);
   constexpr int kAheadLoads = RING * NS * (BITS == 2 ? 2 : 3);
 
@@ -371,14 +372,20 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
       if constexpr (joined) part_issue(ra);
       stage_issue(*ka, ra, 0, min(KP, KSl));
       p_start(*ka, ra);
-      exp_issue(*ka, ra);
-      fetch_from(0, 0, own > 0);
-#pragma unroll
-      for (int i = 0; i < RING; ++i) fetch(ring[i]);
     }
+    // The first turn of the ring and the rows' exponents, requested last, stay in flight over the wait for the copies to LDS: in one place
+    // for all passes, for registers that two places load are moved where the two meet, behind a wait for all loads (16 of the 24
+    // kernels had one), and spill: scalar spills W1|W3 at 2 bits with part sums 171 -> 120, with 3-bit pairs 308 -> 188, vector spills at 4
+    // bits 3 to 11 registers -> 0.  Whole forward, Mixtral shape T = 64: 143.9 -> 140.5 us on one box, 132.6 -> 131.7 on another;
+    // T = 1, T = 13 at 3 bits, Qwen3 T = 64 the same.
+    fetch_from(0, 0, own > 0);
+#pragma unroll
+    for (int i = 0; i < RING; ++i) fetch(ring[i]);
+    __builtin_amdgcn_sched_barrier(0);
+    exp_issue(*kern_args(), again(r));
+    __builtin_amdgcn_sched_barrier(0);
     if constexpr (joined) p_join(again(r));
-    if (r > 0) wait_loads_barrier();
-    else wait_loads_barrier_but<kAheadLoads>();          // (the first turn of the ring stays in flight)
+    wait_loads_barrier_but<kAheadLoads + MT>();
 
     float4_t acc[TS][MT][NS];
 #pragma unroll

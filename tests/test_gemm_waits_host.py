@@ -1,6 +1,8 @@
 """What the built code has to show of three kernels.  The grouped GEMM's k-steps with two slots of weights wait for the copy of the
 activations and leave the weights requested after it in flight: the loads between the two are exactly as many as the wait leaves
-out.  The decode kernels request a rank step while another is on its way.  The tiled gate's products follow each other without branches."""
+out.  The decode kernels request a rank step while another is on its way, and their copies to LDS have arrived at every barrier.  The
+tiled gate's products follow each other without branches."""
+import math
 import os
 import re
 import struct
@@ -79,6 +81,73 @@ def test_decode_kernels_refill_a_slot_while_the_other_rank_step_is_on_its_way(tm
         parts = [part for part in events.split("B") if part.strip("L") and part.count("P") < 32]
         assert sorted(part.count("P") for part in parts) == [8, 16], (name, parts)         # one row tile, two
         assert all(part.count("L") == 4 and "LLL" not in part for part in parts), (name, parts)
+
+
+def _blocks(tmp_path, kernel):
+    """(name, basic blocks) of the kernel's instantiations: lists of instructions and of the blocks that can follow."""
+    co = tmp_path / "kernel.co"
+    co.write_bytes(_gfx950_code(tmp_path, kernel))
+    text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", str(co)], capture_output=True, text=True, check=True).stdout
+    for start, name, body in re.findall(r"^([0-9a-f]+) <(\S*%s\S*)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)" % kernel, text, re.S | re.M):
+        code = [(int(at, 16), ln.strip(), target and int(start, 16) + int(target, 16))
+                for ln, at, target in re.findall(r"^\s+(\S.*?)\s*// ([0-9A-F]+):[^<\n]*(?:<[^+\n]*\+0x([0-9a-f]+)>)?", body, re.M)]
+        heads = {code[0][0]} | {t for _, _, t in code if t} | {code[i + 1][0] for i, c in enumerate(code[:-1]) if c[2] or c[1] == "s_endpgm"}
+        blocks, at = {}, None
+        for i, (addr, ln, target) in enumerate(code):
+            if addr in heads:
+                at = addr
+                blocks[at] = ([], [])
+            blocks[at][0].append(ln)
+            if target:
+                blocks[at][1].append(target)
+            last = i + 1 == len(code)
+            if not last and code[i + 1][0] in heads and not ln.startswith(("s_branch", "s_endpgm")):
+                blocks[at][1].append(code[i + 1][0])
+        yield name, blocks
+
+
+def _copies_left_at_barriers(blocks):
+    """Barriers that a path reaches with copies to LDS of its wavefront in flight.  Along a path: the least number of loads requested since the
+    last copy that no wait was for (inf: none); a wait that leaves no more than these in flight was for the copy."""
+    state, todo, left = {min(blocks): math.inf}, [min(blocks)], {}
+    while todo:
+        at = todo.pop()
+        since = state[at]
+        for i, ln in enumerate(blocks[at][0]):
+            wait = re.match(r"s_waitcnt .*vmcnt\((\d+)\)", ln)
+            if re.match(r"global_load_lds|buffer_load_.*\blds$", ln):
+                since = 0
+            elif re.match(r"(buffer|global|flat|scratch)_load", ln):
+                since += 1
+            elif wait and since >= int(wait[1]):
+                since = math.inf
+            elif ln.startswith("s_barrier") and since < math.inf:
+                left[at, i] = since
+        for to in blocks[at][1]:
+            if to not in state or since < state[to]:
+                state[to] = since
+                todo.append(to)
+    return left
+
+
+def test_copies_of_the_decode_kernels_have_arrived_at_every_barrier(tmp_path):
+    # A pass's first wait leaves the first turn of the ring in flight (two loads of either stream's slot, three at 3 and 4 bits) and
+    # one load a row tile of the rows' exponents: neither fewer, nor so many that a copy is among them.
+    found = 0
+    for name, blocks in _blocks(tmp_path, "qgemm_decode_kernel"):
+        bits = int(re.search(r"qgemm_decode_kernelILi(\d)", name)[1])
+        waits = [(at, i, int(ln[len("s_waitcnt vmcnt("):].split(")")[0])) for at, (code, _) in blocks.items() for i, ln in enumerate(code[:-1])
+                 if ln.startswith("s_waitcnt vmcnt(") and not ln.startswith("s_waitcnt vmcnt(0)") and code[i + 1].startswith("s_barrier")]
+        ring = 8 if bits == 2 else 12
+        assert sorted(n for _, _, n in waits) == [ring + 1, ring + 2], (name, waits)       # one row tile, two
+        assert not _copies_left_at_barriers(blocks), (name, _copies_left_at_barriers(blocks))
+        # and what it would look like otherwise: a wait that leaves one more load in flight
+        for at, i, n in waits:
+            code = list(blocks[at][0])
+            code[i] = "s_waitcnt vmcnt(%d)" % (n + 1)
+            assert _copies_left_at_barriers({**blocks, at: (code, blocks[at][1])}), (name, at, n)
+        found += 1
+    assert found == 24
 
 
 def test_products_of_the_tiled_gate_between_branches(tmp_path):
