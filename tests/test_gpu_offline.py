@@ -210,11 +210,17 @@ def test_residual_factors_at_the_edges(amd, K, N, r, over, iters):
 
 
 # products of a block per CU: two, three, four and seven chunks of 32 to a block, a last chunk that is partial, two groups of columns, fewer
-# rows than a block takes; shares of the reduction that run over the end of a row block (6500 x 5000, 80 columns; 8300 x 4100; 33000 x
-# 300), and so many row blocks that they are not cut at all
+# rows than a block takes; shares of the reduction that run over the end of a row block (6500 x 5000, 80 columns), and so many row
+# blocks that they are not cut at all
 @pytest.mark.parametrize("K,N,r,over,iters", [(4100, 129, 8, 8, 1), (1700, 3300, 24, 8, 1), (520, 3000, 40, 30, 1), (31, 8192, 16, 8, 1),
-                                              (6500, 5000, 60, 20, 0), (131200, 40, 8, 4, 0), (8300, 4100, 8, 8, 0), (33000, 300, 8, 8, 1)])
+                                              (6500, 5000, 60, 20, 0), (131200, 40, 8, 4, 0)])
 def test_residual_factors_cut_across_row_blocks(amd, K, N, r, over, iters):
+    test_residual_factors_at_the_edges(amd, K, N, r, over, iters)
+
+
+# ... with one group of columns: few row blocks, a last chunk that is partial; many row blocks, ten chunks each
+@pytest.mark.parametrize("K,N,r,over,iters", [(8300, 4100, 8, 8, 0), (33000, 300, 8, 8, 1)])
+def test_residual_factors_of_shares_across_row_blocks(amd, K, N, r, over, iters):
     test_residual_factors_at_the_edges(amd, K, N, r, over, iters)
 
 

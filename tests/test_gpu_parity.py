@@ -860,18 +860,15 @@ def test_x_a13_of_experts_with_several_passes(amd, experts, top_k, busy, tokens,
 
 
 @pytest.mark.parametrize("experts,top_k,tokens", [
-    (32, 2, 32), (32, 2, 33), (16, 2, 64), (16, 3, 43), (8, 2, 128), (8, 1, 129), (8, 2, 129), (33, 1, 5),      # beyond the line
-    (12, 2, 32), (12, 2, 33), (13, 2, 3),  # the most experts, 64 pairs and 66; an expert too many
-    (6, 2, 64), (6, 3, 43), (4, 2, 96),    # 128 pairs and 129; three steps
-    (3, 3, 85), (3, 2, 129), (1, 1, 256),  # 255 pairs, every token has every expert; 258 pairs; one expert
-    (16, 3, 1), (8, 2, 2), (5, 4, 3),      # routed by the launch that groups them
+    (32, 2, 32), (32, 2, 33),              # 64 pairs; a 65th
+    (16, 2, 64), (16, 3, 43),              # two steps; 129 pairs
+    (8, 2, 128), (8, 1, 129), (8, 2, 129), # 256 pairs; three steps; 258 pairs
+    (33, 1, 5), (3, 3, 85), (1, 1, 256),   # many experts; every token has every expert; one expert
 ])
 def test_forward_of_few_pairs_groups_them_as_permute_does(amd, experts, top_k, tokens):
     """forward() groups few pairs by ballots in the launch that prepares the activations, permute() by the histogram: sizes on both
-    sides of the line between them.  The five arrays that forward() leaves in the workspace are permute()'s, bit for bit, and these the
-    oracle's; the output against the oracle (bf16 rounding: TOL) and the four calls (which may round the expert rows to bf16
-    once more, 2^-9)."""
-    import torch
+    sides of the line between them, against the oracle (bf16 rounding: TOL) and the four calls (which may round the expert rows to
+    bf16 once more, 2^-9)."""
     cfg = configs.TINY.with_(n_experts=experts, top_k=top_k, top_n=min(top_k, 2), tokens=tokens, ffn=128, rank=16, name=f"few_E{experts}_T{tokens}")
     layer = fixtures.sample_layer(cfg)
     x_bits = synth.make_tokens(cfg)
@@ -884,19 +881,42 @@ def test_forward_of_few_pairs_groups_them_as_permute_does(amd, experts, top_k, t
     for g, key in zip((counts, offsets, row_pair, pair_row, comp), ("counts", "offsets", "row_pair", "pair_row", "comp_counts")):
         np.testing.assert_array_equal(_to_np(g), ref["perm"][key], err_msg=key)
     four = L.combine(L.expert_ffn(x, offsets, row_pair), w, pair_row, x).clone()
+    out = L.forward(x)
+    assert orc.rel_frobenius(_to_np(out), ref["out"]) <= TOL
+    assert orc.rel_frobenius(_to_np(out), _to_np(four)) <= 2.5e-3
+    L.close()
+
+
+@pytest.mark.parametrize("experts,top_k,tokens", [
+    (32, 2, 32), (32, 2, 33), (16, 2, 64), (16, 3, 43), (8, 2, 128), (8, 1, 129), (8, 2, 129), (33, 1, 5),      # beyond the line
+    (12, 2, 32), (12, 2, 33), (13, 2, 3),  # the most experts, 64 pairs and 66; an expert too many
+    (6, 2, 64), (6, 3, 43), (4, 2, 96),    # 128 pairs and 129; three steps
+    (3, 3, 85), (3, 2, 129), (1, 1, 256),  # 255 pairs, every token has every expert; 258 pairs; one expert
+    (16, 3, 1), (8, 2, 2), (5, 4, 3),      # routed by the launch that groups them
+])
+def test_forward_leaves_the_arrays_of_permute(amd, experts, top_k, tokens):
+    """The five arrays of the grouping that forward() leaves in the workspace are the oracle's, as permute()'s are, on both sides of the line
+    between the ballots of the launch that prepares the activations and the histogram."""
+    import torch
+    cfg = configs.TINY.with_(n_experts=experts, top_k=top_k, top_n=min(top_k, 2), tokens=tokens, ffn=128, rank=16, name=f"few_E{experts}_T{tokens}")
+    layer = fixtures.sample_layer(cfg)
+    x_bits = synth.make_tokens(cfg)
+    x = amd.bf16_tensor(x_bits)
+    ref = fixtures.oracle_forward(cfg, layer, x_bits)
+    L = amd.Layer.from_config(cfg)
+    L.load(layer)
     ws = L.workspace(tokens)
     ws.fill_(0xa5)
     out = L.forward(x)
     torch.cuda.synchronize()
     left, at = ws.cpu().numpy().tobytes(), 0
-    for key, want in zip(("counts", "offsets", "comp_counts", "row_pair", "pair_row"), (counts, offsets, comp, row_pair, pair_row)):
-        want = _to_np(want).astype(np.int32).tobytes()
+    for key in ("counts", "offsets", "comp_counts", "row_pair", "pair_row"):
+        want = np.asarray(ref["perm"][key]).astype(np.int32).tobytes()
         while at < len(left) and left[at:at + len(want)] != want:
             at += 256                          # (the workspace's arrays start at multiples of 256 bytes, in this order)
         assert at < len(left), f"{key} is not in the workspace"
         at += 256
     assert orc.rel_frobenius(_to_np(out), ref["out"]) <= TOL
-    assert orc.rel_frobenius(_to_np(out), _to_np(four)) <= 2.5e-3
     L.close()
 
 
