@@ -16,8 +16,8 @@ constexpr int kSpareUnits = 2048;     // 16-byte units behind them (32 KB): (in 
 constexpr int kRing = 2;              // ring slots of a wavefront (each holds one k-step of two streams)
 constexpr int kStreams = 2;           // streams of a slot: (W1, W3) tiles of one n-tile, or two n-tiles of W2
 
-// A block's n-tiles: block b of the G that share an expert owns tiles [t0, t1).  (G * NT stays far below 2^31: both are at
-// most a few thousand times the 32 n-tiles of a block.)
+// A block's n-tiles: block b of the G that share an expert owns tiles [t0, t1).  (G * NT is at most 2^27: a projection has at most
+// 4096 n-tiles, the wider of a layer's two sizes being 65536 at most, and a launch at most 256 experts times 128 blocks.)
 LRC_HD void block_tiles(int b, int G, int NT, int& t0, int& t1) {
   t0 = (int)(uint32_t(b) * uint32_t(NT) / uint32_t(G));
   t1 = (int)(uint32_t(b + 1) * uint32_t(NT) / uint32_t(G));

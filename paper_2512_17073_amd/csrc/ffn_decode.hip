@@ -376,8 +376,8 @@ __device__ __forceinline__ void decode_body(const KArgs& a, uint4* xs, const Pla
     // The first turn of the ring and the rows' exponents, requested last, stay in flight over the wait for the copies to LDS: in one place
     // for all passes, for registers that two places load are moved where the two meet, behind a wait for all loads (16 of the 24
     // kernels had one), and spill: scalar spills W1|W3 at 2 bits with part sums 171 -> 120, with 3-bit pairs 308 -> 188, vector spills at 4
-    // bits 3 to 11 registers -> 0.  Whole forward, Mixtral shape T = 64: 143.9 -> 140.5 us on one box, 132.6 -> 131.7 on another;
-    // T = 1, T = 13 at 3 bits, Qwen3 T = 64 the same.
+    // bits 3 to 11 registers -> 0.  Whole forward, Mixtral shape T = 64: 143.9 -> 140.5 us on one card, 132.6 -> 131.7 on another, at 4
+    // bits 194.1 -> 191.6; T = 1, T = 13 at 3 bits, Qwen3 T = 64 the same.
     fetch_from(0, 0, own > 0);
 #pragma unroll
     for (int i = 0; i < RING; ++i) fetch(ring[i]);
